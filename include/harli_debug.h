@@ -49,6 +49,9 @@ typedef struct {
   /* Compute units the tile height is chosen for: 0 = those of `hip_stream` (all of the device unless it is a
    * harli_cu_stream), n > 0 = n. */
   int32_t n_cu;
+  /* Ranges of K the tiles past the last full round of workgroups are cut into: 0 leaves the choice to the library, 1
+   * never cuts, n > 1 asks for n (fewer where the contraction is too short). */
+  int32_t ksplit;
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 
@@ -56,8 +59,8 @@ harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
  * its cost on n_cu compute units (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk,
  * grid and the rounds of tiles over the compute units.  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
  * of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over the blocks; slots past the matrix
- * are idle.  The library launches the tile height with the smaller cost, a round of 128-row tiles counted as 0.55 of a
- * round of 256-row tiles. */
+ * are idle.  This is the order of a launch whose tiles are not cut along K; the library chooses tile height and cut by
+ * the cost of its rounds. */
 harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows, int32_t n_cu, int32_t* out);
 
 /* How one GEMM of a decode step above 32 sequences is cut (host logic only, no device needed): `batch` sequences,

@@ -107,6 +107,17 @@ extern "C" harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip
   }
   g.n_cu = d->n_cu > 0 ? d->n_cu : 0;
   gemm2_force_tile_rows(d->tile_rows);
+  gemm2_force_split(d->ksplit);
+  if (d->ksplit != 1) {
+    void* part = nullptr;
+    g.part_bytes = (size_t)64 << 20;
+    if (hipMalloc(&part, g.part_bytes) != hipSuccess) {
+      cleanup();
+      return fail(HARLI_ERR_HIP, "dbg_gemm2: no memory for the partial tiles");
+    }
+    tmp.push_back(part);
+    g.part = static_cast<float*>(part);
+  }
   harli_status rc = gemm2_launch(g, st);
   const int reps = d->reps > 1 ? d->reps : 0;
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -118,6 +129,7 @@ extern "C" harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip
     (void)hipEventRecord(e1, st);
   }
   gemm2_force_tile_rows(0);
+  gemm2_force_split(0);
   const hipError_t se = hipStreamSynchronize(st);
   if (rc == HARLI_OK && se != hipSuccess) rc = fail(HARLI_ERR_HIP, "dbg_gemm2: %s", hipGetErrorString(se));
   if (rc == HARLI_OK && reps) {

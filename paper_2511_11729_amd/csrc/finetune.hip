@@ -26,6 +26,7 @@ using namespace harli;
 namespace harli {
 harli_status pool_free_owned(harli_pool* p, const harli_alloc* a, void* event);  // pool.cpp
 harli_status head_prepare(harli_ctx* c);                                          // head.hip
+size_t head_part_bytes(const harli_ctx* c);
 }
 
 struct harli_saved {
@@ -52,6 +53,8 @@ struct FtWs {
   bf *vT = nullptr, *At[kTargets] = {}, *Bt[kTargets] = {}, *dyb = nullptr, *da = nullptr, *du = nullptr, *dx1b = nullptr, *dob = nullptr,
      *doT = nullptr, *qT = nullptr, *kT = nullptr, *dq = nullptr, *dkq = nullptr,
      *dvq = nullptr, *dk = nullptr, *dv = nullptr, *gs[3] = {}, *An[kTargets] = {}, *Bn[kTargets] = {};
+  float* part = nullptr;   // partial tiles of the weight GEMMs whose tiles are cut along K (gemm2.h)
+  size_t part_bytes = 0;
   float* scale = nullptr;  // [0] sigma, [1] 1/sigma, [2], [3] maxima of this and the next call: gradient scaling of the backward pass
   int scale_parity = 0;
   int Bf = 0, S = 0;
@@ -104,6 +107,19 @@ Dims dims(const harli_ctx* c, int Bf, int S) {
   return D;
 }
 
+// Workspace for partial tiles that lets every weight GEMM of a unit of at most `T` tokens be cut as gemm2_cut wants.
+size_t unit_part_bytes(const Dims& D, size_t T) {
+  auto tiles = [](long long n) { return (int)((n + kG2TileN - 1) / kG2TileN); };
+  auto steps = [](long long k) { return (int)((k + kG2StepK - 1) / kG2StepK); };
+  const int ad = 3 * steps(D.r) + 1, M = (int)T;  // stages of the adapters' and the bias segments
+  size_t n = gemm2_part_bytes(M, tiles(D.QD) + 2 * tiles(D.KVD), steps(D.H) + ad);            // q, k, v
+  n = std::max(n, gemm2_part_bytes(M, tiles(D.H), steps(D.QD) + ad));                         // o
+  n = std::max(n, gemm2_part_bytes(M, (D.F + 127) / 128, steps(D.H) + ad));                   // gate, up
+  n = std::max(n, gemm2_part_bytes(M, tiles(D.H), 2 * steps(D.F) + ad));                      // down, dh2
+  n = std::max(n, gemm2_part_bytes(M, std::max(tiles(D.F), tiles(D.QD)), steps(D.H) + ad));   // dm, do
+  return std::max(n, gemm2_part_bytes(M, tiles(D.H), steps(D.QD) + 2 * steps(D.KVD) + ad));   // dh
+}
+
 // The unit's workspace (backward temporaries, adapter copies, gradient scratch), sized once for max_ft_tokens when the
 // adapters are attached, so that no forward or backward call allocates or frees device memory (either would be a
 // device-wide synchronisation in the middle of serving).  With workspace_in_pool it is one TENSOR allocation of the
@@ -131,6 +147,9 @@ harli_status make_ws(harli_ctx* c) {
   const size_t o_dyb = take(T * D.H * 2), o_da = take(T * D.F * 2), o_du = take(T * D.F * 2), o_dx1b = take(T * D.H * 2);
   const size_t o_dob = take(T * D.QD * 2), o_dq = take(T * D.QD * 2), o_dkq = take(T * D.QD * 2), o_dvq = take(T * D.QD * 2);
   const size_t o_dk = take(T * D.KVD * 2), o_dv = take(T * D.KVD * 2), o_gs = take(3 * al(T * D.r * 2));
+  size_t part_bytes = unit_part_bytes(D, T);
+  part_bytes = std::max(part_bytes, head_part_bytes(c));
+  const size_t o_part = take(part_bytes);
   const size_t o_gpart = take(ft_lora_grad_ws_floats((int)maxdim, D.r) * 4);
   const bool want_pool = c->lora.workspace_in_pool != 0 || c->cfg.memory_in_pool != 0;
   if (off != w.bytes || want_pool != fs->ws_in_pool) {  // first attach, or another rank / placement than before
@@ -155,6 +174,8 @@ harli_status make_ws(harli_ctx* c) {
   w.dvq = (bf*)(b + o_dvq); w.dk = (bf*)(b + o_dk); w.dv = (bf*)(b + o_dv);
   for (int i = 0; i < 3; ++i) w.gs[i] = (bf*)(b + o_gs + i * al(T * D.r * 2));
   w.gpart = (float*)(b + o_gpart);
+  w.part = (float*)(b + o_part);
+  w.part_bytes = part_bytes;
   for (int i = 0; i < kTargets; ++i) {
     w.At[i] = (bf*)(b + o_At + i * ad); w.Bt[i] = (bf*)(b + o_Bt + i * adb);
     w.An[i] = (bf*)(b + o_An + i * adb); w.Bn[i] = (bf*)(b + o_Bn + i * ad);
@@ -227,6 +248,9 @@ Gemm2Args wg_begin(const harli_ctx* c, int T) {
   g.alpha = 1.f;
   g.half = 1;
   g.overflow_flag = c->dw.err_flag;
+  const FtWs& w = static_cast<FtState*>(c->ft_ws)->ws;
+  g.part = w.part;
+  g.part_bytes = w.part_bytes;
   return g;
 }
 void wg_seg(Gemm2Args& g, const bf* A, long long lda, int K, const void* B, int rows, int t0, int t1, const void* B2 = nullptr, int pair = 0) {
@@ -499,6 +523,15 @@ void finetune_device_bytes(const harli_ctx* c, size_t* weights, size_t* workspac
   *weights = fs->weight_bytes;
   *workspace = fs->ws.bytes;
   *in_pool = fs->ws_in_pool ? 1 : 0;
+}
+}  // namespace harli
+
+namespace harli {
+// partial-tile workspace of the finetune task, shared by the unit's and the output layer's GEMMs (one stream order)
+void finetune_partials(const harli_ctx* c, float** part, size_t* bytes) {
+  const FtWs& w = static_cast<FtState*>(c->ft_ws)->ws;
+  *part = w.part;
+  *bytes = w.part_bytes;
 }
 }  // namespace harli
 

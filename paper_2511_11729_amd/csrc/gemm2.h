@@ -78,10 +78,28 @@ struct Gemm2Args {
   int* overflow_flag;  // device int: bit 8 is set when a 16-bit output had to be clamped to the element's range (or null)
   long long* clk;      // clock probe (or null): workgroup 0 writes {shader-clock cycles, 100 MHz ticks} of its K loop
   // compute units the launch's stream may use (Harli Sec. 6.2: the finetune task runs on a share of them); 0: taken
-  // from the stream (harli_cu_stream_create), else the whole device.  The tile height is chosen for it.
+  // from the stream (harli_cu_stream_create), else the whole device.  The tile height and the cut along K are chosen for it.
   int n_cu;
+  // workspace for the partial tiles of a launch whose tiles are cut along K (or null: tiles are never cut); launches
+  // that share it are ordered by their stream
+  float* part;
+  size_t part_bytes;
 };
 
+// How a launch is cut (host logic, gemm2_cut): tiles [0, full) are computed whole, each of the other `rest` tiles in ks
+// ranges of K by ks workgroups that write partial tiles to the workspace; a second kernel adds them and runs the epilogue.
+struct Gemm2Cut {
+  int FM;                      // tile height / 64
+  int ks;                      // 1: nothing is cut
+  int full, rest;
+  int tiles_m, tiles_n, GM;    // tile order of a cut launch: bands of GM row tiles
+  int chunk_full, chunk_cut;   // tiles / pieces per XCD
+  double cost_us;              // what the choice was made by
+};
+// stages: K steps of the longest column tile.  n_cu: compute units of the stream.
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes);
+// bytes of workspace that let gemm2_launch cut every launch of at most max_M rows and max_tiles_n column tiles as it wants
+size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages);
 
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st);
 
@@ -108,6 +126,9 @@ struct BlockJobs {
   int* flag;  // device int or null: bit 8 is set when a converted value lay beyond the destination element's range
 };
 void gemm2_block_jobs(const BlockJobs& jobs, hipStream_t st);
+// measurement hook: fixes the ranges of K of later launches (tiles past the last full round, all of them when one round
+// holds them all; 1: never cut); 0 gives the choice back
+void gemm2_force_split(int ks);
 // measurement hook: 128 or 256 fixes the tile height of every later launch, anything else gives the choice back
 void gemm2_force_tile_rows(int rows);
 // compute units a stream made by harli_cu_stream_create may use; 0 for any other stream (sched.cpp)

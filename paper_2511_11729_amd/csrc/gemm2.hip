@@ -38,14 +38,21 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 #define G2_SB0() __builtin_amdgcn_sched_barrier(0)
 #define G2_SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
 
-// One 32-row slab of a wave's block (the four accumulators c0..c3 side by side, 128 columns) to its destinations.
-template <bool HALF, int EPI>
-__device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1, const f32x16& c2, const f32x16& c3, char* ebuf,
-                                              const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane, int mrow0,
-                                              bool& clamped) {
-  constexpr int ER = (128 + 8) * 4;
-  // a lane of accumulator j holds rows 8 (v/4) + 4 (lane/32) + v%4 of column lane%32 of that 32 x 32 block
+// Stage of the epilogue: accumulator c (32 x 32, column block j of a wave's 128 columns) times alpha to the row-major
+// fp32 buffer the rows are stored from.  A lane holds rows 8 (v/4) + 4 (lane/32) + v%4 of column lane%32.
+constexpr int kG2StageRow = (128 + 8) * 4;  // staged row in bytes; 4 rows further = 32 banks further
+__device__ __forceinline__ void g2_stage_block(const f32x16& c, int j, char* ebuf, float alpha, int lane) {
   const int col_l = lane & 31, rgrp = (lane >> 5) * 4;
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    *reinterpret_cast<float*>(ebuf + (8 * (v >> 2) + rgrp + (v & 3)) * kG2StageRow + (j * 32 + col_l) * 4) = c[v] * alpha;
+}
+
+// Rows [r0, r0 + ROWS) of a staged 32-row slab (128 columns, first row mrow0) to their destinations, by one wave.
+template <bool HALF, int EPI, int ROWS>
+__device__ __forceinline__ void g2_store_rows(const char* ebuf, const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane,
+                                              int mrow0, int r0, bool& clamped) {
+  constexpr int ER = kG2StageRow;
   auto pack8 = [&](const float* v) {
     if (HALF) {
 #pragma unroll
@@ -58,20 +65,14 @@ __device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1
     if (HALF) unpack8h(wv, v);
     else unpack8(wv, v);
   };
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        *reinterpret_cast<float*>(ebuf + (8 * (v >> 2) + rgrp + (v & 3)) * ER + (j * 32 + col_l) * 4) = (j == 0 ? c0 : j == 1 ? c1 : j == 2 ? c2 : c3)[v] * a.alpha;
-    __builtin_amdgcn_wave_barrier();
-        if (EPI == GEMM2_EPI_GATEUP) {
+    if (EPI == GEMM2_EPI_GATEUP) {
       // staged columns [0,32) gate, [32,64) up of output columns 0..31 of this wave's 64; [64,96), [96,128) of 32..63
       const int c8 = (lane & 7) * 8;                              // 8 output columns of the 64
       const int n8 = (tn - out.tile0) * 128 + wn * 64 + c8;       // column in a, u, m
       const int sc = (c8 >> 5) * 64 + (c8 & 31);                  // staged column of the gate values
 #pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int row = it * 8 + (lane >> 3), m = mrow0 + row;
+      for (int it = 0; it < ROWS / 8; ++it) {
+        const int row = r0 + it * 8 + (lane >> 3), m = mrow0 + row;
         const float4 g0 = *reinterpret_cast<const float4*>(ebuf + row * ER + sc * 4);
         const float4 g1 = *reinterpret_cast<const float4*>(ebuf + row * ER + sc * 4 + 16);
         const float4 u0 = *reinterpret_cast<const float4*>(ebuf + row * ER + (sc + 32) * 4);
@@ -93,8 +94,8 @@ __device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1
       // 16-bit outputs only: eight columns (16 bytes) per lane, four rows per pass
       const int c8 = (lane & 15) * 8, n8 = (tn - out.tile0) * BN + wn * 128 + c8;
 #pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int row = it * 4 + (lane >> 4), m = mrow0 + row;
+      for (int it = 0; it < ROWS / 4; ++it) {
+        const int row = r0 + it * 4 + (lane >> 4), m = mrow0 + row;
         const float4 lo = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4);
         const float4 hi = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4 + 16);
         if (m >= a.M || n8 >= out.N) continue;
@@ -120,17 +121,18 @@ __device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1
       const int c4 = (lane & 31) * 4, n = (tn - out.tile0) * BN + wn * 128 + c4;
       const bool nvec = n + 3 < out.N;
 #pragma unroll
-      for (int half8 = 0; half8 < 2; ++half8) {
-        float4 rv[8];
+      for (int half8 = 0; half8 < (ROWS + 15) / 16; ++half8) {
+        constexpr int NIT = ROWS < 16 ? ROWS / 2 : 8;
+        float4 rv[NIT];
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const int m = mrow0 + (half8 * 8 + it) * 2 + (lane >> 5);
+        for (int it = 0; it < NIT; ++it) {
+          const int m = mrow0 + r0 + (half8 * 8 + it) * 2 + (lane >> 5);
           rv[it] = make_float4(0.f, 0.f, 0.f, 0.f);
           if (out.res && nvec && m < a.M) rv[it] = *reinterpret_cast<const float4*>(out.res + (long long)m * out.ldcf + n);
         }
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const int row = (half8 * 8 + it) * 2 + (lane >> 5), m = mrow0 + row;
+        for (int it = 0; it < NIT; ++it) {
+          const int row = r0 + (half8 * 8 + it) * 2 + (lane >> 5), m = mrow0 + row;
           float4 o = *reinterpret_cast<const float4*>(ebuf + row * ER + c4 * 4);
           if (m >= a.M || n >= out.N) continue;
           if (nvec) {
@@ -156,27 +158,73 @@ __device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
-  }
+}
+
+// One 32-row slab of a wave's block (the four accumulators c0..c3 side by side, 128 columns) to its destinations.
+template <bool HALF, int EPI>
+__device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1, const f32x16& c2, const f32x16& c3, char* ebuf,
+                                              const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane, int mrow0,
+                                              bool& clamped) {
+  g2_stage_block(c0, 0, ebuf, a.alpha, lane);
+  g2_stage_block(c1, 1, ebuf, a.alpha, lane);
+  g2_stage_block(c2, 2, ebuf, a.alpha, lane);
+  g2_stage_block(c3, 3, ebuf, a.alpha, lane);
+  __builtin_amdgcn_wave_barrier();
+  g2_store_rows<HALF, EPI, 32>(ebuf, a, out, tn, wn, lane, mrow0, 0, clamped);
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Output block of column tile tn.
+__device__ __forceinline__ Gemm2Out g2_out_of(const Gemm2Args& a, int tn) {
+  Gemm2Out out = a.out[0];
+  if (a.nout > 1 && tn >= a.out[1].tile0) out = a.out[1];
+  if (a.nout > 2 && tn >= a.out[2].tile0) out = a.out[2];
+  return out;
+}
+
+// Tile t of a cut launch: bands of GM row tiles, column by column inside a band, so that consecutive tiles of an XCD's
+// share form compact blocks.
+__device__ __forceinline__ void g2_cut_tile(const Gemm2Cut& c, int t, int& tm, int& tn) {
+  const int band = t / (c.GM * c.tiles_n), rem = t - band * (c.GM * c.tiles_n), rows = min(c.GM, c.tiles_m - band * c.GM);
+  tn = rem / rows;
+  tm = band * c.GM + rem - tn * rows;
+}
 
 template <int FM, bool HALF, int EPI>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_gemm2(Gemm2Args a, int tiles_total, int chunk, int GM, int GN, const uint4* zero16) {
+k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, const uint4* zero16) {
   constexpr int BM = 64 * FM, ASZ = BM * BK * 2, STG = ASZ + BSZ, NS = stages<FM>();
   constexpr int LOADS = FM + 4;  // direct-to-LDS loads a wave issues per stage
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves of (32 FM) x 128
-  // XCD-aware tile order (workgroup w runs on XCD w % 8): every XCD walks blocks of GM x GN tiles, so the workgroups
-  // that share an L2 share operand panels.
   const int w = blockIdx.x;
-  const int slot = (w & 7) * chunk + (w >> 3);
-  if (slot >= tiles_total) return;
-  const int nbn = (a.tiles_n + GN - 1) / GN;
-  const int blk = slot / (GM * GN), within = slot - blk * (GM * GN);
-  const int bm = blk / nbn, bn = blk - bm * nbn;
-  const int tm = bm * GM + within / GN, tn = bn * GN + within % GN;
+  int tm, tn, piece = -1, split = 0;  // piece: index of this workgroup's partial tile, -1 for a whole tile
+  if (cut.ks > 1) {
+    // cut launch (see gemm2_cut): whole tiles first, then the remaining tiles in ranges of K, range by range; either
+    // list is dealt out in eight contiguous shares, one per XCD
+    int slot = (w & 7) * cut.chunk_full + (w >> 3);
+    if (w < 8 * cut.chunk_full) {
+      if (slot >= cut.full) return;
+    } else {
+      const int w2 = w - 8 * cut.chunk_full;
+      piece = (w2 & 7) * cut.chunk_cut + (w2 >> 3);
+      if (piece >= cut.rest * cut.ks) return;
+      split = piece / cut.rest;
+      slot = cut.full + piece - split * cut.rest;
+    }
+    g2_cut_tile(cut, slot, tm, tn);
+  } else {
+    // XCD-aware tile order (workgroup w runs on XCD w % 8): every XCD walks blocks of GM x GN tiles, so the workgroups
+    // that share an L2 share operand panels.
+    const int slot = (w & 7) * chunk + (w >> 3);
+    if (slot >= tiles_total) return;
+    const int nbn = (a.tiles_n + GN - 1) / GN;
+    const int blk = slot / (GM * GN), within = slot - blk * (GM * GN);
+    const int bm = blk / nbn, bn = blk - bm * nbn;
+    tm = bm * GM + within / GN, tn = bn * GN + within % GN;
+  }
   const int m0 = tm * BM;
   if (m0 >= a.M || tn >= a.tiles_n) return;
 
@@ -192,6 +240,12 @@ k_gemm2(Gemm2Args a, int tiles_total, int chunk, int GM, int GN, const uint4* ze
   int n_stage = 0;
   for (int s = 0; s < a.nseg; ++s)
     if (tn >= a.seg[s].tile0 && tn < a.seg[s].tile1) n_stage += (a.seg[s].K + BK - 1) / BK;
+  int skip = 0;  // stages of this tile that belong to earlier ranges of K
+  if (piece >= 0) {
+    const int quads = (n_stage + NS - 1) / NS;  // ranges are whole passes of the stage ring
+    skip = quads * split / cut.ks * NS;
+    n_stage = min(n_stage, quads * (split + 1) / cut.ks * NS) - skip;
+  }
   const int n_step = (n_stage + NS - 1) / NS * NS;  // the loop body covers NS stages; stages past the end multiply zeros
 
   // Loads: instruction j of a wave fills 16 rows of a stage; lane -> row lane/4, LDS slot lane%4, which receives the
@@ -339,6 +393,16 @@ k_gemm2(Gemm2Args a, int tiles_total, int chunk, int GM, int GN, const uint4* ze
   if (probe) c_start = clock64(), w_start = wall_clock64();
   if (n_stage > 0) {
     G2_OPEN_SEG();
+    if (skip > 0) {
+      while (skip * BK >= Kseg) {
+        skip -= (Kseg + BK - 1) / BK;
+        G2_OPEN_SEG();
+      }
+      k0 = skip * BK;
+      soffA += (unsigned)k0 * 2u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) soffB[j] += (unsigned)k0 * (BN * 2u);
+    }
     G2_ISSUE(0);
     G2_ADVANCE();
     G2_ISSUE(1);
@@ -384,14 +448,25 @@ k_gemm2(Gemm2Args a, int tiles_total, int chunk, int GM, int GN, const uint4* ze
 #undef G2_PIPE2
 #undef G2_STEP
 
+  if (piece >= 0) {
+    // a range of K: the accumulators leave as they lie in the registers, 1 KiB per store instruction; k_gemm2_sum reads
+    // them back in the same order
+    float* p = a.part + (((size_t)piece * 4 + wave) * (FM * 4096)) + lane * 4;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(p + ((i * 4 + j) * 4 + q) * 256) =
+              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    return;
+  }
+
   // ---- epilogue ---------------------------------------------------------------------------------------------------
-  // Output block of this tile and its first column inside the block.
-  Gemm2Out out = a.out[0];
-  if (a.nout > 1 && tn >= a.out[1].tile0) out = a.out[1];
-  if (a.nout > 2 && tn >= a.out[2].tile0) out = a.out[2];
-  constexpr int ER = (128 + 8) * 4;  // staged row in bytes; 4 rows further = 32 banks further
-  static_assert(4 * 32 * ER <= NS * STG, "epilogue staging must fit the stage buffers");
-  char* ebuf = smem + wave * (32 * ER);
+  const Gemm2Out out = g2_out_of(a, tn);
+  static_assert(4 * 32 * kG2StageRow <= NS * STG, "epilogue staging must fit the stage buffers");
+  char* ebuf = smem + wave * (32 * kG2StageRow);
   bool clamped = false;
   const int mrow_w = m0 + wm * (FM * 32);
   g2_store_slab<HALF, EPI>(acc[0][0], acc[0][1], acc[0][2], acc[0][3], ebuf, a, out, tn, wn, lane, mrow_w, clamped);
@@ -400,6 +475,44 @@ k_gemm2(Gemm2Args a, int tiles_total, int chunk, int GM, int GN, const uint4* ze
     g2_store_slab<HALF, EPI>(acc[2][0], acc[2][1], acc[2][2], acc[2][3], ebuf, a, out, tn, wn, lane, mrow_w + 64, clamped);
     g2_store_slab<HALF, EPI>(acc[3][0], acc[3][1], acc[3][2], acc[3][3], ebuf, a, out, tn, wn, lane, mrow_w + 96, clamped);
   }
+  if (clamped && a.overflow_flag) atomicOr(a.overflow_flag, 8);
+}
+
+// Sum of the K ranges of the cut tiles, in range order, and their epilogue.  Workgroup: one 32-row slab of one wave's
+// 32 FM x 128 block of one tile.  Wave j adds up the partials of column block j (four 1 KiB loads per range, four ranges
+// in flight), the four waves then store eight rows each.
+template <int FM, bool HALF, int EPI>
+__global__ void __launch_bounds__(256) k_gemm2_sum(Gemm2Args a, Gemm2Cut cut) {
+  __shared__ __align__(16) char ebuf[32 * kG2StageRow];
+  const int lane = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = blockIdx.x % FM, wave = (blockIdx.x / FM) & 3, r = blockIdx.x / (4 * FM);
+  int tm, tn;
+  g2_cut_tile(cut, cut.full + r, tm, tn);
+  const int mrow0 = tm * (64 * FM) + (wave >> 1) * (FM * 32) + i * 32;
+  if (mrow0 >= a.M) return;
+  const size_t stride = (size_t)cut.rest * (4 * FM * 4096);  // floats between two ranges of a tile
+  const float* p = a.part + ((size_t)r * 4 + wave) * (FM * 4096) + (i * 4 + j) * 1024 + lane * 4;
+  f32x16 c;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) c[v] = 0.f;
+  for (int s0 = 0; s0 < cut.ks; s0 += 4) {
+    f32x4 t[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t[u][q] = *reinterpret_cast<const f32x4*>(p + (size_t)min(s0 + u, cut.ks - 1) * stride + q * 256);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < cut.ks)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c[4 * q + e] += t[u][q][e];
+  }
+  g2_stage_block(c, j, ebuf, a.alpha, lane);
+  __syncthreads();
+  bool clamped = false;
+  g2_store_rows<HALF, EPI, 8>(ebuf, a, g2_out_of(a, tn), tn, wave & 1, lane, mrow0, j * 8, clamped);
   if (clamped && a.overflow_flag) atomicOr(a.overflow_flag, 8);
 }
 
@@ -440,10 +553,14 @@ template <int FM>
 constexpr int lds_bytes() { return stages<FM>() * (64 * FM * BK * 2 + BSZ); }
 
 int g_force_fm = 0;  // measurement hook: 2 or 4 fixes the tile height
+int g_force_ks = 0;  // measurement hook: fixes the ranges of K
+constexpr int kMinCutStages = 4, kMaxCut = 16;  // shortest range of K in stages (the ring holds four), most ranges of a tile
 
 }  // namespace
 
 void gemm2_force_tile_rows(int rows) { g_force_fm = rows == 256 ? 4 : rows == 128 ? 2 : 0; }
+
+void gemm2_force_split(int ks) { g_force_ks = ks > 0 ? ks : 0; }
 
 void gemm2_block_jobs(const BlockJobs& jobs, hipStream_t st) {
   if (jobs.n < 1) return;
@@ -463,6 +580,57 @@ Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
   p.grid = p.chunk * 8;
   p.rounds = (tiles_m * tiles_n + n_cu - 1) / n_cu;
   return p;
+}
+
+// Tile height and cut of a launch.  A launch runs in rounds of one workgroup per compute unit; the last round is partly
+// idle, and outputs with fewer tiles than compute units leave the chip idle throughout (1032 x 3584: 126 tiles of 128
+// rows).  So the tiles past the last full round are cut along K until the chip is full: their partial tiles go to the
+// workspace and k_gemm2_sum adds them in a second launch (device-scope fences for a last-arriver sum cost more than the
+// idle compute units: they write back and invalidate a whole XCD's L2).  Measured in us, uncut -> cut as chosen here:
+//   M x N x K            uncut   cut
+//   48 x 4096 x 4096        57    23      2048 x 3584 x 18944   319   290
+//   256 x 4096 x 11008     135    43      2048 x 5120 x 13824   358   315
+//   600 x 5120 x 13824     180   115      4096 x 5120 x 13824   669   563
+//   1032 x 3584 x 37888    628   347      2048 x 4096 x 4096     80    80 (one full round: not cut)
+// Cost in us, fitted to a sweep of ranges for these and 20 more shapes (it picks within 4 % of the best, 8 % at worst):
+// a stage takes 0.71 / 0.456 us in a tile of 256 / 128 rows while few compute units run and up to 0.48 / 0.21 more when
+// all do (clock and fabric); filling, draining and storing a tile about 6; the second launch 4; partial tiles 0.18 per MB.
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes) {
+  Gemm2Cut best{};
+  best.cost_us = -1;
+  for (int FM = 4; FM >= 2; FM -= 2) {
+    if ((g_force_fm && FM != g_force_fm) || (!g_force_fm && FM == 4 && M <= 128)) continue;
+    const int BM = 64 * FM, tiles_m = (M + BM - 1) / BM, T = tiles_m * tiles_n;
+    const double t0 = FM == 4 ? 0.71 : 0.456, t1 = FM == 4 ? 0.48 : 0.21, t_fixed = 6.0;
+    auto step_us = [&](int active) {
+      const double b = std::min(active, 256) / 256.0;
+      return t0 + t1 * b * b;
+    };
+    const int full = T / n_cu * n_cu, rest = T - full;
+    const int ks_max = rest > 0 ? std::max(1, std::min(kMaxCut, stages / kMinCutStages)) : 1;
+    for (int ks = 1; ks <= ks_max; ++ks) {
+      const int pieces = rest * ks, r2 = (pieces + n_cu - 1) / n_cu;
+      const size_t bytes = ks > 1 ? (size_t)pieces * BM * BN * 4 : 0;
+      if (bytes > part_bytes) break;
+      double cost = (T / n_cu) * (stages * step_us(n_cu) + t_fixed);
+      if (r2 > 0) cost += r2 * (((stages + ks - 1) / ks) * step_us(std::min(pieces, n_cu)) + t_fixed);
+      if (ks > 1) cost += 4.0 + bytes / 1048576.0 * 0.18;
+      if (best.cost_us < 0 || (g_force_ks ? ks <= g_force_ks && (ks > best.ks || cost < best.cost_us) : cost < best.cost_us)) {
+        best = Gemm2Cut{};
+        best.FM = FM, best.ks = ks, best.cost_us = cost;
+        best.tiles_m = tiles_m, best.tiles_n = tiles_n, best.GM = std::min(FM == 2 ? 8 : 4, tiles_m);
+        best.full = ks > 1 ? full : T, best.rest = ks > 1 ? rest : 0;
+        best.chunk_full = (best.full + 7) / 8, best.chunk_cut = (best.rest * ks + 7) / 8;
+      }
+    }
+  }
+  return best;
+}
+
+size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages) {
+  const int ks = std::max(1, std::min(kMaxCut, stages / kMinCutStages));
+  if (ks < 2) return 0;
+  return std::min((size_t)((max_M + 127) / 128) * max_tiles_n * ks * (128 * BN * 4), (size_t)64 << 20);
 }
 
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
@@ -530,15 +698,22 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n_cu = prop.multiProcessorCount;
   }
-  const Gemm2Plan p4 = gemm2_plan(a.M, a.tiles_n, 4, n_cu), p2 = gemm2_plan(a.M, a.tiles_n, 2, n_cu);
-  // Tile height: rounds of workgroups over the compute units of the stream, a 128-row tile costed at 0.55 of a 256-row
-  // one (it moves 3/4 of the operand bytes for half the flops).
-  int FM = (a.M > 128 && p4.rounds <= 0.55 * p2.rounds) ? 4 : 2;
-  if (g_force_fm == 2 || g_force_fm == 4) FM = g_force_fm;
-  const Gemm2Plan& pl = FM == 4 ? p4 : p2;
-  const int GM = pl.GM, GN = pl.GN, total = pl.total, chunk = pl.chunk, grid = pl.grid;
-#define G2_LAUNCH(F_, H_, E_) \
-  hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(grid), dim3(NT), lds_bytes<F_>(), st, a, total, chunk, GM, GN, zero16)
+  int stages = 0;  // of the longest column tile
+  for (int s = 0; s < a.nseg; ++s) {
+    int n = 0;
+    for (int q = 0; q < a.nseg; ++q)
+      if (a.seg[q].tile0 <= a.seg[s].tile0 && a.seg[q].tile1 > a.seg[s].tile0) n += (a.seg[q].K + BK - 1) / BK;
+    stages = std::max(stages, n);
+  }
+  const Gemm2Cut cut = gemm2_cut(a.M, a.tiles_n, stages, n_cu, a.part ? a.part_bytes : 0);
+  const int FM = cut.FM;
+  const Gemm2Plan pl = gemm2_plan(a.M, a.tiles_n, FM, n_cu);
+  const int GM = pl.GM, GN = pl.GN, total = pl.total, chunk = pl.chunk, grid = cut.ks > 1 ? 8 * (cut.chunk_full + cut.chunk_cut) : pl.grid;
+#define G2_LAUNCH(F_, H_, E_)                                                                                                \
+  do {                                                                                                                       \
+    hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(grid), dim3(NT), lds_bytes<F_>(), st, a, cut, total, chunk, GM, GN, zero16); \
+    if (cut.ks > 1) hipLaunchKernelGGL((k_gemm2_sum<F_, H_, E_>), dim3(cut.rest * 4 * F_), dim3(256), 0, st, a, cut);         \
+  } while (0)
 #define G2_PICK(F_)                                                                    \
   do {                                                                                 \
     if (a.half) {                                                                      \

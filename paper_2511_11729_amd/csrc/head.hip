@@ -14,6 +14,7 @@
 #include "gemm2.h"
 
 namespace harli {
+void finetune_partials(const harli_ctx* c, float** part, size_t* bytes);  // finetune.hip
 namespace {
 
 struct HeadWs {
@@ -125,6 +126,18 @@ harli_status head_free_ws(harli_ctx* c) {
 
 }  // namespace
 
+// row chunk: at most 2048 rows and about 512 MiB of fp32 logits
+static int head_chunk_rows(int Vp) { return (int)std::max<long long>(64, std::min<long long>(2048, ((512ll << 20) / ((long long)Vp * 4)) / 64 * 64)); }
+
+// partial-tile workspace that lets the two GEMMs of a chunk be cut along K (gemm2.h)
+size_t head_part_bytes(const harli_ctx* c) {
+  if (!c->w_lm || !c->g_final || c->cfg.vocab < 1) return 0;
+  const int V = c->cfg.vocab, H = c->cfg.hidden, Vp = (V + 7) & ~7, M = std::min(head_chunk_rows(Vp), c->cfg.max_ft_tokens);
+  auto tiles = [](int n) { return (n + kG2TileN - 1) / kG2TileN; };
+  auto steps = [](int k) { return (k + kG2StepK - 1) / kG2StepK; };
+  return std::max(gemm2_part_bytes(M, tiles(V), steps(H)), gemm2_part_bytes(M, tiles(H), steps(Vp)));
+}
+
 // Made once when the adapters are attached (the context has an output layer): the blocked copies of the output layer
 // and the workspace for max_ft_tokens rows -- from the unified pool when the adapters were attached with
 // workspace_in_pool, else a library allocation -- so that harli_head_fwd_bwd itself allocates nothing.
@@ -154,8 +167,7 @@ harli_status head_prepare(harli_ctx* c) {
     w.weight_bytes = (blocked_elems(V, H) + blocked_elems(H, Vp)) * 2;
     w.weights_ready = true;
   }
-  // row chunk: at most 2048 rows and about 512 MiB of fp32 logits
-  const int TC = (int)std::max<long long>(64, std::min<long long>(2048, ((512ll << 20) / ((long long)Vp * 4)) / 64 * 64));
+  const int TC = head_chunk_rows(Vp);
   size_t off = 0;
   auto take = [&](size_t n) {
     size_t o = off;
@@ -221,12 +233,15 @@ extern "C" harli_status harli_head_fwd_bwd(harli_ctx* c, const float* x, const i
   harli_status s = HARLI_OK;
   HeadWs& w = *ws_of(c);
   const int V = c->cfg.vocab, H = c->cfg.hidden, Vp = w.Vp;
+  float* part = nullptr;
+  size_t part_bytes = 0;
+  finetune_partials(c, &part, &part_bytes);
   ft_rmsnorm_fwd(x, c->g_final, w.h, w.rho, T, H, c->cfg.rms_eps, c->dw.err_flag, st);
   for (int t0 = 0; t0 < T; t0 += w.TC) {
     const int rows = std::min(w.TC, T - t0);
     {  // logits = h W^T
       Gemm2Args g{};
-      g.M = rows; g.alpha = 1.f; g.half = 1; g.overflow_flag = c->dw.err_flag;
+      g.M = rows; g.alpha = 1.f; g.half = 1; g.overflow_flag = c->dw.err_flag; g.part = part; g.part_bytes = part_bytes;
       g.nseg = 1;
       g.seg[0] = Gemm2Seg{w.h + (size_t)t0 * H, H, H, w.w16, 0, (V + kG2TileN - 1) / kG2TileN, nullptr, 0, V};
       g.nout = 1;
@@ -238,7 +253,7 @@ extern "C" harli_status harli_head_fwd_bwd(harli_ctx* c, const float* x, const i
     hipLaunchKernelGGL(k_ce_row, dim3(rows), dim3(256), 0, st, w.logits, targets + t0, w.dlog, V, Vp, w.rowloss + t0, c->dw.err_flag);
     {  // dh = dlog W   (contraction over the padded vocabulary: pad columns are zero on both sides)
       Gemm2Args g{};
-      g.M = rows; g.alpha = 1.f; g.half = 1; g.overflow_flag = c->dw.err_flag;
+      g.M = rows; g.alpha = 1.f; g.half = 1; g.overflow_flag = c->dw.err_flag; g.part = part; g.part_bytes = part_bytes;
       g.nseg = 1;
       g.seg[0] = Gemm2Seg{w.dlog, Vp, Vp, w.wT, 0, (H + kG2TileN - 1) / kG2TileN, nullptr, 0, H};
       g.nout = 1;

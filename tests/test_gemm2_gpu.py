@@ -167,3 +167,53 @@ def test_full_size_shapes_on_a_nine_tenths_partition():
             print("gemm2 2048 x 4096 x 4096 on 230 compute units, %s: %.0f TFLOP/s" % (name, t))
     finally:
         hb.cu_stream_destroy(st)
+
+
+# ---- tiles cut along K: partial tiles in a workspace, summed by a second kernel ---------------------------------------
+@pytest.mark.parametrize("tile_rows", [128, 256])
+@pytest.mark.parametrize("ksplit", [2, 3, 16])
+@pytest.mark.parametrize("M,N,K,K2", [(8, 8, 512, 8), (300, 520, 1000, 16), (257, 1000, 2080, 64)])
+def test_tiles_cut_along_k(tile_rows, ksplit, M, N, K, K2):
+    """Ranges that end inside the ring of stages, at a segment's border and past the short second segment; rows and
+    columns that fill no tile.  fp32 sums of K products of half operands: 1e-5 of the largest value (K eps / 2 at most)."""
+    A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
+    A2, B2 = rnd((M, K2), True, 3), rnd((N, K2), True, 4, 0.1)
+    segs = [dict(A=A, B=B), dict(A=A2, B=B2)]
+    ref = f64(A) @ f64(B).T + f64(A2) @ f64(B2).T
+    res = torch.randn(M, N, device=DEV)
+    cf = torch.full((M, N), float("nan"), device=DEV)
+    hb.dbg_gemm2(M, segs, [dict(N=N, cf=cf, res=res)], tile_rows=tile_rows, ksplit=ksplit)
+    close(f64(cf), ref + f64(res), "fp32 output", 1e-5)
+    cb = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    hb.dbg_gemm2(M, segs, [dict(N=N, cb=cb)], alpha=0.5, tile_rows=tile_rows, ksplit=ksplit)
+    close(f64(cb), 0.5 * ref, "half output", 2e-3)
+
+
+def test_full_rounds_and_a_cut_remainder():
+    """Seven compute units, 15 tiles: two rounds of whole tiles, the last one in ranges of K; the same bits every time."""
+    M, N, K = 300, 1200, 640
+    A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
+    got = []
+    for _ in range(2):
+        cf = torch.full((M, N), float("nan"), device=DEV)
+        hb.dbg_gemm2(M, [dict(A=A, B=B)], [dict(N=N, cf=cf)], tile_rows=128, n_cu=7, ksplit=4)
+        got.append(cf)
+    close(f64(got[0]), f64(A) @ f64(B).T, "fp32 output", 1e-5)
+    assert torch.equal(got[0], got[1])
+
+
+def test_swiglu_epilogues_of_cut_tiles():
+    M, F, H = 150, 200, 520
+    h2, Wg, Wu = rnd((M, H), True, 40), rnd((F, H), True, 41, 0.08), rnd((F, H), True, 42, 0.08)
+    a = torch.full((M, F), float("nan"), dtype=torch.float16, device=DEV)
+    u, m, da, du = (torch.full_like(a, float("nan")) for _ in range(4))
+    hb.dbg_gemm2(M, [dict(A=h2, B=Wg, B2=Wu, pair=1)], [dict(N=F, cb=a)], epi=3, o0=m, o1=u, lde=F, ksplit=4)
+    ar, ur = f64(a), f64(u)
+    close(ar, f64(h2) @ f64(Wg).T, "gate")
+    close(ur, f64(h2) @ f64(Wu).T, "up")
+    close(f64(m), ar / (1 + np.exp(-ar)) * ur, "silu(a) * u")
+    dy, WdT = rnd((M, H), True, 47), rnd((F, H), True, 48, 0.08)
+    hb.dbg_gemm2(M, [dict(A=dy, B=WdT)], [dict(N=F)], epi=2, e0=a, e1=u, o0=da, o1=du, lde=F, ksplit=4)
+    dm, sg = f64(dy) @ f64(WdT).T, 1 / (1 + np.exp(-ar))
+    close(f64(da), dm * ur * sg * (1 + ar * (1 - sg)), "da")
+    close(f64(du), dm * ar * sg, "du")
