@@ -136,3 +136,22 @@ def test_whole_model_finetune_step_matches_the_oracle():
             assert_close(grads_gpu[l][1][p].cpu().numpy(), grads_ref[l][p][1], "layer %d dB[%s]" % (l, p))
     st = case.pool.stats()
     assert st.tensor_blocks_live == 0 and st.small_bytes_live == 0
+
+
+@pytest.mark.parametrize("vocab", [3, 13, 8193, 16387])
+def test_cross_entropy_rows_around_the_load_groups(vocab):
+    """A vocabulary smaller than one 16-byte group, one that leaves most threads without a value, and ones that end just
+    past one and two rounds of the row kernel's loads; the target of the first row is the last class."""
+    T = 9
+    case = ModelCase(n_layers=1, vocab=vocab, micro_batch=1, seq_len=16)
+    rng = np.random.default_rng(vocab)
+    x = rng.standard_normal((T, case.m.hidden)).astype(np.float32) * 1.5
+    tg = rng.integers(0, vocab, size=T).astype(np.int32)
+    tg[0], tg[4] = vocab - 1, -1
+    loss, dx = torch.zeros(1, device=DEV), torch.empty(T, case.m.hidden, device=DEV)
+    case.ctx.head_fwd_bwd(f32_dev(x), torch.from_numpy(tg).to(DEV), loss, dx)
+    torch.cuda.synchronize()
+    case.ctx.check()
+    ref_loss, ref_dx, _ = O.head_forward_backward(x, case.ex["gf"], case.ex["wlm"], tg, case.m.rms_eps)
+    assert abs(float(loss) - ref_loss) <= 2e-3 * abs(ref_loss), (float(loss), ref_loss)
+    assert_close(dx.cpu().numpy(), ref_dx, "dx")
