@@ -50,8 +50,8 @@ struct FtWs {
   char* base = nullptr;
   float *delta = nullptr, *dh2 = nullptr,
         *dx1 = nullptr, *dh = nullptr, *gpart = nullptr;
-  bf *vT = nullptr, *At[kTargets] = {}, *Bt[kTargets] = {}, *dyb = nullptr, *da = nullptr, *du = nullptr, *dx1b = nullptr, *dob = nullptr,
-     *doT = nullptr, *qT = nullptr, *kT = nullptr, *dq = nullptr, *dkq = nullptr,
+  bf *At[kTargets] = {}, *Bt[kTargets] = {}, *dyb = nullptr, *da = nullptr, *du = nullptr, *dx1b = nullptr, *dob = nullptr,
+     *dq = nullptr, *dkq = nullptr,
      *dvq = nullptr, *dk = nullptr, *dv = nullptr, *gs[3] = {}, *An[kTargets] = {}, *Bn[kTargets] = {};
   float* part = nullptr;   // partial tiles of the weight GEMMs whose tiles are cut along K (gemm2.h)
   size_t part_bytes = 0;
@@ -139,7 +139,6 @@ harli_status make_ws(harli_ctx* c) {
   };
   const size_t o_delta = take(T * D.nq * 4);
   const size_t o_dh2 = take(T * D.H * 4), o_dx1 = take(T * D.H * 4), o_dh = take(T * D.H * 4);
-  const size_t o_vT = take(T * D.KVD * 2), o_kT = take(T * D.KVD * 2), o_qT = take(T * D.QD * 2), o_doT = take(T * D.QD * 2);
   const size_t ad = al(maxdim * D.r * 2);  // one adapter matrix in the compute element, row-major (skinny products)
   const size_t adb = al(blocked_elems((long long)maxdim, D.r) * 2);  // ... in the weight GEMM's blocked order
   const size_t o_At = take(kTargets * ad), o_Bt = take(kTargets * adb);
@@ -168,7 +167,6 @@ harli_status make_ws(harli_ctx* c) {
   char* b = w.base;
   w.delta = (float*)(b + o_delta);
   w.dh2 = (float*)(b + o_dh2); w.dx1 = (float*)(b + o_dx1); w.dh = (float*)(b + o_dh);
-  w.vT = (bf*)(b + o_vT); w.kT = (bf*)(b + o_kT); w.qT = (bf*)(b + o_qT); w.doT = (bf*)(b + o_doT);
   w.dyb = (bf*)(b + o_dyb); w.da = (bf*)(b + o_da); w.du = (bf*)(b + o_du);
   w.dx1b = (bf*)(b + o_dx1b); w.dob = (bf*)(b + o_dob); w.dq = (bf*)(b + o_dq); w.dkq = (bf*)(b + o_dkq);
   w.dvq = (bf*)(b + o_dvq); w.dk = (bf*)(b + o_dk); w.dv = (bf*)(b + o_dv);
@@ -626,12 +624,7 @@ extern "C" harli_status harli_lora_fwd(harli_ctx* c, int32_t layer, const float*
   }
   ft_rope(sv->q, T, S, D.nq, D.d, c->dw.inv_freq, false, c->dw.err_flag, st);
   ft_rope(sv->k, T, S, D.nkv, D.d, c->dw.inv_freq, false, c->dw.err_flag, st);
-  {
-    TransposeJobs tj{};
-    tj.in[0] = sv->v, tj.out[0] = w.vT, tj.C[0] = D.KVD, tj.n = 1;
-    ft_transpose_heads(tj, B_f, S, st);
-  }
-  RUN(ft_attn_fwd(sv->q, sv->k, w.vT, sv->o, sv->lse, B_f, S, D.nq, D.nkv, D.d, st));
+  RUN(ft_attn_fwd(sv->q, sv->k, sv->v, sv->o, sv->lse, B_f, S, D.nq, D.nkv, D.d, st));
   {  // x1 = X + o Wo^T
     proj_us_group(c, 3, 3, sv->o, T, sv, st);
     Gemm2Args g = wg_begin(c, T);
@@ -754,15 +747,7 @@ extern "C" harli_status harli_lora_bwd(harli_ctx* c, int32_t layer, const float*
     RUNB(gemm2_launch(g, st));
   }
   // ---- attention ----
-  {
-    TransposeJobs tj{};
-    tj.in[0] = w.dob, tj.out[0] = w.doT, tj.C[0] = D.QD;
-    tj.in[1] = sv->q, tj.out[1] = w.qT, tj.C[1] = D.QD;
-    tj.in[2] = sv->k, tj.out[2] = w.kT, tj.C[2] = D.KVD;
-    tj.n = 3;
-    ft_transpose_heads(tj, B_f, S, st);
-  }
-  RUNB(ft_attn_bwd(sv->q, sv->k, sv->v, sv->o, w.qT, w.kT, w.dob, w.doT, sv->lse, w.delta, w.dq, w.dkq, w.dvq, B_f, S, D.nq,
+  RUNB(ft_attn_bwd(sv->q, sv->k, sv->v, sv->o, w.dob, sv->lse, w.delta, w.dq, w.dkq, w.dvq, B_f, S, D.nq,
                    D.nkv, D.d, c->dw.err_flag, st));
   const bf *dk = w.dkq, *dv = w.dvq;
   if (D.G > 1) {

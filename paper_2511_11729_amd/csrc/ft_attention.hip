@@ -11,8 +11,19 @@
 //     contraction index is the query.
 // In both cases the second product contracts over the index held in the accumulator's REGISTERS.  Register v of a
 // lane half h is contraction slot v%8 of MFMA step v/8, i.e. row 16*(v/8) + 8*((v%8)/4) + 4h + v%4: the A operand
-// of the second product (a transposed tile V^T, K^T, Q^T or dO^T in LDS) is read with the same permutation, as
-// two 8-byte pieces at columns 4h and 8 + 4h of each 16-column step.  No data moves between lanes.
+// of the second product (V^T, K^T, Q^T or dO^T) wants rows 4h..4h+3 and 8+4h..8+4h+3 of each 16-row step of the
+// streamed tile, eight of them per lane for one column.  The tile lies in LDS as it lies in memory (row-major), and
+// ds_read_b64_tr_b16 turns it on the way out: a 16-lane group points at a 4 x 16 block (lane q at row q/4, columns
+// 4(q%4)..+3) and lane i receives column i of the four rows.  No transposed copies, in memory or in LDS.
+//
+// Blocks go from memory straight to LDS (buffer_load ... lds, two buffers, one barrier per block), the 16-byte chunks
+// of a row permuted by swz() on the way in so that the row reads and the transposing reads are both free of bank
+// conflicts.  Rows past the sequence are out of the buffer resource's range and read as zeros.
+//
+// What bounds them at 512 to 1024 tokens is vector work per score, not MFMA: the exponent is one fma and the bare
+// hardware exponential, masks are applied only to blocks that cross the diagonal, and the running output is rescaled
+// only when a maximum has moved.  4 x 512 tokens, 32 heads of 128: forward 41 -> 24 us, dQ 56 -> 32, dK/dV 121 -> 55
+// (before: transposed copies made by a separate kernel, 36 us; both tiles of an operand in LDS, loaded through registers).
 #include "ft_attention.h"
 
 #include "ft_elem.h"
@@ -21,30 +32,83 @@ namespace harli {
 namespace {
 
 constexpr int KB = 64;            // rows of the streamed operand per block
-constexpr int TS = KB * 2 + 16;   // byte stride of a transposed tile row (64 columns + pad)
 // native vector types: arrays of them stay in registers (arrays of the HIP uint4 struct were left in scratch)
 typedef unsigned __attribute__((ext_vector_type(4))) u32x4;
 typedef unsigned __attribute__((ext_vector_type(2))) u32x2;
-constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+typedef short __attribute__((ext_vector_type(4))) s16x4;
+typedef short __attribute__((ext_vector_type(8))) s16x8;
+typedef _Float16 __attribute__((ext_vector_type(2))) f16x2;
+#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
+constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ f32x16 mma32(const u32x4& a, const u32x4& b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// A fragment of a row-major LDS tile (row stride RS bytes): rows sub*32 + lane%32, k = 16j + 8h .. +7
-template <int RS>
-__device__ __forceinline__ u32x4 frag_rows(const char* tile, int sub, int j, int l31, int h) {
-  return *reinterpret_cast<const u32x4*>(tile + (sub * 32 + l31) * RS + (16 * j + 8 * h) * 2);
+// Chunk (16 bytes) permutation of a staged row: chunk c of row r lies in slot c ^ swz(r).  Eight consecutive rows get
+// eight different even values (row reads: eight lanes of a b128 read hit different slots), four consecutive rows differ
+// above bit 0 (transposing reads: the two chunks a row contributes lie side by side).
+template <int D>
+__device__ __forceinline__ int swz(int r) {
+  return D == 128 ? ((r & 7) << 1) | ((r >> 3) & 1) : ((r & 3) << 1) | ((r >> 2) & 1);
 }
-// A fragment of a transposed LDS tile [rows e][64 columns]: row et*32 + lane%32, columns of step (sub, jj) in the
-// accumulator-register order (see the file header)
-__device__ __forceinline__ u32x4 frag_cols(const char* tile, int et, int sub, int jj, int l31, int h) {
-  const char* p = tile + (et * 32 + l31) * TS + (sub * 32 + 16 * jj + 4 * h) * 2;
-  const u32x2 lo = *reinterpret_cast<const u32x2*>(p), hi = *reinterpret_cast<const u32x2*>(p + 16);
-  return u32x4{lo.x, lo.y, hi.x, hi.y};
+
+// Rows [64 blk, 64 blk + 64) of a [rows][D] operand (row stride ld_bytes, described by rs) to an LDS tile, by four waves.
+template <int D>
+__device__ __forceinline__ void stage_block(__amdgpu_buffer_rsrc_t rs, int blk, unsigned ld_bytes, char* tile, int wave, int lane) {
+  constexpr int CPR = D / 8, RPI = 64 / CPR, NI = KB / RPI / 4;  // chunks per row, rows per instruction, instructions per wave
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int r0 = (wave * NI + i) * RPI, r = r0 + lane / CPR;
+    const unsigned off = (unsigned)(blk * KB + r) * ld_bytes + (unsigned)(((lane % CPR) ^ swz<D>(r)) * 16);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(void, tile + r0 * (D * 2)), 16, (int)off, 0, 0, 0);
+  }
 }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const bf* base, int rows, unsigned ld_bytes, int D) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf*>(base), 0, (int)((unsigned)(rows - 1) * ld_bytes + (unsigned)D * 2u), 0x00020000);
+}
+// this wave's loads have landed, and every wave is past its reads of the other buffer
+__device__ __forceinline__ void block_ready() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Lane offsets into a staged tile: row reads (row lane%32, chunk 2j + lane/32) and the two transposing reads.
+template <int D>
+struct TileLane {
+  int row, t_lo, t_hi;
+  __device__ __forceinline__ explicit TileLane(int lane) {
+    const int l31 = lane & 31, h = lane >> 5, q = lane & 15;
+    row = l31 * (D * 2) + ((h ^ swz<D>(l31)) << 4);
+    const int r_lo = 4 * h + (q >> 2), r_hi = r_lo + 8, c = ((l31 >> 4) << 1) | ((q & 3) >> 1);
+    t_lo = r_lo * (D * 2) + ((c ^ swz<D>(r_lo)) << 4) + (q & 1) * 8;
+    t_hi = r_hi * (D * 2) + ((c ^ swz<D>(r_hi)) << 4) + (q & 1) * 8;
+  }
+};
+// A fragment, rows sub*32 + lane%32, k = 16j + 8h .. +7
+template <int D>
+__device__ __forceinline__ u32x4 frag_rows(const char* tile, const TileLane<D>& t, int sub, int j) {
+  return *reinterpret_cast<const u32x4*>(tile + sub * (32 * D * 2) + (t.row ^ (j << 5)));
+}
+// A fragment of the transposed tile: row (= column of the tile) et*32 + lane%32, contraction slots of step (sub, jj)
+template <int D>
+__device__ __forceinline__ u32x4 frag_cols(char* tile, const TileLane<D>& t, int et, int sub, int jj) {
+  char* p = tile + (sub * 32 + jj * 16) * (D * 2);
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p + (t.t_lo ^ (et << 6))));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p + (t.t_hi ^ (et << 6))));
+  return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ unsigned cvt2(float lo, float hi) { return __builtin_bit_cast(unsigned, f16x2{(_Float16)lo, (_Float16)hi}); }
+__device__ __forceinline__ float clamp_h(float x) { return __builtin_amdgcn_fmed3f(x, -65504.f, 65504.f); }
+// eight accumulator registers to a B fragment; CLAMP where the values may leave half's range
+template <bool CLAMP>
 __device__ __forceinline__ u32x4 pack8(const f32x16& a, int o) {
-  return u32x4{PACK2(a[o], a[o + 1]), PACK2(a[o + 2], a[o + 3]), PACK2(a[o + 4], a[o + 5]), PACK2(a[o + 6], a[o + 7])};
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    r[i] = CLAMP ? cvt2(clamp_h(a[o + 2 * i]), clamp_h(a[o + 2 * i + 1])) : cvt2(a[o + 2 * i], a[o + 2 * i + 1]);
+  return r;
 }
 __device__ __forceinline__ f32x16 zero16f() {
   f32x16 z;
@@ -52,23 +116,36 @@ __device__ __forceinline__ f32x16 zero16f() {
   for (int v = 0; v < 16; ++v) z[v] = 0.f;
   return z;
 }
+// maximum over the two lanes (l, l + 32) that share a column
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 // -------------------------------------------------------------------------------------------- forward
-// grid (ceil(S/128), Bf*n_q); a workgroup owns 128 queries of one head, wave w the 32 queries 32w..32w+31.
+// grid (Bf*n_q, ceil(S/128)): the blocks with the longest causal span of all heads start first, and (with a multiple of
+// eight heads) all blocks of a head run on one XCD, whose L2 then holds the head's K and V.  A workgroup owns 128 queries
+// of one head, wave w the 32 queries 32w..32w+31.
 template <int D>
-__global__ void __launch_bounds__(256, 2) k_attn_fwd(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ vT,
-                                                  bf* __restrict__ o, float* __restrict__ lse, int S, int nq, int nkv,
+__global__ void __launch_bounds__(256, 2) k_attn_fwd(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
+                                                  bf* __restrict__ o, float* __restrict__ lse2, int S, int nq, int nkv,
                                                   float scale_log2) {
-  constexpr int RS = D * 2 + 16, NJ = D / 16, NE = D / 32, CPT = D / 32;
-  extern __shared__ __align__(16) char smem[];
-  char* sK = smem;             // [KB][D] keys x head_dim
-  char* sV = smem + KB * RS;   // [D][KB] head_dim x keys
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
-  const int qb = gridDim.x - 1 - blockIdx.x;  // the blocks with the longest causal span first
-  const int z = blockIdx.y, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
-  const int QD = nq * D, KVD = nkv * D;
+  constexpr int NJ = D / 16, NE = D / 32, TILE = KB * D * 2;
+  extern __shared__ __align__(1024) char smem[];  // two buffers of (K, V)
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qb = gridDim.y - 1 - blockIdx.y;
+  const int z = blockIdx.x, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
+  const int QD = nq * D;
+  const unsigned kv_ld = (unsigned)(nkv * D) * 2u;
   const int q0 = qb * 128 + wave * 32, qrow = q0 + l31, qc = min(qrow, S - 1);
+  const TileLane<D> tl(lane);
+  const auto rsK = rows_rsrc(k + (long long)b * S * nkv * D + hk * D, S, kv_ld, D);
+  const auto rsV = rows_rsrc(v + (long long)b * S * nkv * D + hk * D, S, kv_ld, D);
 
+  const int nkb = min(qb * 128 + 127, S - 1) / KB + 1;
+  stage_block<D>(rsK, 0, kv_ld, smem, wave, lane);
+  stage_block<D>(rsV, 0, kv_ld, smem + TILE, wave, lane);
   u32x4 Qf[NJ];
   {
     const bf* qp = q + ((long long)b * S + qc) * QD + head * D + 8 * h;
@@ -78,84 +155,69 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(const bf* __restrict__ q, c
   f32x16 O[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) O[e] = zero16f();
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;  // maximum of the raw scores; sum over this lane half's keys
 
-  const int nkb = min(qb * 128 + 127, S - 1) / KB + 1;
-  const bf* kbase = k + (long long)b * S * KVD + hk * D;
-  const bf* vbase = vT + (long long)(b * nkv + hk) * D * S;
-  // per-thread chunk coordinates of the two tiles (CPT 16-byte chunks each)
-  u32x4 pk[CPT], pv[CPT];
-#define FWD_FETCH(kb_)                                                                                        \
-  _Pragma("unroll") for (int i = 0; i < CPT; ++i) {                                                           \
-    const int c = tid + 256 * i;                                                                              \
-    const int kr = c / (D / 8), kc = c - kr * (D / 8);                                                        \
-    pk[i] = *reinterpret_cast<const u32x4*>(kbase + (long long)min((kb_) * KB + kr, S - 1) * KVD + kc * 8);   \
-    const int ve = c >> 3, vc = c & 7;                                                                        \
-    pv[i] = *reinterpret_cast<const u32x4*>(vbase + (long long)ve * S + min((kb_) * KB + vc * 8, S - 8));     \
-  }
-  FWD_FETCH(0)
   for (int kb = 0; kb < nkb; ++kb) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = tid + 256 * i;
-      const int kr = c / (D / 8), kc = c - kr * (D / 8);
-      *reinterpret_cast<u32x4*>(sK + kr * RS + kc * 16) = pk[i];
-      const int ve = c >> 3, vc = c & 7;
-      *reinterpret_cast<u32x4*>(sV + ve * TS + vc * 16) = pv[i];
+    block_ready();
+    char* sK = smem + (kb & 1) * (2 * TILE);
+    char* sV = sK + TILE;
+    if (kb + 1 < nkb) {
+      char* nx = smem + ((kb + 1) & 1) * (2 * TILE);
+      stage_block<D>(rsK, kb + 1, kv_ld, nx, wave, lane);
+      stage_block<D>(rsV, kb + 1, kv_ld, nx + TILE, wave, lane);
     }
-    __syncthreads();
-    if (kb + 1 < nkb) { FWD_FETCH(kb + 1) }
     if (kb * KB > q0 + 31) continue;  // every key of the block is past this wave's queries
     f32x16 sc[2];
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       sc[sub] = zero16f();
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) sc[sub] = mma32(frag_rows<RS>(sK, sub, j, l31, h), Qf[j], sc[sub]);
+      for (int j = 0; j < NJ; ++j) sc[sub] = mma32(frag_rows<D>(sK, tl, sub, j), Qf[j], sc[sub]);
     }
-    float mx = -INFINITY;
+    if (kb * KB + KB - 1 > q0) {  // the block crosses the diagonal of this wave's queries
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv)
+          if (kb * KB + sub * 32 + 8 * (vv >> 2) + 4 * h + (vv & 3) > qrow) sc[sub][vv] = -INFINITY;
+    }
+    float mx = m_run;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int key = kb * KB + sub * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        const float s = key > qrow ? -INFINITY : sc[sub][v] * scale_log2;
-        sc[sub][v] = s;
-        mx = fmaxf(mx, s);
-      }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      for (int vv = 0; vv < 16; ++vv) mx = fmaxf(mx, sc[sub][vv]);
     // finite: block 0 holds key 0 <= every query, and later blocks inherit a finite running maximum
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = exp2f(m_run - m_new);
-    float rs = 0.f;
+    mx = max_halves(mx);
+    if (__any(mx > m_run)) {
+      const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * scale_log2);
+      l_run *= alpha;
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) O[e][vv] *= alpha;
+      m_run = mx;
+    }
+    const float off = -m_run * scale_log2;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float p = exp2f(sc[sub][v] - m_new);
-        sc[sub][v] = p;
-        rs += p;
+      for (int vv = 0; vv < 16; ++vv) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sc[sub][vv], scale_log2, off));
+        sc[sub][vv] = p;
+        l_run += p;
       }
-    rs += __shfl_xor(rs, 32, 64);
-    l_run = l_run * alpha + rs;
-    m_run = m_new;
-#pragma unroll
-    for (int e = 0; e < NE; ++e)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) O[e][v] *= alpha;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
-        const u32x4 pf = pack8(sc[sub], 8 * jj);
+        const u32x4 pf = pack8<false>(sc[sub], 8 * jj);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) O[e] = mma32(frag_cols(sV, e, sub, jj, l31, h), pf, O[e]);
+        for (int e = 0; e < NE; ++e) O[e] = mma32(frag_cols<D>(sV, tl, e, sub, jj), pf, O[e]);
       }
   }
-#undef FWD_FETCH
+  const float l_all = l_run + __shfl_xor(l_run, 32, 64);
   if (qrow < S) {
-    const float inv = 1.f / l_run;
+    const float inv = 1.f / l_all;
     bf* op = o + ((long long)b * S + qrow) * QD + head * D;
 #pragma unroll
     for (int e = 0; e < NE; ++e)
@@ -163,31 +225,36 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(const bf* __restrict__ q, c
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<u32x2*>(op + e * 32 + 8 * g + 4 * h) =
             u32x2{PACK2(O[e][4 * g] * inv, O[e][4 * g + 1] * inv), PACK2(O[e][4 * g + 2] * inv, O[e][4 * g + 3] * inv)};
-    if (h == 0) lse[(long long)z * S + qrow] = (m_run + log2f(l_run)) * kLn2;
+    if (h == 0) lse2[(long long)z * S + qrow] = fmaf(m_run, scale_log2, log2f(l_all));
   }
 }
 
 // -------------------------------------------------------------------------------------------- backward: dQ
-// grid (ceil(S/128), Bf*n_q); same ownership as the forward kernel.  dQ^T[e][q] += K^T[e][k] dS^T[k][q].
+// Same grid and ownership as the forward kernel.  dQ^T[e][q] += K^T[e][k] dS^T[k][q].
 // Also computes delta[q] = sum_e dO[q][e] O[q][e] and stores it.
 template <int D>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
-                                                     const bf* __restrict__ kT, const bf* __restrict__ dO,
-                                                     const bf* __restrict__ o, const float* __restrict__ lse,
-                                                     float* __restrict__ delta, bf* __restrict__ dq, int S, int nq, int nkv,
-                                                     float scale, float scale_log2, int* flag) {
-  constexpr int RS = D * 2 + 16, NJ = D / 16, NE = D / 32, CPT = D / 32;
-  extern __shared__ __align__(16) char smem[];
-  char* sK = smem;                  // [KB][D]
-  char* sV = smem + KB * RS;        // [KB][D]
-  char* sKT = smem + 2 * KB * RS;   // [D][KB]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
-  const int qb = gridDim.x - 1 - blockIdx.x;
-  const int z = blockIdx.y, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
-  const int QD = nq * D, KVD = nkv * D;
+                                                     const bf* __restrict__ dO, const bf* __restrict__ o,
+                                                     const float* __restrict__ lse2, float* __restrict__ delta, bf* __restrict__ dq,
+                                                     int S, int nq, int nkv, float scale, float scale_log2, int* flag) {
+  constexpr int NJ = D / 16, NE = D / 32, TILE = KB * D * 2;
+  extern __shared__ __align__(1024) char smem[];  // two buffers of (K, V)
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qb = gridDim.y - 1 - blockIdx.y;
+  const int z = blockIdx.x, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
+  const int QD = nq * D;
+  const unsigned kv_ld = (unsigned)(nkv * D) * 2u;
   const int q0 = qb * 128 + wave * 32, qrow = q0 + l31, qc = min(qrow, S - 1);
+  const TileLane<D> tl(lane);
+  const auto rsK = rows_rsrc(k + (long long)b * S * nkv * D + hk * D, S, kv_ld, D);
+  const auto rsV = rows_rsrc(v + (long long)b * S * nkv * D + hk * D, S, kv_ld, D);
+  const int nkb = min(qb * 128 + 127, S - 1) / KB + 1;
+  stage_block<D>(rsK, 0, kv_ld, smem, wave, lane);
+  stage_block<D>(rsV, 0, kv_ld, smem + TILE, wave, lane);
 
   u32x4 Qf[NJ], Gf[NJ];  // this lane's query row and its dO row as B operands
+  float dl = 0.f;
   {
     const long long ro = ((long long)b * S + qc) * QD + head * D + 8 * h;
 #pragma unroll
@@ -195,16 +262,11 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q
       Qf[j] = *reinterpret_cast<const u32x4*>(q + ro + 16 * j);
       Gf[j] = *reinterpret_cast<const u32x4*>(dO + ro + 16 * j);
     }
-  }
-  const float lse2 = lse[(long long)z * S + qc] * kLog2e;
-  // delta = rowsum(dO * O) of this lane's query: the lane holds half of the row's dO (8 of every 16 elements), its
-  // partner lane the other half.  Stored for the dK / dV kernel, which runs after this one.
-  float dl = 0.f;
-  {
-    const bf* op = o + ((long long)b * S + qc) * QD + head * D + 8 * h;
+    // delta = rowsum(dO * O) of this lane's query: the lane holds half of the row's dO (8 of every 16 elements), its
+    // partner lane the other half.  Stored for the dK / dV kernel, which runs after this one.
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const u32x4 ov = *reinterpret_cast<const u32x4*>(op + 16 * j);
+      const u32x4 ov = *reinterpret_cast<const u32x4*>(o + ro + 16 * j);
       float gf[8], of[8];
       UNPACK8(uint4{Gf[j].x, Gf[j].y, Gf[j].z, Gf[j].w}, gf);
       UNPACK8(uint4{ov.x, ov.y, ov.z, ov.w}, of);
@@ -214,63 +276,45 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q
     dl += __shfl_xor(dl, 32, 64);
     if (h == 0 && qrow < S) delta[(long long)z * S + qrow] = dl;
   }
+  const float off = -lse2[(long long)z * S + qc];
   f32x16 dQ[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) dQ[e] = zero16f();
 
-  const int nkb = min(qb * 128 + 127, S - 1) / KB + 1;
-  const bf* kbase = k + (long long)b * S * KVD + hk * D;
-  const bf* vbase = v + (long long)b * S * KVD + hk * D;
-  const bf* ktbase = kT + (long long)(b * nkv + hk) * D * S;
-  u32x4 pk[CPT], pv[CPT], pt[CPT];
-#define DQ_FETCH(kb_)                                                                                         \
-  _Pragma("unroll") for (int i = 0; i < CPT; ++i) {                                                           \
-    const int c = tid + 256 * i;                                                                              \
-    const int kr = c / (D / 8), kc = c - kr * (D / 8);                                                        \
-    const long long ro = (long long)min((kb_) * KB + kr, S - 1) * KVD + kc * 8;                               \
-    pk[i] = *reinterpret_cast<const u32x4*>(kbase + ro);                                                      \
-    pv[i] = *reinterpret_cast<const u32x4*>(vbase + ro);                                                      \
-    const int te = c >> 3, tc = c & 7;                                                                        \
-    pt[i] = *reinterpret_cast<const u32x4*>(ktbase + (long long)te * S + min((kb_) * KB + tc * 8, S - 8));    \
-  }
-  DQ_FETCH(0)
   for (int kb = 0; kb < nkb; ++kb) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = tid + 256 * i;
-      const int kr = c / (D / 8), kc = c - kr * (D / 8);
-      *reinterpret_cast<u32x4*>(sK + kr * RS + kc * 16) = pk[i];
-      *reinterpret_cast<u32x4*>(sV + kr * RS + kc * 16) = pv[i];
-      const int te = c >> 3, tc = c & 7;
-      *reinterpret_cast<u32x4*>(sKT + te * TS + tc * 16) = pt[i];
+    block_ready();
+    char* sK = smem + (kb & 1) * (2 * TILE);
+    char* sV = sK + TILE;
+    if (kb + 1 < nkb) {
+      char* nx = smem + ((kb + 1) & 1) * (2 * TILE);
+      stage_block<D>(rsK, kb + 1, kv_ld, nx, wave, lane);
+      stage_block<D>(rsV, kb + 1, kv_ld, nx + TILE, wave, lane);
     }
-    __syncthreads();
-    if (kb + 1 < nkb) { DQ_FETCH(kb + 1) }
     if (kb * KB > q0 + 31) continue;
+    const bool diag = kb * KB + KB - 1 > q0;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 sc = zero16f(), dp = zero16f();
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        sc = mma32(frag_rows<RS>(sK, sub, j, l31, h), Qf[j], sc);
-        dp = mma32(frag_rows<RS>(sV, sub, j, l31, h), Gf[j], dp);
+        sc = mma32(frag_rows<D>(sK, tl, sub, j), Qf[j], sc);
+        dp = mma32(frag_rows<D>(sV, tl, sub, j), Gf[j], dp);
+      }
+      if (diag) {
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv)
+          if (kb * KB + sub * 32 + 8 * (vv >> 2) + 4 * h + (vv & 3) > qrow) sc[vv] = -INFINITY;
       }
 #pragma unroll
-      for (int vv = 0; vv < 16; ++vv) {
-        const int key = kb * KB + sub * 32 + 8 * (vv >> 2) + 4 * h + (vv & 3);
-        const float p = key > qrow ? 0.f : exp2f(sc[vv] * scale_log2 - lse2);
-        sc[vv] = p * (dp[vv] - dl);
-      }
+      for (int vv = 0; vv < 16; ++vv) sc[vv] = __builtin_amdgcn_exp2f(fmaf(sc[vv], scale_log2, off)) * (dp[vv] - dl);
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
-        const u32x4 df = pack8(sc, 8 * jj);
+        const u32x4 df = pack8<true>(sc, 8 * jj);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) dQ[e] = mma32(frag_cols(sKT, e, sub, jj, l31, h), df, dQ[e]);
+        for (int e = 0; e < NE; ++e) dQ[e] = mma32(frag_cols<D>(sK, tl, e, sub, jj), df, dQ[e]);
       }
     }
   }
-#undef DQ_FETCH
   if (qrow < S) {
     bf* op = dq + ((long long)b * S + qrow) * QD + head * D;
     bool over = false;
@@ -285,28 +329,39 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q
 }
 
 // -------------------------------------------------------------------------------------------- backward: dK, dV
-// grid (ceil(S/128), Bf*n_q); a workgroup owns 128 keys as seen by one QUERY head, wave w the keys 32w..32w+31, and
+// Same grid; a workgroup owns 128 keys as seen by one QUERY head, wave w the keys 32w..32w+31, and
 // streams the queries from its first key to the end of the sequence.
 //   dV^T[e][k] += dO^T[e][q] P[q][k],   dK^T[e][k] += Q^T[e][q] dS[q][k]
 template <int D>
-__global__ void __launch_bounds__(256) k_attn_bwd_dkv(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
-                                                      const bf* __restrict__ qT, const bf* __restrict__ dO,
-                                                      const bf* __restrict__ dOT, const float* __restrict__ lse,
+__global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
+                                                      const bf* __restrict__ dO, const float* __restrict__ lse2,
                                                       const float* __restrict__ delta, bf* __restrict__ dkq,
                                                       bf* __restrict__ dvq, int S, int nq, int nkv, float scale,
                                                       float scale_log2, int* flag) {
-  constexpr int RS = D * 2 + 16, NJ = D / 16, NE = D / 32, CPT = D / 32;
-  extern __shared__ __align__(16) char smem[];
-  char* sQ = smem;                              // [KB][D] queries x head_dim
-  char* sG = smem + KB * RS;                    // [KB][D] dO
-  char* sQT = smem + 2 * KB * RS;               // [D][KB]
-  char* sGT = smem + 2 * KB * RS + D * TS;      // [D][KB]
-  float* sL = reinterpret_cast<float*>(smem + 2 * KB * RS + 2 * D * TS);  // [KB] lse * log2(e), then [KB] delta
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
-  const int kvb = blockIdx.x;  // block 0 has the longest span of queries and starts first
-  const int z = blockIdx.y, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
+  constexpr int NJ = D / 16, NE = D / 32, TILE = KB * D * 2;
+  constexpr int BUF = 2 * TILE + 2 * KB * 4;  // Q, dO, then lse2 and delta of the block's queries
+  extern __shared__ __align__(1024) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kvb = blockIdx.y;  // block 0 has the longest span of queries
+  const int z = blockIdx.x, b = z / nq, head = z - b * nq, hk = head / (nq / nkv);
   const int QD = nq * D, KVD = nkv * D;
+  const unsigned q_ld = (unsigned)QD * 2u;
   const int k0 = kvb * 128 + wave * 32, krow = k0 + l31, kc_ = min(krow, S - 1);
+  const TileLane<D> tl(lane);
+  const auto rsQ = rows_rsrc(q + (long long)b * S * QD + head * D, S, q_ld, D);
+  const auto rsG = rows_rsrc(dO + (long long)b * S * QD + head * D, S, q_ld, D);
+  const auto rsL = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>((wave & 1 ? delta : lse2) + (long long)z * S), 0, S * 4, 0x00020000);
+  const int qb0 = kvb * 128 / KB, nqb = (S + KB - 1) / KB;
+#define KV_STAGE(qb_)                                                                                                     \
+  do {                                                                                                                    \
+    char* nx_ = smem + ((qb_) & 1) * BUF;                                                                                 \
+    stage_block<D>(rsQ, qb_, q_ld, nx_, wave, lane);                                                                      \
+    stage_block<D>(rsG, qb_, q_ld, nx_ + TILE, wave, lane);                                                               \
+    if (wave < 2)                                                                                                         \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, LDS_PTR(void, nx_ + 2 * TILE + wave * (KB * 4)), 4, ((qb_) * KB + lane) * 4, 0, 0, 0); \
+  } while (0)
+  KV_STAGE(qb0);
 
   u32x4 Kf[NJ], Vf[NJ];  // this lane's key and value rows as B operands
   {
@@ -321,57 +376,24 @@ __global__ void __launch_bounds__(256) k_attn_bwd_dkv(const bf* __restrict__ q, 
 #pragma unroll
   for (int e = 0; e < NE; ++e) dV[e] = zero16f(), dK[e] = zero16f();
 
-  const int qb0 = kvb * 128 / KB, nqb = (S + KB - 1) / KB;
-  const bf* qbase = q + (long long)b * S * QD + head * D;
-  const bf* gbase = dO + (long long)b * S * QD + head * D;
-  const bf* qtbase = qT + (long long)(b * nq + head) * D * S;
-  const bf* gtbase = dOT + (long long)(b * nq + head) * D * S;
-  const float* lbase = lse + (long long)z * S;
-  const float* dbase = delta + (long long)z * S;
-  u32x4 pq[CPT], pg[CPT], pqt[CPT], pgt[CPT];
-  float pl;
-#define KV_FETCH(qb_)                                                                                          \
-  _Pragma("unroll") for (int i = 0; i < CPT; ++i) {                                                            \
-    const int c = tid + 256 * i;                                                                               \
-    const int rr = c / (D / 8), rc = c - rr * (D / 8);                                                         \
-    const long long ro = (long long)min((qb_) * KB + rr, S - 1) * QD + rc * 8;                                 \
-    pq[i] = *reinterpret_cast<const u32x4*>(qbase + ro);                                                       \
-    pg[i] = *reinterpret_cast<const u32x4*>(gbase + ro);                                                       \
-    const int te = c >> 3, tc = c & 7;                                                                         \
-    const long long to = (long long)te * S + min((qb_) * KB + tc * 8, S - 8);                                  \
-    pqt[i] = *reinterpret_cast<const u32x4*>(qtbase + to);                                                     \
-    pgt[i] = *reinterpret_cast<const u32x4*>(gtbase + to);                                                     \
-  }                                                                                                            \
-  {                                                                                                            \
-    const int r = min((qb_) * KB + (tid & 63), S - 1);                                                         \
-    pl = tid < 64 ? lbase[r] * kLog2e : dbase[r];                                                              \
-  }
-  KV_FETCH(qb0)
   for (int qb = qb0; qb < nqb; ++qb) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = tid + 256 * i;
-      const int rr = c / (D / 8), rc = c - rr * (D / 8);
-      *reinterpret_cast<u32x4*>(sQ + rr * RS + rc * 16) = pq[i];
-      *reinterpret_cast<u32x4*>(sG + rr * RS + rc * 16) = pg[i];
-      const int te = c >> 3, tc = c & 7;
-      *reinterpret_cast<u32x4*>(sQT + te * TS + tc * 16) = pqt[i];
-      *reinterpret_cast<u32x4*>(sGT + te * TS + tc * 16) = pgt[i];
-    }
-    if (tid < 128) sL[tid] = pl;
-    __syncthreads();
-    if (qb + 1 < nqb) { KV_FETCH(qb + 1) }
+    block_ready();
+    char* sQ = smem + (qb & 1) * BUF;
+    char* sG = sQ + TILE;
+    const float* sL = reinterpret_cast<const float*>(sQ + 2 * TILE);
+    if (qb + 1 < nqb) KV_STAGE(qb + 1);
     if (qb * KB + KB - 1 < k0) continue;  // every query of the block precedes this wave's keys
-#pragma unroll
+    const bool diag = qb * KB < k0 + 31;
+#pragma unroll 1
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 sc = zero16f(), dp = zero16f();
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        sc = mma32(frag_rows<RS>(sQ, sub, j, l31, h), Kf[j], sc);
-        dp = mma32(frag_rows<RS>(sG, sub, j, l31, h), Vf[j], dp);
+        sc = mma32(frag_rows<D>(sQ, tl, sub, j), Kf[j], sc);
+        dp = mma32(frag_rows<D>(sG, tl, sub, j), Vf[j], dp);
       }
-      // rows of the accumulator are queries: their lse and delta come in runs of four
+      // rows of the accumulator are queries: their lse and delta come in runs of four.  Queries past the sequence have
+      // zero rows in Q and dO (lse and delta zero as well), so whatever p is there adds nothing.
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float4 l4 = *reinterpret_cast<const float4*>(sL + sub * 32 + 8 * g + 4 * h);
@@ -380,24 +402,24 @@ __global__ void __launch_bounds__(256) k_attn_bwd_dkv(const bf* __restrict__ q, 
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const int vv = 4 * g + c;
-          const int qg = qb * KB + sub * 32 + 8 * g + 4 * h + c;
-          const float p = (qg < krow || qg >= S) ? 0.f : exp2f(sc[vv] * scale_log2 - ls[c]);
+          float p = __builtin_amdgcn_exp2f(fmaf(sc[vv], scale_log2, -ls[c]));
+          if (diag && qb * KB + sub * 32 + 8 * g + 4 * h + c < krow) p = 0.f;
           sc[vv] = p;
           dp[vv] = p * (dp[vv] - ds[c]);
         }
       }
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
-        const u32x4 pf = pack8(sc, 8 * jj), df = pack8(dp, 8 * jj);
+        const u32x4 pf = pack8<false>(sc, 8 * jj), df = pack8<true>(dp, 8 * jj);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-          dV[e] = mma32(frag_cols(sGT, e, sub, jj, l31, h), pf, dV[e]);
-          dK[e] = mma32(frag_cols(sQT, e, sub, jj, l31, h), df, dK[e]);
+          dV[e] = mma32(frag_cols<D>(sG, tl, e, sub, jj), pf, dV[e]);
+          dK[e] = mma32(frag_cols<D>(sQ, tl, e, sub, jj), df, dK[e]);
         }
       }
     }
   }
-#undef KV_FETCH
+#undef KV_STAGE
   if (krow < S) {
     const long long ro = ((long long)b * S + krow) * QD + head * D;
     bool over = false;
@@ -416,18 +438,16 @@ __global__ void __launch_bounds__(256) k_attn_bwd_dkv(const bf* __restrict__ q, 
 }
 
 template <int D>
-constexpr int fwd_lds() { return KB * (D * 2 + 16) + D * TS; }
+constexpr int fwd_lds() { return 4 * KB * D * 2; }
 template <int D>
-constexpr int dq_lds() { return 2 * KB * (D * 2 + 16) + D * TS; }
-template <int D>
-constexpr int dkv_lds() { return 2 * KB * (D * 2 + 16) + 2 * D * TS + 2 * KB * 4; }
+constexpr int dkv_lds() { return 2 * (2 * KB * D * 2 + 2 * KB * 4); }
 
 template <int D>
 harli_status set_attrs() {
   static bool done = false;
   if (done) return HARLI_OK;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_fwd<D>), hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds<D>()) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bwd_dq<D>), hipFuncAttributeMaxDynamicSharedMemorySize, dq_lds<D>()) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bwd_dq<D>), hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds<D>()) != hipSuccess ||
       hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bwd_dkv<D>), hipFuncAttributeMaxDynamicSharedMemorySize, dkv_lds<D>()) != hipSuccess)
     return fail(HARLI_ERR_HIP, "attention: could not raise the dynamic LDS limit");
   done = true;
@@ -436,44 +456,46 @@ harli_status set_attrs() {
 
 harli_status check_shape(int Bf, int S, int nq, int nkv, int d) {
   if (!ft_attn_supported(d)) return fail(HARLI_ERR_INVALID, "attention: head_dim %d is not 64 or 128", d);
+  // the kernels address a sequence's rows with 32-bit byte offsets below 2^31
+  if ((long long)(S + 64) * nq * d * 2 >= (1ll << 31)) return fail(HARLI_ERR_INVALID, "attention: a sequence of %d tokens is 2 GiB or more", S);
   if (Bf < 1 || S < 8 || (S & 7) || nq < 1 || nkv < 1 || nq % nkv) return fail(HARLI_ERR_INVALID, "attention: bad shape");
   return HARLI_OK;
 }
 
 }  // namespace
 
-harli_status ft_attn_fwd(const bf* q, const bf* k, const bf* vT, bf* o, float* lse, int Bf, int S, int n_q, int n_kv, int d,
+harli_status ft_attn_fwd(const bf* q, const bf* k, const bf* v, bf* o, float* lse2, int Bf, int S, int n_q, int n_kv, int d,
                          hipStream_t st) {
   harli_status s = check_shape(Bf, S, n_q, n_kv, d);
   if (s != HARLI_OK) return s;
-  const dim3 grid((S + 127) / 128, Bf * n_q), blk(256);
+  const dim3 grid(Bf * n_q, (S + 127) / 128), blk(256);
   const float sl2 = kLog2e / sqrtf((float)d);
   if (d == 128) {
     if ((s = set_attrs<128>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_fwd<128>, grid, blk, fwd_lds<128>(), st, q, k, vT, o, lse, S, n_q, n_kv, sl2);
+    hipLaunchKernelGGL(k_attn_fwd<128>, grid, blk, fwd_lds<128>(), st, q, k, v, o, lse2, S, n_q, n_kv, sl2);
   } else {
     if ((s = set_attrs<64>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_fwd<64>, grid, blk, fwd_lds<64>(), st, q, k, vT, o, lse, S, n_q, n_kv, sl2);
+    hipLaunchKernelGGL(k_attn_fwd<64>, grid, blk, fwd_lds<64>(), st, q, k, v, o, lse2, S, n_q, n_kv, sl2);
   }
   return HARLI_OK;
 }
 
-harli_status ft_attn_bwd(const bf* q, const bf* k, const bf* v, const bf* o, const bf* qT, const bf* kT, const bf* dO,
-                         const bf* dOT, const float* lse, float* delta, bf* dq, bf* dkq, bf* dvq, int Bf, int S, int n_q,
+harli_status ft_attn_bwd(const bf* q, const bf* k, const bf* v, const bf* o, const bf* dO, const float* lse2, float* delta,
+                         bf* dq, bf* dkq, bf* dvq, int Bf, int S, int n_q,
                          int n_kv, int d, int* flag, hipStream_t st) {
   harli_status s = check_shape(Bf, S, n_q, n_kv, d);
   if (s != HARLI_OK) return s;
-  const dim3 grid((S + 127) / 128, Bf * n_q), blk(256);
+  const dim3 grid(Bf * n_q, (S + 127) / 128), blk(256);
   const float sc = 1.f / sqrtf((float)d), sl2 = kLog2e * sc;
   if (d == 128) {
     if ((s = set_attrs<128>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_bwd_dq<128>, grid, blk, dq_lds<128>(), st, q, k, v, kT, dO, o, lse, delta, dq, S, n_q, n_kv, sc, sl2, flag);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<128>, grid, blk, dkv_lds<128>(), st, q, k, v, qT, dO, dOT, lse, delta, dkq, dvq, S, n_q,
+    hipLaunchKernelGGL(k_attn_bwd_dq<128>, grid, blk, fwd_lds<128>(), st, q, k, v, dO, o, lse2, delta, dq, S, n_q, n_kv, sc, sl2, flag);
+    hipLaunchKernelGGL(k_attn_bwd_dkv<128>, grid, blk, dkv_lds<128>(), st, q, k, v, dO, lse2, delta, dkq, dvq, S, n_q,
                        n_kv, sc, sl2, flag);
   } else {
     if ((s = set_attrs<64>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_bwd_dq<64>, grid, blk, dq_lds<64>(), st, q, k, v, kT, dO, o, lse, delta, dq, S, n_q, n_kv, sc, sl2, flag);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<64>, grid, blk, dkv_lds<64>(), st, q, k, v, qT, dO, dOT, lse, delta, dkq, dvq, S, n_q,
+    hipLaunchKernelGGL(k_attn_bwd_dq<64>, grid, blk, fwd_lds<64>(), st, q, k, v, dO, o, lse2, delta, dq, S, n_q, n_kv, sc, sl2, flag);
+    hipLaunchKernelGGL(k_attn_bwd_dkv<64>, grid, blk, dkv_lds<64>(), st, q, k, v, dO, lse2, delta, dkq, dvq, S, n_q,
                        n_kv, sc, sl2, flag);
   }
   return HARLI_OK;

@@ -37,15 +37,6 @@ struct FtConvJobs {
   int* flag;  // device int or null: bit 8 is set when a value lay beyond the compute element's range
 };
 void ft_convert_jobs(const FtConvJobs& jobs, hipStream_t st);
-// head-wise transposes of [Bf*S, C] tensors (C = heads * d, S and C multiples of 8) into [Bf][C][S], up to three in one
-// launch
-struct TransposeJobs {
-  const bf* in[3];
-  bf* out[3];
-  int C[3];
-  int n;
-};
-void ft_transpose_heads(const TransposeJobs& jobs, int Bf, int S, hipStream_t st);
 // skinny NT GEMMs: C[M, N] = alpha * X[M, K] . Bm[N, K]^T, N <= 64 and N % 16 == 0 after padding by the caller's layout;
 // several such products with the same M and alpha in one launch (job = blockIdx.y).
 constexpr int kSkinnyMaxJobs = 4;

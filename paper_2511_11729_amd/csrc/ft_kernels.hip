@@ -133,37 +133,6 @@ __global__ void __launch_bounds__(256) k_rope(bf* x, int S, int heads, int d, co
   elem_flag(over, flag);
 }
 
-// ---------------------------------------------------------------- head-wise transposes (64 x 64 tiles through LDS)
-// Per sequence b: [S][heads*d] -> [heads*d][S].  Up to three tensors per launch (blockIdx.z = job * Bf + b).  Both
-// global sides move 16 bytes per lane (S and heads*d are multiples of 8); the transposition happens in the 2-byte LDS
-// writes.
-__global__ void __launch_bounds__(256) k_transpose_heads(TransposeJobs jobs, int Bf, int S) {
-  __shared__ __align__(16) bf tile[64][72];  // [column][row], rows padded to 144 bytes
-  const int job = blockIdx.z / Bf, b = blockIdx.z - job * Bf;
-  const int C = jobs.C[job];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  if (c0 >= C) return;
-  const bf* src = jobs.in[job] + (long long)b * S * C;
-  bf* dst = jobs.out[job] + (long long)b * S * C;
-  const int t = threadIdx.x, q8 = (t & 7) * 8, p = t >> 3;
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = p + 32 * pass;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r0 + r < S && c0 + q8 < C) v = *reinterpret_cast<const uint4*>(src + (long long)(r0 + r) * C + c0 + q8);
-    const unsigned wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[q8 + e][r] = (bf)(wv[e >> 1] >> (16 * (e & 1)));
-  }
-  __syncthreads();
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int c = p + 32 * pass;
-    if (c0 + c < C && r0 + q8 < S)
-      *reinterpret_cast<uint4*>(dst + (long long)(c0 + c) * S + r0 + q8) = *reinterpret_cast<const uint4*>(&tile[c][q8]);
-  }
-}
-
 // ---------------------------------------------------------------- gradient scaling
 // The backward pass is linear in dY, so dY is multiplied by a power of two sigma that brings its
 // largest magnitude to 2^8 before it is rounded to 16 bits, and 1/sigma is applied where the
@@ -538,12 +507,6 @@ void ft_scale_to_e(const float* x, bf* y, long long n, float* scale, int parity,
   hipLaunchKernelGGL(k_amax, dim3(std::min(nblk(n / 4, 1024), 1024u)), dim3(256), 0, st, x, n / 4, bits + (parity & 1));
   hipLaunchKernelGGL(k_f32_to_e_scaled, dim3(nblk(n / 4, 256)), dim3(256), 0, st, x, y, n / 4, bits + (parity & 1),
                      bits + ((parity & 1) ^ 1), scale, target_log2);
-}
-void ft_transpose_heads(const TransposeJobs& jobs, int Bf, int S, hipStream_t st) {
-  if (jobs.n < 1) return;
-  int cmax = 0;
-  for (int i = 0; i < jobs.n; ++i) cmax = std::max(cmax, jobs.C[i]);
-  hipLaunchKernelGGL(k_transpose_heads, dim3((cmax + 63) / 64, (S + 63) / 64, Bf * jobs.n), dim3(256), 0, st, jobs, Bf, S);
 }
 void ft_skinny_nt_multi(const SkinnyNtJobs& jobs, int M, float alpha, int* flag, hipStream_t st) {
   if (jobs.n < 1) return;

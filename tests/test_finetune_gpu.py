@@ -157,3 +157,12 @@ def test_biases_small_shape_fp32_storage_and_bf16():
         m = dataclasses.replace(w.model, dtype=dtype, qkv_bias=True)
         case = FinetuneCase(w, m, wl.LoraCfg(8, 16.0, ("q", "k", "v", "o")), wl.FinetuneCfg(2, 128))
         check(case, "tiny layer with biases, %s storage" % dtype)
+
+
+@pytest.mark.parametrize("d,n_q,n_kv", [(128, 3, 1), (64, 4, 2)])
+@pytest.mark.parametrize("S", [8, 64, 72, 128, 136, 264])
+def test_attention_blocks_at_their_edges(S, d, n_q, n_kv):
+    """Sequences of one row group, of exactly one and just over one 64-row block, and just over one and two 128-query
+    workgroups; head counts that are no multiple of the eight XCDs, query groups of 2 and 3."""
+    check(build(0, lora=wl.LoraCfg(8, 16.0, ("q", "k", "v", "o")), ft=wl.FinetuneCfg(2, S), hidden=256, n_q=n_q, n_kv=n_kv,
+                head_dim=d, ffn=320), "S %d d %d" % (S, d))
