@@ -52,6 +52,10 @@ typedef struct {
   /* Ranges of K the tiles past the last full round of workgroups are cut into: 0 leaves the choice to the library, 1
    * never cuts, n > 1 asks for n (fewer where the contraction is too short). */
   int32_t ksplit;
+  /* epi 4: rotary embedding on the 16-bit columns of the tiles below rope_tiles; rope: device, (cos, sin) pairs
+   * [position][rope_d / 2], row m at position m % rope_S. */
+  int32_t rope_S, rope_d, rope_tiles;
+  const void* rope;
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 

@@ -548,7 +548,8 @@ class DbgGemm2Desc(C.Structure):
                 ("cb", C.c_void_p * 3), ("ldcb", C.c_int64 * 3), ("cf", C.c_void_p * 3), ("res", C.c_void_p * 3),
                 ("ldcf", C.c_int64 * 3), ("e0", C.c_void_p), ("e1", C.c_void_p), ("o0", C.c_void_p), ("o1", C.c_void_p),
                 ("lde", C.c_int64), ("overflow_flag", C.c_void_p), ("tflops", C.POINTER(C.c_double)),
-                ("shader_mhz", C.POINTER(C.c_double)), ("n_cu", C.c_int32), ("ksplit", C.c_int32)]
+                ("shader_mhz", C.POINTER(C.c_double)), ("n_cu", C.c_int32), ("ksplit", C.c_int32),
+                ("rope_S", C.c_int32), ("rope_d", C.c_int32), ("rope_tiles", C.c_int32), ("rope", C.c_void_p)]
 
 
 def decode_tiled_min_batch() -> int:
@@ -583,7 +584,8 @@ def dbg_gemm2_plan(M: int, tiles_n: int, tile_rows: int, n_cu: int) -> dict:
 
 
 def dbg_gemm2(M, segs, outs, *, half=True, epi=0, alpha=1.0, tile_rows=0, reps=0, e0=None, e1=None, o0=None, o1=None, lde=0,
-              overflow_flag=None, stream=None, n_cu=0, ksplit=0):
+              overflow_flag=None, stream=None, n_cu=0, ksplit=0,
+              rope=None, rope_S=0, rope_d=0, rope_tiles=0):
     """Test hook for the finetune unit's weight GEMM.  segs: dicts with A (device [M, K], 16-bit), optional lda,
     B (device [rows, K] row-major weight side; the hook blocks it), optional B2 and pair, optional tile0 / tile1.
     outs: dicts with N, tile0 and cb (16-bit) or cf (+ res), optional ld.  Tiles are 256 columns (128 + 128 for
@@ -616,6 +618,7 @@ def dbg_gemm2(M, segs, outs, *, half=True, epi=0, alpha=1.0, tile_rows=0, reps=0
     d.overflow_flag = _ptr(overflow_flag)
     d.n_cu = n_cu
     d.ksplit = ksplit
+    d.rope, d.rope_S, d.rope_d, d.rope_tiles = _ptr(rope), rope_S, rope_d, rope_tiles
     t, f = C.c_double(0.0), C.c_double(0.0)
     if reps > 1:
         d.tflops, d.shader_mhz = C.pointer(t), C.pointer(f)

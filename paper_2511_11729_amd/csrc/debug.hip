@@ -106,6 +106,10 @@ extern "C" harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip
     g.clk = clk;
   }
   g.n_cu = d->n_cu > 0 ? d->n_cu : 0;
+  g.rope = static_cast<const float2*>(d->rope);
+  g.rope_S = d->rope_S;
+  g.rope_d = d->rope_d;
+  g.rope_tiles = d->rope_tiles;
   gemm2_force_tile_rows(d->tile_rows);
   gemm2_force_split(d->ksplit);
   if (d->ksplit != 1) {

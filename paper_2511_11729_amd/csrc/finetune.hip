@@ -55,8 +55,8 @@ struct FtWs {
      *dvq = nullptr, *dk = nullptr, *dv = nullptr, *gs[3] = {}, *An[kTargets] = {}, *Bn[kTargets] = {};
   float* part = nullptr;   // partial tiles of the weight GEMMs whose tiles are cut along K (gemm2.h)
   size_t part_bytes = 0;
-  float* scale = nullptr;  // [0] sigma, [1] 1/sigma, [2], [3] maxima of this and the next call: gradient scaling of the backward pass
-  int scale_parity = 0;
+  float2* rope = nullptr;  // [max_ft_tokens][d/2] (cos, sin)
+  float* scale = nullptr;  // [0] sigma, [1] 1/sigma of the backward pass, then kAmaxParts partial maxima (ft_scale_to_e)
   int Bf = 0, S = 0;
 };
 
@@ -142,7 +142,8 @@ harli_status make_ws(harli_ctx* c) {
   const size_t ad = al(maxdim * D.r * 2);  // one adapter matrix in the compute element, row-major (skinny products)
   const size_t adb = al(blocked_elems((long long)maxdim, D.r) * 2);  // ... in the weight GEMM's blocked order
   const size_t o_At = take(kTargets * ad), o_Bt = take(kTargets * adb);
-  const size_t o_An = take(kTargets * adb), o_Bn = take(kTargets * ad), o_scale = take(64);
+  const size_t o_An = take(kTargets * adb), o_Bn = take(kTargets * ad), o_scale = take((2 + kAmaxParts) * 4);
+  const size_t o_rope = take(T * D.d * 4);
   const size_t o_dyb = take(T * D.H * 2), o_da = take(T * D.F * 2), o_du = take(T * D.F * 2), o_dx1b = take(T * D.H * 2);
   const size_t o_dob = take(T * D.QD * 2), o_dq = take(T * D.QD * 2), o_dkq = take(T * D.QD * 2), o_dvq = take(T * D.QD * 2);
   const size_t o_dk = take(T * D.KVD * 2), o_dv = take(T * D.KVD * 2), o_gs = take(3 * al(T * D.r * 2));
@@ -179,8 +180,9 @@ harli_status make_ws(harli_ctx* c) {
     w.An[i] = (bf*)(b + o_An + i * adb); w.Bn[i] = (bf*)(b + o_Bn + i * ad);
   }
   w.scale = (float*)(b + o_scale);
-  HARLI_HIP(hipMemset(w.scale, 0, 64));  // the maxima start at zero; every backward call clears the slot of the next
-  w.scale_parity = 0;
+  w.rope = (float2*)(b + o_rope);
+  ft_rope_table(w.rope, (int)T, D.d, c->dw.inv_freq, nullptr);
+  HARLI_HIP(hipDeviceSynchronize());
   return HARLI_OK;
 }
 
@@ -196,14 +198,13 @@ inline bool adapted(const harli_ctx* c, int t) { return (c->lora.targets >> t) &
 inline float lscale(const harli_ctx* c) { return c->lora.alpha / (float)c->lora.rank; }
 
 // Every adapted projection's A and B (storage type, contents may change between calls) converted to the compute
-// element in two launches.  Forward: A^T [r, in] row-major for the skinny product s x A, and B^T as the weight GEMM's
+// element in one launch.  Forward: A^T [r, in] row-major for the skinny product s x A, and B^T as the weight GEMM's
 // blocked operand [out rows, r].  Backward: B [r, out] row-major for s dy B^T, and A as the blocked operand [in rows, r].
 void convert_adapters(harli_ctx* c, const LayerDev& L, bool forward, hipStream_t st) {
   FtWs& w = state(c)->ws;
-  FtConvJobs jobs{};
-  BlockJobs blk{};
-  blk.half = 1;
-  jobs.flag = blk.flag = c->dw.err_flag;
+  BlockJobs jobs{};
+  jobs.half = 1;
+  jobs.flag = c->dw.err_flag;
   for (int t = 0; t < kTargets; ++t) {
     if (!adapted(c, t)) continue;
     int out, in;
@@ -211,15 +212,14 @@ void convert_adapters(harli_ctx* c, const LayerDev& L, bool forward, hipStream_t
     const int r = c->lora.rank;
     const int f32 = c->cfg.dtype == HARLI_F32 ? 1 : 0;
     if (forward) {
-      jobs.j[jobs.n++] = FtConvJob{L.A[t], w.At[t], in, r, 1, f32};
-      blk.j[blk.n++] = BlockJob{L.B[t], w.Bt[t], r, out, 1, f32};  // operand [n = out][k = r] = B[k][n]
+      jobs.j[jobs.n++] = BlockJob{L.A[t], w.At[t], in, r, 1, f32, 1};  // A^T, row-major
+      jobs.j[jobs.n++] = BlockJob{L.B[t], w.Bt[t], r, out, 1, f32, 0};  // operand [n = out][k = r] = B[k][n]
     } else {
-      blk.j[blk.n++] = BlockJob{L.A[t], w.An[t], in, r, 0, f32};   // operand [n = in][k = r] = A[n][k]
-      jobs.j[jobs.n++] = FtConvJob{L.B[t], w.Bn[t], r, out, 0, f32};
+      jobs.j[jobs.n++] = BlockJob{L.A[t], w.An[t], in, r, 0, f32, 0};   // operand [n = in][k = r] = A[n][k]
+      jobs.j[jobs.n++] = BlockJob{L.B[t], w.Bn[t], r, out, 0, f32, 1};  // B, row-major
     }
   }
-  if (jobs.n) ft_convert_jobs(jobs, st);
-  gemm2_block_jobs(blk, st);
+  gemm2_block_jobs(jobs, st);
 }
 
 // forward of one projection: out = xin . W^T (+ us . Bt^T), us = s * xin . A kept for backward
@@ -620,10 +620,13 @@ extern "C" harli_status harli_lora_fwd(harli_ctx* c, int32_t layer, const float*
     }
     g.nout = 3;
     g.tiles_n = tq + 2 * tk;
+    g.epi = GEMM2_EPI_ROPE;  // q and k leave rotated
+    g.rope = w.rope;
+    g.rope_S = S;
+    g.rope_d = D.d;
+    g.rope_tiles = tq + tk;
     RUN(gemm2_launch(g, st));
   }
-  ft_rope(sv->q, T, S, D.nq, D.d, c->dw.inv_freq, false, c->dw.err_flag, st);
-  ft_rope(sv->k, T, S, D.nkv, D.d, c->dw.inv_freq, false, c->dw.err_flag, st);
   RUN(ft_attn_fwd(sv->q, sv->k, sv->v, sv->o, sv->lse, B_f, S, D.nq, D.nkv, D.d, st));
   {  // x1 = X + o Wo^T
     proj_us_group(c, 3, 3, sv->o, T, sv, st);
@@ -699,7 +702,7 @@ extern "C" harli_status harli_lora_bwd(harli_ctx* c, int32_t layer, const float*
   // ---- FFN ----
   convert_adapters(c, L, false, st);
   // every gradient below carries the factor sigma
-  ft_scale_to_e(dY, w.dyb, (long long)T * D.H, w.scale, w.scale_parity++, 8 - c->lora.grad_headroom_log2, st);
+  ft_scale_to_e(dY, w.dyb, (long long)T * D.H, w.scale, 8 - c->lora.grad_headroom_log2, st);
   const int r = c->lora.rank;
   {  // dm = dy Wd (+ gs A_d^T) -> da, du
     Gemm2Args g = wg_begin(c, T);
@@ -747,7 +750,7 @@ extern "C" harli_status harli_lora_bwd(harli_ctx* c, int32_t layer, const float*
     RUNB(gemm2_launch(g, st));
   }
   // ---- attention ----
-  RUNB(ft_attn_bwd(sv->q, sv->k, sv->v, sv->o, w.dob, sv->lse, w.delta, w.dq, w.dkq, w.dvq, B_f, S, D.nq,
+  RUNB(ft_attn_bwd(sv->q, sv->k, sv->v, sv->o, w.dob, sv->lse, w.delta, w.dq, w.dkq, w.dvq, w.rope, B_f, S, D.nq,
                    D.nkv, D.d, c->dw.err_flag, st));
   const bf *dk = w.dkq, *dv = w.dvq;
   if (D.G > 1) {
@@ -756,8 +759,6 @@ extern "C" harli_status harli_lora_bwd(harli_ctx* c, int32_t layer, const float*
     dk = w.dk;
     dv = w.dv;
   }
-  ft_rope(w.dq, T, S, D.nq, D.d, c->dw.inv_freq, true, c->dw.err_flag, st);
-  ft_rope(const_cast<bf*>(dk), T, S, D.nkv, D.d, c->dw.inv_freq, true, c->dw.err_flag, st);
   // ---- q, k, v projections ----
   {  // dh = dq Wq + dk Wk + dv Wv
     Gemm2Args g = wg_begin(c, T);

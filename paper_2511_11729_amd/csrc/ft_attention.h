@@ -18,8 +18,9 @@ harli_status ft_attn_fwd(const bf* q, const bf* k, const bf* v, bf* o, float* ls
 // Given dO and the forward output o:  delta[z][s] = sum_e dO[s][e] o[s][e] (written to `delta`, a workspace of
 // Bf*n_q*S floats),
 //   dq  = dS k / sqrt(d),  dkq = dS^T q / sqrt(d),  dvq = P^T dO   with P = exp(score) / 2^lse2, dS = P (dP - delta),
-//   dP = dO v^T.  dkq and dvq are per QUERY head ([Bf*S, n_q*d]); the caller sums them over the heads of a group.
+//   dP = dO v^T.  q and k are rotated; dq and dkq leave with the inverse rotary embedding applied (rope[p * d/2 + i] =
+// (cos, sin) of position p), that is as gradients of the projections' outputs.  dkq and dvq are per QUERY head ([Bf*S, n_q*d]); the caller sums them over the heads of a group.
 harli_status ft_attn_bwd(const bf* q, const bf* k, const bf* v, const bf* o, const bf* dO, const float* lse2, float* delta,
-                         bf* dq, bf* dkq, bf* dvq, int Bf, int S, int n_q,
+                         bf* dq, bf* dkq, bf* dvq, const float2* rope, int Bf, int S, int n_q,
                          int n_kv, int d, int* flag, hipStream_t st);
 }  // namespace harli

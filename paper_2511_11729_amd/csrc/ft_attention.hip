@@ -116,6 +116,18 @@ __device__ __forceinline__ f32x16 zero16f() {
   for (int v = 0; v < 16; ++v) z[v] = 0.f;
   return z;
 }
+// Four head-dim rows (e*32 + 8g + 4h ..) of a gradient column and their rotation partners (d/2 further), times scale, with
+// the inverse rotary embedding of the column's position applied: (lo, hi) -> (lo cos + hi sin, hi cos - lo sin).
+__device__ __forceinline__ void unrotate4(const f32x16& lo, const f32x16& hi, int g, const float2* cs, float scale, float* ol, float* oh) {
+  const float4 t0 = *reinterpret_cast<const float4*>(cs), t1 = *reinterpret_cast<const float4*>(cs + 2);
+  const float c[4] = {t0.x, t0.z, t1.x, t1.z}, s[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float a = lo[4 * g + i] * scale, b = hi[4 * g + i] * scale;
+    ol[i] = a * c[i] + b * s[i];
+    oh[i] = b * c[i] - a * s[i];
+  }
+}
 // maximum over the two lanes (l, l + 32) that share a column
 __device__ __forceinline__ float max_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -236,7 +248,8 @@ template <int D>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
                                                      const bf* __restrict__ dO, const bf* __restrict__ o,
                                                      const float* __restrict__ lse2, float* __restrict__ delta, bf* __restrict__ dq,
-                                                     int S, int nq, int nkv, float scale, float scale_log2, int* flag) {
+                                                     const float2* __restrict__ rope, int S, int nq, int nkv, float scale,
+                                                     float scale_log2, int* flag) {
   constexpr int NJ = D / 16, NE = D / 32, TILE = KB * D * 2;
   extern __shared__ __align__(1024) char smem[];  // two buffers of (K, V)
   const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
@@ -319,11 +332,15 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(const bf* __restrict__ q
     bf* op = dq + ((long long)b * S + qrow) * QD + head * D;
     bool over = false;
 #pragma unroll
-    for (int e = 0; e < NE; ++e)
+    for (int e = 0; e < NE / 2; ++e)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<u32x2*>(op + e * 32 + 8 * g + 4 * h) = u32x2{PACK2G(dQ[e][4 * g] * scale, dQ[e][4 * g + 1] * scale, over),
-                                                                       PACK2G(dQ[e][4 * g + 2] * scale, dQ[e][4 * g + 3] * scale, over)};
+      for (int g = 0; g < 4; ++g) {
+        const int eo = e * 32 + 8 * g + 4 * h;
+        float lo[4], hi[4];
+        unrotate4(dQ[e], dQ[e + NE / 2], g, rope + (long long)qrow * (D / 2) + eo, scale, lo, hi);
+        *reinterpret_cast<u32x2*>(op + eo) = u32x2{PACK2G(lo[0], lo[1], over), PACK2G(lo[2], lo[3], over)};
+        *reinterpret_cast<u32x2*>(op + eo + D / 2) = u32x2{PACK2G(hi[0], hi[1], over), PACK2G(hi[2], hi[3], over)};
+      }
     elem_flag(over, flag);
   }
 }
@@ -336,8 +353,8 @@ template <int D>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv(const bf* __restrict__ q, const bf* __restrict__ k, const bf* __restrict__ v,
                                                       const bf* __restrict__ dO, const float* __restrict__ lse2,
                                                       const float* __restrict__ delta, bf* __restrict__ dkq,
-                                                      bf* __restrict__ dvq, int S, int nq, int nkv, float scale,
-                                                      float scale_log2, int* flag) {
+                                                      bf* __restrict__ dvq, const float2* __restrict__ rope, int S, int nq,
+                                                      int nkv, float scale, float scale_log2, int* flag) {
   constexpr int NJ = D / 16, NE = D / 32, TILE = KB * D * 2;
   constexpr int BUF = 2 * TILE + 2 * KB * 4;  // Q, dO, then lse2 and delta of the block's queries
   extern __shared__ __align__(1024) char smem[];
@@ -430,8 +447,16 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dkv(const bf* __restrict__ 
         const int eo = e * 32 + 8 * g + 4 * h;
         *reinterpret_cast<u32x2*>(dvq + ro + eo) =
             u32x2{PACK2G(dV[e][4 * g], dV[e][4 * g + 1], over), PACK2G(dV[e][4 * g + 2], dV[e][4 * g + 3], over)};
-        *reinterpret_cast<u32x2*>(dkq + ro + eo) = u32x2{PACK2G(dK[e][4 * g] * scale, dK[e][4 * g + 1] * scale, over),
-                                                         PACK2G(dK[e][4 * g + 2] * scale, dK[e][4 * g + 3] * scale, over)};
+      }
+#pragma unroll
+    for (int e = 0; e < NE / 2; ++e)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int eo = e * 32 + 8 * g + 4 * h;
+        float lo[4], hi[4];
+        unrotate4(dK[e], dK[e + NE / 2], g, rope + (long long)krow * (D / 2) + eo, scale, lo, hi);
+        *reinterpret_cast<u32x2*>(dkq + ro + eo) = u32x2{PACK2G(lo[0], lo[1], over), PACK2G(lo[2], lo[3], over)};
+        *reinterpret_cast<u32x2*>(dkq + ro + eo + D / 2) = u32x2{PACK2G(hi[0], hi[1], over), PACK2G(hi[2], hi[3], over)};
       }
     elem_flag(over, flag);
   }
@@ -481,7 +506,7 @@ harli_status ft_attn_fwd(const bf* q, const bf* k, const bf* v, bf* o, float* ls
 }
 
 harli_status ft_attn_bwd(const bf* q, const bf* k, const bf* v, const bf* o, const bf* dO, const float* lse2, float* delta,
-                         bf* dq, bf* dkq, bf* dvq, int Bf, int S, int n_q,
+                         bf* dq, bf* dkq, bf* dvq, const float2* rope, int Bf, int S, int n_q,
                          int n_kv, int d, int* flag, hipStream_t st) {
   harli_status s = check_shape(Bf, S, n_q, n_kv, d);
   if (s != HARLI_OK) return s;
@@ -489,13 +514,13 @@ harli_status ft_attn_bwd(const bf* q, const bf* k, const bf* v, const bf* o, con
   const float sc = 1.f / sqrtf((float)d), sl2 = kLog2e * sc;
   if (d == 128) {
     if ((s = set_attrs<128>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_bwd_dq<128>, grid, blk, fwd_lds<128>(), st, q, k, v, dO, o, lse2, delta, dq, S, n_q, n_kv, sc, sl2, flag);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<128>, grid, blk, dkv_lds<128>(), st, q, k, v, dO, lse2, delta, dkq, dvq, S, n_q,
+    hipLaunchKernelGGL(k_attn_bwd_dq<128>, grid, blk, fwd_lds<128>(), st, q, k, v, dO, o, lse2, delta, dq, rope, S, n_q, n_kv, sc, sl2, flag);
+    hipLaunchKernelGGL(k_attn_bwd_dkv<128>, grid, blk, dkv_lds<128>(), st, q, k, v, dO, lse2, delta, dkq, dvq, rope, S, n_q,
                        n_kv, sc, sl2, flag);
   } else {
     if ((s = set_attrs<64>()) != HARLI_OK) return s;
-    hipLaunchKernelGGL(k_attn_bwd_dq<64>, grid, blk, fwd_lds<64>(), st, q, k, v, dO, o, lse2, delta, dq, S, n_q, n_kv, sc, sl2, flag);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<64>, grid, blk, dkv_lds<64>(), st, q, k, v, dO, lse2, delta, dkq, dvq, S, n_q,
+    hipLaunchKernelGGL(k_attn_bwd_dq<64>, grid, blk, fwd_lds<64>(), st, q, k, v, dO, o, lse2, delta, dq, rope, S, n_q, n_kv, sc, sl2, flag);
+    hipLaunchKernelGGL(k_attn_bwd_dkv<64>, grid, blk, dkv_lds<64>(), st, q, k, v, dO, lse2, delta, dkq, dvq, rope, S, n_q,
                        n_kv, sc, sl2, flag);
   }
   return HARLI_OK;

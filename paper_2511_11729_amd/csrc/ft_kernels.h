@@ -16,27 +16,13 @@ void ft_rmsnorm_fwd(const float* x, const float* g, bf* h, float* rho, int T, in
 // dx16: optional 16-bit copy of dx (the next GEMM's operand)
 void ft_rmsnorm_bwd(const float* dh, const float* x, const float* rho, const float* g, const float* dres, float* dx, bf* dx16,
                     int T, int H, const float* res_mul, const float* out_mul, int* flag, hipStream_t st);
-// rotary embedding in place on [T, heads*d] bf16, position = t % S; inverse rotates by the negative angle
-void ft_rope(bf* t, int T, int S, int heads, int d, const double* inv_freq, bool inverse, int* flag, hipStream_t st);
+// table of the rotary embedding: out[p * d/2 + i] = (cos, sin) of p * inv_freq[i], p < n_pos
+void ft_rope_table(float2* out, int n_pos, int d, const double* inv_freq, hipStream_t st);
 // Gradient scaling in two launches: the largest |x| (n a multiple of 4), then y = 16-bit(x * sigma) with sigma the power
-// of two that brings it to 2^target_log2; scale[0] = sigma and scale[1] = 1 / sigma are left for the kernels downstream.
-// scale[2], scale[3] hold the maximum (as bits) of this call and the next: they must be zero before the first call, and
-// `parity` alternates between calls (each call clears the slot of the next).
-void ft_scale_to_e(const float* x, bf* y, long long n, float* scale, int parity, int target_log2, hipStream_t st);
-// Several storage -> compute-element conversions in one launch: src [R][C] (bf16, or fp32 when src_f32 is set) ->
-// dst [R][C], or dst [C][R] when transpose is set (meant for adapter matrices and one-time weight copies: the
-// strided side is not tuned)
-struct FtConvJob {
-  const void* src;
-  bf* dst;
-  int R, C, transpose, src_f32;
-};
-struct FtConvJobs {
-  FtConvJob j[16];
-  int n;
-  int* flag;  // device int or null: bit 8 is set when a value lay beyond the compute element's range
-};
-void ft_convert_jobs(const FtConvJobs& jobs, hipStream_t st);
+// of two that brings it to 2^target_log2; scale[0] = sigma and scale[1] = 1 / sigma are left for the kernels downstream,
+// scale[2 .. 2 + kAmaxParts) is scratch.
+constexpr int kAmaxParts = 512;
+void ft_scale_to_e(const float* x, bf* y, long long n, float* scale, int target_log2, hipStream_t st);
 // skinny NT GEMMs: C[M, N] = alpha * X[M, K] . Bm[N, K]^T, N <= 64 and N % 16 == 0 after padding by the caller's layout;
 // several such products with the same M and alpha in one launch (job = blockIdx.y).
 constexpr int kSkinnyMaxJobs = 4;

@@ -78,68 +78,28 @@ __global__ void __launch_bounds__(256) k_rmsnorm_bwd(const float* dh, const floa
   elem_flag(over, flag);
 }
 
-// ---------------------------------------------------------------- rotary embedding, pairs (i, i + d/2)
-// One workgroup per token.  The d/2 (cos, sin) pairs of the token's position are computed once into LDS (angle
-// reduced in double, as the oracle's positions are exact) and shared by every head.  One thread rotates eight
-// adjacent pairs with two 16-byte loads and stores when d/2 is a multiple of 8 (rows are 16-byte aligned then:
-// heads*d is a multiple of 8); other head sizes take the pair-at-a-time loop.
-constexpr int kRopeMaxHalf = 256;
-__global__ void __launch_bounds__(256) k_rope(bf* x, int S, int heads, int d, const double* inv_freq, float sign, int* flag) {
-  __shared__ float cs_[kRopeMaxHalf], sn_[kRopeMaxHalf];
-  const int t = blockIdx.x, half = d >> 1;
-  const double pos = (double)(t % S);
-  for (int i = threadIdx.x; i < half; i += 256) {
-    const double ang = pos * inv_freq[i];
-    const double red = ang - 6.283185307179586476925 * rint(ang * 0.15915494309189533577);
-    float sn, cs;
-    sincosf((float)red, &sn, &cs);
-    cs_[i] = cs;
-    sn_[i] = sn * sign;
-  }
-  __syncthreads();
-  bf* row = x + (size_t)t * heads * d;
-  bool over = false;
-  if ((half & 7) == 0) {
-    const int per_head = half >> 3;
-    for (int idx = threadIdx.x; idx < heads * per_head; idx += 256) {
-      const int hh = idx / per_head, i0 = (idx - hh * per_head) * 8;
-      bf* p = row + hh * d + i0;
-      const uint4 lo4 = *reinterpret_cast<const uint4*>(p), hi4 = *reinterpret_cast<const uint4*>(p + half);
-      float lo[8], hi[8], ol[8], oh[8];
-      UNPACK8(lo4, lo);
-      UNPACK8(hi4, hi);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float cs = cs_[i0 + e], sn = sn_[i0 + e];
-        ol[e] = lo[e] * cs - hi[e] * sn;
-        oh[e] = hi[e] * cs + lo[e] * sn;
-      }
-      *reinterpret_cast<uint4*>(p) = make_uint4(PACK2G(ol[0], ol[1], over), PACK2G(ol[2], ol[3], over), PACK2G(ol[4], ol[5], over),
-                                                PACK2G(ol[6], ol[7], over));
-      *reinterpret_cast<uint4*>(p + half) = make_uint4(PACK2G(oh[0], oh[1], over), PACK2G(oh[2], oh[3], over),
-                                                       PACK2G(oh[4], oh[5], over), PACK2G(oh[6], oh[7], over));
-    }
-    elem_flag(over, flag);
-    return;
-  }
-  for (int idx = threadIdx.x; idx < heads * half; idx += 256) {
-    const int hh = idx / half, i = idx - hh * half;
-    const float cs = cs_[i], sn = sn_[i];
-    bf* p = row + hh * d + i;
-    const float lo = E2F(p[0]), hi = E2F(p[half]);
-    p[0] = F2EG(lo * cs - hi * sn, over);
-    p[half] = F2EG(hi * cs + lo * sn, over);
-  }
-  elem_flag(over, flag);
+// ---------------------------------------------------------------- rotary embedding table
+// angle reduced in double, as the oracle's positions are exact
+__global__ void __launch_bounds__(256) k_rope_table(float2* out, long long n, int half, const double* inv_freq) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= n) return;
+  const double ang = (double)(idx / half) * inv_freq[idx % half];
+  const double red = ang - 6.283185307179586476925 * rint(ang * 0.15915494309189533577);
+  float sn, cs;
+  sincosf((float)red, &sn, &cs);
+  out[idx] = make_float2(cs, sn);
 }
 
 // ---------------------------------------------------------------- gradient scaling
 // The backward pass is linear in dY, so dY is multiplied by a power of two sigma that brings its
 // largest magnitude to 2^8 before it is rounded to 16 bits, and 1/sigma is applied where the
 // fp32 results leave the unit (dX, dA, dB).  scale[0] = sigma, scale[1] = 1/sigma.
-__global__ void __launch_bounds__(256) k_amax(const float* x, long long n4, unsigned* amax_bits) {
+// Both kernels are bound by their 4 (+ 2) bytes per element.  The maxima of the workgroups go to an array that every
+// workgroup of the second kernel reduces for itself: one atomic per workgroup on a single word made the first kernel
+// 18 us for 33 MB, with the array it takes 8.6.
+__global__ void __launch_bounds__(256) k_amax(const float* x, long long n4, float* parts) {
   // grid-stride over groups of 1024 float4, four independent 16-byte loads per thread in flight (indices past the
-  // end re-read the last element); one atomic per workgroup (same-address atomics serialise)
+  // end re-read the last element)
   __shared__ float wmax[4];
   float m = 0.f;
   for (long long base = (long long)blockIdx.x * 1024 + threadIdx.x; base < n4; base += (long long)gridDim.x * 1024) {
@@ -154,32 +114,39 @@ __global__ void __launch_bounds__(256) k_amax(const float* x, long long n4, unsi
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0)
-    atomicMax(amax_bits, __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))));  // non-negative floats order like their bits
+  if (threadIdx.x == 0) parts[blockIdx.x] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
 }
 // sigma from the largest magnitude: the power of two that brings it to 2^target_log2 (1 for an all-zero or non-finite dY)
-__device__ __forceinline__ float sigma_of(unsigned amax_bits, int target_log2) {
-  const float a = __uint_as_float(amax_bits);
+__device__ __forceinline__ float sigma_of(float a, int target_log2) {
   if (!(a > 0.f && a < INFINITY)) return 1.f;
   int e;
   frexpf(a, &e);  // a = f * 2^e, f in [0.5, 1)
   return ldexpf(1.f, min(max(target_log2 - e, -100), 100));
 }
-// y = 16-bit(x * sigma).  Every workgroup derives sigma from the maximum that k_amax left in bits[0]; workgroup 0 also
-// publishes scale[0] = sigma, scale[1] = 1 / sigma for the kernels downstream and clears bits[1], the slot the next
-// call's k_amax will use (the two slots alternate, so no launch is spent on a reset).
-__global__ void __launch_bounds__(256) k_f32_to_e_scaled(const float* x, bf* y, long long n4, const unsigned* bits_now,
-                                                         unsigned* bits_next, float* scale, int target_log2) {
-  const float sg = sigma_of(*bits_now, target_log2);
+// y = 16-bit(x * sigma), 1024 groups of four elements per workgroup.  Every workgroup derives sigma from the maxima that
+// k_amax left; workgroup 0 also publishes scale[0] = sigma, scale[1] = 1 / sigma for the kernels downstream.
+__global__ void __launch_bounds__(256) k_f32_to_e_scaled(const float* x, bf* y, long long n4, const float* parts, int n_parts,
+                                                         float* scale, int target_log2) {
+  __shared__ float wmax[4];
+  const long long base = (long long)blockIdx.x * 1024 + threadIdx.x;
+  float4 v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const float4*>(x)[min(base + u * 256, n4 - 1)];
+  float m = 0.f;
+  for (int i = threadIdx.x; i < n_parts; i += 256) m = fmaxf(m, parts[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+  __syncthreads();
+  const float sg = sigma_of(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])), target_log2);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     scale[0] = sg;
     scale[1] = 1.f / sg;
-    *bits_next = 0u;
   }
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const float4 v = reinterpret_cast<const float4*>(x)[i];
-  reinterpret_cast<uint2*>(y)[i] = make_uint2(PACK2(v.x * sg, v.y * sg), PACK2(v.z * sg, v.w * sg));
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (base + u * 256 < n4)
+      reinterpret_cast<uint2*>(y)[base + u * 256] = make_uint2(PACK2(v[u].x * sg, v[u].y * sg), PACK2(v[u].z * sg, v[u].w * sg));
 }
 
 // ---------------------------------------------------------------- skinny NT GEMM (LoRA down-projection x.A and dy.B^T)
@@ -469,22 +436,6 @@ __global__ void __launch_bounds__(256) k_sum_groups(const bf* in, bf* out, long 
   elem_flag(over, flag);
 }
 
-__global__ void __launch_bounds__(256) k_convert_jobs(FtConvJobs jobs) {
-  const FtConvJob jb = jobs.j[blockIdx.y];
-  const long long n = (long long)jb.R * jb.C;
-  bool over = false;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-    const unsigned short v = F2EG(jb.src_f32 ? static_cast<const float*>(jb.src)[i] : bf2f(static_cast<const bf*>(jb.src)[i]), over);
-    if (jb.transpose) {
-      const int r = (int)(i / jb.C), c = (int)(i - (long long)r * jb.C);
-      jb.dst[(long long)c * jb.R + r] = v;
-    } else {
-      jb.dst[i] = v;
-    }
-  }
-  elem_flag(over, jobs.flag);
-}
-
 inline unsigned nblk(long long n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
@@ -496,17 +447,14 @@ void ft_rmsnorm_bwd(const float* dh, const float* x, const float* rho, const flo
                     int T, int H, const float* res_mul, const float* out_mul, int* flag, hipStream_t st) {
   hipLaunchKernelGGL(k_rmsnorm_bwd, dim3(T), dim3(256), 0, st, dh, x, rho, g, dres, dx, dx16, H, res_mul, out_mul, flag);
 }
-void ft_rope(bf* t, int T, int S, int heads, int d, const double* inv_freq, bool inverse, int* flag, hipStream_t st) {
-  hipLaunchKernelGGL(k_rope, dim3(T), dim3(256), 0, st, t, S, heads, d, inv_freq, inverse ? -1.f : 1.f, flag);
+void ft_rope_table(float2* out, int n_pos, int d, const double* inv_freq, hipStream_t st) {
+  const long long n = (long long)n_pos * (d / 2);
+  hipLaunchKernelGGL(k_rope_table, dim3(nblk(n, 256)), dim3(256), 0, st, out, n, d / 2, inv_freq);
 }
-void ft_convert_jobs(const FtConvJobs& jobs, hipStream_t st) {
-  hipLaunchKernelGGL(k_convert_jobs, dim3(64, jobs.n), dim3(256), 0, st, jobs);
-}
-void ft_scale_to_e(const float* x, bf* y, long long n, float* scale, int parity, int target_log2, hipStream_t st) {
-  unsigned* bits = reinterpret_cast<unsigned*>(scale + 2);
-  hipLaunchKernelGGL(k_amax, dim3(std::min(nblk(n / 4, 1024), 1024u)), dim3(256), 0, st, x, n / 4, bits + (parity & 1));
-  hipLaunchKernelGGL(k_f32_to_e_scaled, dim3(nblk(n / 4, 256)), dim3(256), 0, st, x, y, n / 4, bits + (parity & 1),
-                     bits + ((parity & 1) ^ 1), scale, target_log2);
+void ft_scale_to_e(const float* x, bf* y, long long n, float* scale, int target_log2, hipStream_t st) {
+  const unsigned parts = std::min(nblk(n / 4, 1024), (unsigned)kAmaxParts);
+  hipLaunchKernelGGL(k_amax, dim3(parts), dim3(256), 0, st, x, n / 4, scale + 2);
+  hipLaunchKernelGGL(k_f32_to_e_scaled, dim3(nblk(n / 4, 1024)), dim3(256), 0, st, x, y, n / 4, scale + 2, (int)parts, scale, target_log2);
 }
 void ft_skinny_nt_multi(const SkinnyNtJobs& jobs, int M, float alpha, int* flag, hipStream_t st) {
   if (jobs.n < 1) return;

@@ -61,6 +61,7 @@ enum Gemm2Epi {
   GEMM2_EPI_NONE = 0,        // plain outputs (the kernel variant for fp32 outputs is picked from out[0].Cf)
   GEMM2_EPI_F32 = 1,         // internal: the variant that writes fp32 (+ residual, + optional 16-bit copy)
   GEMM2_EPI_SWIGLU_BWD = 2,  // as GEMM_EPI_SWIGLU_BWD: C = dm, o0 = da, o1 = du from e0 = a, e1 = u (row stride lde)
+  GEMM2_EPI_ROPE = 4,        // 16-bit outputs, rotary embedding (pairs i, i + d/2) on the columns of tiles below rope_tiles
   GEMM2_EPI_GATEUP = 3       // interleaved pair: a = gate, u = up (16-bit), and o0 = m = silu(a) * u; out[0].Cb = a, o1 = u
 };
 
@@ -75,6 +76,10 @@ struct Gemm2Args {
   const unsigned short *e0, *e1;
   unsigned short *o0, *o1;
   long long lde;
+  // GEMM2_EPI_ROPE: (cos, sin) of position p and rotation index i at rope[p * d/2 + i]; row m is at position m % rope_S.
+  // Heads of d = rope_d (64 or 128) columns start at multiples of d in their output block.
+  const float2* rope;
+  int rope_S, rope_d, rope_tiles;
   int* overflow_flag;  // device int: bit 8 is set when a 16-bit output had to be clamped to the element's range (or null)
   long long* clk;      // clock probe (or null): workgroup 0 writes {shader-clock cycles, 100 MHz ticks} of its K loop
   // compute units the launch's stream may use (Harli Sec. 6.2: the finetune task runs on a share of them); 0: taken
@@ -118,6 +123,7 @@ struct BlockJob {
   const void* src;
   unsigned short* dst;
   int R, C, transpose, src_f32;
+  int plain;  // 1: dst is the operand B[n][k] row-major [N][K] instead of blocked (K a multiple of 8)
 };
 struct BlockJobs {
   BlockJob j[16];

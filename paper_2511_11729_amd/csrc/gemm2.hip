@@ -90,7 +90,7 @@ __device__ __forceinline__ void g2_store_rows(const char* ebuf, const Gemm2Args&
         *reinterpret_cast<uint4*>(a.o1 + (long long)m * a.lde + n8) = up;
         *reinterpret_cast<uint4*>(a.o0 + (long long)m * a.lde + n8) = pack8(mv);
       }
-    } else if (EPI == GEMM2_EPI_SWIGLU_BWD || EPI == GEMM2_EPI_NONE) {
+    } else if (EPI == GEMM2_EPI_SWIGLU_BWD || EPI == GEMM2_EPI_NONE || EPI == GEMM2_EPI_ROPE) {
       // 16-bit outputs only: eight columns (16 bytes) per lane, four rows per pass
       const int c8 = (lane & 15) * 8, n8 = (tn - out.tile0) * BN + wn * 128 + c8;
 #pragma unroll
@@ -99,7 +99,22 @@ __device__ __forceinline__ void g2_store_rows(const char* ebuf, const Gemm2Args&
         const float4 lo = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4);
         const float4 hi = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4 + 16);
         if (m >= a.M || n8 >= out.N) continue;
-        const float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        if (EPI == GEMM2_EPI_ROPE && tn < a.rope_tiles) {
+          // a wave's 128 columns hold whole heads: the partner columns lie in the same staged row
+          const int half = a.rope_d >> 1, cp = c8 ^ half;
+          const float4 pl = *reinterpret_cast<const float4*>(ebuf + row * ER + cp * 4);
+          const float4 ph = *reinterpret_cast<const float4*>(ebuf + row * ER + cp * 4 + 16);
+          const float y[8] = {pl.x, pl.y, pl.z, pl.w, ph.x, ph.y, ph.z, ph.w};
+          const float4* cs = reinterpret_cast<const float4*>(a.rope + (size_t)(m % a.rope_S) * half + (c8 & (half - 1)));
+          const float sgn = (c8 & half) ? 1.f : -1.f;  // (lo, hi) -> (lo cos - hi sin, hi cos + lo sin)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float4 t = cs[e];
+            x[2 * e] = x[2 * e] * t.x + sgn * y[2 * e] * t.y;
+            x[2 * e + 1] = x[2 * e + 1] * t.z + sgn * y[2 * e + 1] * t.w;
+          }
+        }
         if (EPI == GEMM2_EPI_SWIGLU_BWD) {
           float av[8], uv[8], oa[8], ou[8];
           unpack(*reinterpret_cast<const uint4*>(a.e0 + (long long)m * a.lde + n8), av);
@@ -521,13 +536,20 @@ __global__ void __launch_bounds__(256) k_block_jobs(BlockJobs jobs) {
   const BlockJob jb = jobs.j[blockIdx.y];
   const long long N = jb.transpose ? jb.C : jb.R, K = jb.transpose ? jb.R : jb.C;
   const long long ks_n = (K + BK - 1) / BK;
-  const long long total = (long long)blocked_elems(N, K) / 8;  // 16-byte chunks of the destination
+  const long long total = (long long)(jb.plain ? (size_t)(N * K) : blocked_elems(N, K)) / 8;  // 16-byte chunks of the destination
   bool over = false;
   for (long long ci = (long long)blockIdx.x * 256 + threadIdx.x; ci < total; ci += (long long)gridDim.x * 256) {
-    const long long e0 = ci * 8;  // first element of the chunk: ((tile * ks_n + ks) * 256 + row) * 32 + kk
-    const int kk = (int)(e0 & 31), row = (int)((e0 >> 5) & 255);
-    const long long tk = e0 >> 13, ks = tk % ks_n, tile = tk / ks_n;
-    const long long n = tile * BN + row, k = ks * BK + kk;
+    long long e0 = ci * 8, n, k;  // first element of the chunk
+    if (jb.plain) {
+      // lanes run along the contiguous side of the source
+      n = jb.transpose ? ci % N : e0 / K;
+      k = jb.transpose ? ci / N * 8 : e0 - n * K;
+      e0 = n * K + k;
+    } else {  // ((tile * ks_n + ks) * 256 + row) * 32 + kk
+      const int kk = (int)(e0 & 31), row = (int)((e0 >> 5) & 255);
+      const long long tk = e0 >> 13, ks = tk % ks_n, tile = tk / ks_n;
+      n = tile * BN + row, k = ks * BK + kk;
+    }
     unsigned short v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -593,18 +615,21 @@ Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
 //   600 x 5120 x 13824     180   115      4096 x 5120 x 13824   669   563
 //   1032 x 3584 x 37888    628   347      2048 x 4096 x 4096     80    80 (one full round: not cut)
 // Cost in us, fitted to a sweep of ranges for these and 20 more shapes (it picks within 4 % of the best, 8 % at worst):
-// a stage takes 0.71 / 0.456 us in a tile of 256 / 128 rows while few compute units run and up to 0.48 / 0.21 more when
-// all do (clock and fabric); filling, draining and storing a tile about 6; the second launch 4; partial tiles 0.18 per MB.
+// a stage takes 0.68 / 0.41 us in a tile of 256 / 128 rows while few compute units run and up to 0.34 / 0.18 more when
+// 256 / 140 do (clock and fabric); filling, draining and storing a tile about 6; the second launch 4; partial tiles 0.19
+// per MB.  (0.15 would fit the 128-row tiles alone; among the other kernels of a unit the chip holds a lower clock and the
+// 256-row tiles, which move fewer operand bytes per flop, lose less of it: 2048 x 4096 x 11008 as one round of 128-row
+// tiles or as half-length ranges of 256-row ones is 194 against 192 us alone and 213 against 203 inside a unit.)
 Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes) {
   Gemm2Cut best{};
   best.cost_us = -1;
   for (int FM = 4; FM >= 2; FM -= 2) {
     if ((g_force_fm && FM != g_force_fm) || (!g_force_fm && FM == 4 && M <= 128)) continue;
     const int BM = 64 * FM, tiles_m = (M + BM - 1) / BM, T = tiles_m * tiles_n;
-    const double t0 = FM == 4 ? 0.71 : 0.456, t1 = FM == 4 ? 0.48 : 0.21, t_fixed = 6.0;
+    const double t_fixed = 6.0;
     auto step_us = [&](int active) {
-      const double b = std::min(active, 256) / 256.0;
-      return t0 + t1 * b * b;
+      const double b = std::min(1.0, active / (FM == 4 ? 256.0 : 140.0));
+      return FM == 4 ? 0.68 + 0.34 * b * b : 0.41 + 0.18 * b * b;
     };
     const int full = T / n_cu * n_cu, rest = T - full;
     const int ks_max = rest > 0 ? std::max(1, std::min(kMaxCut, stages / kMinCutStages)) : 1;
@@ -614,7 +639,7 @@ Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes) 
       if (bytes > part_bytes) break;
       double cost = (T / n_cu) * (stages * step_us(n_cu) + t_fixed);
       if (r2 > 0) cost += r2 * (((stages + ks - 1) / ks) * step_us(std::min(pieces, n_cu)) + t_fixed);
-      if (ks > 1) cost += 4.0 + bytes / 1048576.0 * 0.18;
+      if (ks > 1) cost += 4.0 + bytes / 1048576.0 * 0.19;
       if (best.cost_us < 0 || (g_force_ks ? ks <= g_force_ks && (ks > best.ks || cost < best.cost_us) : cost < best.cost_us)) {
         best = Gemm2Cut{};
         best.FM = FM, best.ks = ks, best.cost_us = cost;
@@ -668,7 +693,12 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
     if (q.Cf && ((q.ldcf & 3) || ((uintptr_t)q.Cf & 15) || ((uintptr_t)q.res & 15) || (q.Cb && ((q.ldcb & 3) || ((uintptr_t)q.Cb & 7)))))
       return fail(HARLI_ERR_INVALID, "gemm2: an fp32 output needs a row stride that is a multiple of 4 and aligned pointers");
   }
-  if (a.epi != GEMM2_EPI_NONE) {
+  if (a.epi == GEMM2_EPI_ROPE) {
+    if (f32out || !a.rope || a.rope_S < 1 || (a.rope_d != 64 && a.rope_d != 128) || ((uintptr_t)a.rope & 15) || !a.half)
+      return fail(HARLI_ERR_INVALID, "gemm2: the rotary epilogue needs 16-bit outputs, a table and a head size of 64 or 128 (got %d)", a.rope_d);
+    for (int o = 0; o < a.nout; ++o)
+      if (a.out[o].tile0 < a.rope_tiles && a.out[o].N % a.rope_d) return fail(HARLI_ERR_INVALID, "gemm2: output block %d holds no whole heads", o);
+  } else if (a.epi != GEMM2_EPI_NONE) {
     const bool gu = a.epi == GEMM2_EPI_GATEUP;
     if ((a.epi != GEMM2_EPI_GATEUP && a.epi != GEMM2_EPI_SWIGLU_BWD) || a.nout != 1 || a.out[0].Cf || (a.out[0].N & 7) || (a.lde & 7) ||
         !a.o0 || !a.o1 || (gu ? (!a.out[0].Cb) : (!a.e0 || !a.e1 || a.out[0].Cb)) ||
@@ -686,8 +716,10 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
   HARLI_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm2<F_, H_, E_>), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<F_>()))
 #define G2_ATTR4(F_, H_) \
   G2_ATTR(F_, H_, GEMM2_EPI_NONE); G2_ATTR(F_, H_, GEMM2_EPI_F32); G2_ATTR(F_, H_, GEMM2_EPI_SWIGLU_BWD); G2_ATTR(F_, H_, GEMM2_EPI_GATEUP)
-    G2_ATTR4(2, true); G2_ATTR4(4, true); G2_ATTR4(2, false); G2_ATTR4(4, false);
+#define G2_ATTR5(F_) G2_ATTR(F_, true, GEMM2_EPI_ROPE)
+    G2_ATTR5(2); G2_ATTR5(4); G2_ATTR4(2, true); G2_ATTR4(4, true); G2_ATTR4(2, false); G2_ATTR4(4, false);
 #undef G2_ATTR4
+#undef G2_ATTR5
 #undef G2_ATTR
     attr_set = true;
   }
@@ -716,7 +748,9 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
   } while (0)
 #define G2_PICK(F_)                                                                    \
   do {                                                                                 \
-    if (a.half) {                                                                      \
+    if (a.epi == GEMM2_EPI_ROPE) {                                                     \
+      G2_LAUNCH(F_, true, GEMM2_EPI_ROPE);                                             \
+    } else if (a.half) {                                                               \
       if (a.epi == GEMM2_EPI_GATEUP) G2_LAUNCH(F_, true, GEMM2_EPI_GATEUP);            \
       else if (a.epi == GEMM2_EPI_SWIGLU_BWD) G2_LAUNCH(F_, true, GEMM2_EPI_SWIGLU_BWD); \
       else if (f32out) G2_LAUNCH(F_, true, GEMM2_EPI_F32);                             \

@@ -217,3 +217,25 @@ def test_swiglu_epilogues_of_cut_tiles():
     dm, sg = f64(dy) @ f64(WdT).T, 1 / (1 + np.exp(-ar))
     close(f64(da), dm * ur * sg * (1 + ar * (1 - sg)), "da")
     close(f64(du), dm * ar * sg, "du")
+
+
+@pytest.mark.parametrize("d,M,S", [(64, 150, 40), (128, 300, 300)])
+@pytest.mark.parametrize("ksplit", [1, 3])
+def test_rotary_epilogue(d, M, S, ksplit):
+    """Rotary embedding on the first of two output blocks (two heads and a block that ends inside a tile), plain columns
+    after it, whole tiles and tiles cut along K: half outputs, one rounding (2^-11 of a value of the row's size)."""
+    K, Ns = 520, [2 * d, 3 * d]
+    A = rnd((M, K), True, 1)
+    W = [rnd((n, K), True, 2 + i, 0.1) for i, n in enumerate(Ns)]
+    inv = 10000.0 ** (-2.0 * np.arange(d // 2) / d)
+    ang = np.arange(S)[:, None] * inv
+    table = torch.from_numpy(np.stack([np.cos(ang), np.sin(ang)], -1).astype(np.float32)).contiguous().to(DEV)
+    cb = [torch.full((M, n), float("nan"), dtype=torch.float16, device=DEV) for n in Ns]
+    hb.dbg_gemm2(M, [dict(A=A, B=W[0], tile0=0, tile1=1), dict(A=A, B=W[1], tile0=1, tile1=3 if Ns[1] > 256 else 2)],
+                 [dict(N=Ns[0], cb=cb[0], tile0=0), dict(N=Ns[1], cb=cb[1], tile0=1)], epi=4, ksplit=ksplit, rope=table, rope_S=S,
+                 rope_d=d, rope_tiles=1)
+    x = (f64(A) @ f64(W[0]).T).reshape(M, 2, d)
+    c, s = np.cos(ang)[np.arange(M) % S][:, None], np.sin(ang)[np.arange(M) % S][:, None]
+    lo, hi = x[..., : d // 2], x[..., d // 2:]
+    close(f64(cb[0]), np.concatenate([lo * c - hi * s, hi * c + lo * s], -1).reshape(M, -1), "rotated block")
+    close(f64(cb[1]), f64(A) @ f64(W[1]).T, "plain block")
