@@ -83,7 +83,7 @@ inline int ssq_entries(int hidden) { return (((hidden + 15) >> 4) + 15) & ~15; }
 harli_status lib_alloc(harli_ctx* c, void** p, size_t bytes);
 void lib_free(harli_ctx* c, void* p);
 size_t packed_weight_elems(int N, int K);
-harli_status pack_weight(const void* src, void* dst, int N, int K, int row_tile0, hipStream_t st);
+harli_status pack_weight(const void* src, void* dst, int N, int K, int row_tile0, int head_dim, hipStream_t st);
 // element size of the storage dtype
 inline size_t esize(const harli_ctx* c) { return c->cfg.dtype == HARLI_BF16 ? 2 : 4; }
 inline void proj_shape(const harli_model_cfg& m, int t, int* out, int* in) {

@@ -197,19 +197,19 @@ extern "C" harli_status harli_ctx_create(const harli_model_cfg* cfg, const harli
     for (int l = 0; l < m.n_layers; ++l) {
       LayerDev& ld = c->layers[l];
       TRY(dev_alloc(c, &ld.wp[0], packed_weight_elems(QD + 2 * KVD, m.hidden) * 2, false));
-      TRY(pack_weight(ld.w[0], ld.wp[0], QD, m.hidden, 0, nullptr));
-      TRY(pack_weight(ld.w[1], ld.wp[0], KVD, m.hidden, QD / 16, nullptr));
-      TRY(pack_weight(ld.w[2], ld.wp[0], KVD, m.hidden, (QD + KVD) / 16, nullptr));
+      TRY(pack_weight(ld.w[0], ld.wp[0], QD, m.hidden, 0, m.head_dim, nullptr));
+      TRY(pack_weight(ld.w[1], ld.wp[0], KVD, m.hidden, QD / 16, m.head_dim, nullptr));
+      TRY(pack_weight(ld.w[2], ld.wp[0], KVD, m.hidden, (QD + KVD) / 16, m.head_dim, nullptr));
       for (int t = 3; t < kTargets; ++t) {
         int o, i;
         proj_shape(m, t, &o, &i);
         TRY(dev_alloc(c, &ld.wp[t], packed_weight_elems(o, i) * 2, false));
-        TRY(pack_weight(ld.w[t], ld.wp[t], o, i, 0, nullptr));
+        TRY(pack_weight(ld.w[t], ld.wp[t], o, i, 0, 0, nullptr));
       }
     }
     if (c->w_lm) {
       TRY(dev_alloc(c, &c->wlm_p, packed_weight_elems(m.vocab, m.hidden) * 2, false));
-      TRY(pack_weight(c->w_lm, c->wlm_p, m.vocab, m.hidden, 0, nullptr));
+      TRY(pack_weight(c->w_lm, c->wlm_p, m.vocab, m.hidden, 0, 0, nullptr));
     }
     if (hipDeviceSynchronize() != hipSuccess) {
       harli_ctx_destroy(c);

@@ -23,6 +23,17 @@
 // instruction) were measured at 3.6 TB/s against 5.0 TB/s for this layout.
 // A workgroup is TW tiles x KW waves; the KW waves split K and reduce through
 // LDS, so epilogues see complete sums.
+// What bounds these kernels: HBM, as long as enough loads are in flight from the
+// first microsecond on (a plain reading kernel takes 6.7 us for 32 MiB, 16 us for
+// 96 and 41 us for 256: 4.9, 6.2 and 6.5 TB/s), every compute unit gets as many
+// tiles as the others, and the batch fragments, which come from L2 again for every
+// tile, stay few.  So the weights are nontemporal loads issued in whole groups, a
+// short batch loads its own rows of a fragment only, q,k,v tiles need no partner
+// tile (768 single tiles instead of 384 pairs at 32 heads of 128), and from 17 rows
+// on several tiles share a fragment.  One layer of the 7B class at 8 rows, before
+// and after: q,k,v 27.6 -> 18.4 us, output 8.6 -> 7.3, gate/up 37.3 -> 29.3, down
+// 21.9 -> 16.6; of the 13B class at 32 rows 45.6 -> 30.1, 20 -> 15.7, 79.9 -> 48.9,
+// 54.6 -> 37.2.
 #include <mutex>
 
 #include "ctx.h"
@@ -39,64 +50,87 @@ constexpr int kComputeUnits = 256;  // MI355X; only steers a tiling choice
 
 enum { MODE_QKV = 0, MODE_RESID = 1, MODE_GATEUP = 2, MODE_LM = 3 };
 
-__device__ __forceinline__ uint4 ld16(const unsigned short* p) { return *reinterpret_cast<const uint4*>(p); }
+
+// Tile of the packed q, k, v matrix: heads in the order q.., k.., v..; a tile holds eight rotation indices of one head in
+// rows 0..7 and their partners d/2 further in rows 8..15, so that it can be rotated without another tile.
+struct QkvPlace {
+  int which, head;  // 0, 1, 2 = q, k, v; head inside it
+  int idx, col;     // of lane group g: first rotation index, and first of its four columns inside the head
+};
+__device__ __forceinline__ QkvPlace qkv_place(int tile, int per_head, int half, int g, int n_q, int n_kv) {
+  QkvPlace p;
+  const int head = tile / per_head;
+  p.which = head < n_q ? 0 : head < n_q + n_kv ? 1 : 2;
+  p.head = head - (p.which == 0 ? 0 : p.which == 1 ? n_q : n_q + n_kv);
+  p.idx = (tile - head * per_head) * 8 + 4 * (g & 1);
+  p.col = p.idx + (g >> 1) * half;
+  return p;
+}
 
 // RT = 16-row weight tiles per wave: a wave holds RT x NB accumulator tiles, so that a batch fragment fetched for a
 // k-step serves RT weight fragments (at 64 batch rows every wave otherwise pulls four batch fragments through the
-// vector cache for each weight fragment it streams).  RT = 1 for small batches, where the weights are the traffic.
+// vector cache for each weight fragment it streams).  U = k-steps of both operands a wave keeps in flight.
 template <int MODE, int NB, int TW, int KW, int U, int RT>
 __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   constexpr int WAVES = TW * KW;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   const int t_w = wave / KW, ks = wave - t_w * KW;
   const int wg = blockIdx.x;
   const int steps = (a.K + 31) >> 5;
   const int n_tiles = (a.n_rows + 15) >> 4;  // 16-row tiles of the (unpacked) output
 
-  // ---- which 16-row weight tiles this workgroup covers: tile_row0(t, r), t < TW, r < RT ----------
-  int which = 0, hl = 0, pg = 0;  // QKV bookkeeping (uniform over the workgroup)
-  const int half = a.d >> 1;
-  if (MODE == MODE_QKV) {
-    const int ppg = (half >> 4) / RT;  // workgroups per head: the d/2 rotation indices in groups of 16 * RT
-    const int head = wg / ppg;
-    pg = wg - head * ppg;
-    if (head < a.n_q) {
-      which = 0; hl = head;
-    } else if (head < a.n_q + a.n_kv) {
-      which = 1; hl = head - a.n_q;
-    } else {
-      which = 2; hl = head - a.n_q - a.n_kv;
-    }
-  }
-  // first output row (within its projection) of tile (t, r)
+  // ---- which 16-row weight tiles this workgroup covers: first output row of tile (t, r), t < TW, r < RT ----------------
   auto tile_row0 = [&](int t, int r) -> int {
-    if (MODE == MODE_QKV) return hl * a.d + t * half + (pg * RT + r) * 16;
     if (MODE == MODE_GATEUP) return (wg * RT + r) * 16;
     return ((wg * TW + t) * RT + r) * 16;
   };
-  const unsigned short* wt[RT];
-  bool tile_ok[RT];
+  const int half = a.d >> 1, per_head = a.d >> 4;  // rotation indices and tiles of a head
+
+  // ---- the stream: a wave owns steps [s_begin, s_end) of its tiles, 1 KiB contiguous per tile and step ----------------
+  // Both operands are read through buffer resources that end with the wave's range: what a group of U steps asks for past
+  // it comes back as zeros without touching memory, so the last group needs no loop of its own.
+  const int s_begin = (int)(((long long)steps * ks) / KW), s_end = (int)(((long long)steps * (ks + 1)) / KW);
+  const int n_steps = s_end - s_begin;
+  __amdgpu_buffer_rsrc_t rw[RT], rx[NB];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    int tile;  // index of the 16-row tile in the packed matrix this wave reads
-    if (MODE == MODE_QKV) {
-      // q, k and v are packed as one matrix with heads in the order q.., k.., v..
-      const int head = which == 0 ? hl : which == 1 ? a.n_q + hl : a.n_q + a.n_kv + hl;
-      tile = (head * a.d + t_w * half + (pg * RT + r) * 16) >> 4;
-      tile_ok[r] = true;
-    } else {
-      tile = MODE == MODE_GATEUP ? wg * RT + r : (wg * TW + t_w) * RT + r;
-      tile_ok[r] = tile < n_tiles;
-      if (!tile_ok[r]) tile = 0;  // past the last tile: read tile 0 (in bounds), the result is never stored
-    }
+    int tile = tile_row0(t_w, r) >> 4;  // index of the 16-row tile in the packed matrix this wave reads
+    const bool ok = tile < n_tiles;
+    if (!ok) tile = 0;  // past the last tile: an empty range, and the result is never stored
     const unsigned short* base = (MODE == MODE_GATEUP && t_w != 0) ? a.w1 : a.w0;
-    wt[r] = base + ((size_t)tile * steps * 64 + lane) * 8;
+    rw[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(base) + ((size_t)tile * steps + s_begin) * 512, 0,
+                                              ok ? n_steps * 1024 : 0, 0x00020000);
   }
-
-  const unsigned short* xf0[NB];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) xf0[nb] = a.x + (((size_t)((a.b0 >> 4) + nb) * steps) * 64 + lane) * 8;
+  for (int nb = 0; nb < NB; ++nb)
+    rx[nb] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(a.x) + ((size_t)((a.b0 >> 4) + nb) * steps + s_begin) * 512, 0,
+                                               n_steps * 1024, 0x00020000);
+  // batch rows past the batch: lanes outside the resource, zeros (a fragment of B < 16 rows then moves B/16 of its 1 KiB)
+  int vx[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) vx[nb] = a.b0 + nb * 16 + i16 < a.B ? lane * 16 : 0x40000000;
+  uint4 wf[U][RT], xf[U][NB];
+  // weights are read once per step: nontemporal (bit 1 of the cache policy), they leave L2 to the operands that are shared
+#define SK_LOAD(s)                                                                                                                                    \
+  do {                                                                                                                                                \
+    _Pragma("unroll") for (int u = 0; u < U; ++u) {                                                                                                   \
+      _Pragma("unroll") for (int r = 0; r < RT; ++r)                                                                                                  \
+          wf[u][r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw[r], lane * 16 + ((s) + u) * 1024, 0, 2));                     \
+      _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                                                               \
+          xf[u][nb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx[nb], vx[nb] + ((s) + u) * 1024, 0, 0));                      \
+    }                                                                                                                                                 \
+  } while (0)
+#define SK_MFMA()                                                                                                                                     \
+  do {                                                                                                                                                \
+    _Pragma("unroll") for (int u = 0; u < U; ++u) _Pragma("unroll") for (int r = 0; r < RT; ++r)                                                      \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                                                             \
+            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[u][r]),                                                \
+                                                                 __builtin_bit_cast(bf16x8, xf[u][nb]), acc[r][nb], 0, 0, 0);                         \
+  } while (0)
+
+  SK_LOAD(0);  // in flight while the operands of the epilogue are fetched
+  __builtin_amdgcn_sched_barrier(0);
 
   f32x4 acc[RT][NB];
 #pragma unroll
@@ -109,26 +143,25 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   const int jb = a.b0 + wave * 16 + i16;
   const bool active = epi && jb < a.B;
   float pre_ssq = 1.f;
-  float2 pre_cs[RT][4];
   float4 pre_res[RT], pre_g[RT];
+  float4 pre_bias[TW][RT], pre_cs[TW][RT][2];
   int pre_page = -1, pre_slot = 0;
-  float4 pre_b0[RT], pre_b1[RT];  // biases of the two half tiles
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    pre_res[r] = pre_g[r] = pre_b0[r] = pre_b1[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    pre_res[r] = pre_g[r] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pre_cs[r][e] = make_float2(1.f, 0.f);
+    for (int t = 0; t < TW; ++t) pre_bias[t][r] = make_float4(0.f, 0.f, 0.f, 0.f), pre_cs[t][r][0] = pre_cs[t][r][1] = make_float4(1.f, 0.f, 1.f, 0.f);
   }
   // The partial sums of squares of this wave's 16 batch rows.  Small batches (NB <= 2, where a step is short enough
   // for a memory round trip to show): the rows are copied to LDS by loads that need no register and no wait here, and
-  // are added up after the stream; otherwise they are added now (the wave waits for them once, before its stream).
+  // are added up after the stream; otherwise they are added now (the wave waits for them and its first group once).
   constexpr bool kSsqLds = MODE != MODE_RESID && NB <= 2;
   extern __shared__ __attribute__((aligned(1024))) char ssq_lds[];
   const int ssq_stride = (a.ssq_np * 4 + 1023) & ~1023;  // bytes per staged row
-  if (MODE != MODE_RESID && epi) {  // whole waves; rows past the batch read row B - 1
+  if (MODE != MODE_RESID && epi) {  // whole waves; rows past the batch are not staged, or read as row B - 1
     if constexpr (kSsqLds) {
-      for (int r = 0; r < 16; ++r) {
-        const float* row = a.ssq_in + (size_t)min(a.b0 + wave * 16 + r, a.B - 1) * a.ssq_np;
+      for (int r = 0; r < min(16, a.B - a.b0 - wave * 16); ++r) {
+        const float* row = a.ssq_in + (size_t)(a.b0 + wave * 16 + r) * a.ssq_np;
         __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(row), 0, a.ssq_np * 4, 0x00020000);
         for (int k = 0; k < ssq_stride; k += 1024)  // lanes past the row are out of the resource's range: zeros
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(ssq_lds + (wave * 16 + r) * ssq_stride + k),
@@ -141,27 +174,23 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   if (active) {
     if (MODE == MODE_QKV) {
 #pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const int idx0 = (pg * RT + r) * 16 + 4 * g;  // rotation index of this lane's first row in tile r
-        if (a.bias[which]) {  // rows hl*d + idx0 + e and the same + d/2; d % 32 == 0 keeps them 16-byte aligned
-          const float* bp = a.bias[which] + hl * a.d + idx0;
-          pre_b0[r] = *reinterpret_cast<const float4*>(bp);
-          pre_b1[r] = *reinterpret_cast<const float4*>(bp + half);
-        }
-        if (which != 2) {
-          const float* cs = a.rope + ((size_t)jb * half + idx0) * 2;
+      for (int t = 0; t < TW; ++t)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pre_cs[r][e] = make_float2(cs[2 * e], cs[2 * e + 1]);
+        for (int r = 0; r < RT; ++r) {
+          const int tile = tile_row0(t, r) >> 4;
+          if (tile >= n_tiles) continue;
+          const QkvPlace q = qkv_place(tile, per_head, half, g, a.n_q, a.n_kv);
+          if (a.bias[q.which]) pre_bias[t][r] = *reinterpret_cast<const float4*>(a.bias[q.which] + q.head * a.d + q.col);
+          if (q.which != 2) {
+            const float4* cs = reinterpret_cast<const float4*>(a.rope + ((size_t)jb * half + q.idx) * 2);
+            pre_cs[t][r][0] = cs[0], pre_cs[t][r][1] = cs[1];
+          }
         }
-      }
-      if (which != 0) {
-        const int n = a.kv_len[jb];
-        const int lp = n / a.geom.page_tokens;
-        pre_slot = n - lp * a.geom.page_tokens;
-        pre_page = (n >= 0 && lp < a.max_pages)
-                       ? a.page_table[(size_t)jb * a.max_pages + lp]
-                       : -1;
-      }
+      // where the row's next token lies in the cache
+      const int n = a.kv_len[jb];
+      const int lp = n / a.geom.page_tokens;
+      pre_slot = n - lp * a.geom.page_tokens;
+      pre_page = (n >= 0 && lp < a.max_pages) ? a.page_table[(size_t)jb * a.max_pages + lp] : -1;
     }
     if (MODE == MODE_RESID) {
 #pragma unroll
@@ -175,45 +204,18 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
     }
   }
 
-  // ---- stream: each instruction below reads 1 KiB contiguous per wave ---------------------
-  const int s_begin = (int)(((long long)steps * ks) / KW), s_end = (int)(((long long)steps * (ks + 1)) / KW);
-  bool any_ok = false;
-#pragma unroll
-  for (int r = 0; r < RT; ++r) any_ok = any_ok || tile_ok[r];
-  if (any_ok) {
-    int s = s_begin;
-    for (; s + U <= s_end; s += U) {
-      uint4 wf[U][RT], xf[U][NB];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r) wf[u][r] = ld16(wt[r] + (size_t)(s + u) * 512);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) xf[u][nb] = ld16(xf0[nb] + (size_t)(s + u) * 512);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[u][r]),
-                                                                 __builtin_bit_cast(bf16x8, xf[u][nb]), acc[r][nb], 0, 0, 0);
-    }
-    for (; s < s_end; ++s) {
-      uint4 xf[NB];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) xf[nb] = ld16(xf0[nb] + (size_t)s * 512);
-#pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const uint4 wf = ld16(wt[r] + (size_t)s * 512);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf),
-                                                               __builtin_bit_cast(bf16x8, xf[nb]), acc[r][nb], 0, 0, 0);
-      }
-    }
+  for (int s = 0;;) {
+    SK_MFMA();
+    s += U;
+    if (s >= n_steps) break;
+    __builtin_amdgcn_sched_barrier(0);
+    SK_LOAD(s);
+    // the whole group is in flight before the first product: left alone, the compiler interleaves products and loads to
+    // save registers, which takes loads out of flight
+    __builtin_amdgcn_sched_barrier(0);
   }
+#undef SK_LOAD
+#undef SK_MFMA
 
   // ---- per row-tile round r: reduce the K split through LDS, then the epilogue ------------------
   __shared__ float4 red[TW][KW][NB][64];
@@ -260,38 +262,30 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
     // this lane holds output rows tile_row0(t, r) + 4g + {0..3} of batch entry jb
 
     if (MODE == MODE_QKV) {
-      if (active) {
-        const int idx0 = (pg * RT + r) * 16 + 4 * g;  // rotation index of v[.][0]
-        float r0[4], r1[4];
-        const float b0[4] = {pre_b0[r].x, pre_b0[r].y, pre_b0[r].z, pre_b0[r].w};
-        const float b1[4] = {pre_b1[r].x, pre_b1[r].y, pre_b1[r].z, pre_b1[r].w};
+#pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        const int tile = tile_row0(t, r) >> 4;
+        if (tile >= n_tiles) continue;
+        const QkvPlace q = qkv_place(tile, per_head, half, g, a.n_q, a.n_kv);
+        const float4 bias = pre_bias[t][r], cs0 = pre_cs[t][r][0], cs1 = pre_cs[t][r][1];
+        float x[4] = {v[t][0] * rho + bias.x, v[t][1] * rho + bias.y, v[t][2] * rho + bias.z, v[t][3] * rho + bias.w}, o[4];
+        const float c[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, s[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float a0 = v[0][e] * rho + b0[e], a1 = v[TW - 1][e] * rho + b1[e];
-          if (which != 2) {
-            const float2 cs = pre_cs[r][e];
-            r0[e] = a0 * cs.x - a1 * cs.y;
-            r1[e] = a1 * cs.x + a0 * cs.y;
-          } else {
-            r0[e] = a0;
-            r1[e] = a1;
-          }
+          const float y = __shfl_xor(x[e], 32, 64);  // the partner; (lo, hi) -> (lo cos - hi sin, hi cos + lo sin)
+          o[e] = x[e] * c[e] + (g < 2 ? -y : y) * s[e];
         }
-        if (which == 0) {
-          float* q = a.qbuf + (size_t)jb * (a.n_q * a.d) + hl * a.d + idx0;
-          *reinterpret_cast<float4*>(q) = make_float4(r0[0], r0[1], r0[2], r0[3]);
-          *reinterpret_cast<float4*>(q + half) = make_float4(r1[0], r1[1], r1[2], r1[3]);
-        } else {
-          const int page = pre_page, slot = pre_slot;
-          if (page < 0 || page >= a.geom.n_pages_total) {
-            if (g == 0 && r == 0) atomicOr(a.err_flag, 1);
+        if (active) {
+          if (q.which == 0) {
+            *reinterpret_cast<float4*>(a.qbuf + (size_t)jb * (a.n_q * a.d) + q.head * a.d + q.col) = make_float4(o[0], o[1], o[2], o[3]);
+          } else if (pre_page < 0 || pre_page >= a.geom.n_pages_total) {
+            if (g == 0) atomicOr(a.err_flag, 1);
           } else {
             // inside a page the order is [kv head][token slot][head_dim]
-            char* base = a.slab + kv_page_off(a.geom, page, a.layer, which - 1) +
-                         ((size_t)(hl * a.geom.page_tokens + slot) * a.d) * sizeof(unsigned short);
-            unsigned short* dst = reinterpret_cast<unsigned short*>(base) + idx0;
-            *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf2(r0[0], r0[1]), pack_bf2(r0[2], r0[3]));
-            *reinterpret_cast<uint2*>(dst + half) = make_uint2(pack_bf2(r1[0], r1[1]), pack_bf2(r1[2], r1[3]));
+            char* base = a.slab + kv_page_off(a.geom, pre_page, a.layer, q.which - 1) +
+                         ((size_t)(q.head * a.geom.page_tokens + pre_slot) * a.d) * sizeof(unsigned short);
+            *reinterpret_cast<uint2*>(reinterpret_cast<unsigned short*>(base) + q.col) =
+                make_uint2(pack_bf2(o[0], o[1]), pack_bf2(o[2], o[3]));
           }
         }
       }
@@ -343,13 +337,18 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
 // 32 k is 64 lanes x 8 elements, lane = row%16 + 16*((k%32)/8); rows >= N and k >= K are zero.
 // ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_pack_weight(const unsigned short* src, unsigned short* dst, int N, int K,
-                                                     int steps, long long n_frag) {
+                                                     int steps, long long n_frag, int d) {
   const long long f = (long long)blockIdx.x * 256 + threadIdx.x;
   if (f >= n_frag) return;
   const int lane = (int)(f & 63);
   const long long tile = f >> 6;
   const int s = (int)(tile % steps), rt = (int)(tile / steps);
-  const int n = rt * 16 + (lane & 15), k = s * 32 + (lane >> 4) * 8;
+  int n = rt * 16 + (lane & 15);
+  const int k = s * 32 + (lane >> 4) * 8;
+  if (d) {  // q, k, v: rows 0..7 of a tile are eight rotation indices of a head, rows 8..15 their partners d/2 further
+    const int head = n / d, i = n - head * d;
+    n = head * d + (i >> 4) * 8 + (i & 7) + ((i >> 3) & 1) * (d >> 1);
+  }
   uint4 v = make_uint4(0, 0, 0, 0);
   if (n < N && k < K) v = *reinterpret_cast<const uint4*>(src + (size_t)n * K + k);  // K % 8 == 0
   *reinterpret_cast<uint4*>(dst + f * 8) = v;
@@ -725,39 +724,66 @@ void launch_skinny(const SkinnyArgs& a, int n_wg, hipStream_t st) {
   hipLaunchKernelGGL((k_skinny<MODE, NB, TW, KW, U, RT>), dim3((n_wg + RT - 1) / RT), dim3(TW * KW * 64), lds, st, a);
 }
 
-// passes of at most 64 batch rows (128 where the workgroup has eight waves to finish eight batch tiles and more than
-// 64 rows are left: every pass streams the whole weight matrix again); NB = 16-row batch tiles per pass.
-// n_wg: workgroups at one weight tile per wave.
-template <int MODE, int TW, int KW>
-void dispatch_skinny(SkinnyArgs a, int n_wg, hipStream_t st) {
-  // Two weight tiles per wave (RT = 2) halve the workgroups.  Measured on 256 compute units: with 64 rows per pass
-  // it pays only where two workgroups per compute unit remain (gate/up, output layer; the 256-tile projections lost
-  // more from running on half the chip than they gained); with 128 rows per pass it pays everywhere.  q,k,v: the
-  // rotation indices of a head (d/2) split into groups of 16 * RT; d = 32 has a single 16-row group.
-  const bool rt_ok = MODE != MODE_QKV || (a.d >> 5) % 2 == 0;
-  const bool rt2_64 = rt_ok && n_wg >= 2 * kComputeUnits;
+// Weight tiles per wave for a pass of 17 to 32 rows.  A compute unit takes in 9 to 13 TB/s / 256 of weights and batch
+// fragments together, and the fragments are as many bytes as the weights per 16 batch rows and tile: RT tiles share
+// them, but RT times fewer workgroups may leave compute units with fewer tiles than their neighbours.  So: the RT with the
+// fewest tiles on the fullest compute unit, the larger one at equal counts.  Measured at 32 rows, RT 1 / 2 / 4: q,k,v of
+// 960 tiles 42 / 34 / 30 us (4 tiles at most in each), 320-tile projections over K = 13824 47 / 37 / 53 us (2 / 2 / 4),
+// gate/up of 2 x 864 71 / 56 / 49 us; at 21 rows gate/up of 2 x 1184 56 / 53 / 62 us (5 / 6 / 8: 5 against 6 misses by
+// 6 %), 224-tile projections over K = 18944 31 / 44 / 64 us.
+int tiles_per_wave(int n_tiles, int rt_max) {
+  int best = 1, best_n = 1 << 30;
+  for (int rt = 1; rt <= rt_max; rt *= 2) {
+    const int wgs = (n_tiles + rt - 1) / rt, most = (wgs + kComputeUnits - 1) / kComputeUnits * rt;
+    if (most <= best_n) best = rt, best_n = most;
+  }
+  return best;
+}
+
+// Passes of at most 64 batch rows (128 where more than 64 rows are left: every pass streams the whole weight matrix again);
+// NB = 16-row batch tiles per pass; n_tiles = 16-row tiles of the output (of one matrix of a gate/up pair).
+// Up to 16 rows one weight tile per wave is best throughout (7B layer at 8 rows, RT 1 / 2: q,k,v 18.4 / 23.6 us, down
+// 16.6 / 22.7, gate/up 29 / 36) but for the output layer of a large vocabulary (152064 at 12 rows, RT 1 / 4: 186 / 172).
+// Waves and loads in flight per wave are the best measured of {4, 8, 16} waves per tile and {4, 8, 16} loads.
+template <int MODE>
+void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
+  constexpr int TW = MODE == MODE_GATEUP ? 2 : 1;  // a gate/up workgroup takes the same tile of both matrices
+  // workgroups at one tile per wave with two waves side by side
+  const int n_two = MODE == MODE_GATEUP ? n_tiles : (n_tiles + 1) / 2;
   for (int b0 = 0; b0 < a.B;) {
     a.b0 = b0;
     const int left = a.B - b0;
-    if constexpr (TW * KW >= 8) {
-      if (left > 64) {
-        if (rt_ok)
-          launch_skinny<MODE, 8, TW, KW, 1, 2>(a, n_wg, st);
-        else
-          launch_skinny<MODE, 8, TW, KW, 1, 1>(a, n_wg, st);
-        b0 += 128;
-        continue;
-      }
+    if (left > 64) {
+      launch_skinny<MODE, 8, TW, 8 / TW, 1, 2>(a, n_tiles, st);
+      b0 += 128;
+      continue;
     }
-    const int nb = (min(left, 64) + 15) / 16;
-    if (nb == 1)
-      launch_skinny<MODE, 1, TW, KW, 8, 1>(a, n_wg, st);
-    else if (nb == 2)
-      launch_skinny<MODE, 2, TW, KW, 4, 1>(a, n_wg, st);
-    else if (rt2_64)
-      launch_skinny<MODE, 4, TW, KW, 2, 2>(a, n_wg, st);
-    else
-      launch_skinny<MODE, 4, TW, KW, 2, 1>(a, n_wg, st);
+    const int nb = (left + 15) / 16;
+    if (nb == 1) {
+      if (MODE == MODE_QKV) launch_skinny<MODE, 1, 1, 4, 16, 1>(a, n_tiles, st);
+      else if (MODE == MODE_RESID) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
+      else if (MODE == MODE_GATEUP) launch_skinny<MODE, 1, 2, 4, 8, 1>(a, n_tiles, st);
+      else if (left > 8 && n_tiles >= 16 * kComputeUnits) launch_skinny<MODE, 1, 2, 2, 4, 4>(a, n_two, st);
+      else launch_skinny<MODE, 1, 1, 8, 8, 1>(a, n_tiles, st);
+    } else if (nb == 2) {
+      const int rt = tiles_per_wave(n_tiles, MODE == MODE_RESID ? 2 : 4);
+      if (rt == 4 || MODE == MODE_LM) {
+        if (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 8, 4, 4>(a, n_tiles, st);
+        else if (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 4, 4, 4>(a, n_tiles, st);
+        else launch_skinny<MODE, 2, 2, 2, 4, 4>(a, n_two, st);
+      } else if (rt == 2) {
+        if (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 16, 4, 2>(a, n_tiles, st);
+        else if (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 2, 8, 2>(a, n_tiles, st);
+        else launch_skinny<MODE, 2, 1, 8, 8, 2>(a, n_tiles, st);
+      } else {
+        launch_skinny<MODE, 2, TW, 8 / TW, 8, 1>(a, n_tiles, st);
+      }
+    } else if (n_tiles >= 2 * kComputeUnits) {
+      // 64 rows per pass: two tiles per wave pay only where two workgroups per compute unit remain
+      launch_skinny<MODE, 4, TW, 8 / TW, 2, 2>(a, n_tiles, st);
+    } else {
+      launch_skinny<MODE, 4, TW, 8 / TW, 2, 1>(a, n_tiles, st);
+    }
     b0 += 64;
   }
 }
@@ -783,12 +809,13 @@ harli_status decode_step_f32(harli_ctx* c, const harli_decode_batch* b, hipStrea
 size_t packed_weight_elems(int N, int K) { return (size_t)((N + 15) / 16) * ((K + 31) / 32) * 512; }
 
 // dst must hold packed_weight_elems(N, K) bf16; rows [row_tile0*16, ...) of the packed matrix are written
-harli_status pack_weight(const void* src, void* dst, int N, int K, int row_tile0, hipStream_t st) {
+// (head_dim: 0, or the head size of a q, k or v matrix, whose rows are stored in rotation pairs)
+harli_status pack_weight(const void* src, void* dst, int N, int K, int row_tile0, int head_dim, hipStream_t st) {
   const int steps = (K + 31) / 32;
   const long long n_frag = (long long)((N + 15) / 16) * steps * 64;
   unsigned short* d = static_cast<unsigned short*>(dst) + (size_t)row_tile0 * steps * 512;
   hipLaunchKernelGGL(k_pack_weight, dim3((unsigned)((n_frag + 255) / 256)), dim3(256), 0, st,
-                     static_cast<const unsigned short*>(src), d, N, K, steps, n_frag);
+                     static_cast<const unsigned short*>(src), d, N, K, steps, n_frag, head_dim);
   HARLI_HIP(hipGetLastError());
   return HARLI_OK;
 }
@@ -847,7 +874,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
     // --- QKV + rotary + append
     a.x = static_cast<const unsigned short*>(w.hx1);
     a.K = H;
-    a.n_rows = QD;
+    a.n_rows = QD + 2 * m.n_kv_heads * d;
     a.w0 = static_cast<const unsigned short*>(lw.wp[0]);
     a.ssq_np = np;
     a.ssq_in = w.ssq + (size_t)(2 * l) * w.bpad * np;
@@ -867,7 +894,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       harli_status rc = dg_launch(DG_QKV, a, x_tiles, w.part, w.part_bytes, n_cu, st);
       if (rc != HARLI_OK) return rc;
     } else {
-      dispatch_skinny<MODE_QKV, 2, 2>(a, (m.n_q_heads + 2 * m.n_kv_heads) * (d / 32), st);
+      dispatch_skinny<MODE_QKV>(a, (m.n_q_heads + 2 * m.n_kv_heads) * (d / 16), st);
     }
     // --- attention
     if (d == 128 && G == 1) launch_attn<128, 1, 256>(c, w, b, l, st);
@@ -896,7 +923,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       harli_status rc = dg_launch(DG_RESID, a, x_tiles, w.part, w.part_bytes, n_cu, st);
       if (rc != HARLI_OK) return rc;
     } else {
-      dispatch_skinny<MODE_RESID, 1, 8>(a, (H + 15) / 16, st);
+      dispatch_skinny<MODE_RESID>(a, (H + 15) / 16, st);
     }
     // --- gate/up + SwiGLU
     a.x = static_cast<const unsigned short*>(w.hx2);
@@ -910,7 +937,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       harli_status rc = dg_launch(DG_GATEUP, a, x_tiles, w.part, w.part_bytes, n_cu, st);
       if (rc != HARLI_OK) return rc;
     } else {
-      dispatch_skinny<MODE_GATEUP, 2, 4>(a, (F + 15) / 16, st);
+      dispatch_skinny<MODE_GATEUP>(a, (F + 15) / 16, st);
     }
     // --- down projection + residual, operand of the next layer (or of the output layer)
     const bool last = (l == L - 1);
@@ -928,7 +955,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       harli_status rc = dg_launch(DG_RESID, a, x_tiles, w.part, w.part_bytes, n_cu, st);
       if (rc != HARLI_OK) return rc;
     } else {
-      dispatch_skinny<MODE_RESID, 1, 8>(a, (H + 15) / 16, st);
+      dispatch_skinny<MODE_RESID>(a, (H + 15) / 16, st);
     }
     xcur = xnext;
   }
@@ -949,7 +976,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       harli_status rc = dg_launch(DG_LM, a, x_tiles, w.part, w.part_bytes, n_cu, st);
       if (rc != HARLI_OK) return rc;
     } else {
-      dispatch_skinny<MODE_LM, 2, 4>(a, (m.vocab + 31) / 32, st);
+      dispatch_skinny<MODE_LM>(a, (m.vocab + 15) / 16, st);
     }
     if (b->next_token) {
       hipLaunchKernelGGL(k_argmax_part, dim3(kArgSeg, B), dim3(256), 0, st, b->logits, m.vocab, w.amax_v, w.amax_i);

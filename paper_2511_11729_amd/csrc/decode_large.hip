@@ -314,9 +314,10 @@ __global__ void __launch_bounds__(256) k_dg_qkv(SkinnyArgs a, const float* part,
   } else {
     which = 2, hl = head - a.n_q - a.n_kv;
   }
-  // q, k and v are packed as one matrix with heads in the order q.., k.., v..
-  const size_t col0 = (size_t)b * ncols + (size_t)head * a.d + idx0;
-  const float4 s0 = part_sum4(part, ksplit, split_stride, col0), s1 = part_sum4(part, ksplit, split_stride, col0 + half);
+  // q, k and v are packed as one matrix with heads in the order q.., k.., v.., a head as groups of eight rotation indices
+  // followed by their eight partners
+  const size_t col0 = (size_t)b * ncols + (size_t)head * a.d + (idx0 >> 3) * 16 + (idx0 & 7);
+  const float4 s0 = part_sum4(part, ksplit, split_stride, col0), s1 = part_sum4(part, ksplit, split_stride, col0 + 8);
   float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
   if (a.bias[which]) {
     const float* bp = a.bias[which] + hl * a.d + idx0;

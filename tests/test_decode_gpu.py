@@ -401,3 +401,26 @@ def test_vocabulary_that_is_not_a_multiple_of_four(batch):
     logits = case.logits_dev.cpu().numpy()
     assert_close(logits, ref_logits, "logits")
     assert np.array_equal(case.next_dev.cpu().numpy(), np.argmax(logits, axis=-1))
+
+
+# (model, batch): weight tiles of 16 rows per matrix against 256 compute units choose how many tiles a wave takes
+@pytest.mark.parametrize("idx,kw,batch", [
+    (3, dict(ffn=13832), 9),                     # up to 16 rows: one tile per wave; 7 idle rows in the fragment
+    (3, dict(ffn=13832), 17),                    # q,k,v 960 and gate/up 865 tiles (a ragged group of four): four; 320: two
+    (5, dict(vocab=16 * 257 * 16 + 8), 12),      # an output layer of 4113 tiles above 8 rows: four, ragged
+    (5, dict(vocab=1003), 32),                   # q,k,v 288, gate/up 1184 tiles: two; 224: one
+])
+def test_streaming_kernels_at_every_number_of_tiles_per_wave(idx, kw, batch):
+    w, m = variant(idx, n_layers=1, **kw)
+    lengths = np.asarray([(i * 23) % 70 for i in range(batch)], np.int32)
+    full = "vocab" in kw
+    case = DecodeCase(w, m, lengths, full_model=full)
+    if full:
+        tok = wl.make_token_ids(dataclasses.replace(w, model=m), (batch,))
+        hid = case.run_gpu(token_ids=tok)
+        ref_hid, ref_logits, _ = case.run_oracle(token_ids=tok)
+        assert_close(case.logits_dev.cpu().numpy(), ref_logits, "logits")
+    else:
+        hid, ref_hid = case.run_gpu(), case.run_oracle()
+    assert_close(hid, ref_hid, "hidden state")
+    case.check_cache()
