@@ -12,8 +12,14 @@
 //   * four LDS stages: while stage s is multiplied, s+1 has landed and s+2, s+3 are in flight;
 //   * one wave per SIMD has nobody to hide its waits, so the K loop is software pipelined by hand: the fragments of
 //     the next half step are read while the MFMAs of this one issue, and the eight loads a wave owes per stage are
-//     dealt out between MFMAs (sched_group_barrier pins that order).  The loop runs within 14 % of the MFMA issue
-//     bound in cycles; what it delivers is then set by the clock the chip grants under that load (1.5-1.6 GHz).
+//     dealt out between the MFMAs of both half steps (sched_group_barrier pins that order);
+//   * nothing but the loads' scalar offsets moves from stage to stage: every branch and mask of the cursor (end of a
+//     segment, of the range, a partial K step) is behind one comparison that is false on whole stages.
+// What it measures at 256-row tiles: a stage takes 1180 cycles against 1024 of MFMA issue (1500 with the cursor's branches
+// and masks in every stage and the loads on eight consecutive MFMAs).  In time this is 8 % and not 21: on random operands
+// the chip lowers its clock with the rate of products (1.67 -> 1.45 GHz; on zeros it stays at 2.4).
+// 4096 x 16384 x 4096: 526 -> 494 us; the 16 x 16 x 32 product, which drew less power in a bare loop (0.59 against
+// 0.64 us a stage), kept the register allocator copying accumulators between the register files.
 // FM = 2 (128-row tiles) doubles the tile count for outputs that would not fill the chip with 256-row tiles.
 #include "gemm2.h"
 
@@ -281,7 +287,8 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
   unsigned soffA = 0, soffB[4] = {0u, 0u, 0u, 0u};
   bool pairseg = false;
   int seg = -1, k0 = 0, Kseg = 0, issued = 0;
-  bool valid = n_stage > 0;
+  int k_last = 0;           // last k0 of this segment whose stage is a whole one of this tile
+  unsigned vA[FM], vB = 0;  // the offsets the loads use: voffA, voffB or kOut
 
   // (macros rather than lambdas: arrays captured by reference were left in scratch memory by the compiler)
 #define G2_OPEN_SEG()                                                                                                  \
@@ -315,34 +322,44 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
       }                                                                                                                \
     }                                                                                                                  \
   } while (0)
-  // moves the cursor to the stage after the one just issued
-#define G2_ADVANCE()                                                                                                   \
-  do {                                                                                                                 \
-    ++issued;                                                                                                          \
-    valid = issued < n_stage;                                                                                          \
-    if (valid) {                                                                                                       \
-      k0 += BK;                                                                                                        \
-      if (k0 >= Kseg) {                                                                                                \
-        G2_OPEN_SEG();                                                                                                 \
-      } else {                                                                                                         \
-        soffA += BK * 2;                                                                                               \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) soffB[j] += BN * BK * 2;                                         \
-      }                                                                                                                \
-    }                                                                                                                  \
+  // the stage at the cursor is not simply the next 32 k of its segment: past the range, past the segment, or its tail
+#define G2_TURN()                                                                                                     \
+  do {                                                                                                                \
+    if (issued >= n_stage) {                                                                                          \
+      _Pragma("unroll") for (int j = 0; j < FM; ++j) vA[j] = kOut;                                                    \
+      vB = kOut;                                                                                                      \
+      soffA = soffB[0] = soffB[1] = soffB[2] = soffB[3] = 0;                                                          \
+      k_last = 0x7fffffff;                                                                                            \
+    } else {                                                                                                          \
+      if (k0 >= Kseg) G2_OPEN_SEG();                                                                                  \
+      const bool whole = Kseg - k0 >= BK;                                                                             \
+      _Pragma("unroll") for (int j = 0; j < FM; ++j) vA[j] = whole || k0 + dchunk * 8 < Kseg ? voffA[j] : kOut;       \
+      vB = voffB;                                                                                                     \
+      k_last = whole ? min(k0 + (n_stage - issued - 1) * BK, Kseg / BK * BK - BK) : k0;                               \
+    }                                                                                                                 \
   } while (0)
-#define G2_BL(rs, voff, soff, sp) \
+  // moves the cursor to the next stage; G2_TURN follows when it ends up past k_last
+#define G2_NEXT()                                                                                                     \
+  do {                                                                                                                \
+    ++issued;                                                                                                         \
+    k0 += BK;                                                                                                         \
+    soffA += BK * 2;                                                                                                  \
+    _Pragma("unroll") for (int j = 0; j < 4; ++j) soffB[j] += BN * BK * 2;                                            \
+  } while (0)
+#define G2_BL(rs, voff, soff, sp)                                                                                     \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sp), 16, (int)(voff), (int)(soff), 0, 0)
-#define G2_ISSUE(buf)                                                                                                  \
-  do {                                                                                                                 \
-    char* SA = smem + (buf) * STG;                                                                                     \
-    char* SB = SA + ASZ;                                                                                               \
-    const bool kok = valid && (k0 + dchunk * 8 < Kseg);                                                                \
-    _Pragma("unroll") for (int j = 0; j < FM; ++j) G2_BL(rsA, kok ? voffA[j] : kOut, soffA, SA + (wave * FM + j) * 1024); \
-    const unsigned vb = valid ? voffB : kOut;                                                                          \
-    G2_BL(rsB, vb, soffB[0], SB + (wave * 4 + 0) * 1024);                                                              \
-    G2_BL(rsB, vb, soffB[1], SB + (wave * 4 + 1) * 1024);                                                              \
-    G2_BL(rsB2, vb, soffB[2], SB + (wave * 4 + 2) * 1024);                                                             \
-    G2_BL(rsB2, vb, soffB[3], SB + (wave * 4 + 3) * 1024);                                                             \
+#define G2_ISSUE_A(buf)                                                                                               \
+  do {                                                                                                                \
+    char* SA = smem + (buf) * STG;                                                                                    \
+    _Pragma("unroll") for (int j = 0; j < FM; ++j) G2_BL(rsA, vA[j], soffA, SA + (wave * FM + j) * 1024);             \
+  } while (0)
+#define G2_ISSUE_B(buf)                                                                                               \
+  do {                                                                                                                \
+    char* SB = smem + (buf) * STG + ASZ;                                                                              \
+    G2_BL(rsB, vB, soffB[0], SB + (wave * 4 + 0) * 1024);                                                             \
+    G2_BL(rsB, vB, soffB[1], SB + (wave * 4 + 1) * 1024);                                                             \
+    G2_BL(rsB2, vB, soffB[2], SB + (wave * 4 + 2) * 1024);                                                            \
+    G2_BL(rsB2, vB, soffB[3], SB + (wave * 4 + 3) * 1024);                                                            \
   } while (0)
 
   // fragment reads: row lane%32, 16-byte chunk 2 sub + lane/32, swizzled like the loads
@@ -366,41 +383,34 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, FA[i]),                  \
                                                                    __builtin_bit_cast(bf16x8, FB[j]), acc[i][j], 0, 0, 0); \
   } while (0)
-  // issue order of a half step: the FM + 4 fragment reads ride on the first MFMAs, then one load per MFMA
+  // issue order of a half step: the FM + 4 fragment reads ride on the first MFMAs, the loads are spread over the rest
   constexpr int kRd = (FM + 4) / 2;             // MFMAs that carry the fragment reads (two reads each)
   constexpr int kRest = 4 * FM - kRd;           // MFMAs left in the half step
-  constexpr int kLd = LOADS < kRest ? LOADS : kRest;  // loads that get an MFMA of their own
-#define G2_PIPE_RD()                                                                                                   \
-  do {                                                                                                                 \
-    _Pragma("unroll") for (int q = 0; q < kRd; ++q) { G2_SGB(0x008, 1); G2_SGB(0x100, 2); }                            \
+#define G2_PIPE(loads)                                                                                                \
+  do {                                                                                                                \
+    _Pragma("unroll") for (int q = 0; q < kRd; ++q) { G2_SGB(0x008, 1); G2_SGB(0x100, 2); }                           \
+    _Pragma("unroll") for (int q = 0; q < (loads); ++q) { G2_SGB(0x020, 1); G2_SGB(0x008, kRest / (loads)); }         \
+    if (kRest % (loads)) G2_SGB(0x008, kRest % (loads));                                                              \
   } while (0)
-#define G2_PIPE1()                                                                                                     \
-  do {                                                                                                                 \
-    G2_PIPE_RD();                                                                                                      \
-    G2_SGB(0x008, kRest);                                                                                              \
-  } while (0)
-#define G2_PIPE2()                                                                                                     \
-  do {                                                                                                                 \
-    G2_PIPE_RD();                                                                                                      \
-    _Pragma("unroll") for (int q = 0; q < kLd; ++q) { G2_SGB(0x008, 1); G2_SGB(0x020, 1); }                            \
-    if (LOADS > kLd) G2_SGB(0x020, LOADS - kLd);                                                                       \
-    if (kRest > kLd) G2_SGB(0x008, kRest - kLd);                                                                       \
-  } while (0)
-#define G2_STEP(cur, nxt, dma)                                                                                         \
-  do {                                                                                                                 \
-    G2_RD(fa1, fb1, cur, 1);                                                                                           \
-    G2_MM(fa0, fb0);                                                                                                   \
-    G2_PIPE1();                                                                                                        \
-    G2_SB0();                                                                                                          \
-    G2_ADVANCE();                                                                                                      \
-    G2_WAITV((NS - 3) * LOADS); /* all but the NS - 3 newest stages in flight have landed: stage `nxt` is in LDS */   \
-    __builtin_amdgcn_s_barrier();                                                                                      \
-    G2_SB0();                                                                                                          \
-    G2_RD(fa0, fb0, nxt, 0);                                                                                           \
-    G2_ISSUE(dma);                                                                                                     \
-    G2_MM(fa1, fb1);                                                                                                   \
-    G2_PIPE2();                                                                                                        \
-    G2_SB0();                                                                                                          \
+  // One stage: in the first half the weight side of the stage three ahead of the previous one is issued and the cursor
+  // moves on, in the second, when the barrier has freed the oldest buffer, the activation side of the next.
+#define G2_STEP(cur)                                                                                                  \
+  do {                                                                                                                \
+    G2_RD(fa1, fb1, cur, 1);                                                                                          \
+    G2_ISSUE_B(((cur) + 2) % NS);                                                                                     \
+    G2_MM(fa0, fb0);                                                                                                  \
+    G2_NEXT();                                                                                                        \
+    G2_PIPE(4);                                                                                                       \
+    G2_SB0();                                                                                                         \
+    if (k0 > k_last) G2_TURN();                                                                                       \
+    G2_WAITV(LOADS); /* all but the newest stage have landed: the next one is in LDS */                               \
+    __builtin_amdgcn_s_barrier();                                                                                     \
+    G2_SB0();                                                                                                         \
+    G2_RD(fa0, fb0, ((cur) + 1) % NS, 0);                                                                             \
+    G2_ISSUE_A(((cur) + 3) % NS);                                                                                     \
+    G2_MM(fa1, fb1);                                                                                                  \
+    G2_PIPE(FM);                                                                                                      \
+    G2_SB0();                                                                                                         \
   } while (0)
 
   const bool probe = a.clk != nullptr && blockIdx.x == 0;
@@ -418,49 +428,39 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
 #pragma unroll
       for (int j = 0; j < 4; ++j) soffB[j] += (unsigned)k0 * (BN * 2u);
     }
-    G2_ISSUE(0);
-    G2_ADVANCE();
-    G2_ISSUE(1);
-    G2_ADVANCE();
-    G2_ISSUE(2);
-    if constexpr (NS == 6) {
-      G2_ADVANCE();
-      G2_ISSUE(3);
-      G2_ADVANCE();
-      G2_ISSUE(4);
-    }
-    G2_WAITV((NS - 2) * LOADS);
+    G2_TURN();
+    G2_ISSUE_A(0);
+    G2_ISSUE_B(0);
+    G2_NEXT();
+    if (k0 > k_last) G2_TURN();
+    G2_ISSUE_A(1);
+    G2_ISSUE_B(1);
+    G2_NEXT();
+    if (k0 > k_last) G2_TURN();
+    G2_ISSUE_A(2);
+    G2_WAITV(LOADS + FM);
     __builtin_amdgcn_s_barrier();
     G2_RD(fa0, fb0, 0, 0);
     G2_SB0();
     for (int st = 0; st < n_step; st += NS) {
-      if constexpr (NS == 4) {
-        G2_STEP(0, 1, 3);
-        G2_STEP(1, 2, 0);
-        G2_STEP(2, 3, 1);
-        G2_STEP(3, 0, 2);
-      } else {
-        G2_STEP(0, 1, 5);
-        G2_STEP(1, 2, 0);
-        G2_STEP(2, 3, 1);
-        G2_STEP(3, 4, 2);
-        G2_STEP(4, 5, 3);
-        G2_STEP(5, 0, 4);
-      }
+      G2_STEP(0);
+      G2_STEP(1);
+      G2_STEP(2);
+      G2_STEP(3);
     }
     G2_WAITV(0);
   }
   if (probe && tid == 0) a.clk[0] = clock64() - c_start, a.clk[1] = wall_clock64() - w_start;
   __syncthreads();  // every wave is done with the stage buffers: the epilogue reuses them
 #undef G2_OPEN_SEG
-#undef G2_ADVANCE
-#undef G2_ISSUE
+#undef G2_TURN
+#undef G2_NEXT
+#undef G2_ISSUE_A
+#undef G2_ISSUE_B
 #undef G2_BL
 #undef G2_RD
 #undef G2_MM
-#undef G2_PIPE_RD
-#undef G2_PIPE1
-#undef G2_PIPE2
+#undef G2_PIPE
 #undef G2_STEP
 
   if (piece >= 0) {
