@@ -34,6 +34,7 @@
 // and after: q,k,v 27.6 -> 18.4 us, output 8.6 -> 7.3, gate/up 37.3 -> 29.3, down
 // 21.9 -> 16.6; of the 13B class at 32 rows 45.6 -> 30.1, 20 -> 15.7, 79.9 -> 48.9,
 // 54.6 -> 37.2.
+#include <algorithm>
 #include <mutex>
 
 #include "ctx.h"
@@ -620,6 +621,211 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_m
   }
 }
 
+// The same chunk with the products on the matrix units, for five to eight query heads per KV head at d = 128: there the
+// vector form spends 8 G multiply-adds, two unpackings and lane reductions on every 16 bytes it loads and is bound by them
+// (28 query heads on 4, 21 sequences, 38 MB of keys and values a layer: 25.3 -> 14.8 us).  At four heads it is not (996 MB:
+// 235 us in the vector form, 245 in this one), below it is bound by memory.
+// fp32 queries and probabilities are cut into three bf16 terms of eight significand bits each, which is exact, and the
+// terms are columns of products: column c of a 16-wide operand is query c % 8, term c / 8, the third term in a second
+// product.  Keys are the row operand straight from memory (lane: token i16, 16
+// bytes of its vector), S = K q^T leaves lane (i16, g) the scores of tokens 4 g..4 g + 3, and that is the column operand of
+// O^T = V^T P^T as it lies, tokens in the order (page 2 s: 4 g + j, page 2 s + 1: 4 g + j).  V goes to LDS as it lies, its
+// 16-byte chunks permuted on the way in, and is transposed on the way out (ds_read_b64_tr_b16): conflict free both ways.
+// Tokens past the sequence lie behind the page's buffer resource: zeros.
+__device__ __forceinline__ float top16(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+// term `t` (0, 1, 2; others: zero) of x
+__device__ __forceinline__ float bf_term(float x, int t) {
+  const float a = top16(x), r = x - a, b = top16(r);
+  return t == 0 ? a : t == 1 ? b : t == 2 ? r - b : 0.f;
+}
+__device__ __forceinline__ unsigned pack_top(float lo, float hi) {  // two values that are bf16 already
+  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+// eight values of one column: rows 4 g.. of the blocks a 16-lane group points at with p0 and with p1
+__device__ __forceinline__ bf16x8 transposed_8(char* p0, char* p1) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p0);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p1);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int G, int CH>
+__global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const int* kv_len, const int* page_table, int max_pages,
+                                                       int layer, int n_q, int n_kv, const char* slab, KvGeom geom, float* part,
+                                                       int max_chunks, unsigned short* obuf, int* err_flag) {
+  constexpr int D = 128, PW = CH / kPageTokens / 4, QG = 8, NT = 2;  // queries per term, products per step
+  static_assert(G <= QG && PW % 2 == 0 && G * D * 4 <= PW * 4096, "whole steps of 32 tokens; a wave's output fits its share of V");
+  __shared__ __align__(1024) char s_v[4 * PW * 4096];
+  __shared__ float s_m[4][G], s_l[4][G];
+  const int b = blockIdx.z, c = blockIdx.y, ch = blockIdx.x;
+  const int n_tot = kv_len[b] + 1;
+  // the grid covers the caller's bound max_kv_len: a longer sequence would lose its newest tokens without a word
+  if (ch == 0 && c == 0 && threadIdx.x == 0 && (n_tot > (int)gridDim.x * CH || n_tot > max_pages * kPageTokens))
+    atomicOr(err_flag, 4);
+  if (ch * CH >= n_tot) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int QD = n_q * D;
+
+  const int qi = i16 % QG, term = i16 / QG;
+  float4 qr[4][2];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const float* q = qbuf + (size_t)b * QD + (c * G + min(qi, G - 1)) * D + s * 32 + g * 8;
+    qr[s][0] = *reinterpret_cast<const float4*>(q), qr[s][1] = *reinterpret_cast<const float4*>(q + 4);
+  }
+  uint4 kf[PW][4];
+  int n_ok[PW];  // tokens of the page that belong to the sequence
+  char* vw = s_v + wave * (PW * 4096);
+  const int last_lp = min((n_tot - 1) / kPageTokens, max_pages - 1);
+  int pages[PW];
+  const size_t head_off = (size_t)c * kPageTokens * D * sizeof(unsigned short);
+#pragma unroll
+  for (int pp = 0; pp < PW; ++pp) {
+    const int lp = ch * (CH / kPageTokens) + wave * PW + pp;
+    int pg = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + min(lp, last_lp)]);
+    bool pgok = lp <= last_lp;
+    if (pg < 0 || pg >= geom.n_pages_total) {
+      if (pgok && lane == 0) atomicOr(err_flag, 1);
+      pg = 0;
+      pgok = false;
+    }
+    n_ok[pp] = pgok ? min(n_tot - lp * kPageTokens, kPageTokens) : 0;
+    pages[pp] = pg;
+    __amdgpu_buffer_rsrc_t rk =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(slab) + kv_page_off(geom, pg, layer, 0) + head_off, 0, n_ok[pp] * (D * 2), 0x00020000);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      kf[pp][s] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, i16 * 256 + s * 64 + g * 16, 0, 0));
+  }
+#pragma unroll
+  for (int pp = 0; pp < PW; ++pp) {
+    __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(slab) + kv_page_off(geom, pages[pp], layer, 1) + head_off, 0,
+                                                                  n_ok[pp] * (D * 2), 0x00020000);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int tok = it * 4 + g;  // chunk slot i16 of its row receives chunk i16 ^ 2 (tok % 8)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(vw + pp * 4096 + it * 1024), 16,
+                                               tok * 256 + ((i16 ^ ((tok & 7) << 1)) << 4), 0, 0, 0);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- scores: queries are scaled for scores in the log2 domain: s = q.k / sqrt(D) * log2(e) -------------------------------------------------------------
+  const float scale = 1.4426950408889634f * rsqrtf((float)D);
+  uint4 qf[NT][4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    float x[8] = {qr[s][0].x, qr[s][0].y, qr[s][0].z, qr[s][0].w, qr[s][1].x, qr[s][1].y, qr[s][1].z, qr[s][1].w};
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int t = qi < G ? term + 2 * n : 3;
+      float y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = bf_term(x[e] * scale, t);
+      qf[n][s] = make_uint4(pack_top(y[0], y[1]), pack_top(y[2], y[3]), pack_top(y[4], y[5]), pack_top(y[6], y[7]));
+    }
+  }
+  f32x4 sc[PW];
+  float m = -INFINITY;
+#pragma unroll
+  for (int pp = 0; pp < PW; ++pp) {
+    sc[pp] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int n = NT - 1; n >= 0; --n)
+        sc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[pp][s]), __builtin_bit_cast(bf16x8, qf[n][s]), sc[pp], 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v = sc[pp][e];
+      v += dpp_f<0x128>(v);  // the columns of the other terms: the 16-lane row rotated by 8
+      v = 4 * g + e < n_ok[pp] ? v : -INFINITY;
+      sc[pp][e] = v;
+      m = fmaxf(m, v);
+    }
+  }
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  const float m0 = m == -INFINITY ? 0.f : m;  // a wave without a token: every score is -inf, every probability 0
+  float l = 0.f;
+  f32x4 o[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint4 pf[PW / 2][NT];
+#pragma unroll
+  for (int st = 0; st < PW / 2; ++st) {
+    float p[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // the hardware exponential as it is: the argument is <= 0 and a result below the normal range may go to zero
+      p[e] = __builtin_amdgcn_exp2f(sc[2 * st + (e >> 2)][e & 3] - m0);
+      l += p[e];
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      float y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = bf_term(p[e], term + 2 * n);
+      pf[st][n] = make_uint4(pack_top(y[0], y[1]), pack_top(y[2], y[3]), pack_top(y[4], y[5]), pack_top(y[6], y[7]));
+    }
+  }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+
+  // ---- O^T += V^T P^T -------------------------------------------------------------------------------------------------
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's values are in LDS
+  asm volatile("" ::: "memory");
+  const int row = 4 * g + (i16 >> 2);
+#pragma unroll
+  for (int st = 0; st < PW / 2; ++st)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      char* p = vw + st * 8192 + row * 256 + ((dt ^ (row & 7)) << 5) + (i16 & 3) * 8;
+      const bf16x8 v = transposed_8(p, p + 4096);
+#pragma unroll
+      for (int n = NT - 1; n >= 0; --n) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, __builtin_bit_cast(bf16x8, pf[st][n]), o[dt], 0, 0, 0);
+    }
+  asm volatile("" ::: "memory");
+  float* so = reinterpret_cast<float*>(vw);  // the wave's own share of V has been read: its output, [G][D]
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    float r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      r[e] = o[dt][e];
+      r[e] += dpp_f<0x128>(r[e]);
+    }
+    if (i16 < G) *reinterpret_cast<float4*>(so + i16 * D + dt * 16 + 4 * g) = make_float4(r[0], r[1], r[2], r[3]);
+  }
+  if (lane < G) s_m[wave][lane] = m, s_l[wave][lane] = l;
+  __syncthreads();
+  const int steps_o = (QD + 31) >> 5;
+  for (int idx = tid; idx < G * D; idx += 256) {
+    const int gq = idx / D, e = idx - gq * D;
+    const float M = fmaxf(fmaxf(s_m[0][gq], s_m[1][gq]), fmaxf(s_m[2][gq], s_m[3][gq]));
+    float L = 0.f, acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = (s_m[w][gq] == -INFINITY) ? 0.f : exp2f(s_m[w][gq] - M);
+      L += s_l[w][gq] * f;
+      acc += reinterpret_cast<const float*>(s_v + w * (PW * 4096))[idx] * f;
+    }
+    const int head = c * G + gq;
+    if (gridDim.x == 1) {
+      obuf[xfrag_off(b, head * D + e, steps_o)] = f2bf(acc / L);
+    } else {
+      float* p = part + (((size_t)b * n_q + head) * max_chunks + ch) * (D + 2);
+      p[2 + e] = acc;
+      if (e == 0) {
+        p[0] = M;
+        p[1] = L;
+      }
+    }
+  }
+}
+
 // Merge of the per-chunk partials: one workgroup per (query head, sequence).  A separate launch
 // rather than a last-arriver merge inside the attention kernel: a device-scope fence per
 // workgroup writes back and invalidates the whole L2 of its XCD on this chip and was measured
@@ -799,9 +1005,13 @@ template <int D, int G, int CH>
 void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, int layer, hipStream_t st) {
   const harli_model_cfg& m = c->cfg;
   const int n_chunks = (b->max_kv_len + CH - 1) / CH;
-  hipLaunchKernelGGL((k_paged_attn<D, G, CH>), dim3(n_chunks, m.n_kv_heads, b->batch), dim3(256), 0, st, w.qbuf,
-                     b->kv_len, b->page_table, b->max_pages, layer, m.n_q_heads, m.n_kv_heads, c->slab, c->geom,
-                     w.att_part, w.max_chunks, static_cast<unsigned short*>(w.obuf), w.err_flag);
+#define ATTN_LAUNCH(kernel)                                                                                             \
+  hipLaunchKernelGGL(kernel, dim3(n_chunks, m.n_kv_heads, b->batch), dim3(256), 0, st, w.qbuf, b->kv_len, b->page_table, \
+                     b->max_pages, layer, m.n_q_heads, m.n_kv_heads, c->slab, c->geom, w.att_part, w.max_chunks,         \
+                     static_cast<unsigned short*>(w.obuf), w.err_flag)
+  if constexpr (D == 128 && G >= 5) ATTN_LAUNCH((k_paged_attn_mm<G, CH>));
+  else ATTN_LAUNCH((k_paged_attn<D, G, CH>));
+#undef ATTN_LAUNCH
   if (n_chunks > 1)
     hipLaunchKernelGGL((k_attn_merge<D, CH>), dim3(m.n_q_heads, b->batch), dim3(D), 0, st, w.att_part, b->kv_len,
                        m.n_q_heads, w.max_chunks, static_cast<unsigned short*>(w.obuf));

@@ -109,6 +109,14 @@ def test_head_layouts(n_q, n_kv, d):
     run_case(w, m, [0, 37, 300, 16], block_bytes=256 << 10)
 
 
+@pytest.mark.parametrize("G", [5, 6, 7, 8])
+def test_matrix_unit_attention_at_the_edges_of_pages_and_chunks(G):
+    """Groups of five to eight query heads: the last token at the end and at the start of a page, of a wave's 32 tokens and
+    of a chunk of 128; two KV heads."""
+    w, m = variant(0, dtype="bf16", hidden=G * 128, n_q=2 * G, n_kv=2, head_dim=128, ffn=320)
+    run_case(w, m, [15, 31, 32, 126, 127, 128, 255, 256], block_bytes=256 << 10)
+
+
 def test_non_dividing_page_size():
     """Pages that do not divide the block (3 per 64 KiB block with slack), several chunks."""
     w, m = variant(0, dtype="bf16", hidden=640, n_q=5, n_kv=5, head_dim=128, ffn=256)
