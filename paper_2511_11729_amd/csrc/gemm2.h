@@ -101,7 +101,7 @@ struct Gemm2Cut {
   int chunk_full, chunk_cut;   // tiles / pieces per XCD
   double cost_us;              // what the choice was made by
 };
-// stages: K steps of the longest column tile.  n_cu: compute units of the stream.
+// stages: K steps of the longest column tile.  n_cu: compute units of the device, whatever share of them the stream has.
 Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes);
 // bytes of workspace that let gemm2_launch cut every launch of at most max_M rows and max_tiles_n column tiles as it wants
 size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages);

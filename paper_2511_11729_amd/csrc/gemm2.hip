@@ -723,7 +723,9 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
 #undef G2_ATTR
     attr_set = true;
   }
-  int n_cu = a.n_cu > 0 ? a.n_cu : cu_stream_count(st);
+  // The device's compute units, also on a stream confined to a share of them: where a tile is cut decides the order its K is
+  // added up in, and a unit gives the same bits on every partition.
+  int n_cu = a.n_cu;
   if (n_cu < 1) {
     n_cu = 256;
     int dev = 0;
