@@ -82,8 +82,8 @@ struct Gemm2Args {
   int rope_S, rope_d, rope_tiles;
   int* overflow_flag;  // device int: bit 8 is set when a 16-bit output had to be clamped to the element's range (or null)
   long long* clk;      // clock probe (or null): workgroup 0 writes {shader-clock cycles, 100 MHz ticks} of its K loop
-  // compute units the launch's stream may use (Harli Sec. 6.2: the finetune task runs on a share of them); 0: taken
-  // from the stream (harli_cu_stream_create), else the whole device.  The tile height and the cut along K are chosen for it.
+  // compute units the tile height and the cut along K are chosen for; 0: the device's.  Not the stream's share of them
+  // (Harli Sec. 6.2): the cut decides the order K is added up in, and a unit gives the same bits on every partition.
   int n_cu;
   // workspace for the partial tiles of a launch whose tiles are cut along K (or null: tiles are never cut); launches
   // that share it are ordered by their stream
