@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float y = __shfl_xor(x[e], 32, 64);  // the partner; (lo, hi) -> (lo cos - hi sin, hi cos + lo sin)
-          o[e] = x[e] * c[e] + (g < 2 ? -y : y) * s[e];
+          o[e] = q.which == 2 ? x[e] : x[e] * c[e] + (g < 2 ? -y : y) * s[e];  // v as it is: 0 * y is NaN beside an infinity
         }
         if (active) {
           if (q.which == 0) {

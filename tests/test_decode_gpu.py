@@ -432,3 +432,21 @@ def test_streaming_kernels_at_every_number_of_tiles_per_wave(idx, kw, batch):
         hid, ref_hid = case.run_gpu(), case.run_oracle()
     assert_close(hid, ref_hid, "hidden state")
     case.check_cache()
+
+
+@pytest.mark.parametrize("batch", [2, 20, 40])
+def test_an_infinite_value_element_stays_where_it_is(batch):
+    """v is stored as it was computed, rotated with nothing: an infinite element (here through its bias) changes no other
+    element of the appended vector, in particular not its rotation partner d/2 further."""
+    w, m = variant(0, dtype="bf16", qkv_bias=True)
+    lengths = np.asarray([3 + i % 20 for i in range(batch)], np.int32)
+    images = []
+    for value in (0.25, np.inf):
+        def bias(case):
+            case.layers_np[0]["bv"][5] = value
+        case = DecodeCase(w, m, lengths, block_bytes=64 << 10, tweak=bias)
+        case.run_gpu()
+        images.append(case.slab_image())
+    at = [case.geom.head_offset(int(case.table[b, n // 16]), 0, 1, 0, n % 16, m.head_dim * 2) // 2 + 5 for b, n in enumerate(lengths)]
+    assert np.array_equal(np.flatnonzero(images[0] != images[1]), np.sort(at))
+    assert np.all(images[1][at] == 0x7F80)                    # +infinity
