@@ -626,17 +626,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_m
 // (28 query heads on 4, 21 sequences, 38 MB of keys and values a layer: 25.3 -> 14.8 us).  At four heads it is not (996 MB:
 // 235 us in the vector form, 245 in this one), below it is bound by memory.
 // fp32 queries and probabilities are cut into three bf16 terms of eight significand bits each, which is exact, and the
-// terms are columns of products: column c of a 16-wide operand is query c % 8, term c / 8, the third term in a second
-// product.  Keys are the row operand straight from memory (lane: token i16, 16
+// terms are columns of two products: column c of a 16-wide operand is query c % 8, columns below 8 hold half of the first
+// term in either product, the others the second term in the first and the third in the second.  The two columns of a query
+// are added at the end, unless the first one is not finite: an infinite key or value times a lower term of zero is NaN, and
+// the first term alone has the infinity that the whole value would give.  Keys are the row operand straight from memory
+// (lane: token i16, 16
 // bytes of its vector), S = K q^T leaves lane (i16, g) the scores of tokens 4 g..4 g + 3, and that is the column operand of
 // O^T = V^T P^T as it lies, tokens in the order (page 2 s: 4 g + j, page 2 s + 1: 4 g + j).  V goes to LDS as it lies, its
 // 16-byte chunks permuted on the way in, and is transposed on the way out (ds_read_b64_tr_b16): conflict free both ways.
 // Tokens past the sequence lie behind the page's buffer resource: zeros.
 __device__ __forceinline__ float top16(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
-// term `t` (0, 1, 2; others: zero) of x
-__device__ __forceinline__ float bf_term(float x, int t) {
+// what product n takes of x in a column of the first term or (low) of the other two
+__device__ __forceinline__ float bf_term(float x, bool low, int n) {
   const float a = top16(x), r = x - a, b = top16(r);
-  return t == 0 ? a : t == 1 ? b : t == 2 ? r - b : 0.f;
+  return !low ? 0.5f * a : n == 0 ? b : r - b;
+}
+// the two columns of a query (eight lanes apart), the same in both
+__device__ __forceinline__ float sum_terms(float v, bool low) {
+  const float o = dpp_f<0x128>(v), first = low ? o : v;  // the 16-lane row rotated by 8
+  return fabsf(first) < INFINITY ? v + o : first;
 }
 __device__ __forceinline__ unsigned pack_top(float lo, float hi) {  // two values that are bf16 already
   return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
@@ -668,7 +676,8 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
   const int i16 = lane & 15, g = lane >> 4;
   const int QD = n_q * D;
 
-  const int qi = i16 % QG, term = i16 / QG;
+  const int qi = i16 % QG;
+  const bool low = i16 >= QG;
   float4 qr[4][2];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -720,10 +729,9 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
     float x[8] = {qr[s][0].x, qr[s][0].y, qr[s][0].z, qr[s][0].w, qr[s][1].x, qr[s][1].y, qr[s][1].z, qr[s][1].w};
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      const int t = qi < G ? term + 2 * n : 3;
       float y[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = bf_term(x[e] * scale, t);
+      for (int e = 0; e < 8; ++e) y[e] = qi < G ? bf_term(x[e] * scale, low, n) : 0.f;
       qf[n][s] = make_uint4(pack_top(y[0], y[1]), pack_top(y[2], y[3]), pack_top(y[4], y[5]), pack_top(y[6], y[7]));
     }
   }
@@ -739,9 +747,7 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
         sc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[pp][s]), __builtin_bit_cast(bf16x8, qf[n][s]), sc[pp], 0, 0, 0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float v = sc[pp][e];
-      v += dpp_f<0x128>(v);  // the columns of the other terms: the 16-lane row rotated by 8
-      v = 4 * g + e < n_ok[pp] ? v : -INFINITY;
+      const float v = 4 * g + e < n_ok[pp] ? sum_terms(sc[pp][e], low) : -INFINITY;
       sc[pp][e] = v;
       m = fmaxf(m, v);
     }
@@ -767,7 +773,7 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
     for (int n = 0; n < NT; ++n) {
       float y[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = bf_term(p[e], term + 2 * n);
+      for (int e = 0; e < 8; ++e) y[e] = bf_term(p[e], low, n);
       pf[st][n] = make_uint4(pack_top(y[0], y[1]), pack_top(y[2], y[3]), pack_top(y[4], y[5]), pack_top(y[6], y[7]));
     }
   }
@@ -793,10 +799,7 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
   for (int dt = 0; dt < 8; ++dt) {
     float r[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      r[e] = o[dt][e];
-      r[e] += dpp_f<0x128>(r[e]);
-    }
+    for (int e = 0; e < 4; ++e) r[e] = sum_terms(o[dt][e], low);
     if (i16 < G) *reinterpret_cast<float4*>(so + i16 * D + dt * 16 + 4 * g) = make_float4(r[0], r[1], r[2], r[3]);
   }
   if (lane < G) s_m[wave][lane] = m, s_l[wave][lane] = l;

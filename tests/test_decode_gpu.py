@@ -450,3 +450,23 @@ def test_an_infinite_value_element_stays_where_it_is(batch):
     at = [case.geom.head_offset(int(case.table[b, n // 16]), 0, 1, 0, n % 16, m.head_dim * 2) // 2 + 5 for b, n in enumerate(lengths)]
     assert np.array_equal(np.flatnonzero(images[0] != images[1]), np.sort(at))
     assert np.all(images[1][at] == 0x7F80)                    # +infinity
+
+
+@pytest.mark.parametrize("G", [4, 5, 8])
+def test_a_key_with_an_infinite_element_takes_its_token_out(G):
+    """A cached key element of -infinity against a query element that is positive in every head: the token's scores are
+    -infinity, its probability is zero and the step is finite, on the vector and on the matrix units.  (The query element
+    is the slowest rotation index under a large bias, so that no rotation changes its sign.)"""
+    w, m = variant(0, dtype="bf16", hidden=G * 64, n_q=G, n_kv=1, head_dim=128, ffn=320, qkv_bias=True)
+
+    def bias(case):
+        case.layers_np[0]["bq"].reshape(G, 128)[:, 63] = 30.0
+    case = DecodeCase(w, m, np.asarray([20, 150, 300], np.int32), block_bytes=64 << 10, tweak=bias)
+    img = case.img0.copy()
+    for b, n in enumerate(case.kv_len):                       # one token of each sequence, in its first, second or last chunk
+        tok = (3, 140, 299)[b]
+        img[case.geom.head_offset(int(case.table[b, tok // 16]), 0, 0, 0, tok % 16, 256) // 2 + 63] = 0xFF80
+    case.img0 = img
+    case.slab.copy_(torch.from_numpy(img.view(np.uint8)))
+    y = case.run_gpu()
+    assert_close(y, case.run_oracle(), "step with infinite keys")
