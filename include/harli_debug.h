@@ -46,8 +46,8 @@ typedef struct {
   int32_t* overflow_flag;
   double* tflops;
   double* shader_mhz;
-  /* Compute units the tile height is chosen for: 0 = those of `hip_stream` (all of the device unless it is a
-   * harli_cu_stream), n > 0 = n. */
+  /* Compute units the ranges of K are chosen for: 0 = the device's, n > 0 = n.  On a harli_cu_stream the tile height is
+   * chosen for the stream's share of them (harli_dbg_gemm2_cut). */
   int32_t n_cu;
   /* Ranges of K the tiles past the last full round of workgroups are cut into: 0 leaves the choice to the library, 1
    * never cuts, n > 1 asks for n (fewer where the contraction is too short). */
@@ -63,9 +63,19 @@ harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
  * its cost on n_cu compute units (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk,
  * grid and the rounds of tiles over the compute units.  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
  * of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over the blocks; slots past the matrix
- * are idle.  This is the order of a launch whose tiles are not cut along K; the library chooses tile height and cut by
- * the cost of its rounds. */
+ * are idle.  This is the order of a launch whose tiles are not cut along K; harli_dbg_gemm2_cut tells which are. */
 harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows, int32_t n_cu, int32_t* out);
+
+/* Tile height and cut the weight GEMM would choose (host logic only, no device needed) for M rows, tiles_n column tiles,
+ * `stages` K steps of 32 in the longest column tile, on a device of n_cu compute units of which the stream may use
+ * `share`, with part_bytes of workspace for partial tiles.  out[9] (host): tile rows, ranges of K (1: nothing is cut),
+ * tiles computed whole, tiles cut, row tiles, column tiles, row tiles per band, whole tiles and partial tiles per XCD.
+ * Cut launch: workgroups [0, 8 chunk_full) are the whole tiles, workgroup w computing tile (w % 8) * chunk_full + w / 8;
+ * workgroup 8 chunk_full + w computes piece p = (w % 8) * chunk_cut + w / 8, that is range p / rest of tile full + p % rest
+ * (indexes past either list are idle).  Tile t lies in band t / (GM * tiles_n) of GM row tiles (the last band may have
+ * fewer), column by column inside the band. */
+harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int64_t part_bytes,
+                                 int32_t* out);
 
 /* How one GEMM of a decode step above 32 sequences is cut (host logic only, no device needed): `batch` sequences,
  * n_mat (1, or 2 for gate and up) weight matrices of n_rows rows, contraction length K, on n_cu compute units, with

@@ -19,6 +19,16 @@ extern "C" harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t
   return HARLI_OK;
 }
 
+extern "C" harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int64_t part_bytes,
+                                            int32_t* out) {
+  if (!out || M < 1 || tiles_n < 1 || stages < 1 || n_cu < 1 || share < 1 || share > n_cu || part_bytes < 0)
+    return fail(HARLI_ERR_INVALID, "dbg_gemm2_cut: bad argument");
+  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share, (size_t)part_bytes);
+  const int v[9] = {64 * c.FM, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut};
+  for (int i = 0; i < 9; ++i) out[i] = v[i];
+  return HARLI_OK;
+}
+
 extern "C" harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream) {
   if (!d || d->nseg < 1 || d->nseg > kGemm2MaxSeg || d->nout < 1 || d->nout > kGemm2MaxOut)
     return fail(HARLI_ERR_INVALID, "dbg_gemm2: bad descriptor");

@@ -82,8 +82,8 @@ struct Gemm2Args {
   int rope_S, rope_d, rope_tiles;
   int* overflow_flag;  // device int: bit 8 is set when a 16-bit output had to be clamped to the element's range (or null)
   long long* clk;      // clock probe (or null): workgroup 0 writes {shader-clock cycles, 100 MHz ticks} of its K loop
-  // compute units the tile height and the cut along K are chosen for; 0: the device's.  Not the stream's share of them
-  // (Harli Sec. 6.2): the cut decides the order K is added up in, and a unit gives the same bits on every partition.
+  // compute units the cut along K is chosen for; 0: the device's.  The stream's share of them (Harli Sec. 6.2) only moves
+  // the tile height (gemm2_cut): the cut decides the order K is added up in, and a unit gives the same bits on every partition.
   int n_cu;
   // workspace for the partial tiles of a launch whose tiles are cut along K (or null: tiles are never cut); launches
   // that share it are ordered by their stream
@@ -101,8 +101,8 @@ struct Gemm2Cut {
   int chunk_full, chunk_cut;   // tiles / pieces per XCD
   double cost_us;              // what the choice was made by
 };
-// stages: K steps of the longest column tile.  n_cu: compute units of the device, whatever share of them the stream has.
-Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes);
+// stages: K steps of the longest column tile.  n_cu: compute units of the device, share: those the stream may use.
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t part_bytes);
 // bytes of workspace that let gemm2_launch cut every launch of at most max_M rows and max_tiles_n column tiles as it wants
 size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages);
 

@@ -620,33 +620,55 @@ Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
 // per MB.  (0.15 would fit the 128-row tiles alone; among the other kernels of a unit the chip holds a lower clock and the
 // 256-row tiles, which move fewer operand bytes per flop, lose less of it: 2048 x 4096 x 11008 as one round of 128-row
 // tiles or as half-length ranges of 256-row ones is 194 against 192 us alone and 213 against 203 inside a unit.)
-Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, size_t part_bytes) {
+// On a stream confined to `share` of the device's compute units (Harli Sec. 6.2) the ranges of K stay the device's: they
+// decide the order K is added up in, and a unit gives the same bits on every partition.  The height of the tiles does not:
+// where every tile is cut or none is, it is the cheaper one on the share (2048 x 4096 x 4096, not cut: 256 tiles of 128 rows
+// are one round on 256 compute units and a round and 26 stragglers on 230, where 128 tiles of 256 rows are one).  Units on
+// 230 compute units: 3 x 344 tokens of hidden size 3584 2200 -> 1917 us, 4 x 512 of 4096 2767 -> 2736.
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t part_bytes) {
+  const double t_fixed = 6.0;
+  auto step_us = [](int FM, int active) {
+    const double b = std::min(1.0, active / (FM == 4 ? 256.0 : 140.0));
+    return FM == 4 ? 0.68 + 0.34 * b * b : 0.41 + 0.18 * b * b;
+  };
+  auto sum_us = [](size_t bytes) { return bytes ? 4.0 + bytes / 1048576.0 * 0.19 : 0.0; };
+  auto make = [&](int FM, int ks, int full, double cost) {
+    Gemm2Cut c{};
+    c.FM = FM, c.ks = ks, c.cost_us = cost, c.tiles_n = tiles_n;
+    c.tiles_m = (M + 64 * FM - 1) / (64 * FM), c.GM = std::min(FM == 2 ? 8 : 4, c.tiles_m);
+    const int T = c.tiles_m * tiles_n;
+    c.full = ks > 1 ? full : T, c.rest = T - c.full;
+    c.chunk_full = (c.full + 7) / 8, c.chunk_cut = (c.rest * ks + 7) / 8;
+    return c;
+  };
   Gemm2Cut best{};
   best.cost_us = -1;
   for (int FM = 4; FM >= 2; FM -= 2) {
     if ((g_force_fm && FM != g_force_fm) || (!g_force_fm && FM == 4 && M <= 128)) continue;
     const int BM = 64 * FM, tiles_m = (M + BM - 1) / BM, T = tiles_m * tiles_n;
-    const double t_fixed = 6.0;
-    auto step_us = [&](int active) {
-      const double b = std::min(1.0, active / (FM == 4 ? 256.0 : 140.0));
-      return FM == 4 ? 0.68 + 0.34 * b * b : 0.41 + 0.18 * b * b;
-    };
     const int full = T / n_cu * n_cu, rest = T - full;
     const int ks_max = rest > 0 ? std::max(1, std::min(kMaxCut, stages / kMinCutStages)) : 1;
     for (int ks = 1; ks <= ks_max; ++ks) {
       const int pieces = rest * ks, r2 = (pieces + n_cu - 1) / n_cu;
       const size_t bytes = ks > 1 ? (size_t)pieces * BM * BN * 4 : 0;
       if (bytes > part_bytes) break;
-      double cost = (T / n_cu) * (stages * step_us(n_cu) + t_fixed);
-      if (r2 > 0) cost += r2 * (((stages + ks - 1) / ks) * step_us(std::min(pieces, n_cu)) + t_fixed);
-      if (ks > 1) cost += 4.0 + bytes / 1048576.0 * 0.19;
-      if (best.cost_us < 0 || (g_force_ks ? ks <= g_force_ks && (ks > best.ks || cost < best.cost_us) : cost < best.cost_us)) {
-        best = Gemm2Cut{};
-        best.FM = FM, best.ks = ks, best.cost_us = cost;
-        best.tiles_m = tiles_m, best.tiles_n = tiles_n, best.GM = std::min(FM == 2 ? 8 : 4, tiles_m);
-        best.full = ks > 1 ? full : T, best.rest = ks > 1 ? rest : 0;
-        best.chunk_full = (best.full + 7) / 8, best.chunk_cut = (best.rest * ks + 7) / 8;
-      }
+      double cost = (T / n_cu) * (stages * step_us(FM, n_cu) + t_fixed);
+      if (r2 > 0) cost += r2 * (((stages + ks - 1) / ks) * step_us(FM, std::min(pieces, n_cu)) + t_fixed);
+      cost += sum_us(bytes);
+      if (best.cost_us < 0 || (g_force_ks ? ks <= g_force_ks && (ks > best.ks || cost < best.cost_us) : cost < best.cost_us))
+        best = make(FM, ks, full, cost);
+    }
+  }
+  if (share < n_cu && !g_force_fm && M > 128 && (best.ks == 1 || best.full == 0)) {
+    const int ks = best.ks, len = (stages + ks - 1) / ks;
+    best.cost_us = -1;
+    for (int FM = 4; FM >= 2; FM -= 2) {
+      const int BM = 64 * FM, n = (M + BM - 1) / BM * tiles_n * ks, last = n % share;  // workgroups, and those of the last round
+      const size_t bytes = ks > 1 ? (size_t)n * BM * BN * 4 : 0;
+      if (bytes > part_bytes) continue;
+      double cost = (n / share) * (len * step_us(FM, share) + t_fixed) + sum_us(bytes);
+      if (last) cost += len * step_us(FM, last) + t_fixed;
+      if (best.cost_us < 0 || cost < best.cost_us) best = make(FM, ks, 0, cost);
     }
   }
   return best;
@@ -723,8 +745,6 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
 #undef G2_ATTR
     attr_set = true;
   }
-  // The device's compute units, also on a stream confined to a share of them: where a tile is cut decides the order its K is
-  // added up in, and a unit gives the same bits on every partition.
   int n_cu = a.n_cu;
   if (n_cu < 1) {
     n_cu = 256;
@@ -739,7 +759,8 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
       if (a.seg[q].tile0 <= a.seg[s].tile0 && a.seg[q].tile1 > a.seg[s].tile0) n += (a.seg[q].K + BK - 1) / BK;
     stages = std::max(stages, n);
   }
-  const Gemm2Cut cut = gemm2_cut(a.M, a.tiles_n, stages, n_cu, a.part ? a.part_bytes : 0);
+  const int share = cu_stream_count(st);  // 0: not confined
+  const Gemm2Cut cut = gemm2_cut(a.M, a.tiles_n, stages, n_cu, share > 0 ? std::min(share, n_cu) : n_cu, a.part ? a.part_bytes : 0);
   const int FM = cut.FM;
   const Gemm2Plan pl = gemm2_plan(a.M, a.tiles_n, FM, n_cu);
   const int GM = pl.GM, GN = pl.GN, total = pl.total, chunk = pl.chunk, grid = cut.ks > 1 ? 8 * (cut.chunk_full + cut.chunk_cut) : pl.grid;

@@ -153,6 +153,7 @@ def test_full_size_shapes_on_a_nine_tenths_partition():
     timings of both tile heights on the partition for the record."""
     M, N, K = 2048, 4096, 4096
     assert hb.dbg_gemm2_plan(M, N // 256, 128, 230)["rounds"] == 2 and hb.dbg_gemm2_plan(M, N // 256, 256, 230)["rounds"] == 1
+    assert hb.dbg_gemm2_cut(M, N // 256, K // 32, torch.cuda.get_device_properties(0).multi_processor_count, 230)["rows"] == 256
     A, B = rnd((M, K), True, 60, 0.5), rnd((N, K), True, 61, 0.05)
     rows = [0, 1, 255, 256, M // 2 + 7, M - 1]
     ref = f64(A[rows]) @ f64(B).T
@@ -239,3 +240,23 @@ def test_rotary_epilogue(d, M, S, ksplit):
     lo, hi = x[..., : d // 2], x[..., d // 2:]
     close(f64(cb[0]), np.concatenate([lo * c - hi * s, hi * c + lo * s], -1).reshape(M, -1), "rotated block")
     close(f64(cb[1]), f64(A) @ f64(W[1]).T, "plain block")
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 4096, 512), (300, 1024, 4096), (1032, 18944, 2048)])
+def test_a_partition_gives_the_bits_of_the_whole_device(M, N, K):
+    """No tile cut, all of them, and whole tiles beside cut ones: the tile height follows the stream, the sums do not."""
+    A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    out = []
+    for count in (n_cu, n_cu - 26, n_cu // 4):
+        st = hb.cu_stream_create(0, count)
+        try:
+            cf = torch.full((M, N), float("nan"), device=DEV)
+            torch.cuda.synchronize()
+            hb.dbg_gemm2(M, [dict(A=A, B=B)], [dict(N=N, cf=cf)], stream=st)
+            torch.cuda.synchronize()
+            out.append(cf)
+        finally:
+            hb.cu_stream_destroy(st)
+    close(f64(out[0][::97]), f64(A[::97]) @ f64(B).T, "fp32 output", 1e-5)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])

@@ -51,3 +51,21 @@ def test_bad_arguments():
         hb.dbg_gemm2_plan(2048, 16, 100, 230)
     with pytest.raises(hb.HarliError):
         hb.dbg_gemm2_plan(2048, 16, 128, 0)
+
+
+@pytest.mark.parametrize("M,tiles_n,stages", [(2048, 16, 129), (2048, 48, 129), (4096, 20, 434), (48, 16, 345), (600, 20, 434), (129, 5, 40)])
+@pytest.mark.parametrize("share", [230, 128, 26])
+def test_a_share_of_the_compute_units_moves_the_tile_height_and_no_range_of_k(M, tiles_n, stages, share):
+    """The ranges of K decide the order of the sums: those of a confined stream are the device's, over the same tiles."""
+    whole, part = hb.dbg_gemm2_cut(M, tiles_n, stages, 256), hb.dbg_gemm2_cut(M, tiles_n, stages, 256, share)
+    assert part["ks"] == whole["ks"] and (part["full"] == 0) == (whole["full"] == 0)
+    if whole["full"] and whole["rest"]:
+        assert part == whole                                  # which tiles are cut depends on the tile height
+    assert M > 128 or part["rows"] == 128
+
+
+def test_tile_height_on_nine_tenths_of_the_chip():
+    """2048 x 4096 x 4096 is one round of 128-row tiles on 256 compute units, and on 230 one of 256-row tiles."""
+    assert hb.dbg_gemm2_cut(2048, 16, 128, 256)["rows"] == 128
+    part = hb.dbg_gemm2_cut(2048, 16, 128, 256, 230)
+    assert part["rows"] == 256 and part["ks"] == 1 and part["full"] == 128
