@@ -56,6 +56,8 @@ typedef struct {
    * [position][rope_d / 2], row m at position m % rope_S. */
   int32_t rope_S, rope_d, rope_tiles;
   const void* rope;
+  /* Bytes of workspace for the partial tiles: 0 = 64 MiB. */
+  int64_t part_bytes;
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 
@@ -68,12 +70,13 @@ harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows,
 
 /* Tile height and cut the weight GEMM would choose (host logic only, no device needed) for M rows, tiles_n column tiles,
  * `stages` K steps of 32 in the longest column tile, on a device of n_cu compute units of which the stream may use
- * `share`, with part_bytes of workspace for partial tiles.  out[9] (host): tile rows, ranges of K (1: nothing is cut),
- * tiles computed whole, tiles cut, row tiles, column tiles, row tiles per band, whole tiles and partial tiles per XCD.
+ * `share`.  out[10] (host): tile rows, ranges of K (1: nothing is cut), tiles computed whole, tiles cut, row tiles,
+ * column tiles, row tiles per band, whole tiles and partial tiles per XCD, and the tiles that are cut per pass with
+ * part_bytes of workspace for partial tiles (0: it does not hold those of one tile).
  * Cut launch: workgroups [0, 8 chunk_full) are the whole tiles, workgroup w computing tile (w % 8) * chunk_full + w / 8;
  * workgroup 8 chunk_full + w computes piece p = (w % 8) * chunk_cut + w / 8, that is range p / rest of tile full + p % rest
  * (indexes past either list are idle).  Tile t lies in band t / (GM * tiles_n) of GM row tiles (the last band may have
- * fewer), column by column inside the band. */
+ * fewer), column by column inside the band.  A launch in passes cuts as many tiles at a time, the first beside the whole ones. */
 harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int64_t part_bytes,
                                  int32_t* out);
 

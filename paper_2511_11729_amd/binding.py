@@ -550,7 +550,8 @@ class DbgGemm2Desc(C.Structure):
                 ("ldcf", C.c_int64 * 3), ("e0", C.c_void_p), ("e1", C.c_void_p), ("o0", C.c_void_p), ("o1", C.c_void_p),
                 ("lde", C.c_int64), ("overflow_flag", C.c_void_p), ("tflops", C.POINTER(C.c_double)),
                 ("shader_mhz", C.POINTER(C.c_double)), ("n_cu", C.c_int32), ("ksplit", C.c_int32),
-                ("rope_S", C.c_int32), ("rope_d", C.c_int32), ("rope_tiles", C.c_int32), ("rope", C.c_void_p)]
+                ("rope_S", C.c_int32), ("rope_d", C.c_int32), ("rope_tiles", C.c_int32), ("rope", C.c_void_p),
+                ("part_bytes", C.c_int64)]
 
 
 def decode_tiled_min_batch() -> int:
@@ -586,14 +587,14 @@ def dbg_gemm2_plan(M: int, tiles_n: int, tile_rows: int, n_cu: int) -> dict:
 
 def dbg_gemm2_cut(M: int, tiles_n: int, stages: int, n_cu: int, share: int = 0, part_bytes: int = 64 << 20) -> dict:
     """Tile height and cut along K of a launch of the weight GEMM (host logic); share 0: all of n_cu."""
-    out = (C.c_int32 * 9)()
+    out = (C.c_int32 * 10)()
     _check(lib().harli_dbg_gemm2_cut(M, tiles_n, stages, n_cu, share or n_cu, part_bytes, out))
-    return dict(zip(("rows", "ks", "full", "rest", "tiles_m", "tiles_n", "GM", "chunk_full", "chunk_cut"), list(out)))
+    return dict(zip(("rows", "ks", "full", "rest", "tiles_m", "tiles_n", "GM", "chunk_full", "chunk_cut", "per_pass"), list(out)))
 
 
 def dbg_gemm2(M, segs, outs, *, half=True, epi=0, alpha=1.0, tile_rows=0, reps=0, e0=None, e1=None, o0=None, o1=None, lde=0,
               overflow_flag=None, stream=None, n_cu=0, ksplit=0,
-              rope=None, rope_S=0, rope_d=0, rope_tiles=0):
+              rope=None, rope_S=0, rope_d=0, rope_tiles=0, part_bytes=0):
     """Test hook for the finetune unit's weight GEMM.  segs: dicts with A (device [M, K], 16-bit), optional lda,
     B (device [rows, K] row-major weight side; the hook blocks it), optional B2 and pair, optional tile0 / tile1.
     outs: dicts with N, tile0 and cb (16-bit) or cf (+ res), optional ld.  Tiles are 256 columns (128 + 128 for
@@ -626,7 +627,7 @@ def dbg_gemm2(M, segs, outs, *, half=True, epi=0, alpha=1.0, tile_rows=0, reps=0
     d.overflow_flag = _ptr(overflow_flag)
     d.n_cu = n_cu
     d.ksplit = ksplit
-    d.rope, d.rope_S, d.rope_d, d.rope_tiles = _ptr(rope), rope_S, rope_d, rope_tiles
+    d.rope, d.rope_S, d.rope_d, d.rope_tiles, d.part_bytes = _ptr(rope), rope_S, rope_d, rope_tiles, part_bytes
     t, f = C.c_double(0.0), C.c_double(0.0)
     if reps > 1:
         d.tflops, d.shader_mhz = C.pointer(t), C.pointer(f)

@@ -23,9 +23,9 @@ extern "C" harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t 
                                             int32_t* out) {
   if (!out || M < 1 || tiles_n < 1 || stages < 1 || n_cu < 1 || share < 1 || share > n_cu || part_bytes < 0)
     return fail(HARLI_ERR_INVALID, "dbg_gemm2_cut: bad argument");
-  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share, (size_t)part_bytes);
-  const int v[9] = {64 * c.FM, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut};
-  for (int i = 0; i < 9; ++i) out[i] = v[i];
+  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share);
+  const int v[10] = {64 * c.FM, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut, gemm2_pass_tiles(c, (size_t)part_bytes)};
+  for (int i = 0; i < 10; ++i) out[i] = v[i];
   return HARLI_OK;
 }
 
@@ -122,9 +122,9 @@ extern "C" harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip
   g.rope_tiles = d->rope_tiles;
   gemm2_force_tile_rows(d->tile_rows);
   gemm2_force_split(d->ksplit);
-  if (d->ksplit != 1) {
+  {
     void* part = nullptr;
-    g.part_bytes = (size_t)64 << 20;
+    g.part_bytes = d->part_bytes > 0 ? (size_t)d->part_bytes : (size_t)64 << 20;
     if (hipMalloc(&part, g.part_bytes) != hipSuccess) {
       cleanup();
       return fail(HARLI_ERR_HIP, "dbg_gemm2: no memory for the partial tiles");

@@ -107,7 +107,7 @@ Dims dims(const harli_ctx* c, int Bf, int S) {
   return D;
 }
 
-// Workspace for partial tiles that lets every weight GEMM of a unit of at most `T` tokens be cut as gemm2_cut wants.
+// Workspace for partial tiles that lets every weight GEMM of a unit of at most `T` tokens run in one pass.
 size_t unit_part_bytes(const Dims& D, size_t T) {
   auto tiles = [](long long n) { return (int)((n + kG2TileN - 1) / kG2TileN); };
   auto steps = [](long long k) { return (int)((k + kG2StepK - 1) / kG2StepK); };
@@ -148,7 +148,7 @@ harli_status make_ws(harli_ctx* c) {
   const size_t o_dob = take(T * D.QD * 2), o_dq = take(T * D.QD * 2), o_dkq = take(T * D.QD * 2), o_dvq = take(T * D.QD * 2);
   const size_t o_dk = take(T * D.KVD * 2), o_dv = take(T * D.KVD * 2), o_gs = take(3 * al(T * D.r * 2));
   size_t part_bytes = unit_part_bytes(D, T);
-  part_bytes = std::max(part_bytes, head_part_bytes(c));
+  part_bytes = std::max(std::max(part_bytes, head_part_bytes(c)), kG2MinPartBytes);
   const size_t o_part = take(part_bytes);
   const size_t o_gpart = take(ft_lora_grad_ws_floats((int)maxdim, D.r) * 4);
   const bool want_pool = c->lora.workspace_in_pool != 0 || c->cfg.memory_in_pool != 0;

@@ -85,8 +85,8 @@ struct Gemm2Args {
   // compute units the cut along K is chosen for; 0: the device's.  The stream's share of them (Harli Sec. 6.2) only moves
   // the tile height (gemm2_cut): the cut decides the order K is added up in, and a unit gives the same bits on every partition.
   int n_cu;
-  // workspace for the partial tiles of a launch whose tiles are cut along K (or null: tiles are never cut); launches
-  // that share it are ordered by their stream
+  // workspace for the partial tiles of a launch whose tiles are cut along K; launches that share it are ordered by their
+  // stream.  It has to hold those of one tile (kG2MinPartBytes); a launch that needs more than it holds works in passes.
   float* part;
   size_t part_bytes;
 };
@@ -96,15 +96,20 @@ struct Gemm2Args {
 struct Gemm2Cut {
   int FM;                      // tile height / 64
   int ks;                      // 1: nothing is cut
-  int full, rest;
+  int full, rest;              // (of one launch: its whole tiles, and the tiles it cuts)
+  int first;                   // first tile that is cut
   int tiles_m, tiles_n, GM;    // tile order of a cut launch: bands of GM row tiles
   int chunk_full, chunk_cut;   // tiles / pieces per XCD
   double cost_us;              // what the choice was made by
 };
 // stages: K steps of the longest column tile.  n_cu: compute units of the device, share: those the stream may use.
-Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t part_bytes);
-// bytes of workspace that let gemm2_launch cut every launch of at most max_M rows and max_tiles_n column tiles as it wants
-size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages);
+// The workspace plays no part: the bits of a launch do not depend on how much of it there is.
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share);
+// tiles cut per pass with part_bytes of workspace (0: it does not hold the partial tiles of one)
+int gemm2_pass_tiles(const Gemm2Cut& c, size_t part_bytes);
+constexpr size_t kG2MinPartBytes = (size_t)4 << 20;  // sixteen ranges of a tile of 256 rows
+// bytes of workspace that let every launch of at most max_M rows over tiles_n column tiles run in one pass (at most 64 MiB)
+size_t gemm2_part_bytes(int max_M, int tiles_n, int stages);
 
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st);
 

@@ -233,7 +233,7 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
       piece = (w2 & 7) * cut.chunk_cut + (w2 >> 3);
       if (piece >= cut.rest * cut.ks) return;
       split = piece / cut.rest;
-      slot = cut.full + piece - split * cut.rest;
+      slot = cut.first + piece - split * cut.rest;
     }
     g2_cut_tile(cut, slot, tm, tn);
   } else {
@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(256) k_gemm2_sum(Gemm2Args a, Gemm2Cut cut) {
   const int lane = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = blockIdx.x % FM, wave = (blockIdx.x / FM) & 3, r = blockIdx.x / (4 * FM);
   int tm, tn;
-  g2_cut_tile(cut, cut.full + r, tm, tn);
+  g2_cut_tile(cut, cut.first + r, tm, tn);
   const int mrow0 = tm * (64 * FM) + (wave >> 1) * (FM * 32) + i * 32;
   if (mrow0 >= a.M) return;
   const size_t stride = (size_t)cut.rest * (4 * FM * 4096);  // floats between two ranges of a tile
@@ -577,6 +577,13 @@ constexpr int lds_bytes() { return stages<FM>() * (64 * FM * BK * 2 + BSZ); }
 int g_force_fm = 0;  // measurement hook: 2 or 4 fixes the tile height
 int g_force_ks = 0;  // measurement hook: fixes the ranges of K
 constexpr int kMinCutStages = 4, kMaxCut = 16;  // shortest range of K in stages (the ring holds four), most ranges of a tile
+constexpr size_t kMaxPartBytes = (size_t)64 << 20;  // most partial tiles of a launch
+
+int device_cus() {
+  int dev = 0;
+  hipDeviceProp_t prop;
+  return hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess ? prop.multiProcessorCount : 256;
+}
 
 }  // namespace
 
@@ -625,7 +632,7 @@ Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
 // where every tile is cut or none is, it is the cheaper one on the share (2048 x 4096 x 4096, not cut: 256 tiles of 128 rows
 // are one round on 256 compute units and a round and 26 stragglers on 230, where 128 tiles of 256 rows are one).  Units on
 // 230 compute units: 3 x 344 tokens of hidden size 3584 2200 -> 1917 us, 4 x 512 of 4096 2767 -> 2736.
-Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t part_bytes) {
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share) {
   const double t_fixed = 6.0;
   auto step_us = [](int FM, int active) {
     const double b = std::min(1.0, active / (FM == 4 ? 256.0 : 140.0));
@@ -637,7 +644,7 @@ Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t p
     c.FM = FM, c.ks = ks, c.cost_us = cost, c.tiles_n = tiles_n;
     c.tiles_m = (M + 64 * FM - 1) / (64 * FM), c.GM = std::min(FM == 2 ? 8 : 4, c.tiles_m);
     const int T = c.tiles_m * tiles_n;
-    c.full = ks > 1 ? full : T, c.rest = T - c.full;
+    c.full = c.first = ks > 1 ? full : T, c.rest = T - c.full;
     c.chunk_full = (c.full + 7) / 8, c.chunk_cut = (c.rest * ks + 7) / 8;
     return c;
   };
@@ -651,7 +658,7 @@ Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t p
     for (int ks = 1; ks <= ks_max; ++ks) {
       const int pieces = rest * ks, r2 = (pieces + n_cu - 1) / n_cu;
       const size_t bytes = ks > 1 ? (size_t)pieces * BM * BN * 4 : 0;
-      if (bytes > part_bytes) break;
+      if (bytes > kMaxPartBytes) break;
       double cost = (T / n_cu) * (stages * step_us(FM, n_cu) + t_fixed);
       if (r2 > 0) cost += r2 * (((stages + ks - 1) / ks) * step_us(FM, std::min(pieces, n_cu)) + t_fixed);
       cost += sum_us(bytes);
@@ -665,7 +672,7 @@ Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t p
     for (int FM = 4; FM >= 2; FM -= 2) {
       const int BM = 64 * FM, n = (M + BM - 1) / BM * tiles_n * ks, last = n % share;  // workgroups, and those of the last round
       const size_t bytes = ks > 1 ? (size_t)n * BM * BN * 4 : 0;
-      if (bytes > part_bytes) continue;
+      if (bytes > kMaxPartBytes) continue;
       double cost = (n / share) * (len * step_us(FM, share) + t_fixed) + sum_us(bytes);
       if (last) cost += len * step_us(FM, last) + t_fixed;
       if (best.cost_us < 0 || cost < best.cost_us) best = make(FM, ks, 0, cost);
@@ -674,10 +681,23 @@ Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, size_t p
   return best;
 }
 
-size_t gemm2_part_bytes(int max_M, int max_tiles_n, int stages) {
-  const int ks = std::max(1, std::min(kMaxCut, stages / kMinCutStages));
-  if (ks < 2) return 0;
-  return std::min((size_t)((max_M + 127) / 128) * max_tiles_n * ks * (128 * BN * 4), (size_t)64 << 20);
+int gemm2_pass_tiles(const Gemm2Cut& c, size_t part_bytes) {
+  if (c.ks < 2) return 0;
+  const size_t fit = part_bytes / ((size_t)c.ks * c.FM * (64 * BN * 4));
+  if (fit >= (size_t)c.rest) return c.rest;
+  if (fit < 1) return 0;
+  const int passes = (c.rest + (int)fit - 1) / (int)fit;
+  return (c.rest + passes - 1) / passes;
+}
+
+size_t gemm2_part_bytes(int max_M, int tiles_n, int stages) {
+  const int n_cu = device_cus();
+  size_t most = 0;
+  for (int M = std::min(128, max_M);; M = std::min(M + 128, max_M)) {  // a plan depends on the rows through their tiles alone
+    const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, n_cu);
+    if (c.ks > 1) most = std::max(most, (size_t)c.rest * c.ks * c.FM * (64 * BN * 4));
+    if (M == max_M) return most;
+  }
 }
 
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
@@ -745,13 +765,7 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
 #undef G2_ATTR
     attr_set = true;
   }
-  int n_cu = a.n_cu;
-  if (n_cu < 1) {
-    n_cu = 256;
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n_cu = prop.multiProcessorCount;
-  }
+  const int n_cu = a.n_cu > 0 ? a.n_cu : device_cus();
   int stages = 0;  // of the longest column tile
   for (int s = 0; s < a.nseg; ++s) {
     int n = 0;
@@ -760,14 +774,27 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
     stages = std::max(stages, n);
   }
   const int share = cu_stream_count(st);  // 0: not confined
-  const Gemm2Cut cut = gemm2_cut(a.M, a.tiles_n, stages, n_cu, share > 0 ? std::min(share, n_cu) : n_cu, a.part ? a.part_bytes : 0);
-  const int FM = cut.FM;
+  const Gemm2Cut plan = gemm2_cut(a.M, a.tiles_n, stages, n_cu, share > 0 ? std::min(share, n_cu) : n_cu);
+  const int FM = plan.FM;
   const Gemm2Plan pl = gemm2_plan(a.M, a.tiles_n, FM, n_cu);
-  const int GM = pl.GM, GN = pl.GN, total = pl.total, chunk = pl.chunk, grid = cut.ks > 1 ? 8 * (cut.chunk_full + cut.chunk_cut) : pl.grid;
+  const int GM = pl.GM, GN = pl.GN, total = pl.total, chunk = pl.chunk;
+  const int per_pass = gemm2_pass_tiles(plan, a.part ? a.part_bytes : 0);
+  if (plan.ks > 1 && per_pass < 1) return fail(HARLI_ERR_INVALID, "gemm2: no room for the partial tiles of one tile");
+  // Cut launch: the whole tiles with the first pass, then pass after pass (one, unless the workspace is small).
 #define G2_LAUNCH(F_, H_, E_)                                                                                                \
   do {                                                                                                                       \
-    hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(grid), dim3(NT), lds_bytes<F_>(), st, a, cut, total, chunk, GM, GN, zero16); \
-    if (cut.ks > 1) hipLaunchKernelGGL((k_gemm2_sum<F_, H_, E_>), dim3(cut.rest * 4 * F_), dim3(256), 0, st, a, cut);         \
+    Gemm2Cut cut = plan;                                                                                                     \
+    if (cut.ks < 2)                                                                                                          \
+      hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(pl.grid), dim3(NT), lds_bytes<F_>(), st, a, cut, total, chunk, GM, GN, zero16); \
+    for (int done = 0; done < plan.rest; done += cut.rest) {                                                                 \
+      cut.first = plan.first + done;                                                                                         \
+      cut.rest = std::min(per_pass, plan.rest - done);                                                                       \
+      cut.chunk_cut = (cut.rest * cut.ks + 7) / 8;                                                                           \
+      hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(8 * (cut.chunk_full + cut.chunk_cut)), dim3(NT), lds_bytes<F_>(), st, a, cut, total, \
+                         chunk, GM, GN, zero16);                                                                             \
+      hipLaunchKernelGGL((k_gemm2_sum<F_, H_, E_>), dim3(cut.rest * 4 * F_), dim3(256), 0, st, a, cut);                       \
+      cut.full = cut.chunk_full = 0;                                                                                         \
+    }                                                                                                                        \
   } while (0)
 #define G2_PICK(F_)                                                                    \
   do {                                                                                 \

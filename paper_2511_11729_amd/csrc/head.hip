@@ -165,7 +165,7 @@ harli_status head_free_ws(harli_ctx* c) {
 // row chunk: at most 2048 rows and about 512 MiB of fp32 logits
 static int head_chunk_rows(int Vp) { return (int)std::max<long long>(64, std::min<long long>(2048, ((512ll << 20) / ((long long)Vp * 4)) / 64 * 64)); }
 
-// partial-tile workspace that lets the two GEMMs of a chunk be cut along K (gemm2.h)
+// partial-tile workspace that lets the two GEMMs of a chunk run in one pass (gemm2.h)
 size_t head_part_bytes(const harli_ctx* c) {
   if (!c->w_lm || !c->g_final || c->cfg.vocab < 1) return 0;
   const int V = c->cfg.vocab, H = c->cfg.hidden, Vp = (V + 7) & ~7, M = std::min(head_chunk_rows(Vp), c->cfg.max_ft_tokens);

@@ -260,3 +260,17 @@ def test_a_partition_gives_the_bits_of_the_whole_device(M, N, K):
             hb.cu_stream_destroy(st)
     close(f64(out[0][::97]), f64(A[::97]) @ f64(B).T, "fp32 output", 1e-5)
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("tile_rows,M,N,K,n_cu", [(128, 300, 1000, 1088, 0), (256, 300, 1000, 1088, 0), (128, 1100, 1300, 640, 7)])
+def test_a_small_workspace_gives_the_same_bits_in_passes(tile_rows, M, N, K, n_cu):
+    """Room for all partial tiles, for a few and for one, of launches without and with whole tiles."""
+    A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
+    one = 3 * tile_rows * 256 * 4
+    out = []
+    for part_bytes in (0, 4 * one, one):
+        cf = torch.full((M, N), float("nan"), device=DEV)
+        hb.dbg_gemm2(M, [dict(A=A, B=B)], [dict(N=N, cf=cf)], tile_rows=tile_rows, ksplit=3, n_cu=n_cu, part_bytes=part_bytes)
+        out.append(cf)
+    close(f64(out[0]), f64(A) @ f64(B).T, "fp32 output", 1e-5)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])

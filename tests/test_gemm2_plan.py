@@ -69,3 +69,18 @@ def test_tile_height_on_nine_tenths_of_the_chip():
     assert hb.dbg_gemm2_cut(2048, 16, 128, 256)["rows"] == 128
     part = hb.dbg_gemm2_cut(2048, 16, 128, 256, 230)
     assert part["rows"] == 256 and part["ks"] == 1 and part["full"] == 128
+
+
+def test_passes_of_a_small_workspace_cover_the_cut_tiles():
+    """The plan knows no workspace; with less of it than the partial tiles take, equal passes of whole tiles."""
+    full = hb.dbg_gemm2_cut(600, 20, 434, 256)
+    tile = full["ks"] * full["rows"] * 256 * 4
+    assert full["ks"] > 2 and full["per_pass"] == full["rest"]
+    for fit in (full["rest"], full["rest"] - 1, 7, 1, 0):
+        c = hb.dbg_gemm2_cut(600, 20, 434, 256, part_bytes=fit * tile + tile // 2)
+        assert {k: v for k, v in c.items() if k != "per_pass"} == {k: v for k, v in full.items() if k != "per_pass"}
+        assert c["per_pass"] <= fit and (c["per_pass"] > 0) == (fit > 0)
+        assert fit == 0 or -(-c["rest"] // c["per_pass"]) == -(-c["rest"] // fit)   # no more passes than it takes
+    for M, tiles_n, stages in ((4096, 200, 2000), (48, 16, 690), (300, 1, 64)):       # the library's smallest workspace: 4 MiB
+        c = hb.dbg_gemm2_cut(M, tiles_n, stages, 256, part_bytes=4 << 20)
+        assert c["ks"] == 1 or c["per_pass"] >= 1
