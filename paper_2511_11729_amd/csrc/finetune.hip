@@ -47,13 +47,14 @@ inline size_t al(size_t n) { return (n + 255) & ~size_t(255); }
 // workspace carved from one device allocation
 struct FtWs {
   size_t bytes = 0;
+  int rank = 0;            // adapter rank the offsets below were made for
   char* base = nullptr;
   float *delta = nullptr, *dh2 = nullptr,
         *dx1 = nullptr, *dh = nullptr, *gpart = nullptr;
   bf *At[kTargets] = {}, *Bt[kTargets] = {}, *dyb = nullptr, *da = nullptr, *du = nullptr, *dx1b = nullptr, *dob = nullptr,
      *dq = nullptr, *dkq = nullptr,
      *dvq = nullptr, *dk = nullptr, *dv = nullptr, *gs[3] = {}, *An[kTargets] = {}, *Bn[kTargets] = {};
-  float* part = nullptr;   // partial tiles of the weight GEMMs whose tiles are cut along K (gemm2.h)
+  float* part = nullptr;   // partial tiles of the weight GEMMs whose tiles are cut along K (gemm2.h); the same memory as gpart
   size_t part_bytes = 0;
   float2* rope = nullptr;  // [max_ft_tokens][d/2] (cos, sin)
   float* scale = nullptr;  // [0] sigma, [1] 1/sigma of the backward pass, then kAmaxParts partial maxima (ft_scale_to_e)
@@ -147,12 +148,17 @@ harli_status make_ws(harli_ctx* c) {
   const size_t o_dyb = take(T * D.H * 2), o_da = take(T * D.F * 2), o_du = take(T * D.F * 2), o_dx1b = take(T * D.H * 2);
   const size_t o_dob = take(T * D.QD * 2), o_dq = take(T * D.QD * 2), o_dkq = take(T * D.QD * 2), o_dvq = take(T * D.QD * 2);
   const size_t o_dk = take(T * D.KVD * 2), o_dv = take(T * D.KVD * 2), o_gs = take(3 * al(T * D.r * 2));
-  size_t part_bytes = unit_part_bytes(D, T);
-  part_bytes = std::max(std::max(part_bytes, head_part_bytes(c)), kG2MinPartBytes);
-  const size_t o_part = take(part_bytes);
-  const size_t o_gpart = take(ft_lora_grad_ws_floats((int)maxdim, D.r) * 4);
   const bool want_pool = c->lora.workspace_in_pool != 0 || c->cfg.memory_in_pool != 0;
-  if (off != w.bytes || want_pool != fs->ws_in_pool) {  // first attach, or another rank / placement than before
+  // The partial tiles of the weight GEMMs and those of the adapter gradients are never alive together (each is summed by the
+  // launch after the one that writes it), so they share memory.  The gradients need 4 MiB per rank; one pass of the GEMMs
+  // takes up to 64 MiB, more than that at rank 8 alone.  In the pool, whose room a caller has planned, the excess is at most
+  // what transposed copies of q, k, v and dO would take (less the rotary table): GEMMs that need more work in passes there.
+  const size_t gpart_bytes = ft_lora_grad_ws_floats((int)maxdim, D.r) * 4;
+  size_t part_bytes = std::max(unit_part_bytes(D, T), head_part_bytes(c));
+  if (want_pool) part_bytes = std::min(part_bytes, gpart_bytes + T * (2 * D.QD + 2 * D.KVD) * 2 - T * D.d * 4);
+  part_bytes = std::max(std::max(part_bytes, gpart_bytes), kG2MinPartBytes);
+  const size_t o_part = take(part_bytes);
+  if (off != w.bytes || D.r != w.rank || want_pool != fs->ws_in_pool) {  // first attach, or another rank / placement than before
     harli_status r = free_ws(c);
     if (r != HARLI_OK) return r;
     if (want_pool) {
@@ -164,6 +170,7 @@ harli_status make_ws(harli_ctx* c) {
     }
     fs->ws_in_pool = want_pool;
     w.bytes = off;
+    w.rank = D.r;
   }
   char* b = w.base;
   w.delta = (float*)(b + o_delta);
@@ -172,8 +179,7 @@ harli_status make_ws(harli_ctx* c) {
   w.dx1b = (bf*)(b + o_dx1b); w.dob = (bf*)(b + o_dob); w.dq = (bf*)(b + o_dq); w.dkq = (bf*)(b + o_dkq);
   w.dvq = (bf*)(b + o_dvq); w.dk = (bf*)(b + o_dk); w.dv = (bf*)(b + o_dv);
   for (int i = 0; i < 3; ++i) w.gs[i] = (bf*)(b + o_gs + i * al(T * D.r * 2));
-  w.gpart = (float*)(b + o_gpart);
-  w.part = (float*)(b + o_part);
+  w.gpart = w.part = (float*)(b + o_part);
   w.part_bytes = part_bytes;
   for (int i = 0; i < kTargets; ++i) {
     w.At[i] = (bf*)(b + o_At + i * ad); w.Bt[i] = (bf*)(b + o_Bt + i * adb);

@@ -148,3 +148,37 @@ def test_decode_from_pool_memory_gives_the_same_step_and_a_full_pool_refuses_the
     with pytest.raises(hb.HarliError) as e:                      # one spare chunk cannot hold the weight copies
         DecodeCase(w, m, lengths, extra_chunks=1, memory_in_pool=True)
     assert e.value.status == hb.HARLI_ERR_OOM
+
+
+def test_partial_tiles_of_the_weight_gemms_take_no_room_of_their_own():
+    """The GEMMs' partial tiles lie where the adapter gradients' partial sums do.  A pool planned for the tensors of a unit,
+    transposed copies of q, k, v and dO and those sums holds the workspace at every rank, and its place changes no bit."""
+    w = wl.workload(0)
+    m = dataclasses.replace(w.model, dtype="bf16", hidden=1024, n_q=8, n_kv=4, head_dim=128, ffn=2816)
+    T, H, QD, KVD, F = 512, 1024, 1024, 512, 2816
+    al = lambda n: -(-n // 256) * 256
+    fc = FinetuneCase(w, m, wl.LoraCfg(8, 16.0, ("q", "v")), wl.FinetuneCfg(2, 256), n_chunks=96)
+    _, _, dY, _, _ = fc.oracle()
+    Y0, dX0, _ = unit(fc, dY)
+    for rank in (16, 8):
+        lora = wl.make_lora(w, 0, m, wl.LoraCfg(rank, 2.0 * rank, ("q", "v")))
+        A, B = ({p: to_dev(ab[i], "bf16") for p, ab in lora.items()} for i in (0, 1))
+        blocked = lambda n, k: -(-n // 256) * -(-k // 32) * 256 * 32
+        planned = (al(T * m.n_q * 4) + 3 * al(T * H * 4) + 2 * al(T * H * 2) + 2 * al(T * F * 2) + 4 * al(T * QD * 2) + 2 * al(T * KVD * 2)
+                   + 3 * al(T * rank * 2) + 2 * 7 * (al(F * rank * 2) + al(blocked(F, rank) * 2)) + 2 * al(T * QD * 2) + 2 * al(T * KVD * 2)
+                   + al(8 * 512 * 256 * rank * 4) + 256)
+        fc.ctx.lora_attach(rank, 2.0 * rank, ("q", "v"), [A], [B])       # gives the last workspace back
+        taken = []
+        while True:                                                       # leave the pool the planned blocks and no more
+            try:
+                taken.append(fc.pool.alloc(hb.CLS_TENSOR, 2 << 20))
+            except hb.HarliError:
+                break
+        for _ in range(-(-planned // (2 << 20))):
+            fc.pool.free(taken.pop())
+        fc.ctx.lora_attach(rank, 2.0 * rank, ("q", "v"), [A], [B], workspace_in_pool=True)
+        assert fc.ctx.device_bytes().in_pool <= planned
+        for a in taken:
+            fc.pool.free(a)
+    Y1, dX1, _ = unit(fc, dY)                                             # rank 8: the adapters of the first unit
+    assert np.array_equal(Y0, Y1) and np.array_equal(dX0, dX1)
