@@ -964,6 +964,7 @@ int tiles_per_wave(int n_tiles, int rt_max) {
 template <int MODE>
 void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
   constexpr int TW = MODE == MODE_GATEUP ? 2 : 1;  // a gate/up workgroup takes the same tile of both matrices
+  const bool large_vocab = n_tiles >= 16 * kComputeUnits;  // an output layer whose weights pass through many rounds
   // workgroups at one tile per wave with two waves side by side
   const int n_two = MODE == MODE_GATEUP ? n_tiles : (n_tiles + 1) / 2;
   for (int b0 = 0; b0 < a.B;) {
@@ -979,11 +980,11 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
       if (MODE == MODE_QKV) launch_skinny<MODE, 1, 1, 4, 16, 1>(a, n_tiles, st);
       else if (MODE == MODE_RESID) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
       else if (MODE == MODE_GATEUP) launch_skinny<MODE, 1, 2, 4, 8, 1>(a, n_tiles, st);
-      else if (left > 8 && n_tiles >= 16 * kComputeUnits) launch_skinny<MODE, 1, 2, 2, 4, 4>(a, n_two, st);
+      else if (left > 8 && large_vocab) launch_skinny<MODE, 1, 2, 2, 4, 4>(a, n_two, st);
       else launch_skinny<MODE, 1, 1, 8, 8, 1>(a, n_tiles, st);
     } else if (nb == 2) {
       const int rt = tiles_per_wave(n_tiles, MODE == MODE_RESID ? 2 : 4);
-      if (rt == 4 || MODE == MODE_LM) {
+      if (rt == 4 || (MODE == MODE_LM && large_vocab)) {
         if (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 8, 4, 4>(a, n_tiles, st);
         else if (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 4, 4, 4>(a, n_tiles, st);
         else launch_skinny<MODE, 2, 2, 2, 4, 4>(a, n_two, st);
