@@ -81,6 +81,8 @@ __device__ __forceinline__ QkvPlace qkv_place(int tile, int per_head, int half, 
 template <int MODE, int NB, int TW, int KW, int U, int RT>
 __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   constexpr int WAVES = TW * KW;
+  static_assert(MODE != MODE_RESID || TW == 1, "the residual epilogue stores one tile per round");
+  static_assert(MODE != MODE_GATEUP || TW == 2, "a gate tile and its up tile");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   const int t_w = wave / KW, ks = wave - t_w * KW;
@@ -946,7 +948,11 @@ void launch_skinny(const SkinnyArgs& a, int n_wg, hipStream_t st) {
 // fewest tiles on the fullest compute unit, the larger one at equal counts.  Measured at 32 rows, RT 1 / 2 / 4: q,k,v of
 // 960 tiles 42 / 34 / 30 us (4 tiles at most in each), 320-tile projections over K = 13824 47 / 37 / 53 us (2 / 2 / 4),
 // gate/up of 2 x 864 71 / 56 / 49 us; at 21 rows gate/up of 2 x 1184 56 / 53 / 62 us (5 / 6 / 8: 5 against 6 misses by
-// 6 %), 224-tile projections over K = 18944 31 / 44 / 64 us.
+// 6 %), 224-tile projections over K = 18944 31 / 44 / 64 us.  An output layer of a large vocabulary takes four throughout
+// (152064 at 32 rows, two against four by this rule: 248 / 209 us); a small one follows the rule (8000: 49 / 31 us).
+// The compute units are the device's, also on a stream with a share of them: the variants split K over different numbers of
+// waves, and a step gives the same bits on every partition.  (Counting the share's, four layers on half of the chip take
+// 1116 -> 958 us at 21 rows of 28 query heads on 4, 866 -> 769 at 24 of the 7B class, 1247 -> 1381 at 32 of the 13B class.)
 int tiles_per_wave(int n_tiles, int rt_max) {
   int best = 1, best_n = 1 << 30;
   for (int rt = 1; rt <= rt_max; rt *= 2) {
@@ -964,9 +970,8 @@ int tiles_per_wave(int n_tiles, int rt_max) {
 template <int MODE>
 void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
   constexpr int TW = MODE == MODE_GATEUP ? 2 : 1;  // a gate/up workgroup takes the same tile of both matrices
-  const bool large_vocab = n_tiles >= 16 * kComputeUnits;  // an output layer whose weights pass through many rounds
-  // workgroups at one tile per wave with two waves side by side
-  const int n_two = MODE == MODE_GATEUP ? n_tiles : (n_tiles + 1) / 2;
+  [[maybe_unused]] const bool large_vocab = n_tiles >= 16 * kComputeUnits;  // an output layer of 16 tiles per compute unit or more
+  [[maybe_unused]] const int n_two = (n_tiles + 1) / 2;                     // its pairs of tiles: two side by side in a workgroup
   for (int b0 = 0; b0 < a.B;) {
     a.b0 = b0;
     const int left = a.B - b0;
@@ -977,20 +982,20 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
     }
     const int nb = (left + 15) / 16;
     if (nb == 1) {
-      if (MODE == MODE_QKV) launch_skinny<MODE, 1, 1, 4, 16, 1>(a, n_tiles, st);
-      else if (MODE == MODE_RESID) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
-      else if (MODE == MODE_GATEUP) launch_skinny<MODE, 1, 2, 4, 8, 1>(a, n_tiles, st);
+      if constexpr (MODE == MODE_QKV) launch_skinny<MODE, 1, 1, 4, 16, 1>(a, n_tiles, st);
+      else if constexpr (MODE == MODE_RESID) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
+      else if constexpr (MODE == MODE_GATEUP) launch_skinny<MODE, 1, 2, 4, 8, 1>(a, n_tiles, st);
       else if (left > 8 && large_vocab) launch_skinny<MODE, 1, 2, 2, 4, 4>(a, n_two, st);
       else launch_skinny<MODE, 1, 1, 8, 8, 1>(a, n_tiles, st);
     } else if (nb == 2) {
-      const int rt = tiles_per_wave(n_tiles, MODE == MODE_RESID ? 2 : 4);
-      if (rt == 4 || (MODE == MODE_LM && large_vocab)) {
-        if (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 8, 4, 4>(a, n_tiles, st);
-        else if (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 4, 4, 4>(a, n_tiles, st);
-        else launch_skinny<MODE, 2, 2, 2, 4, 4>(a, n_two, st);
+      const int rt = MODE == MODE_LM && large_vocab ? 4 : tiles_per_wave(n_tiles, MODE == MODE_RESID ? 2 : 4);
+      if (rt == 4) {
+        if constexpr (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 8, 4, 4>(a, n_tiles, st);
+        else if constexpr (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 4, 4, 4>(a, n_tiles, st);
+        else if constexpr (MODE == MODE_LM) launch_skinny<MODE, 2, 2, 2, 4, 4>(a, n_two, st);
       } else if (rt == 2) {
-        if (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 16, 4, 2>(a, n_tiles, st);
-        else if (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 2, 8, 2>(a, n_tiles, st);
+        if constexpr (MODE == MODE_QKV) launch_skinny<MODE, 2, 1, 16, 4, 2>(a, n_tiles, st);
+        else if constexpr (MODE == MODE_GATEUP) launch_skinny<MODE, 2, 2, 2, 8, 2>(a, n_tiles, st);
         else launch_skinny<MODE, 2, 1, 8, 8, 2>(a, n_tiles, st);
       } else {
         launch_skinny<MODE, 2, TW, 8 / TW, 8, 1>(a, n_tiles, st);
