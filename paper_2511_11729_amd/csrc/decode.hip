@@ -967,6 +967,10 @@ int tiles_per_wave(int n_tiles, int rt_max) {
 // Up to 16 rows one weight tile per wave is best throughout (7B layer at 8 rows, RT 1 / 2: q,k,v 18.4 / 23.6 us, down
 // 16.6 / 22.7, gate/up 29 / 36) but for the output layer of a large vocabulary (152064 at 12 rows, RT 1 / 4: 186 / 172).
 // Waves and loads in flight per wave are the best measured of {4, 8, 16} waves per tile and {4, 8, 16} loads.
+// The residual projections split K over sixteen waves, below 3072 over eight: shorter, a wave has less than one group of
+// loads (hidden size 512, four layers, 8 sequences 118 / 109 us, 2048 172 / 161; at 3072 115 / 114).
+constexpr int kWideSplit = 3072;
+
 template <int MODE>
 void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
   constexpr int TW = MODE == MODE_GATEUP ? 2 : 1;  // a gate/up workgroup takes the same tile of both matrices
@@ -983,7 +987,10 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
     const int nb = (left + 15) / 16;
     if (nb == 1) {
       if constexpr (MODE == MODE_QKV) launch_skinny<MODE, 1, 1, 4, 16, 1>(a, n_tiles, st);
-      else if constexpr (MODE == MODE_RESID) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
+      else if constexpr (MODE == MODE_RESID) {
+        if (a.K >= kWideSplit) launch_skinny<MODE, 1, 1, 16, 8, 1>(a, n_tiles, st);
+        else launch_skinny<MODE, 1, 1, 8, 8, 1>(a, n_tiles, st);
+      }
       else if constexpr (MODE == MODE_GATEUP) launch_skinny<MODE, 1, 2, 4, 8, 1>(a, n_tiles, st);
       else if (left > 8 && large_vocab) launch_skinny<MODE, 1, 2, 2, 4, 4>(a, n_two, st);
       else launch_skinny<MODE, 1, 1, 8, 8, 1>(a, n_tiles, st);
