@@ -50,10 +50,12 @@ constexpr int kPageTokens = 16;
 constexpr int kComputeUnits = 256;  // MI355X; only steers a tiling choice
 
 // 16 bytes that a step reads once: nontemporal, so that they do not push shared operands out of L2 (one 13B layer at 32
-// sequences, 682 MB of keys and values: 131 -> 120 us, 5.2 -> 5.7 TB/s)
+// sequences, 682 MB of keys and values: 131 -> 120 us, 5.2 -> 5.7 TB/s), unless the caches hold them from step to step
+template <bool CACHED>
 __device__ __forceinline__ uint4 ld16_once(const void* p) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(static_cast<const u32x4*>(p)));
+  const u32x4* q = static_cast<const u32x4*>(p);
+  return __builtin_bit_cast(uint4, CACHED ? *q : __builtin_nontemporal_load(q));
 }
 
 enum { MODE_QKV = 0, MODE_RESID = 1, MODE_GATEUP = 2, MODE_LM = 3 };
@@ -78,7 +80,7 @@ __device__ __forceinline__ QkvPlace qkv_place(int tile, int per_head, int half, 
 // RT = 16-row weight tiles per wave: a wave holds RT x NB accumulator tiles, so that a batch fragment fetched for a
 // k-step serves RT weight fragments (at 64 batch rows every wave otherwise pulls four batch fragments through the
 // vector cache for each weight fragment it streams).  U = k-steps of both operands a wave keeps in flight.
-template <int MODE, int NB, int TW, int KW, int U, int RT>
+template <int MODE, int NB, int TW, int KW, int U, int RT, bool CACHED>
 __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   constexpr int WAVES = TW * KW;
   static_assert(MODE != MODE_RESID || TW == 1, "the residual epilogue stores one tile per round");
@@ -122,11 +124,12 @@ __global__ void __launch_bounds__(TW * KW * 64) k_skinny(SkinnyArgs a) {
   for (int nb = 0; nb < NB; ++nb) vx[nb] = a.b0 + nb * 16 + i16 < a.B ? lane * 16 : 0x40000000;
   uint4 wf[U][RT], xf[U][NB];
   // weights are read once per step: nontemporal (bit 1 of the cache policy), they leave L2 to the operands that are shared
+  // (CACHED: ordinary loads, see step_stream_bytes)
 #define SK_LOAD(s)                                                                                                                                    \
   do {                                                                                                                                                \
     _Pragma("unroll") for (int u = 0; u < U; ++u) {                                                                                                   \
       _Pragma("unroll") for (int r = 0; r < RT; ++r)                                                                                                  \
-          wf[u][r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw[r], lane * 16 + ((s) + u) * 1024, 0, 2));                     \
+          wf[u][r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw[r], lane * 16 + ((s) + u) * 1024, 0, CACHED ? 0 : 2));        \
       _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                                                               \
           xf[u][nb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx[nb], vx[nb] + ((s) + u) * 1024, 0, 0));                      \
     }                                                                                                                                                 \
@@ -460,7 +463,7 @@ __device__ __forceinline__ float token_lanes_sum(float s) {
 template <int D, int G>
 constexpr int attn_min_waves() { return (D == 128 && G == 4) ? 4 : 1; }
 
-template <int D, int G, int CH>
+template <int D, int G, int CH, bool CACHED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, G>(), 8))) k_paged_attn(const float* qbuf, const int* kv_len, const int* page_table,
                                                     int max_pages, int layer, int n_q, int n_kv, const char* slab,
                                                     KvGeom geom, float* part, int max_chunks, unsigned short* obuf,
@@ -508,8 +511,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_m
       const int slot = it * TPI + tl;
       ok[pp][it] = pgok && (tb + slot) < n_tot;
       const size_t eo = ((size_t)(c * kPageTokens + slot) * D + dg * 8) * sizeof(unsigned short);
-      kf[pp][it] = ld16_once(slab + offk + eo);
-      vf[pp][it] = ld16_once(slab + offv + eo);
+      kf[pp][it] = ld16_once<CACHED>(slab + offk + eo);
+      vf[pp][it] = ld16_once<CACHED>(slab + offv + eo);
     }
   }
 #pragma unroll
@@ -939,7 +942,9 @@ template <int MODE, int NB, int TW, int KW, int U, int RT>
 void launch_skinny(const SkinnyArgs& a, int n_wg, hipStream_t st) {
   // dynamic LDS: the staged partial sums of squares of NB x 16 batch rows (small batches of the normalised GEMMs)
   const size_t lds = (MODE != MODE_RESID && NB <= 2) ? (size_t)NB * 16 * (((size_t)a.ssq_np * 4 + 1023) & ~size_t(1023)) : 0;
-  hipLaunchKernelGGL((k_skinny<MODE, NB, TW, KW, U, RT>), dim3((n_wg + RT - 1) / RT), dim3(TW * KW * 64), lds, st, a);
+  const dim3 grid((n_wg + RT - 1) / RT), block(TW * KW * 64);
+  if (a.cached) hipLaunchKernelGGL((k_skinny<MODE, NB, TW, KW, U, RT, true>), grid, block, lds, st, a);
+  else hipLaunchKernelGGL((k_skinny<MODE, NB, TW, KW, U, RT, false>), grid, block, lds, st, a);
 }
 
 // Weight tiles per wave for a pass of 17 to 32 rows.  A compute unit takes in 9 to 13 TB/s / 256 of weights and batch
@@ -1018,7 +1023,7 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
 }
 
 template <int D, int G, int CH>
-void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, int layer, hipStream_t st) {
+void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, int layer, bool cached, hipStream_t st) {
   const harli_model_cfg& m = c->cfg;
   const int n_chunks = (b->max_kv_len + CH - 1) / CH;
 #define ATTN_LAUNCH(kernel)                                                                                             \
@@ -1026,7 +1031,8 @@ void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, i
                      b->max_pages, layer, m.n_q_heads, m.n_kv_heads, c->slab, c->geom, w.att_part, w.max_chunks,         \
                      static_cast<unsigned short*>(w.obuf), w.err_flag)
   if constexpr (D == 128 && G >= 5) ATTN_LAUNCH((k_paged_attn_mm<G, CH>));
-  else ATTN_LAUNCH((k_paged_attn<D, G, CH>));
+  else if (cached) ATTN_LAUNCH((k_paged_attn<D, G, CH, true>));
+  else ATTN_LAUNCH((k_paged_attn<D, G, CH, false>));
 #undef ATTN_LAUNCH
   if (n_chunks > 1)
     hipLaunchKernelGGL((k_attn_merge<D, CH>), dim3(m.n_q_heads, b->batch), dim3(D), 0, st, w.att_part, b->kv_len,
@@ -1078,6 +1084,18 @@ harli_status check_decode_args(harli_ctx* c, const harli_decode_batch* b) {
 }
 
 // The step on bf16 storage; every intermediate buffer comes from `w`.
+// Bytes of weights, keys and values a step reads (the lengths at half their bound, as uneven ones are).  What fits the memory-side cache is there from
+// the step before, and nontemporal loads would fetch it from memory every time.  A step in us with nontemporal / ordinary
+// loads: 37 MiB (hidden size 512) 118 / 106, 175 MiB 193 / 176, 209 MiB (1536) 142 / 130, 278 MiB (2048) 130 / 127, 370 MiB
+// 172 / 174, 439 MiB (one 7B layer) 92 / 97.
+constexpr size_t kMemorySideCache = (size_t)256 << 20;
+size_t step_stream_bytes(const harli_ctx* c, const harli_decode_batch* b) {
+  const harli_model_cfg& m = c->cfg;
+  const size_t QD = (size_t)m.n_q_heads * m.head_dim, KVD = (size_t)m.n_kv_heads * m.head_dim, H = m.hidden;
+  const size_t layer = 2 * H * (QD + KVD) + 3 * H * m.ffn, kv = (size_t)b->batch * b->max_kv_len * KVD;
+  return 2 * (m.n_layers * (layer + kv) + (b->logits ? H * m.vocab : 0));
+}
+
 harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStream_t st, const DecodeWs& w) {
   const harli_model_cfg& m = c->cfg;
   const int B = b->batch, H = m.hidden, d = m.head_dim, QD = m.n_q_heads * d, F = m.ffn, L = m.n_layers;
@@ -1096,11 +1114,13 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
   int n_cu = cu_stream_count(st);  // a stream confined to a share of the compute units (Sec. 6.2)
   if (n_cu < 1) n_cu = c->n_cu;
   const int x_tiles = w.bpad / 16;
+  const bool cached = step_stream_bytes(c, b) <= kMemorySideCache;
 
   for (int l = 0; l < L; ++l) {
     const LayerDev& lw = c->layers[l];
     SkinnyArgs a{};
     a.B = B;
+    a.cached = cached;
     a.eps = m.rms_eps;
     a.inv_dim = 1.f / (float)H;
     a.err_flag = w.err_flag;
@@ -1130,17 +1150,17 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       dispatch_skinny<MODE_QKV>(a, (m.n_q_heads + 2 * m.n_kv_heads) * (d / 16), st);
     }
     // --- attention
-    if (d == 128 && G == 1) launch_attn<128, 1, 256>(c, w, b, l, st);
-    else if (d == 128 && G == 2) launch_attn<128, 2, 256>(c, w, b, l, st);
-    else if (d == 128 && G == 4) launch_attn<128, 4, 128>(c, w, b, l, st);
-    else if (d == 128 && G == 8) launch_attn<128, 8, 128>(c, w, b, l, st);
-    else if (d == 128 && G == 3) launch_attn<128, 3, 128>(c, w, b, l, st);
-    else if (d == 128 && G == 5) launch_attn<128, 5, 128>(c, w, b, l, st);
-    else if (d == 128 && G == 6) launch_attn<128, 6, 128>(c, w, b, l, st);
-    else if (d == 128 && G == 7) launch_attn<128, 7, 128>(c, w, b, l, st);
-    else if (d == 64 && G == 1) launch_attn<64, 1, 256>(c, w, b, l, st);
-    else if (d == 64 && G == 2) launch_attn<64, 2, 256>(c, w, b, l, st);
-    else if (d == 64 && G == 4) launch_attn<64, 4, 256>(c, w, b, l, st);
+    if (d == 128 && G == 1) launch_attn<128, 1, 256>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 2) launch_attn<128, 2, 256>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 4) launch_attn<128, 4, 128>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 8) launch_attn<128, 8, 128>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 3) launch_attn<128, 3, 128>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 5) launch_attn<128, 5, 128>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 6) launch_attn<128, 6, 128>(c, w, b, l, cached, st);
+    else if (d == 128 && G == 7) launch_attn<128, 7, 128>(c, w, b, l, cached, st);
+    else if (d == 64 && G == 1) launch_attn<64, 1, 256>(c, w, b, l, cached, st);
+    else if (d == 64 && G == 2) launch_attn<64, 2, 256>(c, w, b, l, cached, st);
+    else if (d == 64 && G == 4) launch_attn<64, 4, 256>(c, w, b, l, cached, st);
     else return fail(HARLI_ERR_INVALID, "decode_step: head_dim %d with group %d is not supported", d, G);
     // --- output projection + residual, operand of the FFN
     a.x = static_cast<const unsigned short*>(w.obuf);
@@ -1195,6 +1215,7 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
   if (b->logits) {
     SkinnyArgs a{};
     a.B = B;
+    a.cached = cached;
     a.eps = m.rms_eps;
     a.inv_dim = 1.f / (float)H;
     a.x = static_cast<const unsigned short*>(w.hx1);

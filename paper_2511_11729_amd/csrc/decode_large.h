@@ -24,6 +24,7 @@ struct SkinnyArgs {
   const unsigned short* x;  // fragment-order operand
   int B, b0, K;             // batch size, first batch row of this pass, contraction length
   int n_rows;               // output rows (tail masking of stores)
+  bool cached;              // the caches hold the weights from step to step: ordinary loads, else nontemporal ones
   const unsigned short *w0, *w1;  // pre-shuffled weights
   const float* ssq_in;  // partial sums of squares of the operand's source row (rho): [row][ssq_np], or null
   int ssq_np;           // entries per row (a multiple of 16; entries past the producer's tiles are zero)

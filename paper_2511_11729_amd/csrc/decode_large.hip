@@ -43,7 +43,7 @@ template <int FM>
 constexpr int dg_stages() { return FM <= 2 ? 6 : FM == 3 ? 5 : 4; }
 
 // ONCE: one tile of batch rows, so that the weights are read once: nontemporal loads (8B-class step at 256 sequences 2221 ->
-// 2156 us); with several, the tiles of a column share them through L2.
+// 2156 us); with several, the tiles of a column share them through L2, and those of a small model stay in the caches.
 template <int FM, bool ONCE>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_dgemm(DgemmArgs a) {
   constexpr int BM = 64 * FM, ASZ = BM * BK * 2, STG = ASZ + BSZ, NS = dg_stages<FM>();
@@ -439,6 +439,9 @@ harli_status dg_init() {
     allow(reinterpret_cast<const void*>(&k_dgemm<2, true>), dg_lds_bytes<2>());
     allow(reinterpret_cast<const void*>(&k_dgemm<3, true>), dg_lds_bytes<3>());
     allow(reinterpret_cast<const void*>(&k_dgemm<4, true>), dg_lds_bytes<4>());
+    allow(reinterpret_cast<const void*>(&k_dgemm<1, false>), dg_lds_bytes<1>());
+    allow(reinterpret_cast<const void*>(&k_dgemm<2, false>), dg_lds_bytes<2>());
+    allow(reinterpret_cast<const void*>(&k_dgemm<3, false>), dg_lds_bytes<3>());
     allow(reinterpret_cast<const void*>(&k_dgemm<4, false>), dg_lds_bytes<4>());
     g_attr_err = e;
   });
@@ -477,11 +480,17 @@ harli_status dg_gemm(DgKind kind, const SkinnyArgs& a, int x_tiles, float* part,
   g.Mpad = p.Mpad;
   g.part = part;
   const dim3 grid((unsigned)(p.tiles_n * p.tiles_m * p.ksplit));
-  if (p.FM == 1) hipLaunchKernelGGL((k_dgemm<1, true>), grid, dim3(NT), dg_lds_bytes<1>(), st, g);
-  else if (p.FM == 2) hipLaunchKernelGGL((k_dgemm<2, true>), grid, dim3(NT), dg_lds_bytes<2>(), st, g);
-  else if (p.FM == 3) hipLaunchKernelGGL((k_dgemm<3, true>), grid, dim3(NT), dg_lds_bytes<3>(), st, g);
-  else if (p.tiles_m == 1) hipLaunchKernelGGL((k_dgemm<4, true>), grid, dim3(NT), dg_lds_bytes<4>(), st, g);
-  else hipLaunchKernelGGL((k_dgemm<4, false>), grid, dim3(NT), dg_lds_bytes<4>(), st, g);
+  const bool once = p.tiles_m == 1 && !a.cached;
+#define DG_LAUNCH(F_)                                                                             \
+  do {                                                                                            \
+    if (once) hipLaunchKernelGGL((k_dgemm<F_, true>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g); \
+    else hipLaunchKernelGGL((k_dgemm<F_, false>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g);     \
+  } while (0)
+  if (p.FM == 1) DG_LAUNCH(1);
+  else if (p.FM == 2) DG_LAUNCH(2);
+  else if (p.FM == 3) DG_LAUNCH(3);
+  else DG_LAUNCH(4);
+#undef DG_LAUNCH
   HARLI_HIP(hipGetLastError());
   *used = p;
   return HARLI_OK;
