@@ -1084,10 +1084,10 @@ harli_status check_decode_args(harli_ctx* c, const harli_decode_batch* b) {
 }
 
 // The step on bf16 storage; every intermediate buffer comes from `w`.
-// Bytes of weights, keys and values a step reads (the lengths at half their bound, as uneven ones are).  What fits the memory-side cache is there from
-// the step before, and nontemporal loads would fetch it from memory every time.  A step in us with nontemporal / ordinary
-// loads: 37 MiB (hidden size 512) 118 / 106, 175 MiB 193 / 176, 209 MiB (1536) 142 / 130, 278 MiB (2048) 130 / 127, 370 MiB
-// 172 / 174, 439 MiB (one 7B layer) 92 / 97.
+// Bytes of weights, keys and values a step reads (the lengths at half their bound, as uneven ones are).  What fits the
+// memory-side cache is there from the step before, and nontemporal loads would fetch it from memory every time.  A step in us
+// with nontemporal / ordinary loads: 28 MiB (hidden size 512) 118 / 106, 155 MiB (1024) 193 / 176, 199 MiB (1536) 142 / 130,
+// 268 MiB (2048) 130 / 127, 357 MiB 172 / 174, 412 MiB (one 7B layer) 92 / 97.
 constexpr size_t kMemorySideCache = (size_t)256 << 20;
 size_t step_stream_bytes(const harli_ctx* c, const harli_decode_batch* b) {
   const harli_model_cfg& m = c->cfg;

@@ -149,8 +149,8 @@ def test_full_size_shapes_on_sampled_outputs():
 # ---- tile height chosen for the compute units of the stream ------------------------------------------------------------
 def test_full_size_shapes_on_a_nine_tenths_partition():
     """2048 x 4096 x 4096 on a stream masked to 230 compute units: 256 tiles of 128 rows would run as one full round
-    and 26 stragglers, so the library takes 128 tiles of 256 rows there (one round); sampled rows against fp64,
-    timings of both tile heights on the partition for the record."""
+    and 26 stragglers, so the library takes 128 tiles of 256 rows there (one round; its plan for this device and share is
+    asserted); sampled rows against fp64, timings of both tile heights on the partition for the record."""
     M, N, K = 2048, 4096, 4096
     assert hb.dbg_gemm2_plan(M, N // 256, 128, 230)["rounds"] == 2 and hb.dbg_gemm2_plan(M, N // 256, 256, 230)["rounds"] == 1
     assert hb.dbg_gemm2_cut(M, N // 256, K // 32, torch.cuda.get_device_properties(0).multi_processor_count, 230)["rows"] == 256
@@ -274,3 +274,17 @@ def test_a_small_workspace_gives_the_same_bits_in_passes(tile_rows, M, N, K, n_c
         out.append(cf)
     close(f64(out[0]), f64(A) @ f64(B).T, "fp32 output", 1e-5)
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("tile_rows,n_cu", [(128, 0), (256, 0), (128, 20)])
+def test_bands_of_row_tiles_and_columns_with_fewer_stages(tile_rows, n_cu):
+    """Row tiles in two bands, the last one ragged; a long segment that reaches two of six column tiles, so that the ranges of
+    K of the others are short or empty.  Every element against fp64 (1e-5 of the largest: K eps / 2 at most)."""
+    M, N, K, K2 = 1100, 1300, 96, 1000
+    A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
+    A2, B2 = rnd((M, K2), True, 3), rnd((512, K2), True, 4, 0.1)
+    ref = f64(A) @ f64(B).T
+    ref[:, 512:1024] += f64(A2) @ f64(B2).T
+    cf = torch.full((M, N), float("nan"), device=DEV)
+    hb.dbg_gemm2(M, [dict(A=A, B=B), dict(A=A2, B=B2, tile0=2, tile1=4)], [dict(N=N, cf=cf)], tile_rows=tile_rows, ksplit=8, n_cu=n_cu)
+    close(f64(cf), ref, "fp32 output", 1e-5)

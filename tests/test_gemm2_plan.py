@@ -1,7 +1,7 @@
-"""Launch grid of the finetune unit's weight GEMM (host logic, no GPU): with the workgroup-to-tile rule its header
-states every tile of the output is computed exactly once, the workgroups an XCD runs together cover a compact block of
-tiles, and the cost counts rounds over the compute units of the stream's partition (Harli Sec. 6.2: the finetune task
-runs on a share of the compute units)."""
+"""Launch grid of the finetune unit's weight GEMM (host logic, no GPU): with the workgroup-to-tile rules its header
+states every tile of the output, or every range of K of a tile that is cut, is computed exactly once, the workgroups an XCD
+runs together cover a compact block of tiles, the ranges of K follow the device alone, and the tile height follows the share
+of its compute units a stream may use (Harli Sec. 6.2: the finetune task runs on a share of them)."""
 import itertools
 
 import pytest
@@ -84,3 +84,39 @@ def test_passes_of_a_small_workspace_cover_the_cut_tiles():
     for M, tiles_n, stages in ((4096, 200, 2000), (48, 16, 690), (300, 1, 64)):       # the library's smallest workspace: 4 MiB
         c = hb.dbg_gemm2_cut(M, tiles_n, stages, 256, part_bytes=4 << 20)
         assert c["ks"] == 1 or c["per_pass"] >= 1
+
+
+@pytest.mark.parametrize("M,tiles_n,stages", [(1032, 14, 1186), (1100, 5, 40), (48, 16, 345), (2048, 48, 129), (1032, 74, 112), (4096, 20, 434),
+                                              (300, 1, 64), (2304, 3, 17), (129, 172, 33)])
+@pytest.mark.parametrize("n_cu,share", [(256, 256), (256, 230), (256, 26), (7, 7)])
+@pytest.mark.parametrize("part_bytes", [4 << 20, 64 << 20])
+def test_every_range_of_every_tile_is_computed_once(M, tiles_n, stages, n_cu, share, part_bytes):
+    """Cut launches, pass by pass: whole tiles, ranges of the others, several bands of row tiles with a ragged last one."""
+    c = hb.dbg_gemm2_cut(M, tiles_n, stages, n_cu, share, part_bytes)
+    assert c["tiles_m"] == -(-M // c["rows"]) and c["full"] + c["rest"] == c["tiles_m"] * c["tiles_n"]
+    if c["ks"] == 1:
+        assert c["rest"] == 0
+        return
+
+    def place(t):
+        band, rem = divmod(t, c["GM"] * c["tiles_n"])
+        rows = min(c["GM"], c["tiles_m"] - band * c["GM"])
+        return band * c["GM"] + rem % rows, rem // rows
+    done, first, full = {}, c["full"], c["full"]
+    while first < c["full"] + c["rest"]:
+        rest = min(c["per_pass"], c["full"] + c["rest"] - first)
+        assert rest * c["ks"] * c["rows"] * 256 * 4 <= part_bytes
+        chunk_full, chunk_cut = -(-full // 8), -(-rest * c["ks"] // 8)
+        if rest == c["rest"]:
+            assert (chunk_full, chunk_cut) == (c["chunk_full"], c["chunk_cut"])
+        for w in range(8 * chunk_full):
+            slot = (w & 7) * chunk_full + (w >> 3)
+            if slot < full:
+                done.setdefault(place(slot), []).append("whole")
+        for w in range(8 * chunk_cut):
+            piece = (w & 7) * chunk_cut + (w >> 3)
+            if piece < rest * c["ks"]:
+                done.setdefault(place(first + piece % rest), []).append(piece // rest)
+        first, full = first + rest, 0
+    assert set(done) == set(itertools.product(range(c["tiles_m"]), range(c["tiles_n"])))
+    assert all(v == ["whole"] or sorted(v) == list(range(c["ks"])) for v in done.values())
