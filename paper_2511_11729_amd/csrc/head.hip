@@ -38,8 +38,10 @@ inline size_t al(size_t n) { return (n + 255) & ~size_t(255); }
 // cache) and written once in half.  The maximum and the sum of exponentials come from one pass (a thread rescales its sum
 // when a group of values raises its maximum), sixteen bytes per lane and kCeU loads of a thread in flight; three passes of
 // scalar loads took 847 us for 1024 rows of 128256 classes, this takes 256 (0.79 GB: 3.1 TB/s).
-constexpr int kCeT = 512, kCeU = 4;
+// kCeT threads: 512, or one wave where its loads hold the whole row (up to 1024 classes: 2048 rows of 13 8.9 -> 6.1 us, of 1000 13.3 -> 7.9).
+constexpr int kCeU = 4;
 typedef float __attribute__((ext_vector_type(4))) f4;
+template <int kCeT>
 __global__ void __launch_bounds__(kCeT) k_ce_row(const float* __restrict__ logits, const int* __restrict__ targets, bf* __restrict__ dlog,
                                                  int V, int Vp, float* rowloss, int* err_flag) {
   __shared__ float red_m[kCeT / 64], red_s[kCeT / 64];
@@ -286,7 +288,10 @@ extern "C" harli_status harli_head_fwd_bwd(harli_ctx* c, const float* x, const i
       s = gemm2_launch(g, st);
       if (s != HARLI_OK) return s;
     }
-    hipLaunchKernelGGL(k_ce_row, dim3(rows), dim3(kCeT), 0, st, w.logits, targets + t0, w.dlog, V, Vp, w.rowloss + t0, c->dw.err_flag);
+    if (Vp <= 64 * 4 * kCeU)
+      hipLaunchKernelGGL(k_ce_row<64>, dim3(rows), dim3(64), 0, st, w.logits, targets + t0, w.dlog, V, Vp, w.rowloss + t0, c->dw.err_flag);
+    else
+      hipLaunchKernelGGL(k_ce_row<512>, dim3(rows), dim3(512), 0, st, w.logits, targets + t0, w.dlog, V, Vp, w.rowloss + t0, c->dw.err_flag);
     {  // dh = dlog W   (contraction over the padded vocabulary: pad columns are zero on both sides)
       Gemm2Args g{};
       g.M = rows; g.alpha = 1.f; g.half = 1; g.overflow_flag = c->dw.err_flag; g.part = part; g.part_bytes = part_bytes;

@@ -155,3 +155,9 @@ def test_cross_entropy_rows_around_the_load_groups(vocab):
     ref_loss, ref_dx, _ = O.head_forward_backward(x, case.ex["gf"], case.ex["wlm"], tg, case.m.rms_eps)
     assert abs(float(loss) - ref_loss) <= 2e-3 * abs(ref_loss), (float(loss), ref_loss)
     assert_close(dx.cpu().numpy(), ref_dx, "dx")
+
+
+@pytest.mark.parametrize("vocab", [249, 1023, 1025])
+def test_cross_entropy_rows_of_one_wave_and_just_over(vocab):
+    """The last vocabulary whose rows one wave takes, one in the middle of its loads, and the first one for 512 threads."""
+    test_cross_entropy_rows_around_the_load_groups(vocab)
