@@ -61,9 +61,9 @@ typedef struct {
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 
-/* The grid the weight GEMM would launch for M rows and tiles_n column tiles at tile height tile_rows (128 or 256), and
- * its cost on n_cu compute units (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk,
- * grid and the rounds of tiles over the compute units.  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
+/* The grid the weight GEMM would launch for M rows and tiles_n column tiles at tile height tile_rows (128 or 256), none of
+ * them cut along K (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk, grid and the rounds of
+ * tiles over n_cu compute units (a figure for the reader: height and cut are chosen by harli_dbg_gemm2_cut's rule).  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
  * of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over the blocks; slots past the matrix
  * are idle.  This is the order of a launch whose tiles are not cut along K; harli_dbg_gemm2_cut tells which are. */
 harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows, int32_t n_cu, int32_t* out);

@@ -20,6 +20,10 @@
 // of a row permuted by swz() on the way in so that the row reads and the transposing reads are both free of bank
 // conflicts.  Rows past the sequence are out of the buffer resource's range and read as zeros.
 //
+// In k_attn_bwd_dkv<128> the loads of the next block do not overlap the products: at two waves per SIMD its 256 registers
+// are not enough, 13 are spilled (eight lane offsets of the loads, four of a key fragment), and the wait for the reloads is a
+// wait for everything in flight.
+//
 // What bounds them at 512 to 1024 tokens is vector work per score, not MFMA: the exponent is one fma and the bare
 // hardware exponential, masks are applied only to blocks that cross the diagonal, and the running output is rescaled
 // only when a maximum has moved.  4 x 512 tokens, 32 heads of 128: forward 41 -> 24 us, dQ 56 -> 32, dK/dV 121 -> 55

@@ -113,10 +113,10 @@ size_t gemm2_part_bytes(int max_M, int tiles_n, int stages);
 
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st);
 
-// The grid gemm2_launch would use (exposed for the host-side tests of the tile order).
+// The grid of a launch whose tiles are not cut (exposed for the host-side tests of the tile order).
 struct Gemm2Plan {
   int GM, GN, total, chunk, grid;  // block of tiles per XCD pass, padded tile slots, slots per XCD, workgroups launched
-  int rounds;                      // rounds of tiles over the compute units
+  int rounds;                      // rounds of tiles over the compute units (reported only: gemm2_cut makes the choice)
 };
 Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu);
 

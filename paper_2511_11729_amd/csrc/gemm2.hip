@@ -16,7 +16,7 @@
 //   * nothing but the loads' scalar offsets moves from stage to stage: every branch and mask of the cursor (end of a
 //     segment, of the range, a partial K step) is behind one comparison that is false on whole stages.
 // What it measures at 256-row tiles: a stage takes 1180 cycles against 1024 of MFMA issue (1500 with the cursor's branches
-// and masks in every stage and the loads on eight consecutive MFMAs).  In time this is 8 % and not 21: on random operands
+// and masks in every stage and the loads on eight consecutive MFMAs).  In time this is 6 % and not 21: on random operands
 // the chip lowers its clock with the rate of products (1.67 -> 1.45 GHz; on zeros it stays at 2.4).
 // 4096 x 16384 x 4096: 526 -> 494 us; the 16 x 16 x 32 product, which drew less power in a bare loop (0.59 against
 // 0.64 us a stage), kept the register allocator copying accumulators between the register files.
@@ -596,7 +596,7 @@ void gemm2_block_jobs(const BlockJobs& jobs, hipStream_t st) {
   hipLaunchKernelGGL(k_block_jobs, dim3(256, jobs.n), dim3(256), 0, st, jobs);
 }
 
-// Grid of a launch: the XCD-aware tile order of the kernel and its cost in rounds of tiles over n_cu compute units.
+// Grid of a launch whose tiles are not cut: the XCD-aware tile order of the kernel.
 Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
   Gemm2Plan p{};
   const int BM = 64 * FM, tiles_m = (M + BM - 1) / BM;
@@ -623,8 +623,9 @@ Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu) {
 //   1032 x 3584 x 37888    628   347      2048 x 4096 x 4096     80    80 (one full round: not cut)
 // Cost in us, fitted to a sweep of ranges for these and 20 more shapes (it picks within 4 % of the best, 8 % at worst):
 // a stage takes 0.68 / 0.41 us in a tile of 256 / 128 rows while few compute units run and up to 0.34 / 0.18 more when
-// 256 / 140 do (clock and fabric); filling, draining and storing a tile about 6; the second launch 4; partial tiles 0.19
-// per MB.  (0.15 would fit the 128-row tiles alone; among the other kernels of a unit the chip holds a lower clock and the
+// 256 / 140 do (clock and fabric); a round 6 beyond its stages (a fitted constant: the store of a 256-row tile alone takes
+// 11 us with 16-bit and 22 with fp32 outputs, part of which the figures per stage carry); the second launch 4; partial tiles
+// 0.19 per MB.  (0.15 would fit the 128-row tiles alone; among the other kernels of a unit the chip holds a lower clock and the
 // 256-row tiles, which move fewer operand bytes per flop, lose less of it: 2048 x 4096 x 11008 as one round of 128-row
 // tiles or as half-length ranges of 256-row ones is 194 against 192 us alone and 213 against 203 inside a unit.)
 // On a stream confined to `share` of the device's compute units (Harli Sec. 6.2) the ranges of K stay the device's: they
