@@ -369,7 +369,7 @@ def main():
                 "decode_step_latency_ms_p50": float(np.percentile(closed["steplat"], 50)),
                 "decode_step_latency_ms_p99": float(np.percentile(closed["steplat"], 99))},
         "roofline": {"bound": "mfma", "achieved": ach_tf, "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": ach_tf / PEAK_MFMA_TFLOPS, "traffic": traffic_gemm, "kernel": "k_gemm2 (all tile heights and epilogues)",
+                     "frac": ach_tf / PEAK_MFMA_TFLOPS, "traffic": traffic_gemm, "kernel": "k_gemm2 with k_gemm2_sum (all tile heights and epilogues)",
                      "launches": int(gemm_n), "avg_launch_us": gemm_ms * 1e3 / max(gemm_n, 1),
                      "solo_unit_frac": (4.0 * T * m.layer_params) / (ft_solo_ms * 1e-3) / 1e12 / PEAK_MFMA_TFLOPS,
                      "note": "co-located with decode; flops = 2 M K per valid output column of every K segment; every %d-th "
