@@ -136,11 +136,12 @@ class LayerHarness:
             del self._ft_done[:32]
 
     def drain(self):
-        """Waits for the finetune units issued so far and lets go of their events (call before destroying a stream
-        they ran on: an event must not be asked about after its stream is gone)."""
+        """Waits for the finetune units issued so far and lets go of their events, the pool's of their saved tensors too
+        (call before destroying a stream they ran on: an event must not be asked about after its stream is gone)."""
         for ev in self._ft_done:
             ev.synchronize()
         self._ft_done = []
+        self.pool.stats()                                  # looks at every pending free
 
     def decode_bytes(self, batch=None, kv_len=None):
         kv = self.kv_len if kv_len is None else kv_len
