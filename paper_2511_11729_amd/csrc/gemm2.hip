@@ -1,29 +1,30 @@
 // Weight GEMM of the finetune unit (see gemm2.h for the operand layouts).
 //
 // Workgroup tile (64 FM) x 256, K step 32, FOUR waves -- one per SIMD, each with the whole register file: a wave owns
-// a (32 FM) x 128 block of the tile = FM x 4 accumulators of v_mfma_f32_32x32x16 (256 accumulator registers at FM = 4).
+// a (32 FM) x 128 block of the tile = 2 FM x 8 accumulators of v_mfma_f32_16x16x32 (256 accumulator registers at FM = 4).
 // What this shape buys on gfx950, measured:
 //   * operand bytes per flop through L2 and through LDS fall with the tile edge: a CU pulls no more than ~22-41 B/clk
 //     from L2 and LDS serves 128 B/clk, and 64 x 64 wave tiles (two waves per SIMD) need all of the latter at the full
 //     MFMA rate.  128 x 128 per wave needs half;
-//   * operands go from global memory straight into LDS (global_load_lds, 16 B per lane, no register staging); the
+//   * operands go from global memory straight into LDS (buffer_load ... lds, 16 B per lane, no register staging); the
 //     rows of a stage are XOR-swizzled in 16-byte chunks on the way in (each lane picks the global chunk that belongs
-//     in its LDS slot), which makes the 32-row fragment reads conflict free;
-//   * four LDS stages: while stage s is multiplied, s+1 has landed and s+2, s+3 are in flight;
-//   * one wave per SIMD has nobody to hide its waits, so the K loop is software pipelined by hand: the fragments of
-//     the next half step are read while the MFMAs of this one issue, and the eight loads a wave owes per stage are
-//     dealt out between the MFMAs of both half steps (sched_group_barrier pins that order);
+//     in its LDS slot), which makes the 16-row fragment reads conflict free;
+//   * four LDS stages, three of them in flight: the fragments of a stage are read during the stage before, so a stage's
+//     buffer is free again as soon as its products begin;
+//   * one wave per SIMD has nobody to hide its waits, so reads and loads are dealt out between the products by hand;
 //   * nothing but the loads' scalar offsets moves from stage to stage: every branch and mask of the cursor (end of a
 //     segment, of the range, a partial K step) is behind one comparison that is false on whole stages.
-// What it measures at 256-row tiles: a stage takes 1180 cycles against 1024 of MFMA issue (1500 with the cursor's branches
-// and masks in every stage and the loads on eight consecutive MFMAs).  In time this is 6 % and not 21: on random operands
-// the chip lowers its clock with the rate of products (1.67 -> 1.45 GHz; on zeros it stays at 2.4).
-// 4096 x 16384 x 4096: 526 -> 494 us; the 16 x 16 x 32 product, which drew less power in a bare loop (0.59 against
-// 0.64 us a stage), kept the register allocator copying accumulators between the register files.
+// What bounds it: power.  On random operands the chip holds 1.6-1.7 GHz under this loop (2.4 on zeros, and with the loads
+// bunched together the clock rises as the cycles do), so energy per product counts: v_mfma_f32_16x16x32 draws less than
+// 32x32x16 and the loop takes 1105-1160 cycles a 256-row stage (1024 of them product issue; 32x32x16: 1180).  A workgroup
+// spends another 3-5 us before its first product and 4 (16-bit) or 8-11 us (fp32) on its store.  Alone, 4096 x 16384 x 4096:
+// 484 us with 32x32x16 products and a store through LDS, 403 now (1365 TFLOP/s; the vendor's library 368); fp32 output with
+// a residual 606 -> 545; one round, 2048 x 8192 x 8192: 190 (1450 TFLOP/s; 183).
 // FM = 2 (128-row tiles) doubles the tile count for outputs that would not fill the chip with 256-row tiles.
 #include "gemm2.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ctx.h"
 #include "device_utils.h"
@@ -42,27 +43,139 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 #define G2_WAITV(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 #define G2_SB0() __builtin_amdgcn_sched_barrier(0)
-#define G2_SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
 
-// Stage of the epilogue: accumulator c (32 x 32, column block j of a wave's 128 columns) times alpha to the row-major
-// fp32 buffer the rows are stored from.  A lane holds rows 8 (v/4) + 4 (lane/32) + v%4 of column lane%32.
-constexpr int kG2StageRow = (128 + 8) * 4;  // staged row in bytes; 4 rows further = 32 banks further
-__device__ __forceinline__ void g2_stage_block(const f32x16& c, int j, char* ebuf, float alpha, int lane) {
-  const int col_l = lane & 31, rgrp = (lane >> 5) * 4;
+// ---- products and accumulators -----------------------------------------------------------------------------------------
+// A wave owns FM x 2 by 8 accumulators of v_mfma_f32_16x16x32, in accumulator registers NAMED BY HAND: accumulator t = 8 i + j
+// is a[4t .. 4t+3].  The compiler's allocator copied more than half of 64 four-register accumulators between the register
+// files in every pass of the stage ring; named, none moves, and the code between two products is exactly what stands there.
+// The kernel claims the whole range in its first statement and nothing else in it uses accumulator registers (the compiler
+// would only to spill, and it has 256 other registers for about 150 values): tests/test_gemm2_isa.py reads that off the
+// built library.  Hazards the compiler does not fill in for assembly: the products of one accumulator are 16 FM products
+// apart, its first use lies a barrier behind the zeros and the reads of the epilogue behind the idle cycles of g2_drain().
+// The weight fragment is the FIRST operand: a lane then holds four neighbouring columns 16 j + 4 (lane / 16) + v of row
+// 16 i + lane % 16, and the epilogue stores from registers.
+template <bool HALF, int T>
+__device__ __forceinline__ void g2_mm(u32x4 b, u32x4 a) {
+  if (HALF)
+    asm volatile("v_mfma_f32_16x16x32_f16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(b), "v"(a), "n"(4 * T), "n"(4 * T + 3));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(b), "v"(a), "n"(4 * T), "n"(4 * T + 3));
+}
+template <int R>
+__device__ __forceinline__ float g2_acc() {
+  float r;
+  asm volatile("v_accvgpr_read_b32 %0, a%c1" : "=v"(r) : "n"(R));
+  return r;
+}
+template <int FM>
+__device__ __forceinline__ void g2_claim() {
+#define G2_R10(p) p "0", p "1", p "2", p "3", p "4", p "5", p "6", p "7", p "8", p "9"
+#define G2_R128                                                                                                        \
+  G2_R10("a"), G2_R10("a1"), G2_R10("a2"), G2_R10("a3"), G2_R10("a4"), G2_R10("a5"), G2_R10("a6"), G2_R10("a7"),       \
+      G2_R10("a8"), G2_R10("a9"), G2_R10("a10"), G2_R10("a11"), "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127"
+  if (FM == 4)
+    asm volatile("" ::: G2_R128, "a128", "a129", G2_R10("a13"), G2_R10("a14"), G2_R10("a15"), G2_R10("a16"), G2_R10("a17"),
+                 G2_R10("a18"), G2_R10("a19"), G2_R10("a20"), G2_R10("a21"), G2_R10("a22"), G2_R10("a23"), G2_R10("a24"), "a250",
+                 "a251", "a252", "a253", "a254", "a255");
+  else
+    asm volatile("" ::: G2_R128);
+#undef G2_R128
+#undef G2_R10
+}
+// calls f(0), f(1), .., f(N - 1) with compile-time numbers
+template <int N, int Q = 0, typename F>
+__device__ __forceinline__ void g2_steps(F&& f) {
+  if constexpr (Q < N) {
+    f(std::integral_constant<int, Q>{});
+    g2_steps<N, Q + 1>(f);
+  }
+}
+// the last product's result may be read 18 cycles later (8 passes and the way out of the pipeline)
+__device__ __forceinline__ void g2_drain() { asm volatile("s_nop 15\n\ts_nop 15"); }
+
+// ---- epilogue: a slab of 16 rows x 128 columns, as the accumulators hold it -----------------------------------------------
+// x[j] of a lane: columns 16 j + 4 (lane / 16) .. + 3 of row lane % 16.  fp32 outputs are stored like that (16 rows x 64
+// bytes per instruction).  For 16-bit outputs neighbouring accumulators trade rows of 16 lanes (v_permlane16_swap), after
+// which a lane holds EIGHT neighbouring columns of a pair of accumulators p -- 32 p + 16 (g & 1) + 8 (g >> 1), g = lane / 16
+// -- and everything an epilogue combines (gate and up, the two halves of a rotary pair) lies in the same lane.  No LDS, no
+// barrier: the store of a 256 x 256 tile takes 4.1 us with 16-bit and 8 to 11 with fp32 outputs (11 and 22 through LDS).
+struct G2Pre {
+  u32x4 v[8];  // what the epilogue of a slab reads: residual, or stored a and u
+};
+
+// (rows past M and columns past N read some valid element instead: loads without a condition stay in flight together)
+template <int EPI>
+__device__ __forceinline__ void g2_epi_load(G2Pre& e, const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane, int m) {
+  const int mc = min(m, a.M - 1), g = lane >> 4, n0 = (tn - out.tile0) * BN + wn * 128;
+  if (EPI == GEMM2_EPI_SWIGLU_BWD) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v)
-    *reinterpret_cast<float*>(ebuf + (8 * (v >> 2) + rgrp + (v & 3)) * kG2StageRow + (j * 32 + col_l) * 4) = c[v] * alpha;
+    for (int p = 0; p < 4; ++p) {
+      const int n = n0 + p * 32 + (g & 1) * 16 + (g >> 1) * 8, nc = n < out.N ? n : 0;
+      e.v[2 * p] = *reinterpret_cast<const u32x4*>(a.e0 + (long long)mc * a.lde + nc);
+      e.v[2 * p + 1] = *reinterpret_cast<const u32x4*>(a.e1 + (long long)mc * a.lde + nc);
+    }
+  } else if (EPI == GEMM2_EPI_F32) {
+    if (out.res)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int n = n0 + j * 16 + g * 4, nc = n + 3 < out.N ? n : 0;
+        e.v[j] = out.N > 3 ? *reinterpret_cast<const u32x4*>(out.res + (long long)mc * out.ldcf + nc) : u32x4{0, 0, 0, 0};
+      }
+  }
 }
 
-// Rows [r0, r0 + ROWS) of a staged 32-row slab (128 columns, first row mrow0) to their destinations, by one wave.
-template <bool HALF, int EPI, int ROWS>
-__device__ __forceinline__ void g2_store_rows(const char* ebuf, const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane,
-                                              int mrow0, int r0, bool& clamped) {
-  constexpr int ER = kG2StageRow;
+template <bool HALF, int EPI>
+__device__ __forceinline__ void g2_epi_store(f32x4 (&x)[8], const G2Pre& e, const Gemm2Args& a, const Gemm2Out& out, int tn, int wn,
+                                             int lane, int m, bool& clamped) {
+  const int g = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] *= a.alpha;
+  if (EPI == GEMM2_EPI_F32) {
+    const int n0 = (tn - out.tile0) * BN + wn * 128 + g * 4;
+    if (m >= a.M) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = n0 + j * 16;
+      if (n + 3 < out.N) {
+        f32x4 o = x[j];
+        if (out.res) o += __builtin_bit_cast(f32x4, e.v[j]);
+        *reinterpret_cast<f32x4*>(out.Cf + (long long)m * out.ldcf + n) = o;
+        if (out.Cb) {
+          if (HALF)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) clamped = clamped || !(fabsf(o[v]) <= 65504.f);
+          *reinterpret_cast<uint2*>(out.Cb + (long long)m * out.ldcb + n) =
+              HALF ? make_uint2(pack_h2(o[0], o[1]), pack_h2(o[2], o[3])) : make_uint2(pack_bf2(o[0], o[1]), pack_bf2(o[2], o[3]));
+        }
+      } else {  // the last columns of a matrix whose width is not a multiple of four
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (n + v < out.N) {
+            float o = x[j][v];
+            if (out.res) o += out.res[(long long)m * out.ldcf + n + v];
+            out.Cf[(long long)m * out.ldcf + n + v] = o;
+            if (out.Cb) out.Cb[(long long)m * out.ldcb + n + v] = HALF ? f2h(o) : f2bf(o);
+          }
+      }
+    }
+    return;
+  }
+  // 16-bit outputs: y[p][0..7] = eight columns
+  float y[4][8];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[2 * p][v]), __float_as_uint(x[2 * p + 1][v]), false, false);
+      y[p][v] = __uint_as_float(t[0]);
+      y[p][4 + v] = __uint_as_float(t[1]);
+    }
+  if (m >= a.M) return;
+  const int c0 = (g & 1) * 16 + (g >> 1) * 8;
   auto pack8 = [&](const float* v) {
     if (HALF) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) clamped = clamped || !(fabsf(v[e]) <= 65504.f);
+      for (int k = 0; k < 8; ++k) clamped = clamped || !(fabsf(v[k]) <= 65504.f);
       return make_uint4(pack_h2(v[0], v[1]), pack_h2(v[2], v[3]), pack_h2(v[4], v[5]), pack_h2(v[6], v[7]));
     }
     return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]));
@@ -71,128 +184,60 @@ __device__ __forceinline__ void g2_store_rows(const char* ebuf, const Gemm2Args&
     if (HALF) unpack8h(wv, v);
     else unpack8(wv, v);
   };
-    if (EPI == GEMM2_EPI_GATEUP) {
-      // staged columns [0,32) gate, [32,64) up of output columns 0..31 of this wave's 64; [64,96), [96,128) of 32..63
-      const int c8 = (lane & 7) * 8;                              // 8 output columns of the 64
-      const int n8 = (tn - out.tile0) * 128 + wn * 64 + c8;       // column in a, u, m
-      const int sc = (c8 >> 5) * 64 + (c8 & 31);                  // staged column of the gate values
+  if (EPI == GEMM2_EPI_GATEUP) {
 #pragma unroll
-      for (int it = 0; it < ROWS / 8; ++it) {
-        const int row = r0 + it * 8 + (lane >> 3), m = mrow0 + row;
-        const float4 g0 = *reinterpret_cast<const float4*>(ebuf + row * ER + sc * 4);
-        const float4 g1 = *reinterpret_cast<const float4*>(ebuf + row * ER + sc * 4 + 16);
-        const float4 u0 = *reinterpret_cast<const float4*>(ebuf + row * ER + (sc + 32) * 4);
-        const float4 u1 = *reinterpret_cast<const float4*>(ebuf + row * ER + (sc + 32) * 4 + 16);
-        if (m >= a.M || n8 >= out.N) continue;
-        const float gx[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        const float ux[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-        const uint4 gp = pack8(gx), up = pack8(ux);
-        float av[8], uv[8], mv[8];
-        unpack(gp, av);  // the rounded values, as the backward pass will read them
-        unpack(up, uv);
+    for (int h = 0; h < 2; ++h) {  // pairs 0, 2: gate; 1, 3: up of the same 32 output columns
+      const int n = (tn - out.tile0) * 128 + wn * 64 + h * 32 + c0;
+      if (n >= out.N) continue;
+      const uint4 gp = pack8(y[2 * h]), up = pack8(y[2 * h + 1]);
+      float av[8], uv[8], mv[8];
+      unpack(gp, av);  // the rounded values, as the backward pass will read them
+      unpack(up, uv);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) mv[e] = av[e] / (1.f + __expf(-av[e])) * uv[e];
-        *reinterpret_cast<uint4*>(out.Cb + (long long)m * out.ldcb + n8) = gp;
-        *reinterpret_cast<uint4*>(a.o1 + (long long)m * a.lde + n8) = up;
-        *reinterpret_cast<uint4*>(a.o0 + (long long)m * a.lde + n8) = pack8(mv);
-      }
-    } else if (EPI == GEMM2_EPI_SWIGLU_BWD || EPI == GEMM2_EPI_NONE || EPI == GEMM2_EPI_ROPE) {
-      // 16-bit outputs only: eight columns (16 bytes) per lane, four rows per pass
-      const int c8 = (lane & 15) * 8, n8 = (tn - out.tile0) * BN + wn * 128 + c8;
-#pragma unroll
-      for (int it = 0; it < ROWS / 4; ++it) {
-        const int row = r0 + it * 4 + (lane >> 4), m = mrow0 + row;
-        const float4 lo = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4);
-        const float4 hi = *reinterpret_cast<const float4*>(ebuf + row * ER + c8 * 4 + 16);
-        if (m >= a.M || n8 >= out.N) continue;
-        float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        if (EPI == GEMM2_EPI_ROPE && tn < a.rope_tiles) {
-          // a wave's 128 columns hold whole heads: the partner columns lie in the same staged row
-          const int half = a.rope_d >> 1, cp = c8 ^ half;
-          const float4 pl = *reinterpret_cast<const float4*>(ebuf + row * ER + cp * 4);
-          const float4 ph = *reinterpret_cast<const float4*>(ebuf + row * ER + cp * 4 + 16);
-          const float y[8] = {pl.x, pl.y, pl.z, pl.w, ph.x, ph.y, ph.z, ph.w};
-          const float4* cs = reinterpret_cast<const float4*>(a.rope + (size_t)(m % a.rope_S) * half + (c8 & (half - 1)));
-          const float sgn = (c8 & half) ? 1.f : -1.f;  // (lo, hi) -> (lo cos - hi sin, hi cos + lo sin)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float4 t = cs[e];
-            x[2 * e] = x[2 * e] * t.x + sgn * y[2 * e] * t.y;
-            x[2 * e + 1] = x[2 * e + 1] * t.z + sgn * y[2 * e + 1] * t.w;
-          }
-        }
-        if (EPI == GEMM2_EPI_SWIGLU_BWD) {
-          float av[8], uv[8], oa[8], ou[8];
-          unpack(*reinterpret_cast<const uint4*>(a.e0 + (long long)m * a.lde + n8), av);
-          unpack(*reinterpret_cast<const uint4*>(a.e1 + (long long)m * a.lde + n8), uv);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float sg = 1.f / (1.f + __expf(-av[e]));
-            oa[e] = x[e] * uv[e] * sg * (1.f + av[e] * (1.f - sg));
-            ou[e] = x[e] * av[e] * sg;
-          }
-          *reinterpret_cast<uint4*>(a.o0 + (long long)m * a.lde + n8) = pack8(oa);
-          *reinterpret_cast<uint4*>(a.o1 + (long long)m * a.lde + n8) = pack8(ou);
-        } else {
-          *reinterpret_cast<uint4*>(out.Cb + (long long)m * out.ldcb + n8) = pack8(x);
-        }
-      }
-    } else {
-      // fp32 output (+ residual, + optional 16-bit copy): four columns per lane, two rows per pass
-      const int c4 = (lane & 31) * 4, n = (tn - out.tile0) * BN + wn * 128 + c4;
-      const bool nvec = n + 3 < out.N;
-#pragma unroll
-      for (int half8 = 0; half8 < (ROWS + 15) / 16; ++half8) {
-        constexpr int NIT = ROWS < 16 ? ROWS / 2 : 8;
-        float4 rv[NIT];
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-          const int m = mrow0 + r0 + (half8 * 8 + it) * 2 + (lane >> 5);
-          rv[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (out.res && nvec && m < a.M) rv[it] = *reinterpret_cast<const float4*>(out.res + (long long)m * out.ldcf + n);
-        }
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-          const int row = r0 + (half8 * 8 + it) * 2 + (lane >> 5), m = mrow0 + row;
-          float4 o = *reinterpret_cast<const float4*>(ebuf + row * ER + c4 * 4);
-          if (m >= a.M || n >= out.N) continue;
-          if (nvec) {
-            o.x += rv[it].x, o.y += rv[it].y, o.z += rv[it].z, o.w += rv[it].w;
-            *reinterpret_cast<float4*>(out.Cf + (long long)m * out.ldcf + n) = o;
-            if (out.Cb) {
-              const float ov[4] = {o.x, o.y, o.z, o.w};
-              if (HALF) clamped = clamped || !(fabsf(ov[0]) <= 65504.f) || !(fabsf(ov[1]) <= 65504.f) || !(fabsf(ov[2]) <= 65504.f) || !(fabsf(ov[3]) <= 65504.f);
-              *reinterpret_cast<uint2*>(out.Cb + (long long)m * out.ldcb + n) =
-                  HALF ? make_uint2(pack_h2(o.x, o.y), pack_h2(o.z, o.w)) : make_uint2(pack_bf2(o.x, o.y), pack_bf2(o.z, o.w));
-            }
-          } else {  // the last columns of a matrix whose width is not a multiple of four
-            const float ov[4] = {o.x, o.y, o.z, o.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (n + e < out.N) {
-                float x = ov[e];
-                if (out.res) x += out.res[(long long)m * out.ldcf + n + e];
-                out.Cf[(long long)m * out.ldcf + n + e] = x;
-                if (out.Cb) out.Cb[(long long)m * out.ldcb + n + e] = HALF ? f2h(x) : f2bf(x);
-              }
-          }
-        }
-      }
+      for (int k = 0; k < 8; ++k) mv[k] = av[k] / (1.f + __expf(-av[k])) * uv[k];
+      *reinterpret_cast<uint4*>(out.Cb + (long long)m * out.ldcb + n) = gp;
+      *reinterpret_cast<uint4*>(a.o1 + (long long)m * a.lde + n) = up;
+      *reinterpret_cast<uint4*>(a.o0 + (long long)m * a.lde + n) = pack8(mv);
     }
-}
-
-// One 32-row slab of a wave's block (the four accumulators c0..c3 side by side, 128 columns) to its destinations.
-template <bool HALF, int EPI>
-__device__ __forceinline__ void g2_store_slab(const f32x16& c0, const f32x16& c1, const f32x16& c2, const f32x16& c3, char* ebuf,
-                                              const Gemm2Args& a, const Gemm2Out& out, int tn, int wn, int lane, int mrow0,
-                                              bool& clamped) {
-  g2_stage_block(c0, 0, ebuf, a.alpha, lane);
-  g2_stage_block(c1, 1, ebuf, a.alpha, lane);
-  g2_stage_block(c2, 2, ebuf, a.alpha, lane);
-  g2_stage_block(c3, 3, ebuf, a.alpha, lane);
-  __builtin_amdgcn_wave_barrier();
-  g2_store_rows<HALF, EPI, 32>(ebuf, a, out, tn, wn, lane, mrow0, 0, clamped);
-  __builtin_amdgcn_wave_barrier();
+    return;
+  }
+  const int n0 = (tn - out.tile0) * BN + wn * 128 + c0;
+  if (EPI == GEMM2_EPI_ROPE && tn < a.rope_tiles) {
+    // a wave's 128 columns hold whole heads: (lo, hi) -> (lo cos - hi sin, hi cos + lo sin), hi half a head further right
+    const int half = a.rope_d >> 1;
+    const float4* cs = reinterpret_cast<const float4*>(a.rope + (size_t)(m % a.rope_S) * half);
+    auto rotate = [&](float* lo, float* hi, int idx) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 t = cs[(idx >> 1) + k];
+        const float l0 = lo[2 * k], l1 = lo[2 * k + 1], h0 = hi[2 * k], h1 = hi[2 * k + 1];
+        lo[2 * k] = l0 * t.x - h0 * t.y, hi[2 * k] = h0 * t.x + l0 * t.y;
+        lo[2 * k + 1] = l1 * t.z - h1 * t.w, hi[2 * k + 1] = h1 * t.z + l1 * t.w;
+      }
+    };
+    if (half == 64) rotate(y[0], y[2], c0), rotate(y[1], y[3], 32 + c0);
+    else rotate(y[0], y[1], c0), rotate(y[2], y[3], c0);
+  }
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int n = n0 + p * 32;
+    if (n >= out.N) continue;
+    if (EPI == GEMM2_EPI_SWIGLU_BWD) {
+      float av[8], uv[8], oa[8], ou[8];
+      unpack(__builtin_bit_cast(uint4, e.v[2 * p]), av);
+      unpack(__builtin_bit_cast(uint4, e.v[2 * p + 1]), uv);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float sg = 1.f / (1.f + __expf(-av[k]));
+        oa[k] = y[p][k] * uv[k] * sg * (1.f + av[k] * (1.f - sg));
+        ou[k] = y[p][k] * av[k] * sg;
+      }
+      *reinterpret_cast<uint4*>(a.o0 + (long long)m * a.lde + n) = pack8(oa);
+      *reinterpret_cast<uint4*>(a.o1 + (long long)m * a.lde + n) = pack8(ou);
+    } else {
+      *reinterpret_cast<uint4*>(out.Cb + (long long)m * out.ldcb + n) = pack8(y[p]);
+    }
+  }
 }
 
 // Output block of column tile tn.
@@ -217,6 +262,7 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
   constexpr int BM = 64 * FM, ASZ = BM * BK * 2, STG = ASZ + BSZ, NS = stages<FM>();
   constexpr int LOADS = FM + 4;  // direct-to-LDS loads a wave issues per stage
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  g2_claim<FM>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves of (32 FM) x 128
@@ -249,25 +295,15 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
   const int m0 = tm * BM;
   if (m0 >= a.M || tn >= a.tiles_n) return;
 
-  f32x16 acc[FM][4];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
   // ---- stage bookkeeping (uniform): the segments that cover this tile, 32 k at a time -------------------------------
   int n_stage = 0;
   for (int s = 0; s < a.nseg; ++s)
     if (tn >= a.seg[s].tile0 && tn < a.seg[s].tile1) n_stage += (a.seg[s].K + BK - 1) / BK;
   int skip = 0;  // stages of this tile that belong to earlier ranges of K
   if (piece >= 0) {
-    const int quads = (n_stage + NS - 1) / NS;  // ranges are whole passes of the stage ring
-    skip = quads * split / cut.ks * NS;
-    n_stage = min(n_stage, quads * (split + 1) / cut.ks * NS) - skip;
+    skip = n_stage * split / cut.ks;
+    n_stage = n_stage * (split + 1) / cut.ks - skip;
   }
-  const int n_step = (n_stage + NS - 1) / NS * NS;  // the loop body covers NS stages; stages past the end multiply zeros
 
   // Loads: instruction j of a wave fills 16 rows of a stage; lane -> row lane/4, LDS slot lane%4, which receives the
   // global chunk slot ^ ((row/2)%4).  They are buffer loads (buffer_load_dwordx4 ... lds): the operand is described by
@@ -348,68 +384,47 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
   } while (0)
 #define G2_BL(rs, voff, soff, sp)                                                                                     \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sp), 16, (int)(voff), (int)(soff), 0, 0)
-#define G2_ISSUE_A(buf)                                                                                               \
-  do {                                                                                                                \
-    char* SA = smem + (buf) * STG;                                                                                    \
-    _Pragma("unroll") for (int j = 0; j < FM; ++j) G2_BL(rsA, vA[j], soffA, SA + (wave * FM + j) * 1024);             \
-  } while (0)
-#define G2_ISSUE_B(buf)                                                                                               \
-  do {                                                                                                                \
-    char* SB = smem + (buf) * STG + ASZ;                                                                              \
-    G2_BL(rsB, vB, soffB[0], SB + (wave * 4 + 0) * 1024);                                                             \
-    G2_BL(rsB, vB, soffB[1], SB + (wave * 4 + 1) * 1024);                                                             \
-    G2_BL(rsB2, vB, soffB[2], SB + (wave * 4 + 2) * 1024);                                                            \
-    G2_BL(rsB2, vB, soffB[3], SB + (wave * 4 + 3) * 1024);                                                            \
-  } while (0)
+#define G2_LDA(buf, j) G2_BL(rsA, vA[j], soffA, smem + (buf) * STG + (wave * FM + (j)) * 1024)
+#define G2_LDB(buf, j) G2_BL((j) < 2 ? rsB : rsB2, vB, soffB[j], smem + (buf) * STG + ASZ + (wave * 4 + (j)) * 1024)
 
-  // fragment reads: row lane%32, 16-byte chunk 2 sub + lane/32, swizzled like the loads
-  const int sw = ((lane & 31) >> 1) & 3;
-  const int fo0 = (lane & 31) * 64 + ((lane >> 5) ^ sw) * 16;
-  const int fo1 = fo0 ^ 32;
-  const int aoff = wm * (FM * 32) * 64, boff = ASZ + wn * 128 * 64;
-  u32x4 fa0[FM], fb0[4], fa1[FM], fb1[4];
-#define G2_RD(FA, FB, buf, sub)                                                                                        \
-  do {                                                                                                                 \
-    const char* sa_ = smem + (buf) * STG + aoff + ((sub) ? fo1 : fo0);                                                 \
-    const char* sb_ = smem + (buf) * STG + boff + ((sub) ? fo1 : fo0);                                                 \
-    _Pragma("unroll") for (int i = 0; i < FM; ++i) FA[i] = *reinterpret_cast<const u32x4*>(sa_ + i * 2048);            \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) FB[j] = *reinterpret_cast<const u32x4*>(sb_ + j * 2048);             \
-  } while (0)
-#define G2_MM(FA, FB)                                                                                                  \
-  do {                                                                                                                 \
-    _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < 4; ++j)                       \
-        acc[i][j] = HALF ? __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, FA[i]),                    \
-                                                                  __builtin_bit_cast(f16x8, FB[j]), acc[i][j], 0, 0, 0) \
-                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, FA[i]),                  \
-                                                                   __builtin_bit_cast(bf16x8, FB[j]), acc[i][j], 0, 0, 0); \
-  } while (0)
-  // issue order of a half step: the FM + 4 fragment reads ride on the first MFMAs, the loads are spread over the rest
-  constexpr int kRd = (FM + 4) / 2;             // MFMAs that carry the fragment reads (two reads each)
-  constexpr int kRest = 4 * FM - kRd;           // MFMAs left in the half step
-#define G2_PIPE(loads)                                                                                                \
+  // fragment reads: row lane%16, 16-byte chunk lane/16, swizzled like the loads
+  const int fo = (lane & 15) * 64 + ((lane >> 4) ^ ((lane >> 1) & 3)) * 16;
+  const int aoff = wm * (FM * 32) * 64 + fo, boff = ASZ + wn * 128 * 64 + fo;
+  u32x4 fa[2][2 * FM], fb[2][8];
+#define G2_RDA(p, buf, i) fa[p][i] = *reinterpret_cast<const u32x4*>(smem + (buf) * STG + aoff + (i) * 1024)
+#define G2_RDB(p, buf, j) fb[p][j] = *reinterpret_cast<const u32x4*>(smem + (buf) * STG + boff + (j) * 1024)
+  // One stage: 16 FM products from fragments p.  Behind the first kBar of them every wave has all its fragments of this
+  // stage in registers and its share of the next stage has landed, so the barrier there opens the next stage's buffer for
+  // reading and this one's for the stage four ahead; the fragment reads and the loads are dealt out between the other
+  // products.  Rows of products alternate their direction, so that one operand stays from each product to the next.
+  constexpr int kBar = 3, kRdStep = FM == 4 ? 3 : 2, kLdStep = FM == 4 ? 6 : 4, kRd0 = kBar + 1, kLd0 = kBar + 2;
+  static_assert(kRd0 + (2 * FM + 8 - 1) * kRdStep < 16 * FM && kLd0 + (LOADS - 1) * kLdStep < 16 * FM, "a stage must hold its reads and loads");
+#define G2_STEP(cur, p)                                                                                               \
   do {                                                                                                                \
-    _Pragma("unroll") for (int q = 0; q < kRd; ++q) { G2_SGB(0x008, 1); G2_SGB(0x100, 2); }                           \
-    _Pragma("unroll") for (int q = 0; q < (loads); ++q) { G2_SGB(0x020, 1); G2_SGB(0x008, kRest / (loads)); }         \
-    if (kRest % (loads)) G2_SGB(0x008, kRest % (loads));                                                              \
-  } while (0)
-  // One stage: in the first half the weight side of the stage three ahead of the previous one is issued and the cursor
-  // moves on, in the second, when the barrier has freed the oldest buffer, the activation side of the next.
-#define G2_STEP(cur)                                                                                                  \
-  do {                                                                                                                \
-    G2_RD(fa1, fb1, cur, 1);                                                                                          \
-    G2_ISSUE_B(((cur) + 2) % NS);                                                                                     \
-    G2_MM(fa0, fb0);                                                                                                  \
+    g2_steps<16 * FM>([&](auto q_) __attribute__((always_inline)) {                                                   \
+      constexpr int q = decltype(q_)::value, i = q >> 3, j = i & 1 ? 7 - (q & 7) : q & 7;                             \
+      g2_mm<HALF, i * 8 + j>(fb[p][j], fa[p][i]);                                                                     \
+      if constexpr (q == kBar) {                                                                                      \
+        G2_SB0();                                                                                                     \
+        __builtin_amdgcn_s_waitcnt(0x0070 | ((2 * LOADS) & 15) | (((2 * LOADS) >> 4) << 14)); /* vmcnt, lgkmcnt 0 */  \
+        __builtin_amdgcn_s_barrier();                                                                                 \
+        G2_SB0();                                                                                                     \
+      }                                                                                                               \
+      if constexpr (q >= kRd0 && (q - kRd0) % kRdStep == 0 && (q - kRd0) / kRdStep < 2 * FM + 8) {                    \
+        constexpr int r = (q - kRd0) / kRdStep;                                                                       \
+        if constexpr (r < 8) G2_RDB((p) ^ 1, ((cur) + 1) % NS, r);                                                    \
+        else G2_RDA((p) ^ 1, ((cur) + 1) % NS, r - 8);                                                                \
+        G2_SB0();                                                                                                     \
+      }                                                                                                               \
+      if constexpr (q >= kLd0 && (q - kLd0) % kLdStep == 0 && (q - kLd0) / kLdStep < LOADS) {                         \
+        constexpr int r = (q - kLd0) / kLdStep;                                                                       \
+        if constexpr (r < FM) G2_LDA(cur, r);                                                                         \
+        else G2_LDB(cur, r - FM);                                                                                     \
+        G2_SB0();                                                                                                     \
+      }                                                                                                               \
+    });                                                                                                               \
     G2_NEXT();                                                                                                        \
-    G2_PIPE(4);                                                                                                       \
-    G2_SB0();                                                                                                         \
     if (k0 > k_last) G2_TURN();                                                                                       \
-    G2_WAITV(LOADS); /* all but the newest stage have landed: the next one is in LDS */                               \
-    __builtin_amdgcn_s_barrier();                                                                                     \
-    G2_SB0();                                                                                                         \
-    G2_RD(fa0, fb0, ((cur) + 1) % NS, 0);                                                                             \
-    G2_ISSUE_A(((cur) + 3) % NS);                                                                                     \
-    G2_MM(fa1, fb1);                                                                                                  \
-    G2_PIPE(FM);                                                                                                      \
     G2_SB0();                                                                                                         \
   } while (0)
 
@@ -429,105 +444,119 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN, c
       for (int j = 0; j < 4; ++j) soffB[j] += (unsigned)k0 * (BN * 2u);
     }
     G2_TURN();
-    G2_ISSUE_A(0);
-    G2_ISSUE_B(0);
-    G2_NEXT();
-    if (k0 > k_last) G2_TURN();
-    G2_ISSUE_A(1);
-    G2_ISSUE_B(1);
-    G2_NEXT();
-    if (k0 > k_last) G2_TURN();
-    G2_ISSUE_A(2);
-    G2_WAITV(LOADS + FM);
-    __builtin_amdgcn_s_barrier();
-    G2_RD(fa0, fb0, 0, 0);
-    G2_SB0();
-    for (int st = 0; st < n_step; st += NS) {
-      G2_STEP(0);
-      G2_STEP(1);
-      G2_STEP(2);
-      G2_STEP(3);
+#pragma unroll
+    for (int b = 0; b < NS; ++b) {
+#pragma unroll
+      for (int j = 0; j < FM; ++j) G2_LDA(b, j);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) G2_LDB(b, j);
+      G2_NEXT();
+      if (k0 > k_last) G2_TURN();
     }
-    G2_WAITV(0);
+    g2_steps<64 * FM>([&](auto r) __attribute__((always_inline)) { asm volatile("v_accvgpr_write_b32 a%c0, 0" ::"n"(decltype(r)::value)); });
+    G2_WAITV(3 * LOADS);
+    __builtin_amdgcn_s_barrier();
+    G2_SB0();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) G2_RDB(0, 0, j);
+#pragma unroll
+    for (int i = 0; i < 2 * FM; ++i) G2_RDA(0, 0, i);
+    G2_SB0();
+    for (int st = 0;; st += NS) {  // the last stages load (zeros) past the end, which nobody multiplies
+      G2_STEP(0, 0);
+      if (st + 1 >= n_stage) break;
+      G2_STEP(1, 1);
+      if (st + 2 >= n_stage) break;
+      G2_STEP(2, 0);
+      if (st + 3 >= n_stage) break;
+      G2_STEP(3, 1);
+      if (st + 4 >= n_stage) break;
+    }
+    G2_WAITV(0);  // no load may land after the workgroup has given its LDS back
+  } else {
+    g2_steps<64 * FM>([&](auto r) __attribute__((always_inline)) { asm volatile("v_accvgpr_write_b32 a%c0, 0" ::"n"(decltype(r)::value)); });
   }
+  g2_drain();
   if (probe && tid == 0) a.clk[0] = clock64() - c_start, a.clk[1] = wall_clock64() - w_start;
-  __syncthreads();  // every wave is done with the stage buffers: the epilogue reuses them
 #undef G2_OPEN_SEG
 #undef G2_TURN
 #undef G2_NEXT
-#undef G2_ISSUE_A
-#undef G2_ISSUE_B
 #undef G2_BL
-#undef G2_RD
-#undef G2_MM
-#undef G2_PIPE
+#undef G2_LDA
+#undef G2_LDB
+#undef G2_RDA
+#undef G2_RDB
 #undef G2_STEP
 
   if (piece >= 0) {
     // a range of K: the accumulators leave as they lie in the registers, 1 KiB per store instruction; k_gemm2_sum reads
     // them back in the same order
     float* p = a.part + (((size_t)piece * 4 + wave) * (FM * 4096)) + lane * 4;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4*>(p + ((i * 4 + j) * 4 + q) * 256) =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    g2_steps<16 * FM>([&](auto t_) __attribute__((always_inline)) {
+      constexpr int t = decltype(t_)::value;
+      *reinterpret_cast<f32x4*>(p + t * 256) = f32x4{g2_acc<4 * t>(), g2_acc<4 * t + 1>(), g2_acc<4 * t + 2>(), g2_acc<4 * t + 3>()};
+    });
     return;
   }
 
-  // ---- epilogue ---------------------------------------------------------------------------------------------------
+  // ---- epilogue: slab by slab, what the next two slabs read in flight --------------------------------------------------
   const Gemm2Out out = g2_out_of(a, tn);
-  static_assert(4 * 32 * kG2StageRow <= NS * STG, "epilogue staging must fit the stage buffers");
-  char* ebuf = smem + wave * (32 * kG2StageRow);
   bool clamped = false;
-  const int mrow_w = m0 + wm * (FM * 32);
-  g2_store_slab<HALF, EPI>(acc[0][0], acc[0][1], acc[0][2], acc[0][3], ebuf, a, out, tn, wn, lane, mrow_w, clamped);
-  g2_store_slab<HALF, EPI>(acc[1][0], acc[1][1], acc[1][2], acc[1][3], ebuf, a, out, tn, wn, lane, mrow_w + 32, clamped);
-  if constexpr (FM == 4) {
-    g2_store_slab<HALF, EPI>(acc[2][0], acc[2][1], acc[2][2], acc[2][3], ebuf, a, out, tn, wn, lane, mrow_w + 64, clamped);
-    g2_store_slab<HALF, EPI>(acc[3][0], acc[3][1], acc[3][2], acc[3][3], ebuf, a, out, tn, wn, lane, mrow_w + 96, clamped);
-  }
+  const int mrow = m0 + wm * (FM * 32) + (lane & 15);
+  constexpr int SL = 2 * FM;
+  G2Pre pre[3];
+  g2_epi_load<EPI>(pre[0], a, out, tn, wn, lane, mrow);
+  g2_epi_load<EPI>(pre[1], a, out, tn, wn, lane, mrow + 16);
+  g2_steps<SL>([&](auto i_) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_)::value;
+    if constexpr (i + 2 < SL) g2_epi_load<EPI>(pre[(i + 2) % 3], a, out, tn, wn, lane, mrow + (i + 2) * 16);
+    f32x4 x[8];
+    g2_steps<8>([&](auto j_) __attribute__((always_inline)) {
+      constexpr int t = i * 8 + decltype(j_)::value;
+      x[decltype(j_)::value] = f32x4{g2_acc<4 * t>(), g2_acc<4 * t + 1>(), g2_acc<4 * t + 2>(), g2_acc<4 * t + 3>()};
+    });
+    g2_epi_store<HALF, EPI>(x, pre[i % 3], a, out, tn, wn, lane, mrow + i * 16, clamped);
+  });
   if (clamped && a.overflow_flag) atomicOr(a.overflow_flag, 8);
 }
 
-// Sum of the K ranges of the cut tiles, in range order, and their epilogue.  Workgroup: one 32-row slab of one wave's
-// 32 FM x 128 block of one tile.  Wave j adds up the partials of column block j (four 1 KiB loads per range, four ranges
-// in flight), the four waves then store eight rows each.
+// Sum of the K ranges of the cut tiles, in range order, and their epilogue.  A wave takes one slab of 16 rows of one wave's
+// block of one tile: eight 1 KiB loads per range, up to four ranges in flight.
 template <int FM, bool HALF, int EPI>
 __global__ void __launch_bounds__(256) k_gemm2_sum(Gemm2Args a, Gemm2Cut cut) {
-  __shared__ __align__(16) char ebuf[32 * kG2StageRow];
-  const int lane = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i = blockIdx.x % FM, wave = (blockIdx.x / FM) & 3, r = blockIdx.x / (4 * FM);
+  const int lane = threadIdx.x & 63, id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = id % (2 * FM), wave = (id / (2 * FM)) & 3, r = id / (8 * FM);
   int tm, tn;
   g2_cut_tile(cut, cut.first + r, tm, tn);
-  const int mrow0 = tm * (64 * FM) + (wave >> 1) * (FM * 32) + i * 32;
+  const int mrow0 = tm * (64 * FM) + (wave >> 1) * (FM * 32) + i * 16;
   if (mrow0 >= a.M) return;
+  const Gemm2Out out = g2_out_of(a, tn);
+  G2Pre pre;
+  g2_epi_load<EPI>(pre, a, out, tn, wave & 1, lane, mrow0 + (lane & 15));
   const size_t stride = (size_t)cut.rest * (4 * FM * 4096);  // floats between two ranges of a tile
-  const float* p = a.part + ((size_t)r * 4 + wave) * (FM * 4096) + (i * 4 + j) * 1024 + lane * 4;
-  f32x16 c;
+  const float* p = a.part + ((size_t)r * 4 + wave) * (FM * 4096) + i * 2048 + lane * 4;
+  f32x4 x[8];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) c[v] = 0.f;
-  for (int s0 = 0; s0 < cut.ks; s0 += 4) {
-    f32x4 t[4][4];
+  for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const f32x4*>(p + j * 256);
+  auto add = [&](auto n_) {
+    constexpr int n = decltype(n_)::value;
+    f32x4 t[n][8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < n; ++u)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) t[u][q] = *reinterpret_cast<const f32x4*>(p + (size_t)min(s0 + u, cut.ks - 1) * stride + q * 256);
+      for (int j = 0; j < 8; ++j) t[u][j] = *reinterpret_cast<const f32x4*>(p + (u + 1) * stride + j * 256);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < cut.ks)
+    for (int u = 0; u < n; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) c[4 * q + e] += t[u][q][e];
-  }
-  g2_stage_block(c, j, ebuf, a.alpha, lane);
-  __syncthreads();
+      for (int j = 0; j < 8; ++j) x[j] += t[u][j];
+    p += n * stride;
+  };
+  int left = cut.ks - 1;
+  for (; left >= 3; left -= 3) add(std::integral_constant<int, 3>{});
+  if (left == 2) add(std::integral_constant<int, 2>{});
+  else if (left == 1) add(std::integral_constant<int, 1>{});
   bool clamped = false;
-  g2_store_rows<HALF, EPI, 8>(ebuf, a, g2_out_of(a, tn), tn, wave & 1, lane, mrow0, j * 8, clamped);
+  g2_epi_store<HALF, EPI>(x, pre, a, out, tn, wave & 1, lane, mrow0 + (lane & 15), clamped);
   if (clamped && a.overflow_flag) atomicOr(a.overflow_flag, 8);
 }
 
@@ -793,7 +822,7 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
       cut.chunk_cut = (cut.rest * cut.ks + 7) / 8;                                                                           \
       hipLaunchKernelGGL((k_gemm2<F_, H_, E_>), dim3(8 * (cut.chunk_full + cut.chunk_cut)), dim3(NT), lds_bytes<F_>(), st, a, cut, total, \
                          chunk, GM, GN, zero16);                                                                             \
-      hipLaunchKernelGGL((k_gemm2_sum<F_, H_, E_>), dim3(cut.rest * 4 * F_), dim3(256), 0, st, a, cut);                       \
+      hipLaunchKernelGGL((k_gemm2_sum<F_, H_, E_>), dim3(cut.rest * 2 * F_), dim3(256), 0, st, a, cut);                       \
       cut.full = cut.chunk_full = 0;                                                                                         \
     }                                                                                                                        \
   } while (0)
