@@ -20,7 +20,7 @@ extern "C" {
  *   matrices of the pair and either may be NULL) and its weight rows start at the first column of tile0.  Output block
  *   o starts at tile out_tile0[o] and has out_n[o] valid columns; all blocks are 16-bit (cb) or all fp32 (cf, optional
  *   res).  epi 0: plain; 2: SwiGLU backward (cf/cb unused: o0 = da, o1 = du from e0 = a, e1 = u); 3: gate/up pair
- *   (cb[0] = a, o1 = u, o0 = silu(a) * u).  tile_rows 128 or 256 fixes the tile height, 0 leaves the choice to the
+ *   (cb[0] = a, o1 = u, o0 = silu(a) * u).  tile_rows 128, 160, 192, 224 or 256 (bfloat16: 128 or 256) fixes the tile height, 0 leaves the choice to the
  *   library.  reps > 1 repeats the launch and writes TFLOP/s over HIP events and the shader clock of the last launch
  *   to the host pointers (either may be NULL). */
 typedef struct {
@@ -61,7 +61,7 @@ typedef struct {
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 
-/* The grid the weight GEMM would launch for M rows and tiles_n column tiles at tile height tile_rows (128 or 256), none of
+/* The grid the weight GEMM would launch for M rows and tiles_n column tiles at tile height tile_rows (128, 160, .., 256), none of
  * them cut along K (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk, grid and the rounds of
  * tiles over n_cu compute units (a figure for the reader: height and cut are chosen by harli_dbg_gemm2_cut's rule).  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
  * of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over the blocks; slots past the matrix

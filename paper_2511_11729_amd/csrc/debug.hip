@@ -11,9 +11,9 @@
 using namespace harli;
 
 extern "C" harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows, int32_t n_cu, int32_t* out) {
-  if (!out || M < 1 || tiles_n < 1 || n_cu < 1 || (tile_rows != 128 && tile_rows != 256))
+  if (!out || M < 1 || tiles_n < 1 || n_cu < 1 || tile_rows < 128 || tile_rows > 256 || tile_rows % 32)
     return fail(HARLI_ERR_INVALID, "dbg_gemm2_plan: bad argument");
-  const Gemm2Plan p = gemm2_plan(M, tiles_n, tile_rows / 64, n_cu);
+  const Gemm2Plan p = gemm2_plan(M, tiles_n, tile_rows / 32, n_cu);
   const int v[6] = {p.GM, p.GN, p.total, p.chunk, p.grid, p.rounds};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
   return HARLI_OK;
@@ -23,8 +23,8 @@ extern "C" harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t 
                                             int32_t* out) {
   if (!out || M < 1 || tiles_n < 1 || stages < 1 || n_cu < 1 || share < 1 || share > n_cu || part_bytes < 0)
     return fail(HARLI_ERR_INVALID, "dbg_gemm2_cut: bad argument");
-  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share);
-  const int v[10] = {64 * c.FM, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut, gemm2_pass_tiles(c, (size_t)part_bytes)};
+  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share, true, false);
+  const int v[10] = {32 * c.RT, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut, gemm2_pass_tiles(c, (size_t)part_bytes)};
   for (int i = 0; i < 10; ++i) out[i] = v[i];
   return HARLI_OK;
 }

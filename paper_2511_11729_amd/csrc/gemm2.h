@@ -94,7 +94,7 @@ struct Gemm2Args {
 // How a launch is cut (host logic, gemm2_cut): tiles [0, full) are computed whole, each of the other `rest` tiles in ks
 // ranges of K by ks workgroups that write partial tiles to the workspace; a second kernel adds them and runs the epilogue.
 struct Gemm2Cut {
-  int FM;                      // tile height / 64
+  int RT;                      // tile height / 32
   int ks;                      // 1: nothing is cut
   int full, rest;              // (of one launch: its whole tiles, and the tiles it cuts)
   int first;                   // first tile that is cut
@@ -102,9 +102,10 @@ struct Gemm2Cut {
   int chunk_full, chunk_cut;   // tiles / pieces per XCD
   double cost_us;              // what the choice was made by
 };
+// half: IEEE half operands (bfloat16 has tiles of 128 and 256 rows alone).  f32out: fp32 outputs.
 // stages: K steps of the longest column tile.  n_cu: compute units of the device, share: those the stream may use.
 // The workspace plays no part: the bits of a launch do not depend on how much of it there is.
-Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share);
+Gemm2Cut gemm2_cut(int M, int tiles_n, int stages, int n_cu, int share, bool half, bool f32out);
 // tiles cut per pass with part_bytes of workspace (0: it does not hold the partial tiles of one)
 int gemm2_pass_tiles(const Gemm2Cut& c, size_t part_bytes);
 constexpr size_t kG2MinPartBytes = (size_t)4 << 20;  // sixteen ranges of a tile of 256 rows
@@ -118,7 +119,11 @@ struct Gemm2Plan {
   int GM, GN, total, chunk, grid;  // block of tiles per XCD pass, padded tile slots, slots per XCD, workgroups launched
   int rounds;                      // rounds of tiles over the compute units (reported only: gemm2_cut makes the choice)
 };
-Gemm2Plan gemm2_plan(int M, int tiles_n, int FM, int n_cu);
+Gemm2Plan gemm2_plan(int M, int tiles_n, int RT, int n_cu);
+
+// One tile height's launches (gemm2_kernel.h, compiled by gemm2_rows*.hip).  banded: tiles in the order of a cut launch.
+template <int RT>
+harli_status gemm2_run(const Gemm2Args& a, const Gemm2Cut& plan, const Gemm2Plan& pl, bool banded, int per_pass, hipStream_t st);
 
 // Blocked copies.  src is [R][C] row-major in the storage type (bf16; fp32 when src_f32 is 1; 16-bit elements that
 // are already in the compute element and are copied bit for bit when src_f32 is 2); the operand is B[n][k] =
@@ -140,7 +145,7 @@ void gemm2_block_jobs(const BlockJobs& jobs, hipStream_t st);
 // measurement hook: fixes the ranges of K of later launches (tiles past the last full round, all of them when one round
 // holds them all; 1: never cut); 0 gives the choice back
 void gemm2_force_split(int ks);
-// measurement hook: 128 or 256 fixes the tile height of every later launch, anything else gives the choice back
+// measurement hook: 128, 160, 192, 224 or 256 (128 or 256 for bfloat16 operands) fixes the tile height of every later launch, anything else gives the choice back
 void gemm2_force_tile_rows(int rows);
 // compute units a stream made by harli_cu_stream_create may use; 0 for any other stream (sched.cpp)
 int cu_stream_count(void* hip_stream);

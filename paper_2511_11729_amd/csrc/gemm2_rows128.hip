@@ -1,0 +1,6 @@
+// Weight GEMM of the finetune unit: tiles of 128 rows.
+#include "gemm2_kernel.h"
+
+namespace harli {
+template harli_status gemm2_run<4>(const Gemm2Args&, const Gemm2Cut&, const Gemm2Plan&, bool, int, hipStream_t);
+}

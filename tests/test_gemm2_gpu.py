@@ -120,6 +120,26 @@ def test_gate_up_pair_with_swiglu_epilogue_and_its_backward(half, M, F, H):
     close(f64(du), dm * ar * sg, "du", tol)
 
 
+@pytest.mark.parametrize("tile_rows", [128, 160, 192, 224, 256])
+@pytest.mark.parametrize("M,N,K,ksplit", [(1, 260, 264, 1), (353, 1001, 40, 1), (417, 520, 1000, 3), (225, 261, 136, 4)])
+def test_tile_heights_at_their_edges(tile_rows, M, N, K, ksplit):
+    """Every tile height, whole and in ranges of K: one row, rows past the last whole 16 of a tile, columns past the last
+    whole four (fp32 output with a residual and its 16-bit copy) and, N rounded down to eights, a 16-bit output."""
+    A, B = rnd((M, K), True, 80), rnd((N, K), True, 81, 0.1)
+    ref = f64(A) @ f64(B).T
+    ld = (N + 7) // 8 * 8
+    res = rnd((M, ld), True, 82).float()
+    cf, cb = torch.full((M, ld), 7.0, device=DEV), torch.full((M, ld), 7.0, dtype=torch.float16, device=DEV)
+    hb.dbg_gemm2(M, [dict(A=A, B=B)], [dict(N=N, cf=cf, cb=cb, res=res, ld=ld)], tile_rows=tile_rows, ksplit=ksplit)
+    close(f64(cf)[:, :N], ref + f64(res)[:, :N], "fp32 output", 1e-5)
+    close(f64(cb)[:, :N], ref + f64(res)[:, :N], "16-bit copy")
+    assert (cf[:, N:] == 7).all() and (cb[:, N:] == 7).all()
+    N8 = N // 8 * 8
+    ch = torch.full((M, N8), float("nan"), dtype=torch.float16, device=DEV)
+    hb.dbg_gemm2(M, [dict(A=A, B=B[:N8].contiguous())], [dict(N=N8, cb=ch)], tile_rows=tile_rows, ksplit=ksplit)
+    close(f64(ch), ref[:, :N8], "16-bit output")
+
+
 def test_an_output_beyond_the_range_of_half_sets_the_flag():
     M, N, K = 128, 256, 64
     A = torch.full((M, K), 200.0, dtype=torch.float16, device=DEV)
