@@ -181,14 +181,6 @@ extern "C" harli_status harli_ctx_create(const harli_model_cfg* cfg, const harli
     TRY(dev_alloc(c, &d.part, d.part_bytes, false));
     TRY(dg_init());
   }
-  // fp32 path: scratch for attention scores, one row of max_seq_len per (sequence, query head)
-  if (m.dtype == HARLI_F32) {
-    TRY(dev_alloc(c, &d.scores, bp * m.n_q_heads * (size_t)m.max_seq_len * 4, true));
-    TRY(dev_alloc(c, &d.fk, bp * m.n_kv_heads * m.head_dim * 4, true));
-    TRY(dev_alloc(c, &d.fv, bp * m.n_kv_heads * m.head_dim * 4, true));
-    TRY(dev_alloc(c, &d.fa, bp * m.ffn * 4, true));
-    TRY(dev_alloc(c, &d.fu, bp * m.ffn * 4, true));
-  }
   c->decode_ws_bytes = g_tally;
   g_tally = 0;
   // decode-private pre-shuffled weights (bf16 path): the inference instance keeps its own copy
@@ -239,7 +231,7 @@ extern "C" harli_status harli_ctx_device_bytes(const harli_ctx* c, harli_device_
 extern "C" void harli_ctx_destroy(harli_ctx* c) {
   if (!c) return;
   DecodeWs& d = c->dw;
-  void* bufs[] = {d.hx1, d.obuf, d.hx2, d.mbuf, d.qbuf, d.x1, d.xa, d.xb, d.ssq, d.rope, d.att_part, d.amax_v, d.amax_i, d.err_flag, d.part, d.scores, d.inv_freq, d.fk, d.fv, d.fa, d.fu};
+  void* bufs[] = {d.hx1, d.obuf, d.hx2, d.mbuf, d.qbuf, d.x1, d.xa, d.xb, d.ssq, d.rope, d.att_part, d.amax_v, d.amax_i, d.err_flag, d.part, d.inv_freq};
   (void)hipDeviceSynchronize();  // steps in flight may still read what goes back to the pool here
   for (void* p : bufs) lib_free(c, p);
   for (LayerDev& ld : c->layers)

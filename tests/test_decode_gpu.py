@@ -337,6 +337,24 @@ def test_biases_small_shapes_bf16_and_fp32():
         run_case(w, m, [0, 5, 16, 31, 77])
 
 
+@pytest.mark.parametrize("hidden,n_q,n_kv,d,ffn,lengths", [
+    (256, 4, 4, 64, 688, [96]), (254, 6, 2, 64, 690, [0, 300]), (256, 2, 1, 96, 64, [255, 256, 257]),
+    (130, 1, 1, 256, 33, [600, 1, 3, 17, 31]), (64, 2, 2, 320, 48, [5, 90, 16, 15, 2, 3, 7, 40, 520])])
+def test_fp32_path_at_its_edges(hidden, n_q, n_kv, d, ffn, lengths):
+    """The fp32 path over every number of batch rows a wave carries (1, 2, 4, 8, and a second tile of rows), contractions
+    with and without 16-byte loads, head sizes of one to five lanes' elements and blocks of 256 tokens; two layers, biases,
+    embedding and logits."""
+    w, m = variant(0, n_layers=2, hidden=hidden, n_q=n_q, n_kv=n_kv, head_dim=d, ffn=ffn, vocab=37, qkv_bias=True)
+    lengths = np.asarray(lengths, np.int32)
+    case = DecodeCase(w, m, lengths, full_model=True, block_bytes=64 << 10)
+    tok = wl.make_token_ids(dataclasses.replace(w, model=m), (len(lengths),))
+    hid = case.run_gpu(token_ids=tok)
+    ref_hid, ref_logits, _ = case.run_oracle(token_ids=tok)
+    assert_close(hid, ref_hid, "hidden state", **F32_BAR)
+    assert_close(case.logits_dev.cpu().numpy(), ref_logits, "logits", **F32_BAR)
+    case.check_cache(1e-4, 2e-5)
+
+
 def test_tiled_path_on_a_compute_unit_partition_and_in_a_replayed_graph():
     """The cut of the tiled GEMMs follows the compute units of the stream the step runs on (fewer ranges of K on a small
     partition): the result meets the oracle there too.  And the step is capturable: a replayed HIP graph gives the bits
