@@ -150,13 +150,19 @@ __global__ void __launch_bounds__(256) k_f32_to_e_scaled(const float* x, bf* y, 
 }
 
 // ---------------------------------------------------------------- skinny NT GEMM (LoRA down-projection x.A and dy.B^T)
-// Workgroup = 16 rows of X, 8 waves split K, one 16x16x32 MFMA column tile per 16 outputs.  Full 32-wide K steps are
-// loaded four at a time, unconditionally; only a last partial step (K % 32) masks its operands.
+// Workgroup = 16 RM rows of X, 8 waves split K, RM x NT accumulators of 16x16x32 each; one workgroup per compute unit.  What
+// bounds it is what a compute unit takes in -- its rows of X and all of Bm -- and the latency of that: a wave's K steps are
+// loaded U at a time, unconditionally, and where a launch has more than a round of workgroups, more rows share a read of Bm
+// (ft_skinny_nt_multi).  Loading every step's registers again as soon as its products had read them was slower (4096 x 64 x
+// 5120 26 -> 34 us, 2048 x 16 x 4096 10 -> 18): two neighbouring steps share the cache lines of a row.
 typedef unsigned __attribute__((ext_vector_type(4))) u32x4;  // native vector: arrays of it stay in registers
 __device__ __forceinline__ f32x4 mma16(const u32x4& a, const u32x4& b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
-template <int NT>
+// K steps a wave loads together: 20 to 40 loads of 16 bytes
+template <int NT, int RM>
+constexpr int skinny_steps() { return NT + RM == 2 ? 16 : NT + RM <= 5 ? 8 : 4; }
+template <int NT, int RM>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_skinny_nt(SkinnyNtJobs jobs, int M, float alpha, int* flag) {
   const SkinnyNtJob& jb = jobs.j[blockIdx.y];
   const bf* X = jb.X;
@@ -164,73 +170,88 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   bf* C = jb.C;
   const long long ldx = jb.ldx, ldb = jb.ldb, ldc = jb.ldc;
   const int N = jb.N, K = jb.K;
-  constexpr int NW = 8, U = NT == 1 ? 16 : NT == 2 ? 8 : 4;  // K steps in flight per wave: a wave has few steps, latency is what it waits for
+  constexpr int NW = 8, U = skinny_steps<NT, RM>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, g = lane >> 4;
-  const int m0 = blockIdx.x * 16;
-  const int mr = min(m0 + i16, M - 1);
-  const bf* xr = X + (long long)mr * ldx + g * 8;
-  const bf* br[NT];
+  const int m0 = blockIdx.x * (16 * RM);
+  const bf *xr[RM], *br[NT];
+#pragma unroll
+  for (int q = 0; q < RM; ++q) xr[q] = X + (long long)min(m0 + q * 16 + i16, M - 1) * ldx + g * 8;
 #pragma unroll
   for (int t = 0; t < NT; ++t) br[t] = Bm + (long long)min(t * 16 + i16, N - 1) * ldb + g * 8;
-  f32x4 acc[NT];
+  f32x4 acc[RM][NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int q = 0; q < RM; ++q)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int full = K >> 5;  // whole 32-wide steps
   const int s0 = full * wave / NW, s1 = full * (wave + 1) / NW;
+  u32x4 xf[U][RM], bfr[U][NT];
+  auto load = [&](int u, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < RM; ++q) xf[u][q] = *reinterpret_cast<const u32x4*>(xr[q] + (s << 5));
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bfr[u][t] = *reinterpret_cast<const u32x4*>(br[t] + (s << 5));
+  };
+  auto mma = [&](int u) __attribute__((always_inline)) {  // rows of X = MFMA rows, rows of Bm = columns
+#pragma unroll
+    for (int q = 0; q < RM; ++q)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[q][t] = mma16(xf[u][q], bfr[u][t], acc[q][t]);
+  };
   int s = s0;
   for (; s + U <= s1; s += U) {
-    u32x4 xf[U], bfr[NT][U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      xf[u] = *reinterpret_cast<const u32x4*>(xr + ((s + u) << 5));
-#pragma unroll
-      for (int t = 0; t < NT; ++t) bfr[t][u] = *reinterpret_cast<const u32x4*>(br[t] + ((s + u) << 5));
-    }
+    for (int u = 0; u < U; ++u) load(u, s + u);
     __builtin_amdgcn_sched_barrier(0);  // every load of the group is issued before the first product waits for one
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = mma16(xf[u], bfr[t][u], acc[t]);  // rows of X = MFMA rows, rows of Bm = columns
+    for (int u = 0; u < U; ++u) mma(u);
   }
-  for (; s < s1; ++s) {
-    const u32x4 xf = *reinterpret_cast<const u32x4*>(xr + (s << 5));
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = mma16(xf, *reinterpret_cast<const u32x4*>(br[t] + (s << 5)), acc[t]);
-  }
+  for (int u = 0; u < U; ++u)
+    if (s + u < s1) load(u, s + u);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (s + u < s1) mma(u);
   if (wave == NW - 1 && (K & 31)) {  // partial last step: lanes whose 8 k lie past K contribute zeros
     const int k = full << 5;
     const bool ok = k + g * 8 < K;
     const int kc = ok ? k : 0;
-    u32x4 xf = *reinterpret_cast<const u32x4*>(xr + kc);
-    if (!ok) xf = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = mma16(xf, *reinterpret_cast<const u32x4*>(br[t] + kc), acc[t]);
+    for (int q = 0; q < RM; ++q) {
+      xf[0][q] = *reinterpret_cast<const u32x4*>(xr[q] + kc);
+      if (!ok) xf[0][q] = u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bfr[0][t] = *reinterpret_cast<const u32x4*>(br[t] + kc);
+    mma(0);
   }
   __shared__ float4 red[NW][NT][64];
+  bool over = false;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) red[wave][t][lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-  __syncthreads();
-  if (wave == 0) {
-    bool over = false;
+  for (int q = 0; q < RM; ++q) {
+    if (q) __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      float4 sm = red[0][t][lane];
+    for (int t = 0; t < NT; ++t) red[wave][t][lane] = make_float4(acc[q][t][0], acc[q][t][1], acc[q][t][2], acc[q][t][3]);
+    __syncthreads();
+    if (wave < NT) {  // one column tile per wave
+      float4 sm = red[0][wave][lane];
 #pragma unroll
       for (int w = 1; w < NW; ++w) {
-        const float4 o = red[w][t][lane];
+        const float4 o = red[w][wave][lane];
         sm.x += o.x; sm.y += o.y; sm.z += o.z; sm.w += o.w;
       }
       // lane holds D[m = 4g + e][n = i16]
-      const int n = t * 16 + i16;
+      const int n = wave * 16 + i16;
       const float v[4] = {sm.x, sm.y, sm.z, sm.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = m0 + 4 * g + e;
+        const int m = m0 + q * 16 + 4 * g + e;
         if (m < M && n < N) C[(long long)m * ldc + n] = F2EG(v[e] * alpha, over);
       }
     }
-    elem_flag(over, flag);
   }
+  elem_flag(over, flag);
 }
 
 // ---------------------------------------------------------------- adapter gradients: G[j, r] += sum_t X[t, j] U[t, r]
@@ -410,17 +431,47 @@ __global__ void __launch_bounds__(256) k_lora_grad_reduce(const float* part, int
   *g += sum * (out_mul ? *out_mul : 1.f);
 }
 
-__global__ void __launch_bounds__(256) k_lora_grad_reduce_multi(LoraGradJobs jobs, const float* part_all, int R, const float* out_mul) {
+// The same for several jobs.  A workgroup adds up 32 columns j x R ranks; where j is not the contiguous index of G (dA: [in, r])
+// the sums turn in LDS, so that both the partial sums and G are read and written in whole rows (lanes along j at a stride of R
+// floats were 64 separate accesses a wave: six sums of 64 x 5120 took 45 us).
+template <int R>
+__global__ void __launch_bounds__(256) k_lora_grad_reduce_multi(LoraGradJobs jobs, const float* part_all, const float* out_mul) {
+  constexpr int JW = 32, RS = 256 / JW, N = R / RS;  // columns of a workgroup, ranks side by side, sums per thread
   const LoraGradJob& jb = jobs.j[blockIdx.y];
-  const long long RJ = (long long)R * jb.J;
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= RJ) return;
-  const int r = (int)(i / jb.J), j = (int)(i - (long long)r * jb.J);
+  const int J = jb.J, j0 = blockIdx.x * JW, tid = threadIdx.x;
+  if (j0 >= J) return;
+  const long long RJ = (long long)R * J;
   const float* part = part_all + jb.part_off;
-  float sum = 0.f;
-  for (int c = 0; c < jb.nch; ++c) sum += part[c * RJ + i];
-  float* g = jb.G + (long long)j * jb.sj + (long long)r * jb.sr;
-  *g += sum * (out_mul ? *out_mul : 1.f);
+  const float mul = out_mul ? *out_mul : 1.f;
+  float sum[N];
+  const int jl = tid % JW, r0 = tid / JW, j = min(j0 + jl, J - 1);
+#pragma unroll
+  for (int n = 0; n < N; ++n) sum[n] = 0.f;
+#pragma unroll 2
+  for (int c = 0; c < jb.nch; ++c)
+#pragma unroll
+    for (int n = 0; n < N; ++n) sum[n] += part[c * RJ + (long long)(n * RS + r0) * J + j];
+  if (jb.sj == 1) {
+    if (j0 + jl < J)
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        float* g = jb.G + (long long)(n * RS + r0) * jb.sr + j;
+        *g += sum[n] * mul;
+      }
+    return;
+  }
+  __shared__ float turn[JW][R + 1];
+#pragma unroll
+  for (int n = 0; n < N; ++n) turn[jl][n * RS + r0] = sum[n];
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const int i = n * 256 + tid, jj = i / R, r = i % R;
+    if (j0 + jj < J) {
+      float* g = jb.G + (long long)(j0 + jj) * jb.sj + (long long)r * jb.sr;
+      *g += turn[jj][r] * mul;
+    }
+  }
 }
 
 __global__ void __launch_bounds__(256) k_sum_groups(const bf* in, bf* out, long long total, int n_kv, int G, int d, int* flag) {
@@ -460,11 +511,31 @@ void ft_skinny_nt_multi(const SkinnyNtJobs& jobs, int M, float alpha, int* flag,
   if (jobs.n < 1) return;
   int nmax = 0;
   for (int i = 0; i < jobs.n; ++i) nmax = std::max(nmax, jobs.j[i].N);
-  const int nt = (nmax + 15) / 16;  // jobs with fewer columns mask their stores
-  const dim3 grid((M + 15) / 16, jobs.n), blk(512);
-  if (nt == 1) hipLaunchKernelGGL(k_skinny_nt<1>, grid, blk, 0, st, jobs, M, alpha, flag);
-  else if (nt == 2) hipLaunchKernelGGL(k_skinny_nt<2>, grid, blk, 0, st, jobs, M, alpha, flag);
-  else hipLaunchKernelGGL(k_skinny_nt<4>, grid, blk, 0, st, jobs, M, alpha, flag);
+  const int nt = nmax <= 16 ? 1 : nmax <= 32 ? 2 : 4;  // jobs with fewer columns mask their stores
+  // Rows per workgroup: the fewest bytes through the fullest compute unit, 16 (RM + NT) K 2 per workgroup of it.  Measured,
+  // 4096 rows, 64 columns, us with 16 rows and as chosen: three jobs over K = 5120 74 / 43 (64 rows), two 51 / 33 (32 rows), two
+  // over 13824 128 / 85 (32 rows); 2048 rows, 16 columns, three jobs over 4096 17.7 / 14.7 (32 rows).
+  static const int n_cu = [] {
+    int dev = 0, n = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+  }();
+  int rm = 1;
+  long long least = 0;
+  for (int q = 1; q <= 4; q *= 2) {
+    const long long wgs = (long long)((M + 16 * q - 1) / (16 * q)) * jobs.n, cost = (wgs + n_cu - 1) / n_cu * (q + nt);
+    if (q == 1 || cost < least) rm = q, least = cost;
+  }
+  const dim3 grid((M + 16 * rm - 1) / (16 * rm), jobs.n), blk(512);
+#define SKINNY(NT_)                                                                                          \
+  do {                                                                                                       \
+    if (rm == 1) hipLaunchKernelGGL((k_skinny_nt<NT_, 1>), grid, blk, 0, st, jobs, M, alpha, flag);          \
+    else if (rm == 2) hipLaunchKernelGGL((k_skinny_nt<NT_, 2>), grid, blk, 0, st, jobs, M, alpha, flag);     \
+    else hipLaunchKernelGGL((k_skinny_nt<NT_, 4>), grid, blk, 0, st, jobs, M, alpha, flag);                  \
+  } while (0)
+  if (nt == 1) SKINNY(1);
+  else if (nt == 2) SKINNY(2);
+  else SKINNY(4);
+#undef SKINNY
 }
 // floats of partial sums one job of the MFMA path can need: nch * J with nch <= max(1, 512 / column tiles)
 static size_t lora_grad_job_floats(int J, int R) { return (size_t)std::max(512 * kLmJ, (J + kLmJ - 1) / kLmJ * kLmJ) * R; }
@@ -498,14 +569,17 @@ void ft_lora_grad_multi(LoraGradJobs& jobs, int T, int R, const float* out_mul, 
     for (int i = 0; i < jobs.n; ++i) lora_grad_vector(jobs.j[i], T, R, out_mul, part, st);
     return;
   }
-  // about two workgroups per compute unit per job and whole groups of steps in flight
-  int max_jt = 0, max_nch = 0, max_j = 0;
+  // About three workgroups per compute unit in all jobs together and whole groups of steps in flight: every chunk of tokens
+  // costs a partial sum of R x J floats, written and read (two workgroups per compute unit for each of six jobs of 64 x 5120 x
+  // 4096 wrote 126 MB beside 252 MB of operands and took 74 us, now 55).
+  int max_jt = 0, max_nch = 0, max_j = 0, sum_jt = 0;
+  for (int i = 0; i < jobs.n; ++i) sum_jt += (jobs.j[i].J + kLmJ - 1) / kLmJ;
   long long off = 0;
   const int unit = kLmT * kLmPF;
   for (int i = 0; i < jobs.n; ++i) {
     LoraGradJob& b = jobs.j[i];
     b.jt = (b.J + kLmJ - 1) / kLmJ;
-    const int want = std::min(kLgMaxChunks, std::max(1, 512 / b.jt));
+    const int want = std::min({kLgMaxChunks, std::max(1, 512 / b.jt), std::max(1, 768 / sum_jt)});
     b.tpm = std::max(unit, ((T + want - 1) / want + unit - 1) / unit * unit);
     b.nch = (T + b.tpm - 1) / b.tpm;
     b.part_off = off;
@@ -519,7 +593,11 @@ void ft_lora_grad_multi(LoraGradJobs& jobs, int T, int R, const float* out_mul, 
   else if (R == 16) hipLaunchKernelGGL(k_lora_grad_mfma<16>, grid, dim3(256), 0, st, jobs, part, T);
   else if (R == 32) hipLaunchKernelGGL(k_lora_grad_mfma<32>, grid, dim3(256), 0, st, jobs, part, T);
   else hipLaunchKernelGGL(k_lora_grad_mfma<64>, grid, dim3(256), 0, st, jobs, part, T);
-  hipLaunchKernelGGL(k_lora_grad_reduce_multi, dim3(nblk((long long)R * max_j, 256), jobs.n), dim3(256), 0, st, jobs, part, R, out_mul);
+  const dim3 rgrid((max_j + 31) / 32, jobs.n);
+  if (R == 8) hipLaunchKernelGGL(k_lora_grad_reduce_multi<8>, rgrid, dim3(256), 0, st, jobs, part, out_mul);
+  else if (R == 16) hipLaunchKernelGGL(k_lora_grad_reduce_multi<16>, rgrid, dim3(256), 0, st, jobs, part, out_mul);
+  else if (R == 32) hipLaunchKernelGGL(k_lora_grad_reduce_multi<32>, rgrid, dim3(256), 0, st, jobs, part, out_mul);
+  else hipLaunchKernelGGL(k_lora_grad_reduce_multi<64>, rgrid, dim3(256), 0, st, jobs, part, out_mul);
 }
 void ft_lora_grad(const bf* X, long long ldx, const bf* U, long long ldu, float* G, long long sj, long long sr, int T, int J,
                   int R, const float* out_mul, float* part, hipStream_t st) {

@@ -69,6 +69,15 @@ def test_gqa_and_head_sizes(n_q, n_kv, d):
                 hidden=n_q * d // 2, n_q=n_q, n_kv=n_kv, head_dim=d, ffn=320))
 
 
+@pytest.mark.parametrize("micro,seq,rank,targets", [
+    (5, 824, 64, ("q", "k", "v", "o", "gate", "up", "down")), (11, 200, 16, ("q", "k", "v", "o")), (6, 344, 32, ("q", "v", "gate", "up")),
+    (13, 328, 8, ("q", "k", "v"))])
+def test_adapter_products_of_many_rows(micro, seq, rank, targets):
+    """Adapter products with 16, 32 and 64 rows of a workgroup (rows that fill none of them), every rank, and gradients of one
+    to six products in a launch over fewer chunks of tokens."""
+    check(build(0, lora=wl.LoraCfg(rank, 2.0 * rank, targets), ft=wl.FinetuneCfg(micro, seq), ffn=264))
+
+
 def test_long_sequence_crosses_several_tiles():
     check(build(0, ft=wl.FinetuneCfg(1, 600), lora=wl.LoraCfg(32, 64.0, ("q", "o", "down"))))
 
