@@ -95,6 +95,9 @@ harli_status dg_launch(DgKind kind, const SkinnyArgs& a, int x_tiles, float* par
 harli_status dg_gemm(DgKind kind, const SkinnyArgs& a, int x_tiles, float* part, size_t part_bytes, int n_cu, hipStream_t st, DgPlan* used);
 harli_status dg_epilogue(DgKind kind, const SkinnyArgs& a, const DgPlan& p, const float* part, hipStream_t st);
 void dg_force_ksplit(int ksplit);
+// The output layer of a plan with one range of K: the GEMM writes the logits itself, and, where next_token is given, finds
+// their argmax on the way.  ws holds the rows' norm factors and the maxima of slices of columns.
+harli_status dg_lm_direct(const SkinnyArgs& a, int x_tiles, const DgPlan& p, float* ws, size_t ws_bytes, int* next_token, hipStream_t st);
 // smallest batch that takes the tiled path (measurement hook; 0 gives the default back)
 void dg_set_min_batch(int b);
 int dg_min_batch();

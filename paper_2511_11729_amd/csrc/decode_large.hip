@@ -31,6 +31,12 @@ struct DgemmArgs {
   int tiles_n1, tiles_n;           // 256-row tiles of one matrix, of all matrices
   int tiles_m, ksplit, Mpad;
   float* part;                     // [ksplit][Mpad][tiles_n * 256]
+  // LM: logits straight from the accumulators (one range of K)
+  const float* rho;                // norm factor of every row
+  int B, n_rows;
+  float* logits;                   // [B][n_rows]
+  float* amax_v;                   // first maximum of every 64 columns, [B][4 tiles_n], or null
+  int* amax_i;
 };
 
 #define DG_WAITV(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
@@ -44,7 +50,10 @@ constexpr int dg_stages() { return FM <= 2 ? 6 : FM == 3 ? 5 : 4; }
 
 // ONCE: one tile of batch rows, so that the weights are read once: nontemporal loads (8B-class step at 256 sequences 2221 ->
 // 2156 us); with several, the tiles of a column share them through L2, and those of a small model stay in the caches.
-template <int FM, bool ONCE>
+// LM: the output layer where its tiles fill the chip without ranges of K: logits and the argmax of each lane's columns leave from
+// the staged slab (256 sequences of 128256 classes over 4096, with the argmax: partial tiles, their sum and a pass over the
+// logits took 339 us, this 264).
+template <int FM, bool ONCE, bool LM>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_dgemm(DgemmArgs a) {
   constexpr int BM = 64 * FM, ASZ = BM * BK * 2, STG = ASZ + BSZ, NS = dg_stages<FM>();
   constexpr int LOADS = FM + 4;  // direct-to-LDS loads a wave issues per stage
@@ -211,8 +220,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
   char* ebuf = smem + wave * (32 * ER);
   const int col_l = lane & 31, rgrp = (lane >> 5) * 4;
   const size_t ncols = (size_t)a.tiles_n * BN;
-  float* prow = a.part + ((size_t)split * a.Mpad + (size_t)tm * BM + wm * (FM * 32)) * ncols + (size_t)tn * BN + wn * 128;
+  const int row0 = tm * BM + wm * (FM * 32), col0 = tn * BN + wn * 128;
+  float* prow = LM ? nullptr : a.part + ((size_t)split * a.Mpad + row0) * ncols + col0;
   const int c4 = (lane & 31) * 4;
+  const bool vec = (a.n_rows & 3) == 0;  // rows of the logits are 16-byte aligned
+  static_assert(4 * 32 * ER + 64 * FM * 4 <= NS * STG, "the row factors lie behind the staged slabs");
+  float* rs = reinterpret_cast<float*>(smem + 4 * 32 * ER);
+  if (LM) {
+    if (tid < BM) rs[tid] = a.rho[min(tm * BM + tid, a.B - 1)];
+    __syncthreads();
+  }
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
 #pragma unroll
@@ -224,10 +241,75 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
     for (int it = 0; it < 16; ++it) {
       const int row = it * 2 + (lane >> 5);
-      const float4 o = *reinterpret_cast<const float4*>(ebuf + row * ER + c4 * 4);
-      *reinterpret_cast<float4*>(prow + (size_t)(i * 32 + row) * ncols + c4) = o;
+      float4 o = *reinterpret_cast<const float4*>(ebuf + row * ER + c4 * 4);
+      if constexpr (LM) {
+        const int b = row0 + i * 32 + row, n = col0 + c4;
+        if (b >= a.B || n >= a.n_rows) continue;
+        const float rho = rs[wm * (FM * 32) + i * 32 + row];
+        o.x *= rho, o.y *= rho, o.z *= rho, o.w *= rho;
+        float* q = a.logits + (size_t)b * a.n_rows + n;
+        if (vec) {
+          *reinterpret_cast<float4*>(q) = o;
+        } else {
+          const float v[4] = {o.x, o.y, o.z, o.w};
+          for (int e = 0; e < 4 && n + e < a.n_rows; ++e) q[e] = v[e];
+        }
+      } else {
+        *reinterpret_cast<float4*>(prow + (size_t)(i * 32 + row) * ncols + c4) = o;
+      }
+    }
+    if constexpr (LM) {
+      // a lane looks for the maximum of 64 columns of one row, in ascending order: the first one is kept
+      const int b = row0 + i * 32 + (lane & 31), n0 = col0 + (lane >> 5) * 64;
+      if (a.amax_v && b < a.B) {
+        const float rho = rs[wm * (FM * 32) + i * 32 + (lane & 31)];
+        float best = -INFINITY;
+        int bi = 0x7fffffff;
+        for (int c = 0; c < 16; ++c) {
+          const float4 o = *reinterpret_cast<const float4*>(ebuf + (lane & 31) * ER + ((lane >> 5) * 64 + c * 4) * 4);
+          const float v[4] = {o.x * rho, o.y * rho, o.z * rho, o.w * rho};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+          {
+            const bool take = v[e] > best && n0 + c * 4 + e < a.n_rows;
+            best = take ? v[e] : best;
+            bi = take ? n0 + c * 4 + e : bi;
+          }
+        }
+        const size_t at = (size_t)b * (4 * a.tiles_n) + tn * 4 + wn * 2 + (lane >> 5);
+        a.amax_v[at] = best;
+        a.amax_i[at] = bi;
+      }
     }
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Norm factor of every row of the batch.
+__global__ void __launch_bounds__(64) k_dg_rho(const float* ssq, int np, float inv_dim, float eps, float* rho) {
+  const float s = ssq_row_sum(ssq + (size_t)blockIdx.x * np, np, threadIdx.x >> 4);
+  if (threadIdx.x == 0) rho[blockIdx.x] = rsqrtf(s * inv_dim + eps);
+}
+
+// The first maximum of a row from those of its n slices of columns.
+__global__ void __launch_bounds__(256) k_dg_argmax(const float* v, const int* idx, int n, int* next_token) {
+  __shared__ float sv[4];
+  __shared__ int si[4];
+  const int tid = threadIdx.x;
+  v += (size_t)blockIdx.x * n;
+  idx += (size_t)blockIdx.x * n;
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+  auto take = [&](float ov, int oi) {
+    if (ov > best || (ov == best && oi < bi)) best = ov, bi = oi;
+  };
+  for (int i = tid; i < n; i += 256) take(v[i], idx[i]);
+  for (int o = 1; o < 64; o <<= 1) take(__shfl_xor(best, o, 64), __shfl_xor(bi, o, 64));
+  if ((tid & 63) == 0) sv[tid >> 6] = best, si[tid >> 6] = bi;
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w) take(sv[w], si[w]);
+    next_token[blockIdx.x] = bi;
   }
 }
 
@@ -451,37 +533,36 @@ harli_status dg_init() {
     auto allow = [&](const void* kernel, int bytes) {
       if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     };
-    allow(reinterpret_cast<const void*>(&k_dgemm<1, true>), dg_lds_bytes<1>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<2, true>), dg_lds_bytes<2>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<3, true>), dg_lds_bytes<3>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<4, true>), dg_lds_bytes<4>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<1, false>), dg_lds_bytes<1>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<2, false>), dg_lds_bytes<2>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<3, false>), dg_lds_bytes<3>());
-    allow(reinterpret_cast<const void*>(&k_dgemm<4, false>), dg_lds_bytes<4>());
+#define DG_ALLOW(F_)                                                                          \
+  allow(reinterpret_cast<const void*>(&k_dgemm<F_, true, false>), dg_lds_bytes<F_>());        \
+  allow(reinterpret_cast<const void*>(&k_dgemm<F_, false, false>), dg_lds_bytes<F_>());       \
+  allow(reinterpret_cast<const void*>(&k_dgemm<F_, true, true>), dg_lds_bytes<F_>());         \
+  allow(reinterpret_cast<const void*>(&k_dgemm<F_, false, true>), dg_lds_bytes<F_>())
+    DG_ALLOW(1);
+    DG_ALLOW(2);
+    DG_ALLOW(3);
+    DG_ALLOW(4);
+#undef DG_ALLOW
     g_attr_err = e;
   });
   HARLI_HIP(g_attr_err);
   return HARLI_OK;
 }
 
-harli_status dg_gemm(DgKind kind, const SkinnyArgs& a, int x_tiles, float* part, size_t part_bytes, int n_cu, hipStream_t st, DgPlan* used) {
-  {
-    harli_status rc = dg_init();
-    if (rc != HARLI_OK) return rc;
-  }
+namespace {
+
+// Checks a launch and fills in its arguments but for the destinations.
+harli_status dg_args(DgKind kind, const SkinnyArgs& a, int x_tiles, const DgPlan& p, DgemmArgs* out) {
   const int n_mat = kind == DG_GATEUP ? 2 : 1;
   const int n_rows = kind == DG_QKV ? (a.n_q + 2 * a.n_kv) * a.d : a.n_rows;
   const int steps = (a.K + BK - 1) / BK, w_tiles16 = (n_rows + 15) / 16;
-  if (!part || a.B < 1 || x_tiles * 16 < a.B || (kind == DG_GATEUP && !a.w1))
+  if (a.B < 1 || x_tiles * 16 < a.B || (kind == DG_GATEUP && !a.w1))
     return fail(HARLI_ERR_INVALID, "decode (large batch): bad arguments (batch %d, %d operand tiles)", a.B, x_tiles);
   if ((kind != DG_LM && (a.n_rows & 7)) || (kind == DG_QKV && (a.d & 31)))
     return fail(HARLI_ERR_INVALID, "decode (large batch): %d output rows, head size %d", a.n_rows, a.d);
   // the kernel addresses both operands with 32-bit byte offsets below 2^31
   if ((long long)(w_tiles16 + 16) * steps * 1024 >= (1ll << 31) || (long long)x_tiles * steps * 1024 >= (1ll << 31))
     return fail(HARLI_ERR_INVALID, "decode (large batch): an operand of 2 GiB or more (%d rows, K %d)", n_rows, a.K);
-  const DgPlan p = dg_plan(a.B, n_rows, n_mat, a.K, n_cu, part_bytes);
-  if (p.ksplit < 1) return fail(HARLI_ERR_INVALID, "decode (large batch): a workspace of %zu bytes cannot hold one partial matrix", part_bytes);
   DgemmArgs g{};
   g.x = a.x;
   g.x_tiles = x_tiles;
@@ -494,21 +575,68 @@ harli_status dg_gemm(DgKind kind, const SkinnyArgs& a, int x_tiles, float* part,
   g.tiles_m = p.tiles_m;
   g.ksplit = p.ksplit;
   g.Mpad = p.Mpad;
-  g.part = part;
-  const dim3 grid((unsigned)(p.tiles_n * p.tiles_m * p.ksplit));
-  const bool once = p.tiles_m == 1 && !a.cached;
-#define DG_LAUNCH(F_)                                                                             \
-  do {                                                                                            \
-    if (once) hipLaunchKernelGGL((k_dgemm<F_, true>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g); \
-    else hipLaunchKernelGGL((k_dgemm<F_, false>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g);     \
+  g.B = a.B;
+  g.n_rows = a.n_rows;
+  *out = g;
+  return HARLI_OK;
+}
+
+template <bool LM>
+harli_status dg_kernel(int FM, bool once, const DgemmArgs& g, hipStream_t st) {
+  const dim3 grid((unsigned)(g.tiles_n * g.tiles_m * g.ksplit));
+#define DG_LAUNCH(F_)                                                                                 \
+  do {                                                                                                \
+    if (once) hipLaunchKernelGGL((k_dgemm<F_, true, LM>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g); \
+    else hipLaunchKernelGGL((k_dgemm<F_, false, LM>), grid, dim3(NT), dg_lds_bytes<F_>(), st, g);     \
   } while (0)
-  if (p.FM == 1) DG_LAUNCH(1);
-  else if (p.FM == 2) DG_LAUNCH(2);
-  else if (p.FM == 3) DG_LAUNCH(3);
+  if (FM == 1) DG_LAUNCH(1);
+  else if (FM == 2) DG_LAUNCH(2);
+  else if (FM == 3) DG_LAUNCH(3);
   else DG_LAUNCH(4);
 #undef DG_LAUNCH
   HARLI_HIP(hipGetLastError());
+  return HARLI_OK;
+}
+
+}  // namespace
+
+harli_status dg_gemm(DgKind kind, const SkinnyArgs& a, int x_tiles, float* part, size_t part_bytes, int n_cu, hipStream_t st, DgPlan* used) {
+  harli_status rc = dg_init();
+  if (rc != HARLI_OK) return rc;
+  const int n_rows = kind == DG_QKV ? (a.n_q + 2 * a.n_kv) * a.d : a.n_rows;
+  if (!part || a.B < 1) return fail(HARLI_ERR_INVALID, "decode (large batch): no workspace or no sequences (batch %d)", a.B);
+  const DgPlan p = dg_plan(a.B, n_rows, kind == DG_GATEUP ? 2 : 1, a.K, n_cu, part_bytes);
+  DgemmArgs g;
+  rc = dg_args(kind, a, x_tiles, p, &g);
+  if (rc != HARLI_OK) return rc;
+  if (p.ksplit < 1) return fail(HARLI_ERR_INVALID, "decode (large batch): a workspace of %zu bytes cannot hold one partial matrix", part_bytes);
+  g.part = part;
+  rc = dg_kernel<false>(p.FM, p.tiles_m == 1 && !a.cached, g, st);
   *used = p;
+  return rc;
+}
+
+harli_status dg_lm_direct(const SkinnyArgs& a, int x_tiles, const DgPlan& p, float* ws, size_t ws_bytes, int* next_token, hipStream_t st) {
+  harli_status rc = dg_init();
+  if (rc != HARLI_OK) return rc;
+  DgemmArgs g;
+  if (!ws || a.B < 1 || p.ksplit != 1) return fail(HARLI_ERR_INVALID, "decode (large batch): no workspace, or no plan in one range (batch %d)", a.B);
+  rc = dg_args(DG_LM, a, x_tiles, p, &g);
+  if (rc != HARLI_OK) return rc;
+  // the workspace: norm factors, then the maxima of every slice of columns
+  const size_t n_slices = (size_t)4 * p.tiles_n, rows = (size_t)(a.B + 63) / 64 * 64, need = (rows + 2 * n_slices * a.B) * 4;
+  if (need > ws_bytes) return fail(HARLI_ERR_INVALID, "decode (large batch): a workspace of %zu bytes, the output layer needs %zu", ws_bytes, need);
+  g.rho = ws;
+  g.logits = a.logits;
+  if (next_token) {
+    g.amax_v = ws + rows;
+    g.amax_i = reinterpret_cast<int*>(g.amax_v + n_slices * a.B);
+  }
+  hipLaunchKernelGGL(k_dg_rho, dim3(a.B), dim3(64), 0, st, a.ssq_in, a.ssq_np, a.inv_dim, a.eps, ws);
+  rc = dg_kernel<true>(p.FM, p.tiles_m == 1 && !a.cached, g, st);
+  if (rc != HARLI_OK) return rc;
+  if (next_token) hipLaunchKernelGGL(k_dg_argmax, dim3(a.B), dim3(256), 0, st, g.amax_v, g.amax_i, (int)n_slices, next_token);
+  HARLI_HIP(hipGetLastError());
   return HARLI_OK;
 }
 

@@ -286,6 +286,24 @@ def test_config2_width_batch256():
     run_case(w, m, [100 + (i * 37) % 400 for i in range(256)])
 
 
+@pytest.mark.parametrize("batch,vocab", [(34, 1003), (70, 1000), (130, 260), (200, 64), (256, 515)])
+def test_output_layer_straight_from_the_tiles(batch, vocab):
+    """Above 32 sequences, an output layer in one range of K: logits and argmax from the GEMM, every tile height, ragged last
+    tiles and rows that are not 16-byte aligned.  Two equal rows of the output matrix give equal logits: the first maximum
+    of every row is chosen."""
+    def twins(case):
+        wlm = case.extras_np["wlm"]
+        wlm[vocab // 2 + 7:] = wlm[: vocab - vocab // 2 - 7]
+    w, m = variant(0, dtype="bf16", n_layers=1, vocab=vocab)
+    case = DecodeCase(w, m, np.asarray([3 + (i * 7) % 40 for i in range(batch)], np.int32), full_model=True, block_bytes=64 << 10, tweak=twins)
+    tok = wl.make_token_ids(dataclasses.replace(w, model=m), (batch,))
+    case.run_gpu(token_ids=tok)
+    _, ref_logits, _ = case.run_oracle(token_ids=tok)
+    logits = case.logits_dev.cpu().numpy()
+    assert_close(logits, ref_logits, "logits")
+    assert (case.next_dev.cpu().numpy() == logits.argmax(1)).all()
+
+
 @pytest.mark.parametrize("batch", [70, 150, 200])
 def test_config4_width_batches_that_split_into_uneven_passes(batch):
     """Batches above 64 rows on the GQA layer: tiles of 128, 192 and 256 batch rows (70: 58 idle rows; 150: 42; 200: 56),
