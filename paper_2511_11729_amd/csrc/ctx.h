@@ -39,6 +39,7 @@ struct DecodeWs {
   float* rope = nullptr;      // [bpad][d/2][2]
   double* inv_freq = nullptr; // [d/2] base^(-2i/d)
   float* att_part = nullptr;  // [bpad][n_q][max_chunks][d+2]
+  int* att_list = nullptr;    // chunks the attention reads: their number, then (from entry 16) sequence << 16 | chunk; or null
   float* amax_v = nullptr;    // [bpad][64] per-slice maxima of the logits (full-model mode)
   int* amax_i = nullptr;      // [bpad][64] and their indices
   int* err_flag = nullptr;    // device int set when a kernel sees an out-of-range page id

@@ -367,6 +367,19 @@ __global__ void __launch_bounds__(256) k_pack_weight(const unsigned short* src, 
   *reinterpret_cast<uint4*>(dst + f * 8) = v;
 }
 
+// Chunks of cached tokens the step's attention has to read, sequence by sequence: item[k] = sequence << 16 | chunk, and their
+// number.  A grid over the longest sequence for all of them is mostly empty at uneven lengths (256 sequences of mean 950, longest
+// 4125: 16 256 of 67 584 workgroups hold tokens), and an empty workgroup occupies its slots for a dependent load.  With the list the
+// empty ones are the last ones and leave on a word that every one of them reads: 222 -> 211 us a layer for those, 32 sequences of
+// one query head per KV head and mean 1200 (four layers) 1124 -> 1088 us.
+struct AttnList {
+  int* item;    // null: no list, the grid covers every chunk of every sequence
+  int* total;
+  int chunk;    // tokens per chunk
+  int n_chunks; // most chunks of a sequence
+};
+
+
 // ---------------------------------------------------------------------------------------------
 // Step preparation: operand and sum of squares of the first layer, rotary table, cleared
 // accumulators.  One workgroup per sequence; loads are issued in groups of four 16-byte words
@@ -375,7 +388,7 @@ __global__ void __launch_bounds__(256) k_pack_weight(const unsigned short* src, 
 __global__ void __launch_bounds__(256) k_decode_prep(int H, int d, int n_ssq, int bpad, int ssq_np, const int* token_ids,
                                                      const unsigned short* emb, int vocab, const float* x_in, float* xa,
                                                      const float* g1, unsigned short* hx1, float* ssq, float* rope,
-                                                     const int* kv_len, const double* inv_freq, int* err_flag) {
+                                                     const int* kv_len, const double* inv_freq, int* err_flag, AttnList list) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const int steps = (H + 31) >> 5;
   float s2 = 0.f;
@@ -417,6 +430,18 @@ __global__ void __launch_bounds__(256) k_decode_prep(int H, int d, int n_ssq, in
     ssq[((size_t)slot * bpad + b) * ssq_np + e] = 0.f;
   }
   const int half = d >> 1;
+  if (list.item) {
+    // where this sequence's chunks begin: the chunks of the sequences before it (blockIdx.x < 256)
+    __shared__ int before[4];
+    auto chunks = [&](int i) { return max(0, min((kv_len[i] + list.chunk) / list.chunk, list.n_chunks)); };
+    int n = tid < b ? chunks(tid) : 0;
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+    if ((tid & 63) == 0) before[tid >> 6] = n;
+    __syncthreads();
+    const int first = (before[0] + before[1]) + (before[2] + before[3]), mine = chunks(b);
+    for (int i = tid; i < mine; i += 256) list.item[first + i] = b << 16 | i;
+    if (b == (int)gridDim.x - 1 && tid == 0) *list.total = first + mine;
+  }
   const double pos = (double)kv_len[b];
   for (int i = tid; i < half; i += 256) {
     // angle = pos * base^(-2i/d) in double, reduced to [-pi, pi] before the fp32 sin/cos
@@ -463,19 +488,35 @@ __device__ __forceinline__ float token_lanes_sum(float s) {
 template <int D, int G>
 constexpr int attn_min_waves() { return (D == 128 && G == 4) ? 4 : 1; }
 
-template <int D, int G, int CH, bool CACHED>
+// Which chunk of which sequence and KV head a workgroup of the attention reads (uniform); false: none.
+template <bool LIST>
+__device__ __forceinline__ bool attn_place(const AttnList& list, int n_kv, int& b, int& c, int& ch) {
+  if (!LIST) {
+    b = blockIdx.z, c = blockIdx.y, ch = blockIdx.x;
+    return true;
+  }
+  const int at = blockIdx.x / n_kv;
+  c = blockIdx.x - at * n_kv;
+  if (at >= *list.total) return false;
+  const int item = list.item[at];
+  b = item >> 16, ch = item & 0xffff;
+  return true;
+}
+
+template <int D, int G, int CH, bool CACHED, bool LIST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, G>(), 8))) k_paged_attn(const float* qbuf, const int* kv_len, const int* page_table,
                                                     int max_pages, int layer, int n_q, int n_kv, const char* slab,
                                                     KvGeom geom, float* part, int max_chunks, unsigned short* obuf,
-                                                    int* err_flag) {
+                                                    int* err_flag, AttnList list) {
   constexpr int LPT = D / 8;         // lanes per token
   constexpr int TPI = 64 / LPT;      // tokens per load instruction
   constexpr int IT = kPageTokens / TPI;
   constexpr int PW = CH / kPageTokens / 4;  // pages per wave
-  const int b = blockIdx.z, c = blockIdx.y, ch = blockIdx.x;
+  int b, c, ch;
+  if (!attn_place<LIST>(list, n_kv, b, c, ch)) return;
   const int n_tot = kv_len[b] + 1;
   // the grid covers the caller's bound max_kv_len: a longer sequence would lose its newest tokens without a word
-  if (ch == 0 && c == 0 && threadIdx.x == 0 && (n_tot > (int)gridDim.x * CH || n_tot > max_pages * kPageTokens))
+  if (ch == 0 && c == 0 && threadIdx.x == 0 && (n_tot > list.n_chunks * CH || n_tot > max_pages * kPageTokens))
     atomicOr(err_flag, 4);
   if (ch * CH >= n_tot) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -613,7 +654,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(attn_m
       o += s_o[w][gq][e] * f;
     }
     const int head = c * G + gq;
-    if (gridDim.x == 1) {
+    if (list.n_chunks == 1) {
       obuf[xfrag_off(b, head * D + e, steps_o)] = f2bf(o / L);
     } else {
       float* p = part + (((size_t)b * n_q + head) * max_chunks + ch) * (D + 2);
@@ -663,18 +704,19 @@ __device__ __forceinline__ bf16x8 transposed_8(char* p0, char* p1) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <int G, int CH>
+template <int G, int CH, bool LIST>
 __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const int* kv_len, const int* page_table, int max_pages,
                                                        int layer, int n_q, int n_kv, const char* slab, KvGeom geom, float* part,
-                                                       int max_chunks, unsigned short* obuf, int* err_flag) {
+                                                       int max_chunks, unsigned short* obuf, int* err_flag, AttnList list) {
   constexpr int D = 128, PW = CH / kPageTokens / 4, QG = 8, NT = 2;  // queries per term, products per step
   static_assert(G <= QG && PW % 2 == 0 && G * D * 4 <= PW * 4096, "whole steps of 32 tokens; a wave's output fits its share of V");
   __shared__ __align__(1024) char s_v[4 * PW * 4096];
   __shared__ float s_m[4][G], s_l[4][G];
-  const int b = blockIdx.z, c = blockIdx.y, ch = blockIdx.x;
+  int b, c, ch;
+  if (!attn_place<LIST>(list, n_kv, b, c, ch)) return;
   const int n_tot = kv_len[b] + 1;
   // the grid covers the caller's bound max_kv_len: a longer sequence would lose its newest tokens without a word
-  if (ch == 0 && c == 0 && threadIdx.x == 0 && (n_tot > (int)gridDim.x * CH || n_tot > max_pages * kPageTokens))
+  if (ch == 0 && c == 0 && threadIdx.x == 0 && (n_tot > list.n_chunks * CH || n_tot > max_pages * kPageTokens))
     atomicOr(err_flag, 4);
   if (ch * CH >= n_tot) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -821,7 +863,7 @@ __global__ void __launch_bounds__(256) k_paged_attn_mm(const float* qbuf, const 
       acc += reinterpret_cast<const float*>(s_v + w * (PW * 4096))[idx] * f;
     }
     const int head = c * G + gq;
-    if (gridDim.x == 1) {
+    if (list.n_chunks == 1) {
       obuf[xfrag_off(b, head * D + e, steps_o)] = f2bf(acc / L);
     } else {
       float* p = part + (((size_t)b * n_q + head) * max_chunks + ch) * (D + 2);
@@ -1022,17 +1064,29 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
   }
 }
 
+// tokens per attention chunk, as decode_step_bf16 launches them
+constexpr int attn_chunk(int d, int G) { return d == 64 || G <= 2 ? 256 : 128; }
+// Workgroups of the attention grid from which it follows a list: a few rounds over the chip (a step of few sequences gains
+// nothing from it and pays a dependent load in every layer).
+constexpr int kListedWorkgroups = 4096;
+
 template <int D, int G, int CH>
-void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, int layer, bool cached, hipStream_t st) {
+void launch_attn(harli_ctx* c, const DecodeWs& w, const harli_decode_batch* b, int layer, bool cached, AttnList list, hipStream_t st) {
   const harli_model_cfg& m = c->cfg;
-  const int n_chunks = (b->max_kv_len + CH - 1) / CH;
+  static_assert(CH == attn_chunk(D, G), "the list counts these chunks");
+  const int n_chunks = list.n_chunks;
 #define ATTN_LAUNCH(kernel)                                                                                             \
-  hipLaunchKernelGGL(kernel, dim3(n_chunks, m.n_kv_heads, b->batch), dim3(256), 0, st, w.qbuf, b->kv_len, b->page_table, \
+  hipLaunchKernelGGL(kernel, list.item ? dim3(n_chunks * m.n_kv_heads * b->batch) : dim3(n_chunks, m.n_kv_heads, b->batch), dim3(256), 0, st, w.qbuf, b->kv_len, b->page_table, \
                      b->max_pages, layer, m.n_q_heads, m.n_kv_heads, c->slab, c->geom, w.att_part, w.max_chunks,         \
-                     static_cast<unsigned short*>(w.obuf), w.err_flag)
-  if constexpr (D == 128 && G >= 5) ATTN_LAUNCH((k_paged_attn_mm<G, CH>));
-  else if (cached) ATTN_LAUNCH((k_paged_attn<D, G, CH, true>));
-  else ATTN_LAUNCH((k_paged_attn<D, G, CH, false>));
+                     static_cast<unsigned short*>(w.obuf), w.err_flag, list)
+  if constexpr (D == 128 && G >= 5) {
+    if (list.item) ATTN_LAUNCH((k_paged_attn_mm<G, CH, true>));
+    else ATTN_LAUNCH((k_paged_attn_mm<G, CH, false>));
+  } else {
+    if (cached) ATTN_LAUNCH((k_paged_attn<D, G, CH, true, false>));
+    else if (list.item) ATTN_LAUNCH((k_paged_attn<D, G, CH, false, true>));
+    else ATTN_LAUNCH((k_paged_attn<D, G, CH, false, false>));
+  }
 #undef ATTN_LAUNCH
   if (n_chunks > 1)
     hipLaunchKernelGGL((k_attn_merge<D, CH>), dim3(m.n_q_heads, b->batch), dim3(D), 0, st, w.att_part, b->kv_len,
@@ -1101,20 +1155,25 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
   const int B = b->batch, H = m.hidden, d = m.head_dim, QD = m.n_q_heads * d, F = m.ffn, L = m.n_layers;
   const int n_ssq = 2 * L + 1;
   const int np = ssq_entries(H);
+  const int G = m.n_q_heads / m.n_kv_heads;
+  const bool cached = step_stream_bytes(c, b) <= kMemorySideCache;
+  AttnList list{};
+  list.chunk = attn_chunk(d, G);
+  list.n_chunks = (b->max_kv_len + list.chunk - 1) / list.chunk;
+  const long long att_wgs = (long long)list.n_chunks * B * m.n_kv_heads;
+  if (w.att_list && !cached && att_wgs >= kListedWorkgroups && att_wgs < (1ll << 23) && list.n_chunks < (1 << 16)) list.total = w.att_list, list.item = w.att_list + 16;
   hipLaunchKernelGGL(k_decode_prep, dim3(B), dim3(256), 0, st, H, d, n_ssq, w.bpad, np, b->token_ids,
                      static_cast<const unsigned short*>(c->emb), m.vocab, b->x_in, w.xa, c->layers[0].g1,
-                     static_cast<unsigned short*>(w.hx1), w.ssq, w.rope, b->kv_len, w.inv_freq, w.err_flag);
+                     static_cast<unsigned short*>(w.hx1), w.ssq, w.rope, b->kv_len, w.inv_freq, w.err_flag, list);
 
   const float* xcur = b->token_ids ? w.xa : b->x_in;
   float* ping[2] = {w.xb, w.xa};  // layer l writes ping[l&1]; layer 0 must not overwrite xa (it can be its input)
-  const int G = m.n_q_heads / m.n_kv_heads;
   // above 32 sequences the layer GEMMs run as tiled MFMA GEMMs with their epilogues in a second kernel (decode_large.h);
   // a caller's buffer without the workspace for their partial tiles keeps every batch on the small-batch kernels
   const bool large = B >= dg_min_batch() && w.part != nullptr;
   int n_cu = cu_stream_count(st);  // a stream confined to a share of the compute units (Sec. 6.2)
   if (n_cu < 1) n_cu = c->n_cu;
   const int x_tiles = w.bpad / 16;
-  const bool cached = step_stream_bytes(c, b) <= kMemorySideCache;
 
   for (int l = 0; l < L; ++l) {
     const LayerDev& lw = c->layers[l];
@@ -1150,17 +1209,17 @@ harli_status decode_step_bf16(harli_ctx* c, const harli_decode_batch* b, hipStre
       dispatch_skinny<MODE_QKV>(a, (m.n_q_heads + 2 * m.n_kv_heads) * (d / 16), st);
     }
     // --- attention
-    if (d == 128 && G == 1) launch_attn<128, 1, 256>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 2) launch_attn<128, 2, 256>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 4) launch_attn<128, 4, 128>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 8) launch_attn<128, 8, 128>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 3) launch_attn<128, 3, 128>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 5) launch_attn<128, 5, 128>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 6) launch_attn<128, 6, 128>(c, w, b, l, cached, st);
-    else if (d == 128 && G == 7) launch_attn<128, 7, 128>(c, w, b, l, cached, st);
-    else if (d == 64 && G == 1) launch_attn<64, 1, 256>(c, w, b, l, cached, st);
-    else if (d == 64 && G == 2) launch_attn<64, 2, 256>(c, w, b, l, cached, st);
-    else if (d == 64 && G == 4) launch_attn<64, 4, 256>(c, w, b, l, cached, st);
+    if (d == 128 && G == 1) launch_attn<128, 1, 256>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 2) launch_attn<128, 2, 256>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 4) launch_attn<128, 4, 128>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 8) launch_attn<128, 8, 128>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 3) launch_attn<128, 3, 128>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 5) launch_attn<128, 5, 128>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 6) launch_attn<128, 6, 128>(c, w, b, l, cached, list, st);
+    else if (d == 128 && G == 7) launch_attn<128, 7, 128>(c, w, b, l, cached, list, st);
+    else if (d == 64 && G == 1) launch_attn<64, 1, 256>(c, w, b, l, cached, list, st);
+    else if (d == 64 && G == 2) launch_attn<64, 2, 256>(c, w, b, l, cached, list, st);
+    else if (d == 64 && G == 4) launch_attn<64, 4, 256>(c, w, b, l, cached, list, st);
     else return fail(HARLI_ERR_INVALID, "decode_step: head_dim %d with group %d is not supported", d, G);
     // --- output projection + residual, operand of the FFN
     a.x = static_cast<const unsigned short*>(w.obuf);

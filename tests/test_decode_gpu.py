@@ -286,6 +286,17 @@ def test_config2_width_batch256():
     run_case(w, m, [100 + (i * 37) % 400 for i in range(256)])
 
 
+@pytest.mark.parametrize("n_q,n_kv,d,longest", [(4, 4, 64, 1500), (8, 2, 128, 1500), (7, 1, 128, 2700), (3, 3, 128, 1600)])
+def test_uneven_lengths_with_a_list_of_chunks(n_q, n_kv, d, longest):
+    """200 sequences, two of them long: the attention's grid follows the list of chunks that hold tokens (every kernel form, empty
+    caches, whole and just begun chunks, two layers)."""
+    lengths = np.asarray([(i * 7) % 45 for i in range(200)], np.int32)
+    lengths[[3, 77, 199]] = longest, longest - 44, 255
+    lengths[[10, 11, 12]] = 127, 128, 256
+    w, m = variant(0, dtype="bf16", n_layers=2, hidden=256, n_q=n_q, n_kv=n_kv, head_dim=d, ffn=264)
+    run_case(w, m, lengths)
+
+
 @pytest.mark.parametrize("batch,vocab", [(34, 1003), (70, 1000), (130, 260), (200, 64), (256, 515)])
 def test_output_layer_straight_from_the_tiles(batch, vocab):
     """Above 32 sequences, an output layer in one range of K: logits and argmax from the GEMM, every tile height, ragged last
