@@ -260,6 +260,19 @@ __device__ __forceinline__ void g2_cut_tile(const Gemm2Cut& c, int t, int& tm, i
   tm = band * c.GM + rem - tn * rows;
 }
 
+// The arguments are a kilobyte, read here and there by branches, and a cold cache line of them comes from as far away as host
+// memory.  One load from each line, all at once, is one trip instead of one after the other (twelve segments looked at in turn took
+// 2 us a launch).
+template <int BYTES>
+__device__ __forceinline__ void g2_touch_args() {
+  const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  int any = 0;
+#pragma unroll
+  for (int l = 0; l < (BYTES + 63) / 64; ++l) any |= p[l * 16];
+  asm volatile("" ::"s"(any));
+}
+constexpr int kG2ArgBytes = sizeof(Gemm2Args) + sizeof(Gemm2Cut);
+
 template <int RT, bool HALF, int EPI>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN) {
@@ -267,6 +280,7 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN) {
   constexpr int LOADS = AG + 4;  // direct-to-LDS loads a wave issues per stage
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   g2_claim<RT>();
+  g2_touch_args<kG2ArgBytes>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves of (16 RT) x 128
@@ -505,22 +519,29 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN) {
   }
 
   // ---- epilogue: slab by slab, what the next two slabs read in flight --------------------------------------------------
+  // A loop, and only the reads of the accumulators written out: every launch finds the instruction cache cold, and the whole
+  // epilogue written out RT times was much of a kernel's code (with g2_touch_args 1.4 to 1.9 % of a finetune unit).
   const Gemm2Out out = g2_out_of(a, tn);
   bool clamped = false;
   const int mrow = m0 + wm * (RT * 16) + (lane & 15);
-  G2Pre pre[3];
-  g2_epi_load<EPI>(pre[0], a, out, tn, wn, lane, mrow);
-  g2_epi_load<EPI>(pre[1], a, out, tn, wn, lane, mrow + 16);
-  g2_steps<RT>([&](auto i_) __attribute__((always_inline)) {
-    constexpr int i = decltype(i_)::value;
-    if constexpr (i + 2 < RT) g2_epi_load<EPI>(pre[(i + 2) % 3], a, out, tn, wn, lane, mrow + (i + 2) * 16);
+  G2Pre pre, pre1, pre2;
+  g2_epi_load<EPI>(pre, a, out, tn, wn, lane, mrow);
+  g2_epi_load<EPI>(pre1, a, out, tn, wn, lane, mrow + 16);
+#pragma unroll 1
+  for (int i = 0; i < RT; ++i) {
+    g2_epi_load<EPI>(pre2, a, out, tn, wn, lane, mrow + (i + 2) * 16);  // (past the tile: a valid row, never used)
     f32x4 x[8];
-    g2_steps<8>([&](auto j_) __attribute__((always_inline)) {
-      constexpr int t = i * 8 + decltype(j_)::value;
-      x[decltype(j_)::value] = f32x4{g2_acc<4 * t>(), g2_acc<4 * t + 1>(), g2_acc<4 * t + 2>(), g2_acc<4 * t + 3>()};
+    g2_steps<RT>([&](auto i_) __attribute__((always_inline)) {
+      if (i == decltype(i_)::value)
+        g2_steps<8>([&](auto j_) __attribute__((always_inline)) {
+          constexpr int t = decltype(i_)::value * 8 + decltype(j_)::value;
+          x[decltype(j_)::value] = f32x4{g2_acc<4 * t>(), g2_acc<4 * t + 1>(), g2_acc<4 * t + 2>(), g2_acc<4 * t + 3>()};
+        });
     });
-    g2_epi_store<HALF, EPI>(x, pre[i % 3], a, out, tn, wn, lane, mrow + i * 16, clamped);
-  });
+    g2_epi_store<HALF, EPI>(x, pre, a, out, tn, wn, lane, mrow + i * 16, clamped);
+    pre = pre1;
+    pre1 = pre2;
+  }
   if (clamped && a.overflow_flag) atomicOr(a.overflow_flag, 8);
 }
 
@@ -528,6 +549,7 @@ k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN) {
 // block of one tile: eight 1 KiB loads per range, up to four ranges in flight.
 template <int RT, bool HALF, int EPI>
 __global__ void __launch_bounds__(256) k_gemm2_sum(Gemm2Args a, Gemm2Cut cut) {
+  g2_touch_args<kG2ArgBytes>();
   const int lane = threadIdx.x & 63, id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = id % RT, wave = (id / RT) & 3, r = id / (4 * RT);
   int tm, tn;
