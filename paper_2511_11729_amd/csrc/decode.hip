@@ -1066,8 +1066,8 @@ void dispatch_skinny(SkinnyArgs a, int n_tiles, hipStream_t st) {
 
 // tokens per attention chunk, as decode_step_bf16 launches them
 constexpr int attn_chunk(int d, int G) { return d == 64 || G <= 2 ? 256 : 128; }
-// Workgroups of the attention grid from which it follows a list: a few rounds over the chip (a step of few sequences gains
-// nothing from it and pays a dependent load in every layer).
+// Workgroups of the attention grid from which it follows a list: a few rounds over the chip.  A step of fewer gains nothing
+// from it and pays a dependent load in every layer (1932 workgroups, 636 of them with tokens: a step 736 / 752 us).
 constexpr int kListedWorkgroups = 4096;
 
 template <int D, int G, int CH>

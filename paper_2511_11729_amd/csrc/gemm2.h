@@ -121,7 +121,9 @@ struct Gemm2Plan {
 };
 Gemm2Plan gemm2_plan(int M, int tiles_n, int RT, int n_cu);
 
-// One tile height's launches (gemm2_kernel.h, compiled by gemm2_rows*.hip).  banded: tiles in the order of a cut launch.
+// One tile height (gemm2_kernel.h, compiled by gemm2_rows*.hip): what its kernels need once per process, and its launches.  banded: tiles in the order of a cut launch.
+template <int RT>
+harli_status gemm2_init();
 template <int RT>
 harli_status gemm2_run(const Gemm2Args& a, const Gemm2Cut& plan, const Gemm2Plan& pl, bool banded, int per_pass, hipStream_t st);
 

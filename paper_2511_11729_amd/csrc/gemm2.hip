@@ -242,6 +242,12 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
     for (int s = 0; s < a.nseg; ++s)
       if ((a.seg[s].pair != 0) != gu) return fail(HARLI_ERR_INVALID, "gemm2: interleaved pairs go with the gate/up epilogue and only with it");
   }
+  static bool ready = false;  // every height with the first launch, so that no later one (a captured one included) is the first to ask
+  if (!ready) {
+    for (harli_status rc : {gemm2_init<4>(), gemm2_init<5>(), gemm2_init<6>(), gemm2_init<7>(), gemm2_init<8>()})
+      if (rc != HARLI_OK) return rc;
+    ready = true;
+  }
   const int n_cu = a.n_cu > 0 ? a.n_cu : device_cus();
   int stages = 0;  // of the longest column tile
   for (int s = 0; s < a.nseg; ++s) {

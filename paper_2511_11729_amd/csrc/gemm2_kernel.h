@@ -591,24 +591,26 @@ constexpr int lds_bytes() { return ring(RT) * stage_bytes(RT); }
 
 }  // namespace
 
+// The kernels need more dynamic LDS than the default limit.
+template <int RT>
+harli_status gemm2_init() {
+  auto set = [](auto kernel) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<RT>());
+  };
+  for (auto kernel : {&k_gemm2<RT, true, GEMM2_EPI_NONE>, &k_gemm2<RT, true, GEMM2_EPI_F32>, &k_gemm2<RT, true, GEMM2_EPI_SWIGLU_BWD>,
+                      &k_gemm2<RT, true, GEMM2_EPI_GATEUP>, &k_gemm2<RT, true, GEMM2_EPI_ROPE>})
+    HARLI_HIP(set(kernel));
+  if constexpr (RT == 4 || RT == 8)
+    for (auto kernel : {&k_gemm2<RT, false, GEMM2_EPI_NONE>, &k_gemm2<RT, false, GEMM2_EPI_F32>, &k_gemm2<RT, false, GEMM2_EPI_SWIGLU_BWD>,
+                        &k_gemm2<RT, false, GEMM2_EPI_GATEUP>})
+      HARLI_HIP(set(kernel));
+  return HARLI_OK;
+}
+
 // A launch of one tile height: the whole tiles with the first pass, then pass after pass (one, unless the workspace is small).
 template <int RT>
 harli_status gemm2_run(const Gemm2Args& a, const Gemm2Cut& plan, const Gemm2Plan& pl, bool banded, int per_pass, hipStream_t st) {
   const bool f32out = a.out[0].Cf != nullptr;
-  static bool attr_set = false;
-  if (!attr_set) {
-    auto set = [](auto kernel) {
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<RT>());
-    };
-    for (auto kernel : {&k_gemm2<RT, true, GEMM2_EPI_NONE>, &k_gemm2<RT, true, GEMM2_EPI_F32>, &k_gemm2<RT, true, GEMM2_EPI_SWIGLU_BWD>,
-                        &k_gemm2<RT, true, GEMM2_EPI_GATEUP>, &k_gemm2<RT, true, GEMM2_EPI_ROPE>})
-      HARLI_HIP(set(kernel));
-    if constexpr (RT == 4 || RT == 8)
-      for (auto kernel : {&k_gemm2<RT, false, GEMM2_EPI_NONE>, &k_gemm2<RT, false, GEMM2_EPI_F32>, &k_gemm2<RT, false, GEMM2_EPI_SWIGLU_BWD>,
-                          &k_gemm2<RT, false, GEMM2_EPI_GATEUP>})
-        HARLI_HIP(set(kernel));
-    attr_set = true;
-  }
   auto launch = [&](auto kernel, auto sum) -> harli_status {
     Gemm2Cut cut = plan;
     const int chunk = banded ? 0 : pl.chunk;
