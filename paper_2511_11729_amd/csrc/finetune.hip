@@ -423,6 +423,10 @@ extern "C" harli_status harli_lora_attach(harli_ctx* c, const harli_lora_cfg* cf
     for (int t = 0; t < kTargets; ++t)
       if (((cfg->targets >> t) & 1u) && (!A[l * kTargets + t] || !B[l * kTargets + t]))
         return fail(HARLI_ERR_INVALID, "lora_attach: layer %d target %d has a null adapter", l, t);
+  {
+    const harli_status rc = gemm2_prepare();
+    if (rc != HARLI_OK) return rc;
+  }
   c->lora = *cfg;
   c->lora_attached = false;  // until everything below has succeeded
   for (int l = 0; l < c->cfg.n_layers; ++l) {

@@ -112,6 +112,9 @@ constexpr size_t kG2MinPartBytes = (size_t)4 << 20;  // sixteen ranges of a tile
 // bytes of workspace that let every launch of at most max_M rows over tiles_n column tiles run in one pass (at most 64 MiB)
 size_t gemm2_part_bytes(int max_M, int tiles_n, int stages);
 
+// What the kernels of every tile height need once per process (harli_lora_attach calls it, so that no unit -- a captured one
+// included -- is the first to ask).
+harli_status gemm2_prepare();
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st);
 
 // The grid of a launch whose tiles are not cut (exposed for the host-side tests of the tile order).

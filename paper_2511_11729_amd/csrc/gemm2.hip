@@ -2,6 +2,7 @@
 #include "gemm2.h"
 
 #include <algorithm>
+#include <mutex>
 
 #include "ctx.h"
 #include "device_utils.h"
@@ -193,6 +194,20 @@ size_t gemm2_part_bytes(int max_M, int tiles_n, int stages) {
   }
 }
 
+// Once per process, whichever thread comes first; a failure is not kept, the next caller tries again.
+harli_status gemm2_prepare() {
+  static std::mutex mu;
+  static bool ready = false;
+  std::lock_guard<std::mutex> lk(mu);
+  if (ready) return HARLI_OK;
+  for (harli_status (*init)() : {&gemm2_init<4>, &gemm2_init<5>, &gemm2_init<6>, &gemm2_init<7>, &gemm2_init<8>}) {
+    const harli_status rc = init();
+    if (rc != HARLI_OK) return rc;
+  }
+  ready = true;
+  return HARLI_OK;
+}
+
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
   if (a.M < 1 || a.nseg < 1 || a.nseg > kGemm2MaxSeg || a.nout < 1 || a.nout > kGemm2MaxOut || a.tiles_n < 1)
     return fail(HARLI_ERR_INVALID, "gemm2: bad shape M %d nseg %d nout %d tiles %d", a.M, a.nseg, a.nout, a.tiles_n);
@@ -242,11 +257,9 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
     for (int s = 0; s < a.nseg; ++s)
       if ((a.seg[s].pair != 0) != gu) return fail(HARLI_ERR_INVALID, "gemm2: interleaved pairs go with the gate/up epilogue and only with it");
   }
-  static bool ready = false;  // every height with the first launch, so that no later one (a captured one included) is the first to ask
-  if (!ready) {
-    for (harli_status rc : {gemm2_init<4>(), gemm2_init<5>(), gemm2_init<6>(), gemm2_init<7>(), gemm2_init<8>()})
-      if (rc != HARLI_OK) return rc;
-    ready = true;
+  {
+    const harli_status rc = gemm2_prepare();
+    if (rc != HARLI_OK) return rc;
   }
   const int n_cu = a.n_cu > 0 ? a.n_cu : device_cus();
   int stages = 0;  // of the longest column tile

@@ -175,3 +175,37 @@ def test_attention_blocks_at_their_edges(S, d, n_q, n_kv):
     workgroups; head counts that are no multiple of the eight XCDs, query groups of 2 and 3."""
     check(build(0, lora=wl.LoraCfg(8, 16.0, ("q", "k", "v", "o")), ft=wl.FinetuneCfg(2, S), hidden=256, n_q=n_q, n_kv=n_kv,
                 head_dim=d, ffn=320), "S %d d %d" % (S, d))
+
+
+def test_two_host_threads_with_a_context_each():
+    """Attach and unit from two threads at once, each with its own context, pool and stream: what the kernels need once per
+    process is set up by whichever comes first, and both give the bits of a unit that runs alone."""
+    import threading
+
+    alone = build(0)
+    Y0, (_, _, dY, _, _) = alone.forward_gpu(), alone.oracle()
+    dX0, g0 = alone.backward_gpu(dY)
+    out, failed = {}, []
+
+    def work(i):
+        try:
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st):             # the inputs and cleared gradients on the unit's own stream
+                case = build(0)
+                torch.cuda.synchronize()
+                for _ in range(3):
+                    Y = case.forward_gpu(stream=st)
+                    dX, g = case.backward_gpu(dY, stream=st)
+            out[i] = Y, dX, g
+        except Exception as e:                      # surfaces in the main thread below
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not failed, failed
+    for Y, dX, g in out.values():
+        assert np.array_equal(Y, Y0) and np.array_equal(dX, dX0)
+        assert all(np.array_equal(g[p][k], g0[p][k]) for p in g0 for k in range(2))
