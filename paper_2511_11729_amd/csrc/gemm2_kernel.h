@@ -52,9 +52,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // is a[4t .. 4t+3].  The compiler's allocator copied more than half of 64 four-register accumulators between the register
 // files in every pass of the stage ring; named, none moves, and the code between two products is exactly what stands there.
 // The kernel claims the whole range in its first statement and nothing else in it uses accumulator registers (the compiler
-// would only to spill, and it has 256 other registers for about 150 values): tests/test_gemm2_isa.py reads that off the
-// built library.  Hazards the compiler does not fill in for assembly: the products of one accumulator are 8 RT products
-// apart, its first use lies a barrier behind the zeros and the reads of the epilogue behind the idle cycles of g2_drain().
+// would only to spill, and it has 256 other registers for about 150 values).  Hazards the compiler does not fill in for
+// assembly: the products of one accumulator are 8 RT products apart, its first use lies a barrier behind the zeros and the
+// reads of the epilogue behind the idle cycles of g2_drain(); a vector instruction that writes a fragment has to lie two
+// slots before the product that reads it, and there is none: fragments come from LDS, whose reads the compiler waits for.  The
+// build (build.py) reads the compiled kernels back and refuses any in which one of this does not hold.
 // The weight fragment is the FIRST operand: a lane then holds four neighbouring columns 16 j + 4 (lane / 16) + v of row
 // 16 i + lane % 16, and the epilogue stores from registers.
 template <bool HALF, int T>
