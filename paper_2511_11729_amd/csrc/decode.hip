@@ -433,7 +433,10 @@ __global__ void __launch_bounds__(256) k_decode_prep(int H, int d, int n_ssq, in
   if (list.item) {
     // where this sequence's chunks begin: the chunks of the sequences before it (blockIdx.x < 256)
     __shared__ int before[4];
-    auto chunks = [&](int i) { return max(0, min((kv_len[i] + list.chunk) / list.chunk, list.n_chunks)); };
+    auto chunks = [&](int i) {  // (no sum that a length near the largest integer could overflow)
+      const int n = kv_len[i];
+      return n < 0 ? 0 : min(n / list.chunk + 1, list.n_chunks);
+    };
     int n = tid < b ? chunks(tid) : 0;
     for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
     if ((tid & 63) == 0) before[tid >> 6] = n;

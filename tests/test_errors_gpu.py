@@ -97,6 +97,23 @@ def test_device_side_checks_report_through_ctx_check_and_every_kernel_exits_norm
     case.check_cache()
 
 
+def test_a_length_near_the_largest_integer_is_reported_where_the_attention_follows_a_list_of_chunks():
+    """200 sequences up to 1500 tokens: the grid follows the list of chunks that hold tokens.  The sum of such a length and a
+    chunk's tokens overflows; the sequence is longer than the step was sized for all the same."""
+    w = wl.workload(0)
+    m = dataclasses.replace(w.model, dtype="bf16", n_layers=2)
+    lengths = np.asarray([(i * 7) % 45 for i in range(200)], np.int32)
+    lengths[77] = 1500
+    case = DecodeCase(w, m, lengths, block_bytes=64 << 10)
+    case.kv_len_dev[5] = 2**31 - 100
+    with pytest.raises(hb.HarliError) as e:
+        case.run_gpu()
+    assert e.value.status == hb.HARLI_ERR_INVALID and "longer than max_kv_len" in str(e.value), str(e.value)
+    case.kv_len_dev[5] = int(lengths[5])
+    case.slab.copy_(torch.from_numpy(case.img0.view(np.uint8)))
+    assert_close(case.run_gpu(), case.run_oracle(), "decode output after the flagged step")
+
+
 def test_finetune_entry_points_reject_bad_arguments_and_keep_the_pool_clean():
     w = wl.workload(0)
     m = dataclasses.replace(w.model, dtype="bf16")
