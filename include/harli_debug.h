@@ -20,8 +20,8 @@ extern "C" {
  *   matrices of the pair and either may be NULL) and its weight rows start at the first column of tile0.  Output block
  *   o starts at tile out_tile0[o] and has out_n[o] valid columns; all blocks are 16-bit (cb) or all fp32 (cf, optional
  *   res).  epi 0: plain; 2: SwiGLU backward (cf/cb unused: o0 = da, o1 = du from e0 = a, e1 = u); 3: gate/up pair
- *   (cb[0] = a, o1 = u, o0 = silu(a) * u).  tile_rows 128, 160, 192, 224 or 256 (bfloat16: 128 or 256) fixes the tile height, 0 leaves the choice to the
- *   library.  reps > 1 repeats the launch and writes TFLOP/s over HIP events and the shader clock of the last launch
+ *   (cb[0] = a, o1 = u, o0 = silu(a) * u).  tile_rows 128, 160, 192, 224 or 256 (bfloat16: 128 or 256) fixes the tile height,
+ *   0 leaves the choice to the library.  reps > 1 repeats the launch and writes TFLOP/s over HIP events and the shader clock of the last launch
  *   to the host pointers (either may be NULL). */
 typedef struct {
   int32_t M, nseg, nout, tiles_n, half, epi, tile_rows, reps;
@@ -61,24 +61,27 @@ typedef struct {
 } harli_dbg_gemm2_desc;
 harli_status harli_dbg_gemm2(const harli_dbg_gemm2_desc* d, void* hip_stream);
 
-/* The grid the weight GEMM would launch for M rows and tiles_n column tiles at tile height tile_rows (128, 160, .., 256), none of
- * them cut along K (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk, grid and the rounds of
- * tiles over n_cu compute units (a figure for the reader: height and cut are chosen by harli_dbg_gemm2_cut's rule).  Workgroup w computes the tile in slot (w % 8) * chunk + w / 8
- * of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over the blocks; slots past the matrix
- * are idle.  This is the order of a launch whose tiles are not cut along K; harli_dbg_gemm2_cut tells which are. */
+/* The grid of the weight GEMM in blocks of tiles, for M rows and tiles_n column tiles at tile height tile_rows (128, 160, ..,
+ * 256) (host logic only, no device needed).  out[6] (host) receives GM, GN, total, chunk, grid and the rounds of tiles over
+ * n_cu compute units (a figure for the reader: height and cut are chosen by harli_dbg_gemm2_cut's rule).  Workgroup w computes
+ * the tile in slot (w % 8) * chunk + w / 8 of the XCD-aware order: blocks of GM x GN tiles, row-major inside a block and over
+ * the blocks; slots past the matrix are idle.  Launches that harli_dbg_gemm2_cut reports as not banded run in this order: no
+ * tile is cut, and whole blocks cover the matrix (total = row tiles * column tiles). */
 harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t tile_rows, int32_t n_cu, int32_t* out);
 
-/* Tile height and cut the weight GEMM would choose (host logic only, no device needed) for M rows, tiles_n column tiles,
+/* Tile height, cut and order the weight GEMM chooses (host logic only, no device needed) for M rows, tiles_n column tiles,
  * `stages` K steps of 32 in the longest column tile, on a device of n_cu compute units of which the stream may use
- * `share`.  out[10] (host): tile rows, ranges of K (1: nothing is cut), tiles computed whole, tiles cut, row tiles,
- * column tiles, row tiles per band, whole tiles and partial tiles per XCD, and the tiles that are cut per pass with
- * part_bytes of workspace for partial tiles (0: it does not hold those of one tile).
- * Cut launch: workgroups [0, 8 chunk_full) are the whole tiles, workgroup w computing tile (w % 8) * chunk_full + w / 8;
+ * `share`; half: IEEE half operands (else bfloat16), f32out: fp32 outputs (else 16-bit).  out[11] (host): tile rows, ranges of
+ * K (1: nothing is cut), tiles computed whole, tiles cut, row tiles, column tiles, row tiles per band, whole tiles and partial
+ * tiles per XCD, the tiles that are cut per pass with part_bytes of workspace for partial tiles (0: nothing is cut, or it does
+ * not hold those of one tile), and 1 where the tiles go out in bands.
+ * Banded launch: workgroups [0, 8 chunk_full) are the whole tiles, workgroup w computing tile (w % 8) * chunk_full + w / 8;
  * workgroup 8 chunk_full + w computes piece p = (w % 8) * chunk_cut + w / 8, that is range p / rest of tile full + p % rest
  * (indexes past either list are idle).  Tile t lies in band t / (GM * tiles_n) of GM row tiles (the last band may have
- * fewer), column by column inside the band.  A launch in passes cuts as many tiles at a time, the first beside the whole ones. */
-harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int64_t part_bytes,
-                                 int32_t* out);
+ * fewer), column by column inside the band.  A launch in passes cuts as many tiles at a time, the first beside the whole ones.
+ * Any other launch has the order of harli_dbg_gemm2_plan. */
+harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int32_t half, int32_t f32out,
+                                 int64_t part_bytes, int32_t* out);
 
 /* How one GEMM of a decode step above 32 sequences is cut (host logic only, no device needed): `batch` sequences,
  * n_mat (1, or 2 for gate and up) weight matrices of n_rows rows, contraction length K, on n_cu compute units, with

@@ -153,7 +153,7 @@ _SIGS = {
                                         C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "harli_dbg_gemm2": (C.c_int, [C.c_void_p, C.c_void_p]),
     "harli_dbg_gemm2_plan": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
-    "harli_dbg_gemm2_cut": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64, C.POINTER(C.c_int32)]),
+    "harli_dbg_gemm2_cut": (C.c_int, [C.c_int32] * 7 + [C.c_int64, C.POINTER(C.c_int32)]),
     "harli_dbg_decode_large_min_batch": (None, [C.c_int32]),
     "harli_dbg_decode_gemm_plan": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64, C.POINTER(C.c_int64)]),
     "harli_dbg_decode_gemm_time": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_float), C.c_void_p]),
@@ -585,11 +585,12 @@ def dbg_gemm2_plan(M: int, tiles_n: int, tile_rows: int, n_cu: int) -> dict:
     return dict(zip(("GM", "GN", "total", "chunk", "grid", "rounds"), list(out)))
 
 
-def dbg_gemm2_cut(M: int, tiles_n: int, stages: int, n_cu: int, share: int = 0, part_bytes: int = 64 << 20) -> dict:
-    """Tile height and cut along K of a launch of the weight GEMM (host logic); share 0: all of n_cu."""
-    out = (C.c_int32 * 10)()
-    _check(lib().harli_dbg_gemm2_cut(M, tiles_n, stages, n_cu, share or n_cu, part_bytes, out))
-    return dict(zip(("rows", "ks", "full", "rest", "tiles_m", "tiles_n", "GM", "chunk_full", "chunk_cut", "per_pass"), list(out)))
+def dbg_gemm2_cut(M: int, tiles_n: int, stages: int, n_cu: int, share: int = 0, part_bytes: int = 64 << 20, half: bool = True,
+                  f32out: bool = False) -> dict:
+    """Tile height, cut along K and order of a launch of the weight GEMM (host logic); share 0: all of n_cu."""
+    out = (C.c_int32 * 11)()
+    _check(lib().harli_dbg_gemm2_cut(M, tiles_n, stages, n_cu, share or n_cu, int(half), int(f32out), part_bytes, out))
+    return dict(zip(("rows", "ks", "full", "rest", "tiles_m", "tiles_n", "GM", "chunk_full", "chunk_cut", "per_pass", "banded"), list(out)))
 
 
 def dbg_gemm2(M, segs, outs, *, half=True, epi=0, alpha=1.0, tile_rows=0, reps=0, e0=None, e1=None, o0=None, o1=None, lde=0,

@@ -19,13 +19,14 @@ extern "C" harli_status harli_dbg_gemm2_plan(int32_t M, int32_t tiles_n, int32_t
   return HARLI_OK;
 }
 
-extern "C" harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int64_t part_bytes,
-                                            int32_t* out) {
+extern "C" harli_status harli_dbg_gemm2_cut(int32_t M, int32_t tiles_n, int32_t stages, int32_t n_cu, int32_t share, int32_t half, int32_t f32out,
+                                            int64_t part_bytes, int32_t* out) {
   if (!out || M < 1 || tiles_n < 1 || stages < 1 || n_cu < 1 || share < 1 || share > n_cu || part_bytes < 0)
     return fail(HARLI_ERR_INVALID, "dbg_gemm2_cut: bad argument");
-  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share, true, false);
-  const int v[10] = {32 * c.RT, c.ks, c.full, c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut, gemm2_pass_tiles(c, (size_t)part_bytes)};
-  for (int i = 0; i < 10; ++i) out[i] = v[i];
+  const Gemm2Cut c = gemm2_cut(M, tiles_n, stages, n_cu, share, half != 0, f32out != 0);
+  const int v[11] = {32 * c.RT, c.ks,          c.full,      c.rest, c.tiles_m, c.tiles_n, c.GM, c.chunk_full, c.chunk_cut, gemm2_pass_tiles(c, (size_t)part_bytes),
+                     gemm2_banded(c, gemm2_plan(M, tiles_n, c.RT, n_cu))};
+  for (int i = 0; i < 11; ++i) out[i] = v[i];
   return HARLI_OK;
 }
 

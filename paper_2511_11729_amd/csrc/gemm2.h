@@ -117,12 +117,14 @@ size_t gemm2_part_bytes(int max_M, int tiles_n, int stages);
 harli_status gemm2_prepare();
 harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st);
 
-// The grid of a launch whose tiles are not cut (exposed for the host-side tests of the tile order).
+// The block order of a launch (exposed for the host-side tests of the tile order).
 struct Gemm2Plan {
   int GM, GN, total, chunk, grid;  // block of tiles per XCD pass, padded tile slots, slots per XCD, workgroups launched
   int rounds;                      // rounds of tiles over the compute units (reported only: gemm2_cut makes the choice)
 };
 Gemm2Plan gemm2_plan(int M, int tiles_n, int RT, int n_cu);
+// Which order the tiles of a launch go out in: bands of GM row tiles (as the cut tiles do), or the grid's blocks.
+bool gemm2_banded(const Gemm2Cut& c, const Gemm2Plan& p);
 
 // One tile height (gemm2_kernel.h, compiled by gemm2_rows*.hip): what its kernels need once per process, and its launches.  banded: tiles in the order of a cut launch.
 template <int RT>

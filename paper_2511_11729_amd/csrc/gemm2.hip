@@ -77,7 +77,12 @@ void gemm2_block_jobs(const BlockJobs& jobs, hipStream_t st) {
   hipLaunchKernelGGL(k_block_jobs, dim3(256, jobs.n), dim3(256), 0, st, jobs);
 }
 
-// Grid of a launch whose tiles are not cut: the XCD-aware tile order of the kernel.
+// Uncut outputs that whole blocks of tiles cover go out block by block.  Any other would pad the blocks, and the XCDs whose
+// shares hold the fewest empty slots would run a round more than the rest (12 x 20 tiles of 3000 x 5120 x 13824 took 550 us
+// in blocks, 347 in bands): bands have no empty slots.
+bool gemm2_banded(const Gemm2Cut& c, const Gemm2Plan& p) { return c.ks > 1 || p.total != c.tiles_m * c.tiles_n; }
+
+// Grid of a launch in blocks of tiles: the XCD-aware tile order of the kernel.
 Gemm2Plan gemm2_plan(int M, int tiles_n, int RT, int n_cu) {
   Gemm2Plan p{};
   const int BM = 32 * RT, tiles_m = (M + BM - 1) / BM;
@@ -272,10 +277,7 @@ harli_status gemm2_launch(const Gemm2Args& a, hipStream_t st) {
   const int share = cu_stream_count(st);  // 0: not confined
   const Gemm2Cut plan = gemm2_cut(a.M, a.tiles_n, stages, n_cu, share > 0 ? std::min(share, n_cu) : n_cu, a.half != 0, f32out);
   const Gemm2Plan pl = gemm2_plan(a.M, a.tiles_n, plan.RT, n_cu);
-  // Uncut outputs that whole blocks of tiles cover go out block by block.  Any other would pad the blocks, and the XCDs whose
-  // shares hold the fewest empty slots would run a round more than the rest (12 x 20 tiles of 3000 x 5120 x 13824 took 550 us
-  // in blocks, 347 in bands): bands have no empty slots.
-  const bool banded = plan.ks > 1 || pl.total != plan.tiles_m * plan.tiles_n;
+  const bool banded = gemm2_banded(plan, pl);
   const int per_pass = gemm2_pass_tiles(plan, a.part ? a.part_bytes : 0);
   if (plan.ks > 1 && per_pass < 1) return fail(HARLI_ERR_INVALID, "gemm2: no room for the partial tiles of one tile");
   // flops asked for: 2 M K per valid output column a segment reaches (an interleaved pair fills both halves of a tile)

@@ -120,3 +120,78 @@ def test_every_range_of_every_tile_is_computed_once(M, tiles_n, stages, n_cu, sh
         first, full = first + rest, 0
     assert set(done) == set(itertools.product(range(c["tiles_m"]), range(c["tiles_n"])))
     assert all(v == ["whole"] or sorted(v) == list(range(c["ks"])) for v in done.values())
+
+
+# ---- every launch in the order it runs in, by operand and output type -------------------------------------------------
+def tile_of(c, t):
+    band, rem = divmod(t, c["GM"] * c["tiles_n"])
+    rows = min(c["GM"], c["tiles_m"] - band * c["GM"])
+    return band * c["GM"] + rem % rows, rem // rows
+
+
+@pytest.mark.parametrize("half,f32out", [(True, False), (True, True), (False, False), (False, True)])
+@pytest.mark.parametrize("share", [256, 230, 26])
+def test_every_tile_of_an_uncut_launch_is_computed_once(half, f32out, share):
+    """Both orders: blocks where whole ones cover the matrix, else bands without an empty slot; every tile height."""
+    seen = set()
+    for M, tiles_n, stages in itertools.product((1, 130, 160, 300, 600, 1032, 1100, 2048, 2304, 3000, 3400, 4096), (1, 5, 16, 43, 48, 86, 100), (3, 33, 129)):
+        c = hb.dbg_gemm2_cut(M, tiles_n, stages, 256, share, half=half, f32out=f32out)
+        assert c["tiles_m"] == -(-M // c["rows"]) and c["full"] + c["rest"] == c["tiles_m"] * tiles_n
+        p = hb.dbg_gemm2_plan(M, tiles_n, c["rows"], 256)
+        whole_blocks = p["total"] == c["tiles_m"] * tiles_n
+        assert c["banded"] == (c["ks"] > 1 or not whole_blocks)
+        if c["ks"] > 1:
+            continue
+        seen.add((c["rows"], c["banded"]))
+        if c["banded"]:
+            assert c["rest"] == 0 and c["full"] == c["tiles_m"] * tiles_n and c["chunk_full"] == -(-c["full"] // 8)
+            slots = [(w & 7) * c["chunk_full"] + (w >> 3) for w in range(8 * c["chunk_full"])]
+            done = [tile_of(c, s) for s in slots if s < c["full"]]
+        else:
+            cover = tiles_of(p, M, tiles_n, c["rows"])
+            done = [t for t, ws in cover.items() for _ in ws]
+        assert sorted(done) == list(itertools.product(range(c["tiles_m"]), range(tiles_n)))
+    heights = {128, 160, 192, 224, 256} if half and share == 256 else {128, 256}
+    assert {rows for rows, _ in seen} >= heights and {b for _, b in seen} == {0, 1}
+
+
+@pytest.mark.parametrize("tile_rows", [160, 192, 224])
+@pytest.mark.parametrize("M,tiles_n", SHAPES + [(2240, 16), (3840, 40)])
+def test_the_block_order_of_the_other_heights(tile_rows, M, tiles_n):
+    p = hb.dbg_gemm2_plan(M, tiles_n, tile_rows, 256)
+    cover = tiles_of(p, M, tiles_n, tile_rows)
+    assert set(cover) == set(itertools.product(range(-(-M // tile_rows)), range(tiles_n)))
+    assert all(len(ws) == 1 for ws in cover.values()) and p["grid"] == p["chunk"] * 8
+
+
+@pytest.mark.parametrize("half", [True, False])
+@pytest.mark.parametrize("share", [256, 230, 26])
+def test_every_range_of_every_tile_with_fp32_outputs_or_bfloat16_operands(half, share):
+    """As above for cut launches; passes of a small workspace."""
+    cut = 0
+    for (M, tiles_n, stages), part_bytes in itertools.product(((2048, 16, 129), (1032, 14, 1186), (600, 20, 434), (300, 1, 64), (4096, 20, 434),
+                                                               (1100, 5, 40), (2304, 3, 17)), (4 << 20, 64 << 20)):
+        c = hb.dbg_gemm2_cut(M, tiles_n, stages, 256, share, part_bytes, half=half, f32out=True)
+        assert c["tiles_m"] == -(-M // c["rows"]) and c["full"] + c["rest"] == c["tiles_m"] * tiles_n
+        assert half or c["rows"] in (128, 256)
+        if c["ks"] == 1:
+            continue
+        cut += 1
+        done, first, full = [], c["full"], c["full"]
+        while first < c["full"] + c["rest"]:
+            rest = min(c["per_pass"], c["full"] + c["rest"] - first)
+            assert rest > 0 and rest * c["ks"] * c["rows"] * 256 * 4 <= part_bytes
+            chunk_full, chunk_cut = -(-full // 8), -(-rest * c["ks"] // 8)
+            done += [(tile_of(c, s), "whole") for s in ((w & 7) * chunk_full + (w >> 3) for w in range(8 * chunk_full)) if s < full]
+            done += [(tile_of(c, first + q % rest), q // rest) for q in ((w & 7) * chunk_cut + (w >> 3) for w in range(8 * chunk_cut)) if q < rest * c["ks"]]
+            first, full = first + rest, 0
+        want = [(tile_of(c, t), "whole") for t in range(c["full"])] + [(tile_of(c, t), r) for t in range(c["full"], c["full"] + c["rest"]) for r in range(c["ks"])]
+        assert sorted(done, key=str) == sorted(want, key=str) and len({tile_of(c, t) for t in range(c["tiles_m"] * tiles_n)}) == c["tiles_m"] * tiles_n
+    assert cut >= 6
+
+
+def test_the_output_type_moves_the_plan():
+    """A store of fp32 with its residual costs more than one of 16 bits: 2048 x 4096 over 129 stages goes out whole in 128 rows
+    as half, and in two ranges of 256 rows as fp32 (the o projection of the 7B shape)."""
+    a, b = hb.dbg_gemm2_cut(2048, 16, 129, 256), hb.dbg_gemm2_cut(2048, 16, 129, 256, f32out=True)
+    assert (a["rows"], a["ks"]) == (128, 1) and (b["rows"], b["ks"]) == (256, 2)
