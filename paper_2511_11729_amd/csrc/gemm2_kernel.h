@@ -11,7 +11,7 @@
 //     rows of a stage are XOR-swizzled in 16-byte chunks on the way in (each lane picks the global chunk that belongs
 //     in its LDS slot), which makes the 16-row fragment reads conflict free;
 //   * the fragments of a stage are read during the stage before, so a stage's buffer is free again as soon as its products
-//     begin: of five LDS stages (six at 128 rows: all that fit) four are in flight;
+//     begin: of four LDS stages three are in flight;
 //   * one wave per SIMD has nobody to hide its waits, so reads and loads are dealt out between the products by hand;
 //   * nothing but the loads' scalar offsets moves from stage to stage: every branch and mask of the cursor (end of a
 //     segment, of the range, a partial K step) is behind one comparison that is false on whole stages.
@@ -40,8 +40,10 @@ constexpr int BSZ = BN * BK * 2;  // 16 KiB: one stage of the weight-side tile
 // the operand's range and cost no traffic: every wave has to count the same number of loads)
 constexpr int a_groups(int RT) { return (RT + 1) / 2; }
 constexpr int stage_bytes(int RT) { return a_groups(RT) * 4096 + BSZ; }
-// LDS stages: as many as fit (six at 128-row tiles, five at the others)
-constexpr int ring(int RT) { return 160 * 1024 / stage_bytes(RT); }
+// LDS stages.  As many as fit (six at 128 rows, five at the others) are no faster: 252 units of eleven layer shapes, 8 to 4096
+// tokens, take 0.7 % less time with four (the best of four runs each), a 7B unit 1865 us with four and 1864 with five, a 13B unit
+// 5495 and 5479, within the runs' spread.  Four leave 64 (128 rows) to 32 KiB (256 rows) of a compute unit's LDS free.
+constexpr int kStages = 4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 #define G2_WAITV(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
@@ -278,7 +280,7 @@ constexpr int kG2ArgBytes = sizeof(Gemm2Args) + sizeof(Gemm2Cut);
 template <int RT, bool HALF, int EPI>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 k_gemm2(Gemm2Args a, Gemm2Cut cut, int tiles_total, int chunk, int GM, int GN) {
-  constexpr int BM = 32 * RT, AG = a_groups(RT), ASZ = AG * 4096, STG = stage_bytes(RT), NS = ring(RT);
+  constexpr int BM = 32 * RT, AG = a_groups(RT), ASZ = AG * 4096, STG = stage_bytes(RT), NS = kStages;
   constexpr int LOADS = AG + 4;  // direct-to-LDS loads a wave issues per stage
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   g2_claim<RT>();
@@ -589,7 +591,7 @@ __global__ void __launch_bounds__(256) k_gemm2_sum(Gemm2Args a, Gemm2Cut cut) {
 }
 
 template <int RT>
-constexpr int lds_bytes() { return ring(RT) * stage_bytes(RT); }
+constexpr int lds_bytes() { return kStages * stage_bytes(RT); }
 
 }  // namespace
 
