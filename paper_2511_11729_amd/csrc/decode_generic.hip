@@ -259,17 +259,16 @@ __global__ void __launch_bounds__(256) g_attention(const float* q, const int* kv
       if (page >= 0 && page < geom.n_pages_total) {
         const float* kp = base + kv_page_off(geom, page, layer, 0) / 4 + in_page;
         const float* qe = EL < 16 ? qs : qv;
-        if (d % 4 == 0) {
+        // 16 bytes a load for every head size: element by element, heads of 86 took 1414 us of a step of 256 sequences of 600
+        // tokens, where this step takes 320 (the cache lines of 256 tokens do not stay in L1 for 86 visits)
+        int e = 0;
 #pragma unroll 4
-          for (int e = 0; e < d; e += 4) {
-            float kv[4];
-            __builtin_memcpy(kv, kp + e, 16);
-            s += qe[e] * kv[0] + qe[e + 1] * kv[1] + qe[e + 2] * kv[2] + qe[e + 3] * kv[3];
-          }
-        } else {
-#pragma unroll 1
-          for (int e = 0; e < d; ++e) s += qe[e] * kp[e];
+        for (; e + 4 <= d; e += 4) {
+          float kv[4];
+          __builtin_memcpy(kv, kp + e, 16);
+          s += qe[e] * kv[0] + qe[e + 1] * kv[1] + qe[e + 2] * kv[2] + qe[e + 3] * kv[3];
         }
+        if (e < d) s += qe[e] * kp[e] + qe[e + 1] * kp[e + 1];  // (head sizes are even)
         at[tid] = (long long)(kv_page_off(geom, page, layer, 1) / 4 + in_page);
       } else {
         atomicOr(err_flag, 1);

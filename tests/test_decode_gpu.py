@@ -368,10 +368,11 @@ def test_biases_small_shapes_bf16_and_fp32():
 
 @pytest.mark.parametrize("hidden,n_q,n_kv,d,ffn,lengths", [
     (256, 4, 4, 64, 688, [96]), (254, 6, 2, 64, 690, [0, 300]), (256, 2, 1, 96, 64, [255, 256, 257]),
+    (510, 6, 3, 86, 130, [300, 0, 255, 77, 16, 511]), (130, 3, 1, 2, 34, [40, 1]), (64, 1, 1, 322, 48, [270, 3]),
     (130, 1, 1, 256, 33, [600, 1, 3, 17, 31]), (64, 2, 2, 320, 48, [5, 90, 16, 15, 2, 3, 7, 40, 520])])
 def test_fp32_path_at_its_edges(hidden, n_q, n_kv, d, ffn, lengths):
     """The fp32 path over every number of batch rows a wave carries (1, 2, 4, 8, and a second tile of rows), contractions
-    with and without 16-byte loads, head sizes of one to five lanes' elements and blocks of 256 tokens; two layers, biases,
+    with and without 16-byte loads, head sizes of one to five lanes' elements, multiples of four and not, and blocks of 256 tokens; two layers, biases,
     embedding and logits."""
     w, m = variant(0, n_layers=2, hidden=hidden, n_q=n_q, n_kv=n_kv, head_dim=d, ffn=ffn, vocab=37, qkv_bias=True)
     lengths = np.asarray(lengths, np.int32)
