@@ -379,7 +379,6 @@ struct AttnList {
   int n_chunks; // most chunks of a sequence
 };
 
-
 // ---------------------------------------------------------------------------------------------
 // Step preparation: operand and sum of squares of the first layer, rotary table, cleared
 // accumulators.  One workgroup per sequence; loads are issued in groups of four 16-byte words
@@ -1072,10 +1071,9 @@ constexpr int attn_chunk(int d, int G) { return d == 64 || G <= 2 ? 256 : 128; }
 // Workgroups of the attention grid from which it follows a list.  What the list is worth follows the share of them that hold tokens,
 // which only the device knows.  Measured with and without it at 50 points (five shapes of heads, 16 to 200 sequences, two layers,
 // us a layer): 768 workgroups, 296 of them with tokens, 0.5 more with the list; 1500 to 4096: 0 to 3 less where under half hold
-// tokens, 1 to 2 more where all do; 4096 to 16 000: 1 to 6 less of 150 to 280 where lengths are uneven (two points of 24: up to 1
-// more), at even lengths from 4 less to 4 more (64-element heads; 1 % of the step).  No number of workgroups separates the
-// two: the line is where the gain of uneven lengths is larger than the loss of even ones.  (Reading the number of chunks and the
-// item in one trip changes none of this.)
+// tokens, 1 to 2 more where all do; 4096 to 16 000: up to 6 less of 150 to 280 where lengths are uneven (five of 25 points: up to 1
+// more), from 3 less to 4 more where they are even (1 % of the step).  No number of workgroups separates the two: from this line
+// on the gain at uneven lengths is the larger.  (Reading the number of chunks and the item in one trip changes none of this.)
 constexpr int kListedWorkgroups = 4096;
 
 template <int D, int G, int CH>
