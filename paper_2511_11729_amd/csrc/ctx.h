@@ -30,7 +30,8 @@ struct LayerDev {
   void* B[kTargets];
 };
 
-// Device buffers of the decode path, sized by max_batch (rounded up to 16).
+// Device buffers of the decode path, sized by max_batch (rounded up to 16).  fp32 contexts hold obuf, mbuf, qbuf, x1, xa, xb,
+// inv_freq and err_flag.
 struct DecodeWs {
   int bpad = 0;
   void *hx1 = nullptr, *obuf = nullptr, *hx2 = nullptr, *mbuf = nullptr;  // GEMM operands in storage dtype

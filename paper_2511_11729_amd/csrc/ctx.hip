@@ -151,19 +151,23 @@ extern "C" harli_status harli_ctx_create(const harli_model_cfg* cfg, const harli
   d.bpad = (m.max_batch + 15) / 16 * 16;
   d.max_chunks = (m.max_seq_len + 127) / 128;  // the smallest attention chunk is 128 tokens
   const size_t bp = d.bpad;
-  TRY(dev_alloc(c, &d.hx1, bp * m.hidden * 4, true));
   TRY(dev_alloc(c, &d.obuf, bp * QD * 4, true));
-  TRY(dev_alloc(c, &d.hx2, bp * m.hidden * 4, true));
   TRY(dev_alloc(c, &d.mbuf, bp * m.ffn * 4, true));
   TRY(dev_alloc(c, &d.qbuf, bp * QD * 4, true));
   TRY(dev_alloc(c, &d.x1, bp * m.hidden * 4, true));
   TRY(dev_alloc(c, &d.xa, bp * m.hidden * 4, true));
   TRY(dev_alloc(c, &d.xb, bp * m.hidden * 4, true));
-  TRY(dev_alloc(c, &d.ssq, bp * (2 * m.n_layers + 1) * (size_t)ssq_entries(m.hidden) * 4, true));
-  TRY(dev_alloc(c, &d.rope, bp * m.head_dim * 4, true));
-  if (m.vocab > 0) {
-    TRY(dev_alloc(c, &d.amax_v, bp * 64 * 4, true));
-    TRY(dev_alloc(c, &d.amax_i, bp * 64 * 4, true));
+  if (m.dtype == HARLI_BF16) {  // the fp32 step norms on the way, makes its angles where it needs them and keeps its scores in LDS
+    TRY(dev_alloc(c, &d.hx1, bp * m.hidden * 4, true));
+    TRY(dev_alloc(c, &d.hx2, bp * m.hidden * 4, true));
+    TRY(dev_alloc(c, &d.ssq, bp * (2 * m.n_layers + 1) * (size_t)ssq_entries(m.hidden) * 4, true));
+    TRY(dev_alloc(c, &d.rope, bp * m.head_dim * 4, true));
+    TRY(dev_alloc(c, &d.att_part, bp * m.n_q_heads * d.max_chunks * (m.head_dim + 2) * 4, true));
+    TRY(dev_alloc(c, &d.att_list, (16 + bp * d.max_chunks) * 4, true));
+    if (m.vocab > 0) {
+      TRY(dev_alloc(c, &d.amax_v, bp * 64 * 4, true));
+      TRY(dev_alloc(c, &d.amax_i, bp * 64 * 4, true));
+    }
   }
   {
     TRY(dev_alloc(c, &d.inv_freq, (m.head_dim / 2) * sizeof(double), false));
@@ -174,9 +178,7 @@ extern "C" harli_status harli_ctx_create(const harli_model_cfg* cfg, const harli
       return fail(HARLI_ERR_HIP, "ctx_create: copying the rotary table failed");
     }
   }
-  TRY(dev_alloc(c, &d.att_part, bp * m.n_q_heads * d.max_chunks * (m.head_dim + 2) * 4, true));
   TRY(dev_alloc(c, &d.err_flag, 16, true));
-  TRY(dev_alloc(c, &d.att_list, (16 + bp * d.max_chunks) * 4, true));
   d.part_bytes = dg_workspace_bytes(m, c->n_cu);
   if (d.part_bytes) {
     TRY(dev_alloc(c, &d.part, d.part_bytes, false));

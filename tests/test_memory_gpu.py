@@ -182,3 +182,18 @@ def test_partial_tiles_of_the_weight_gemms_take_no_room_of_their_own():
             fc.pool.free(a)
     Y1, dX1, _ = unit(fc, dY)                                             # rank 8: the adapters of the first unit
     assert np.array_equal(Y0, Y1) and np.array_equal(dX0, dX1)
+
+
+def test_an_fp32_context_takes_only_what_the_fp32_step_reads():
+    """Residual, query, attention output and SwiGLU product of 16 rows; nothing that grows with the longest sequence."""
+    from tests.gpu_util import DecodeCase
+    w = wl.workload(0)
+    m = dataclasses.replace(w.model, n_layers=2, vocab=100)
+    case = DecodeCase(w, m, np.asarray([2000, 3], np.int32), full_model=True, block_bytes=64 << 10)
+    read = 16 * 4 * (3 * m.hidden + 2 * m.n_q * m.head_dim + m.ffn)
+    assert read <= case.ctx.device_bytes().decode_workspace <= read + 1024   # the rotary frequencies and the flag
+    tok = wl.make_token_ids(dataclasses.replace(w, model=m), (2,))
+    hid = case.run_gpu(token_ids=tok)
+    ref_hid, ref_logits, _ = case.run_oracle(token_ids=tok)
+    assert_close(hid, ref_hid, "hidden state")
+    assert_close(case.logits_dev.cpu().numpy(), ref_logits, "logits")
