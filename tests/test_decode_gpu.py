@@ -11,7 +11,8 @@ import pytest
 import torch
 
 import workloads as wl
-from tests.gpu_util import DecodeCase, assert_close
+from paper_2511_11729_amd import binding as hb
+from tests.gpu_util import DEV, DecodeCase, assert_close
 
 pytestmark = pytest.mark.gpu
 
@@ -313,6 +314,46 @@ def test_output_layer_straight_from_the_tiles(batch, vocab):
     logits = case.logits_dev.cpu().numpy()
     assert_close(logits, ref_logits, "logits")
     assert (case.next_dev.cpu().numpy() == logits.argmax(1)).all()
+
+
+def test_output_layer_straight_from_the_tiles_with_weights_read_once():
+    """A step past the size of the caches and more weight tiles than compute units, at 40 and 200 sequences (the lowest and the
+    tallest tile): the logits against the product of the same 16-bit operands in float64 -- fp32 sums of 1024 products, 1e-5 of
+    the largest -- and the first maximum of every row."""
+    w, m = variant(0, dtype="bf16", n_layers=1, hidden=1024, n_q=8, n_kv=8, head_dim=128, ffn=1024, vocab=131000)
+    B, n_cu = 200, torch.cuda.get_device_properties(0).multi_processor_count
+    assert -(-m.vocab // 256) > n_cu and 2 * (m.vocab * m.hidden + m.layer_params) > 256 << 20
+    case = DecodeCase(w, m, np.asarray([3 + (i * 7) % 40 for i in range(B)], np.int32), full_model=True, block_bytes=256 << 10)
+    tok = torch.from_numpy(wl.make_token_ids(dataclasses.replace(w, model=m), (B,)).astype(np.int32)).to(DEV)
+    for batch in (40, 200):
+        assert hb.dbg_decode_gemm_plan(batch, m.vocab, 1, m.hidden, n_cu, 192 << 20)["ksplit"] == 1
+        case.slab.copy_(torch.from_numpy(case.img0.view(np.uint8)))
+        y, nxt = torch.empty(batch, m.hidden, device=DEV), torch.empty(batch, dtype=torch.int32, device=DEV)
+        logits = torch.full((batch, m.vocab), float("nan"), device=DEV)
+        case.ctx.decode_step(batch=batch, kv_len=case.kv_len_dev, page_table=case.table_dev, max_pages=case.max_pages,
+                             max_kv_len=int(case.kv_len.max()) + 1, token_ids=tok, logits=logits, next_token=nxt, x_out=y)
+        torch.cuda.synchronize()
+        case.ctx.check()
+        x = y.double()
+        rho = torch.rsqrt((x * x).mean(1, keepdim=True) + m.rms_eps)
+        ref = rho * ((y * case.gf_dev).bfloat16().double() @ case.wlm_dev.double().t().contiguous())
+        assert float((logits.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+        assert torch.equal(nxt.long(), torch.from_numpy(logits.cpu().numpy().argmax(1)).to(DEV))
+
+
+@pytest.mark.parametrize("batch", [40, 100, 200])
+def test_output_layer_in_ranges_of_k_with_unaligned_rows(batch):
+    """The partial sums' own kernel, its stores element by element and the argmax in two passes: vocabulary 1003 in ranges of K."""
+    w, m = variant(0, dtype="bf16", n_layers=1, hidden=1024, n_q=8, n_kv=8, head_dim=128, ffn=1024, vocab=1003)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    case = DecodeCase(w, m, np.asarray([3 + (i * 11) % 40 for i in range(batch)], np.int32), full_model=True, block_bytes=256 << 10)
+    assert hb.dbg_decode_gemm_plan(batch, m.vocab, 1, m.hidden, n_cu, 192 << 20)["ksplit"] > 1
+    tok = wl.make_token_ids(dataclasses.replace(w, model=m), (batch,))
+    case.run_gpu(token_ids=tok)
+    _, ref_logits, _ = case.run_oracle(token_ids=tok)
+    logits = case.logits_dev.cpu().numpy()
+    assert_close(logits, ref_logits, "logits")
+    assert np.array_equal(case.next_dev.cpu().numpy(), np.argmax(logits, axis=-1))
 
 
 @pytest.mark.parametrize("batch", [70, 150, 200])

@@ -121,10 +121,11 @@ def test_gate_up_pair_with_swiglu_epilogue_and_its_backward(half, M, F, H):
 
 
 @pytest.mark.parametrize("tile_rows", [128, 160, 192, 224, 256])
-@pytest.mark.parametrize("M,N,K,ksplit", [(1, 260, 264, 1), (353, 1001, 40, 1), (417, 520, 1000, 3), (225, 261, 136, 4)])
+@pytest.mark.parametrize("M,N,K,ksplit", [(1, 260, 264, 1), (353, 1001, 40, 1), (417, 520, 1000, 3), (225, 261, 520, 4)])
 def test_tile_heights_at_their_edges(tile_rows, M, N, K, ksplit):
     """Every tile height, whole and in ranges of K: one row, rows past the last whole 16 of a tile, columns past the last
     whole four (fp32 output with a residual and its 16-bit copy) and, N rounded down to eights, a 16-bit output."""
+    assert ksplit == 1 or -(-K // 32) // 4 >= ksplit          # a range of K has four stages or more: all asked for are taken
     A, B = rnd((M, K), True, 80), rnd((N, K), True, 81, 0.1)
     ref = f64(A) @ f64(B).T
     ld = (N + 7) // 8 * 8
@@ -191,7 +192,7 @@ def test_full_size_shapes_on_a_nine_tenths_partition():
 
 
 # ---- tiles cut along K: partial tiles in a workspace, summed by a second kernel ---------------------------------------
-@pytest.mark.parametrize("tile_rows", [128, 256])
+@pytest.mark.parametrize("tile_rows", [128, 160, 192, 224, 256])
 @pytest.mark.parametrize("ksplit", [2, 3, 16])
 @pytest.mark.parametrize("M,N,K,K2", [(8, 8, 512, 8), (300, 520, 1000, 16), (257, 1000, 2080, 64)])
 def test_tiles_cut_along_k(tile_rows, ksplit, M, N, K, K2):
@@ -223,18 +224,20 @@ def test_full_rounds_and_a_cut_remainder():
     assert torch.equal(got[0], got[1])
 
 
-def test_swiglu_epilogues_of_cut_tiles():
-    M, F, H = 150, 200, 520
+@pytest.mark.parametrize("tile_rows,ksplit", [(0, 4)] + [(r, k) for r in (128, 160, 192, 224, 256) for k in (1, 4)])
+def test_swiglu_epilogues_of_cut_tiles(tile_rows, ksplit):
+    """Both fused epilogues in ranges of K, and at every tile height cut and whole."""
+    M, F, H = 150 if tile_rows == 0 else 2 * tile_rows - 10, 200, 520
     h2, Wg, Wu = rnd((M, H), True, 40), rnd((F, H), True, 41, 0.08), rnd((F, H), True, 42, 0.08)
     a = torch.full((M, F), float("nan"), dtype=torch.float16, device=DEV)
     u, m, da, du = (torch.full_like(a, float("nan")) for _ in range(4))
-    hb.dbg_gemm2(M, [dict(A=h2, B=Wg, B2=Wu, pair=1)], [dict(N=F, cb=a)], epi=3, o0=m, o1=u, lde=F, ksplit=4)
+    hb.dbg_gemm2(M, [dict(A=h2, B=Wg, B2=Wu, pair=1)], [dict(N=F, cb=a)], epi=3, o0=m, o1=u, lde=F, ksplit=ksplit, tile_rows=tile_rows)
     ar, ur = f64(a), f64(u)
     close(ar, f64(h2) @ f64(Wg).T, "gate")
     close(ur, f64(h2) @ f64(Wu).T, "up")
     close(f64(m), ar / (1 + np.exp(-ar)) * ur, "silu(a) * u")
     dy, WdT = rnd((M, H), True, 47), rnd((F, H), True, 48, 0.08)
-    hb.dbg_gemm2(M, [dict(A=dy, B=WdT)], [dict(N=F)], epi=2, e0=a, e1=u, o0=da, o1=du, lde=F, ksplit=4)
+    hb.dbg_gemm2(M, [dict(A=dy, B=WdT)], [dict(N=F)], epi=2, e0=a, e1=u, o0=da, o1=du, lde=F, ksplit=ksplit, tile_rows=tile_rows)
     dm, sg = f64(dy) @ f64(WdT).T, 1 / (1 + np.exp(-ar))
     close(f64(da), dm * ur * sg * (1 + ar * (1 - sg)), "da")
     close(f64(du), dm * ar * sg, "du")
@@ -242,7 +245,8 @@ def test_swiglu_epilogues_of_cut_tiles():
 
 @pytest.mark.parametrize("d,M,S", [(64, 150, 40), (128, 300, 300)])
 @pytest.mark.parametrize("ksplit", [1, 3])
-def test_rotary_epilogue(d, M, S, ksplit):
+@pytest.mark.parametrize("tile_rows", [0, 160, 192, 224])
+def test_rotary_epilogue(d, M, S, ksplit, tile_rows):
     """Rotary embedding on the first of two output blocks (two heads and a block that ends inside a tile), plain columns
     after it, whole tiles and tiles cut along K: half outputs, one rounding (2^-11 of a value of the row's size)."""
     K, Ns = 520, [2 * d, 3 * d]
@@ -254,7 +258,7 @@ def test_rotary_epilogue(d, M, S, ksplit):
     cb = [torch.full((M, n), float("nan"), dtype=torch.float16, device=DEV) for n in Ns]
     hb.dbg_gemm2(M, [dict(A=A, B=W[0], tile0=0, tile1=1), dict(A=A, B=W[1], tile0=1, tile1=3 if Ns[1] > 256 else 2)],
                  [dict(N=Ns[0], cb=cb[0], tile0=0), dict(N=Ns[1], cb=cb[1], tile0=1)], epi=4, ksplit=ksplit, rope=table, rope_S=S,
-                 rope_d=d, rope_tiles=1)
+                 rope_d=d, rope_tiles=1, tile_rows=tile_rows)
     x = (f64(A) @ f64(W[0]).T).reshape(M, 2, d)
     c, s = np.cos(ang)[np.arange(M) % S][:, None], np.sin(ang)[np.arange(M) % S][:, None]
     lo, hi = x[..., : d // 2], x[..., d // 2:]
@@ -282,7 +286,8 @@ def test_a_partition_gives_the_bits_of_the_whole_device(M, N, K):
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
 
 
-@pytest.mark.parametrize("tile_rows,M,N,K,n_cu", [(128, 300, 1000, 1088, 0), (256, 300, 1000, 1088, 0), (128, 1100, 1300, 640, 7)])
+@pytest.mark.parametrize("tile_rows,M,N,K,n_cu", [(128, 300, 1000, 1088, 0), (256, 300, 1000, 1088, 0), (128, 1100, 1300, 640, 7),
+                                                  (160, 300, 1000, 1088, 0), (192, 1100, 1300, 640, 7), (224, 1100, 1300, 640, 7)])
 def test_a_small_workspace_gives_the_same_bits_in_passes(tile_rows, M, N, K, n_cu):
     """Room for all partial tiles, for a few and for one, of launches without and with whole tiles."""
     A, B = rnd((M, K), True, 1), rnd((N, K), True, 2, 0.1)
@@ -296,7 +301,7 @@ def test_a_small_workspace_gives_the_same_bits_in_passes(tile_rows, M, N, K, n_c
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
 
 
-@pytest.mark.parametrize("tile_rows,n_cu", [(128, 0), (256, 0), (128, 20)])
+@pytest.mark.parametrize("tile_rows,n_cu", [(128, 0), (256, 0), (128, 20), (160, 0), (160, 20), (192, 0), (192, 20), (224, 0)])
 def test_bands_of_row_tiles_and_columns_with_fewer_stages(tile_rows, n_cu):
     """Row tiles in two bands, the last one ragged; a long segment that reaches two of six column tiles, so that the ranges of
     K of the others are short or empty.  Every element against fp64 (1e-5 of the largest: K eps / 2 at most)."""
