@@ -185,14 +185,14 @@ def test_two_host_threads_with_a_context_each():
     alone = build(0)
     Y0, (_, _, dY, _, _) = alone.forward_gpu(), alone.oracle()
     dX0, g0 = alone.backward_gpu(dY)
+    cases = [FinetuneCase(alone.w, alone.m, alone.lora, alone.ft, attach=False) for _ in range(2)]   # (contexts are made one by one)
     out, failed = {}, []
 
     def work(i):
         try:
-            st = torch.cuda.Stream()
-            with torch.cuda.stream(st):             # the inputs and cleared gradients on the unit's own stream
-                case = build(0)
-                torch.cuda.synchronize()
+            st, case = torch.cuda.Stream(), cases[i]
+            with torch.cuda.stream(st):             # cleared gradients on the unit's own stream
+                case.ctx.lora_attach(case.lora.rank, case.lora.alpha, case.lora.targets, [case.A_dev], [case.B_dev])
                 for _ in range(3):
                     Y = case.forward_gpu(stream=st)
                     dX, g = case.backward_gpu(dY, stream=st)
