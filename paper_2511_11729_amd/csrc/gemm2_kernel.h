@@ -15,12 +15,13 @@
 //   * one wave per SIMD has nobody to hide its waits, so reads and loads are dealt out between the products by hand;
 //   * nothing but the loads' scalar offsets moves from stage to stage: every branch and mask of the cursor (end of a
 //     segment, of the range, a partial K step) is behind one comparison that is false on whole stages.
-// What bounds it: power.  On random operands the chip holds 1.6-1.7 GHz under this loop (2.4 on zeros, and with the loads
+// What bounds it: power.  On random operands the chip holds 1.65-1.75 GHz under this loop (2.4 on zeros, and with the loads
 // bunched together the clock rises as the cycles do), so energy per product counts: v_mfma_f32_16x16x32 draws less than
-// 32x32x16 and the loop takes 1105-1160 cycles a 256-row stage (1024 of them product issue; 32x32x16: 1180).  A workgroup
-// spends another 3-5 us before its first product and 4 (16-bit) or 8-11 us (fp32) on its store.  Alone, 4096 x 16384 x 4096:
-// 484 us with 32x32x16 products and a store through LDS, 403 now (1365 TFLOP/s; the vendor's library 368); fp32 output with
-// a residual 606 -> 545; one round, 2048 x 8192 x 8192: 190 (1450 TFLOP/s; 183).
+// 32x32x16.  A stage takes 1142 cycles at 256 rows (1024 of them product issue), 880 (768) at 192, 635 (512) at 128: the clock
+// of workgroup 0's loop, K = 8192 less K = 4096, one round of tiles.  A workgroup spends another 3-5 us before its first
+// product and 4 (16-bit) or 8-11 us (fp32) on its store.  Back to back on normal operands (harli_dbg_gemm2), 4096 x 16384 x
+// 4096: 487 us with 32x32x16 products and a store through LDS, 435 now (1263 TFLOP/s; the vendor's library 382); fp32 output
+// with a residual 590 -> 545; one round, 2048 x 8192 x 8192: 236 -> 208 (1320 TFLOP/s; 196); 2048 x 22016 x 4096: 339 -> 304 (410).
 // RT = 4 .. 8, tiles of 128, 160, .., 256 rows: the height whose tiles fit the rows and the rounds best (gemm2_cut).
 #pragma once
 #include "gemm2.h"
